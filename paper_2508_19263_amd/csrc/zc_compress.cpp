@@ -85,6 +85,12 @@ TensorLists device_code_lists(const Geometry &g, const CompressShape &sh, uint64
     TensorLists L = {};
     const uint64_t bytes = (n_elems * (uint64_t)elem_bits(g.fmt) + 7) / 8;
     const uint32_t whole_chunks = (uint32_t)(n_elems / g.elems_per_chunk);
+    if (sh.split_all) {
+        // (the list takes the room of the four chunk lists, which lie one behind the other and hold a quarter of it each)
+        L.hist = {0, (uint32_t)((bytes + kHistBlockBytes - 1) / kHistBlockBytes), 1};
+        L.slow = {0, (uint32_t)nc, 1};
+        return L;
+    }
     // a histogram block is a chunk when sh.lanes is set: whole chunks go to the kernel that counts per lane too
     const uint32_t lane_blocks = (sh.lanes || sh.lanes8 || sh.lanes_e5m2) ? whole_chunks : 0;
     L.lane_hist = {0, lane_blocks, 1};
@@ -94,19 +100,21 @@ TensorLists device_code_lists(const Geometry &g, const CompressShape &sh, uint64
     if (fast_shape) L.fast = {0, whole_chunks, sh.fast_step};
     if (sh.whole_shape) L.whole = {0, whole_chunks, sh.whole_step};
     else if (fast_shape) L.other = {0, whole_chunks, sh.cpi};
-    L.slow = {(fast_shape || sh.whole_shape) ? whole_chunks : 0u, (uint32_t)nc, sh.cpi};
+    L.slow = {(fast_shape || sh.whole_shape) ? whole_chunks : 0u, (uint32_t)nc, sh.split_rest ? 1u : sh.cpi};
     return L;
 }
 
-CompressShape compress_shape(const Geometry &g, bool device_codes, uint64_t all_chunks)
+CompressShape compress_shape(const Geometry &g, bool device_codes, uint64_t all_chunks, bool delta)
 {
     CompressShape sh;
     sh.cpi = chunks_per_work_item(g.S);
-    sh.lanes = device_codes && lane_counts_shape(g);
-    sh.lanes8 = device_codes && lane_counts8_shape(g);
-    sh.lanes_e5m2 = device_codes && lane_counts_e5m2_shape(g);
     sh.bf16 = g.fmt == ZC_FMT_BF16;
     sh.whole_shape = g.S == 64 && g.chunk_bytes % 1024 == 0;
+    sh.split_all = g.S == 64 && g.nf == 2 && g.chunk_bytes >= kSplitChunkBytes && all_chunks <= split_chunk_limit(g.fmt, delta);
+    sh.split_rest = sh.split_all || (sh.whole_shape && g.nf == 2);      // (what is left over is a tensor's short last chunk)
+    sh.lanes = device_codes && !sh.split_all && lane_counts_shape(g);
+    sh.lanes8 = device_codes && !sh.split_all && lane_counts8_shape(g);
+    sh.lanes_e5m2 = device_codes && !sh.split_all && lane_counts_e5m2_shape(g);
     sh.rows8 = sh.whole_shape && (g.fmt == ZC_FMT_BF16 || g.fmt == ZC_FMT_FP8_E4M3_BYTES || g.fmt == ZC_FMT_FP8_E5M2);
     // FP4 elements rarely compress, so their fields are stored plainly and a chunk's rows can be shared by the four
     // wavefronts of a workgroup: one chunk per work item there
@@ -167,9 +175,9 @@ zc_status CompressQueue::queue_sizes_and_scan() const
     else
         LAUNCH_TRY(launch_sizes(g.fmt, sh.whole_mode, sh.lanes8 ? 0x6 : 0x2, d_descs(), d_list(w.whole_work), n_whole, d_enc(), d_units(), stream));
     LAUNCH_TRY(launch_sizes(g.fmt, 0, 0x6, d_descs(), d_list(w.other_work), n_other, d_enc(), d_units(), stream));
-    // what the whole-chunk kernels leave over: with 64 lanes and chunks of whole rows only a tensor's short last chunk,
-    // sized from its lanes' bit totals; otherwise every chunk, walked by the generic size pass
-    if (sh.whole_shape && g.nf == 2) LAUNCH_TRY(launch_sizes_tail(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
+    // what the whole-chunk kernels leave over: with 64 lanes and chunks of whole rows only a tensor's short last chunk, and
+    // every chunk of a call of few, sixteen wavefronts each; otherwise every chunk, walked by the generic size pass
+    if (sh.split_rest) LAUNCH_TRY(launch_sizes_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
     else LAUNCH_TRY(launch_sizes(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
     // the chained kernel has placed and written the tensors of its route (FP8: 1, BF16: 2) itself
     LAUNCH_TRY(launch_scan(d_descs(), T, (int)g.nf, g.reversed, chained ? (sh.bf16 ? 0x4 : 0x2) : 0, d_units(), (ScanOut *)(ws + w.scan), stats_only ? nullptr : ws + w.blobs,
@@ -186,7 +194,8 @@ zc_status CompressQueue::queue_encoders() const
     LAUNCH_TRY(launch_encode(g.fmt, sh.whole_mode, 0x6, d_descs(), d_list(w.whole_work), n_whole, d_enc(), stream));
     if (sh.rows8) LAUNCH_TRY(launch_encode_bf16(g.fmt, d_descs(), d_list(w.whole_work), n_whole, d_enc(), stream));
     LAUNCH_TRY(launch_encode(g.fmt, 0, 0x6, d_descs(), d_list(w.other_work), n_other, d_enc(), stream));
-    LAUNCH_TRY(launch_encode(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
+    if (sh.split_rest) LAUNCH_TRY(launch_encode_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
+    else LAUNCH_TRY(launch_encode(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
     return ZC_OK;
 }
 
@@ -454,7 +463,9 @@ private:
         fast_shapes.resize(T);
         uint64_t units_off = 0, all_chunks = 0;
         for (uint32_t t = 0; t < T; t++) { check_count(g, tensors[t].n_elems, &ncs[t]); all_chunks += ncs[t]; }
-        sh = compress_shape(g, uses_device_codes(), all_chunks);
+        bool delta = false;
+        for (uint32_t t = 0; t < T; t++) delta = delta || tensors[t].d_xor_base;
+        sh = compress_shape(g, uses_device_codes(), all_chunks, delta);
         for (uint32_t t = 0; t < T; t++) {
             zc_tensor &x = tensors[t];
             const uint64_t nc = ncs[t];
@@ -797,12 +808,16 @@ private:
         const bool chained = !pages_fit_one_workgroup() && pages_in_one_pass();
         for (uint32_t t = 0; t < T; t++) {
             // the route is known, so every chunk is listed once
+            if (sh.split_all) {
+                append(slow_work, t, {0, (uint32_t)ncs[t], 1});
+                continue;
+            }
             const uint64_t whole_chunks = tensors[t].n_elems / g.elems_per_chunk;
             const uint32_t n_fast = (descs[t].route == 1 || (descs[t].route == 2 && !sh.whole_shape)) ? (uint32_t)whole_chunks : 0;
             const uint32_t n_whole = (descs[t].route != 1 && sh.whole_shape) ? (uint32_t)whole_chunks : 0;
             append(fast_work, t, {0, n_fast, chained ? chained_step() : sh.fast_step});
             append(whole_work, t, {0, n_whole, sh.whole_step});
-            append(slow_work, t, {n_fast + n_whole, (uint32_t)ncs[t], sh.cpi});
+            append(slow_work, t, {n_fast + n_whole, (uint32_t)ncs[t], sh.split_rest ? 1u : sh.cpi});
         }
         if (codes_out) *codes_out = codes;
         if (!chained) order_for_xcds(fast_work);                   // the chain runs through the items in the list's order

@@ -99,10 +99,12 @@ struct CompressShape {
     bool bf16;
     bool rows8;                 // 64 lanes, whole rows, 8 or 16 symbols of 8 bits per run and field (BF16, FP8 in byte symbols, FP8 E5M2): the 64-lane encoder written for BF16
     bool whole_shape;           // 64 lanes, chunks of whole 1 KiB rows: the generic encoder's whole-chunk build
+    bool split_rest;            // 64 lanes, two fields: what the whole-chunk kernels leave over goes through the kernels that give a chunk sixteen wavefronts
+    bool split_all;             // so few chunks that all of them do (then no other chunk list and no counts per lane)
     int whole_mode;             // 2: one whole chunk per work item, shared by its four wavefronts
     uint32_t whole_step, fast_step, cpi;    // chunks per work item of the whole-chunk list, the fast list, the generic kernels
 };
-CompressShape compress_shape(const Geometry &g, bool device_codes, uint64_t all_chunks);
+CompressShape compress_shape(const Geometry &g, bool device_codes, uint64_t all_chunks, bool delta);
 bool compress_fast_shape(const Geometry &g, uint64_t n_elems, uint64_t bound_bytes);
 
 // work items first, first + step, ... below end

@@ -97,6 +97,16 @@ constexpr uint32_t kHistBlockBytes = 256 * 1024;
 // chunks (or chunk slots) handled by one workgroup of the chunk kernels
 constexpr uint32_t kWavesPerGroup = 4;
 
+// A compress call (64 lanes, two fields) of at most split_chunk_limit() chunks of at least kSplitChunkBytes (two rows per
+// wavefront) leaves all of them to the kernels that give a chunk sixteen wavefronts.  One wavefront per chunk takes as long
+// for one chunk as for a thousand; sixteen per chunk take time in proportion to the chunks from 512 (two workgroups per
+// compute unit) on, and read the source twice.  Measured on MI355X, whole calls over chunks of 256 KiB, one wavefront |
+// sixteen, in us: FP8 128: 230 | 114, 512: 252 | 192, 768: 279 | 243, 1024: 345 | 324, 1536: 413 | 468; BF16 768: 283 | 256,
+// 896: 305 | 300; E5M2, whose runs have twice the symbols, 1024: 464 | 395, 1536: 582 | 558; BF16 deltas, both fields table
+// coded, 512: 362 | 296, 640: 386 | 397.  Chunks of 64 KiB cross at the same counts (both sides are proportional to the rows).
+constexpr uint32_t kSplitChunkBytes = 32 * 1024;
+inline uint64_t split_chunk_limit(uint32_t fmt, bool delta) { return delta ? 512 : fmt == ZC_FMT_FP8_E5M2 ? 1024 : 768; }
+
 // per-tensor scratch written by the scan kernel and read back by the host
 struct ScanOut { uint32_t field_units[kMaxFields]; uint32_t total_units; };
 
@@ -172,9 +182,9 @@ int launch_sizes_e5m2_counts(const TensorDev *d_descs, const WorkItem *d_work, u
 int launch_hist_rows8_lanes(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint64_t *d_hist, uint32_t *d_lane_counts, void *stream);
 int launch_sizes_rows8_counts(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc,
                               const uint32_t *d_lane_counts, uint32_t *d_units, void *stream);
-// Two-field formats, 64 lanes: stream sizes of the chunks of a generic work list (up to kWavesPerGroup chunks per item)
-// from the closed form over the lanes' bit totals; meant for the short last chunks of tensors (zc_hist_lanes.hip)
-int launch_sizes_tail(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream);
+// Two-field formats, 64 lanes, any chunks, one per work item: sixteen wavefronts to a chunk (zc_encode_split.hip)
+int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream);
+int launch_encode_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream);
 int launch_sizes_fp8_counts(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint16_t *d_lane_counts,
                             uint32_t *d_units, void *stream);
 int launch_encode_fp8(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream);
