@@ -338,12 +338,16 @@ typedef struct {
     uint32_t fast_kernel;                       /* 0 none, 1 FP8 specialised, 2 64-lane full-chunk kernel, 3 FP8 small chunks,
                                                    4 = 2 with every chunk shared by four wavefronts (no table-decoded element field),
                                                    5 BF16 small chunks, 6 BF16 with 64 lanes (table-decoded exponents),
-                                                   7 FP8 E5M2 with 64 lanes (table-decoded exponents, flat 3-bit sign+mantissa code) */
-    uint32_t fast_exp_kind, fast_sm_kind, n_rings /* kernels 3, 5: slots per workgroup */, xor_delta;
+                                                   7 FP8 E5M2 with 64 lanes (table-decoded exponents, flat 3-bit sign+mantissa code),
+                                                   8 BF16, FP8 and FP8 in byte symbols with 64 lanes: 7 and 8 look up two symbols at
+                                                   a time and take every chunk, short last ones and id lists included */
+    uint32_t fast_exp_kind, fast_sm_kind /* bits 8 up: tail_kernel 3's table-decoded fields */,
+        n_rings /* kernels 3, 5: slots per workgroup; 7, 8: table-decoded fields * 64 + chunks per workgroup */, xor_delta;
     uint32_t scattered;                         /* some tensor decodes an id list */
     uint32_t tail_kernel;                       /* the second work list (chunks that are not whole rows, id lists with 64 lanes):
                                                    0 generic kernel, 1 the 64-lane kernel's build for such chunks (two-field formats),
-                                                   2 = 1 leaving whole chunks to the FP8 kernel's build for id lists */
+                                                   2 = 1 leaving whole chunks to the FP8 kernel's build for id lists, 3 the kernels
+                                                   that look up two symbols at a time */
     uint64_t fast_work_offset, work_offset;     /* byte offsets of the two work lists in d_ws */
 } zc_batch_plan;
 zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors, void *d_ws, uint64_t ws_bytes,

@@ -56,13 +56,9 @@ uint32_t bf16_s64_rings(const zc_info &info)
     return 1;
 }
 
-// Can the E5M2 kernel decode this container's full chunks?  64 lanes, chunks of whole rows, exponent field table
-// decoded on a refill period of 2, 4 or 8, sign+mantissa field coded with the flat 3-bit code over the values 0..7.
-bool e5m2_s64_ok(const zc_info &info)
+// Is the sign+mantissa field coded with the flat 3-bit code over the values 0..7?
+bool e5m2_flat3(const zc_info &info)
 {
-    if (info.format != ZC_FMT_FP8_E5M2 || !s64_rings(info)) return false;
-    const TensorDev d = make_desc(info);
-    if (d.kind[0] != 0 || (d.period[0] != 2 && d.period[0] != 4 && d.period[0] != 8)) return false;
     if (info.mode[1] != ZC_MODE_HUFF) return false;
     for (int v = 0; v < 256; v++) if (info.code_len[1][v] != (v < 8 ? 3 : 0)) return false;
     return true;
@@ -74,6 +70,32 @@ bool s64_tail_ok(const zc_info &info)
 {
     if (info.streams != 64 || info.n_fields != 2 || is_fp4(info.format)) return false;
     return info.mode[0] != ZC_MODE_EMPTY && info.mode[1] != ZC_MODE_EMPTY;
+}
+
+// Can the kernels that look up two symbols at a time decode this container's chunks, whichever they are?  64 lanes, a format of
+// two fields, exponent field table decoded, sign+mantissa field table decoded on the same refill period or stored plainly (FP8
+// E4M3: only the latter; E5M2: its flat 3-bit code).  Returns the table-decoded fields (1 or 2), 0 if not.
+uint32_t pairs_fields(const zc_info &info)
+{
+    if (!s64_tail_ok(info)) return 0;
+    const TensorDev d = make_desc(info);
+    if (d.kind[0] != 0 || (d.period[0] != 2 && d.period[0] != 4 && d.period[0] != 8)) return 0;
+    if (info.format == ZC_FMT_FP8_E5M2) return e5m2_flat3(info) ? 1 : 0;
+    if (info.format == ZC_FMT_FP8_E4M3) return ((d.kind[1] == 1 || d.kind[1] == 2) && d.period[0] != 8) ? 1 : 0;
+    if (d.kind[1] == 0) return d.period[1] == d.period[0] ? 2 : 0;
+    return 1;
+}
+
+// Chunks per workgroup of those kernels for a call of `slots` chunks, 0: another kernel is faster.  FP8 E4M3: from 1,024 chunks
+// on k_decode_fp8, bound by its traffic, is ahead (1,536 chunks: 249 against 280 us still, but with tables of 13 bits that lose
+// 10 % to those of 14 below; 2,048: 282 against 288).  Two table-decoded fields fill the compute units' LDS with 4,096
+// chunks, and a few more take a second round (4,096 and one: 723 us against 708 in k_decode_bf16_s64; 3,072: 435 | 662;
+// 6,144: 866 | 893).
+uint32_t pairs_waves(uint32_t fmt, uint32_t fields, uint64_t slots)
+{
+    if (fmt == ZC_FMT_FP8_E4M3) return slots <= 1024 ? 4 : 0;
+    if (fmt == ZC_FMT_BF16 && fields == 2 && slots > 3072 && slots <= 5120) return 0;
+    return slots <= 1024 ? 4 : 8;
 }
 
 // Are both element fields stored plainly (flat code, raw, constant)?  Then the rows of a chunk do not depend on
@@ -176,7 +198,7 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
     const uint32_t cpi = chunks_per_work_item(info.streams);
     const FastKind fk = fast_kind(info);
     uint32_t first_slot = 0;
-    const uint32_t rings = s64_rings(info);
+    const uint32_t rings = s64_rings(info), pairs = pairs_fields(info);
     const uint64_t elems_per_chunk = (uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(info.format);
     if (sub_ok(info, need) && (!by_ids || info.n_elems % elems_per_chunk == 0)) {
         // small chunks (pages): several per wavefront.  An id list may name a short last chunk, which
@@ -186,12 +208,15 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         if (info.format == ZC_FMT_BF16) LAUNCH_TRY(launch_decode_bf16_sub(info.streams, info.xor_delta != 0, nullptr, nullptr, (n_fast + spg - 1) / spg, &d, spg, stream));
         else LAUNCH_TRY(launch_decode_fp8_sub(info.streams, info.xor_delta != 0, by_ids, nullptr, nullptr, (n_fast + spg - 1) / spg, &d, spg, stream));
         first_slot = n_fast;
+    } else if (pairs && pairs_waves(info.format, pairs, slots)) {
+        const uint32_t waves = pairs_waves(info.format, pairs, slots);
+        LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, waves, nullptr, nullptr, (slots + waves - 1) / waves, &d, 0, stream));
+        first_slot = slots;
     } else if ((fk.ok || rings) && !by_ids) {
         // full chunks through a specialised kernel, a short last chunk through the generic one
         const uint32_t n_full = (uint32_t)(info.n_elems / ((uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(info.format)));
         const uint32_t n_fast = (n_full + kWavesPerGroup - 1) / kWavesPerGroup;
         if (fk.ok) LAUNCH_TRY(launch_decode_fp8_fast(fk.exp_kind, fk.sm_kind, info.xor_delta != 0, false, nullptr, nullptr, n_fast, &d, stream));
-        else if (e5m2_s64_ok(info)) LAUNCH_TRY(launch_decode_e5m2(info.xor_delta != 0, nullptr, nullptr, n_fast, &d, stream));
         else if (bf16_s64_rings(info)) LAUNCH_TRY(launch_decode_bf16_s64(bf16_s64_rings(info), info.xor_delta != 0, nullptr, nullptr, n_fast, &d, stream));
         else {
             const bool split = s64_split_ok(info);
@@ -210,7 +235,8 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         // what is left: chunks that are not whole rows and id lists with 64 lanes (the 64-lane kernel's build for those, for
         // the formats of two fields), geometries no specialised kernel takes
         const uint32_t n_work = (slots - first_slot + cpi - 1) / cpi;
-        if (s64_tail_ok(info)) LAUNCH_TRY(launch_decode_s64_tail(info.format, info.xor_delta != 0, nullptr, nullptr, n_work, &d, first_slot, false, stream));
+        if (pairs) LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, kWavesPerGroup, nullptr, nullptr, n_work, &d, first_slot, stream));
+        else if (s64_tail_ok(info)) LAUNCH_TRY(launch_decode_s64_tail(info.format, info.xor_delta != 0, nullptr, nullptr, n_work, &d, first_slot, false, stream));
         else LAUNCH_TRY(launch_decode(info.format, nullptr, nullptr, n_work, cpi, &d, first_slot, stream));
     }
     return ZC_OK;
@@ -303,8 +329,6 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     }
     bool split = rings != 0;
     for (uint32_t t = 0; t < n_tensors && split; t++) split = s64_split_ok(tensors[t].info);
-    bool e5m2 = rings != 0;
-    for (uint32_t t = 0; t < n_tensors && e5m2; t++) e5m2 = e5m2_s64_ok(tensors[t].info);
     // BF16 sets whose every tensor has the shape of the BF16 kernel go there instead
     uint32_t bf16_rings = rings ? 1 : 0;
     for (uint32_t t = 0; t < n_tensors && bf16_rings; t++) {
@@ -314,7 +338,16 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     const bool fast = fk.ok || rings != 0 || sub;
     uint64_t all_slots = 0;
     for (uint32_t t = 0; t < n_tensors; t++) all_slots += tensors[t].d_chunk_ids ? tensors[t].n_chunk_ids : tensors[t].info.n_chunks;
-    const uint32_t spg = sub ? sub_slots_per_group(S, all_slots) : split ? 1u : kWavesPerGroup;
+    // the kernels that look up two symbols at a time, when every tensor with any chunks qualifies: they take all chunks there are
+    uint32_t pair_fields = 1;
+    for (uint32_t t = 0; t < n_tensors && pair_fields; t++) {
+        if (tensors[t].info.n_chunks == 0) continue;
+        const uint32_t k = pairs_fields(tensors[t].info);
+        if (k == 0 || tensors[t].info.xor_delta != tensors[0].info.xor_delta) pair_fields = 0;
+        else if (k > pair_fields) pair_fields = k;
+    }
+    const uint32_t pair_waves = pair_fields ? pairs_waves(fmt, pair_fields, all_slots) : 0;
+    const uint32_t spg = pair_waves ? pair_waves : sub ? sub_slots_per_group(S, all_slots) : split ? 1u : kWavesPerGroup;
     std::vector<TensorDev> descs(n_tensors);
     std::vector<WorkItem> fast_work, work;
     for (uint32_t t = 0; t < n_tensors; t++) {
@@ -332,7 +365,10 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
         const uint32_t slots = x.d_chunk_ids ? x.n_chunk_ids : info.n_chunks;
         uint32_t first_generic = 0;
         const uint64_t per_chunk = (uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(fmt);
-        if (fast && (sub || !x.d_chunk_ids)) {
+        if (pair_waves) {
+            for (uint32_t c = 0; c < slots; c += spg) fast_work.push_back({t, c});
+            first_generic = slots;
+        } else if (fast && (sub || !x.d_chunk_ids)) {
             const uint32_t n_full = (uint32_t)(info.n_elems / per_chunk);
             const uint32_t n_fast = x.d_chunk_ids ? slots : n_full;        // lists reach here only when every chunk is whole
             for (uint32_t c = 0; c < n_fast; c += spg) fast_work.push_back({t, c});
@@ -360,8 +396,8 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     plan->format = fmt; plan->streams = S; plan->n_tensors = n_tensors;
     plan->n_fast_work = (uint32_t)fast_work.size(); plan->n_work = (uint32_t)work.size();
     plan->fast_exp_kind = (uint32_t)fk.exp_kind; plan->fast_sm_kind = (uint32_t)fk.sm_kind; plan->xor_delta = tensors[0].info.xor_delta;
-    plan->fast_kernel = fk.ok ? 1u : (rings ? (e5m2 ? 7u : bf16_rings ? 6u : split ? 4u : 2u) : (sub ? (fmt == ZC_FMT_BF16 ? 5u : 3u) : 0u));
-    plan->n_rings = sub ? spg : (bf16_rings ? bf16_rings : rings);
+    plan->fast_kernel = pair_waves ? (fmt == ZC_FMT_FP8_E5M2 ? 7u : 8u) : fk.ok ? 1u : (rings ? (bf16_rings ? 6u : split ? 4u : 2u) : (sub ? (fmt == ZC_FMT_BF16 ? 5u : 3u) : 0u));
+    plan->n_rings = pair_waves ? pair_fields * 64 + pair_waves : sub ? spg : (bf16_rings ? bf16_rings : rings);
     plan->scattered = 0;
     for (uint32_t t = 0; t < n_tensors; t++) if (tensors[t].d_chunk_ids) plan->scattered = 1;
     // the second list (chunks that are not whole rows, id lists with 64 lanes) goes through the 64-lane kernel's build for
@@ -371,6 +407,8 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
         if (tensors[t].info.n_elems && (!s64_tail_ok(tensors[t].info) || tensors[t].info.xor_delta != tensors[0].info.xor_delta)) plan->tail_kernel = 0;
     // lists over containers the FP8 kernel takes: that kernel has the whole chunks of the second list
     if (plan->tail_kernel && fk.ok && plan->scattered) plan->tail_kernel = 2;
+    // short last chunks of tensors whose code suits them: the kernels that look up two symbols at a time
+    else if (plan->tail_kernel && pair_fields) { plan->tail_kernel = 3; plan->fast_sm_kind |= pair_fields << 8; }
     plan->fast_work_offset = descs_bytes; plan->work_offset = descs_bytes + fast_bytes;
     return ZC_OK;
 }
@@ -382,7 +420,7 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
     if (!d_ws || !elem_bits(plan->format) || plan->streams == 0 || plan->streams > 64 || (plan->streams & (plan->streams - 1))) return ZC_ERR_INVALID_ARG;
     const uint8_t *ws = (const uint8_t *)d_ws;
     if (plan->n_fast_work && plan->fast_kernel == 1)
-        LAUNCH_TRY(launch_decode_fp8_fast((int)plan->fast_exp_kind, (int)plan->fast_sm_kind, plan->xor_delta != 0, plan->scattered != 0, (const TensorDev *)ws,
+        LAUNCH_TRY(launch_decode_fp8_fast((int)plan->fast_exp_kind, (int)(plan->fast_sm_kind & 255u), plan->xor_delta != 0, plan->scattered != 0, (const TensorDev *)ws,
                                           (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
     else if (plan->n_fast_work && (plan->fast_kernel == 2 || plan->fast_kernel == 4))
         LAUNCH_TRY(launch_decode_s64(plan->format, plan->n_rings, plan->xor_delta != 0, plan->fast_kernel == 4, (const TensorDev *)ws,
@@ -390,8 +428,9 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
     else if (plan->n_fast_work && plan->fast_kernel == 6)
         LAUNCH_TRY(launch_decode_bf16_s64(plan->n_rings, plan->xor_delta != 0, (const TensorDev *)ws,
                                           (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
-    else if (plan->n_fast_work && plan->fast_kernel == 7)
-        LAUNCH_TRY(launch_decode_e5m2(plan->xor_delta != 0, (const TensorDev *)ws, (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
+    else if (plan->n_fast_work && (plan->fast_kernel == 8 || plan->fast_kernel == 7))
+        LAUNCH_TRY(launch_decode_pairs(plan->format, plan->n_rings / 64 == 2, plan->xor_delta != 0, plan->n_rings % 64, (const TensorDev *)ws,
+                                       (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, 0, stream));
     else if (plan->n_fast_work && plan->fast_kernel == 3)
         LAUNCH_TRY(launch_decode_fp8_sub(plan->streams, plan->xor_delta != 0, plan->scattered != 0, (const TensorDev *)ws,
                                          (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, plan->n_rings, stream));
@@ -399,7 +438,10 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
         LAUNCH_TRY(launch_decode_bf16_sub(plan->streams, plan->xor_delta != 0, (const TensorDev *)ws,
                                           (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, plan->n_rings, stream));
     else if (plan->n_fast_work) return ZC_ERR_INVALID_ARG;
-    if (plan->n_work && (plan->tail_kernel == 1 || plan->tail_kernel == 2) && plan->streams == 64)
+    if (plan->n_work && plan->tail_kernel == 3 && plan->streams == 64)
+        LAUNCH_TRY(launch_decode_pairs(plan->format, plan->fast_sm_kind >> 8 == 2, plan->xor_delta != 0, kWavesPerGroup, (const TensorDev *)ws,
+                                       (const WorkItem *)(ws + plan->work_offset), plan->n_work, nullptr, 0, stream));
+    else if (plan->n_work && (plan->tail_kernel == 1 || plan->tail_kernel == 2) && plan->streams == 64)
         LAUNCH_TRY(launch_decode_s64_tail(plan->format, plan->xor_delta != 0, (const TensorDev *)ws, (const WorkItem *)(ws + plan->work_offset), plan->n_work,
                                           nullptr, 0, plan->tail_kernel == 2, stream));
     else if (plan->n_work)

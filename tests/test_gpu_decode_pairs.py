@@ -1,0 +1,97 @@
+"""The 64-lane decoders that look up two symbols at a time: containers of the oracle decode to the original bytes, over the refill
+periods, unresolved pairs and long codes, lanes whose every period takes 32 bits, short last chunks, deltas and lists of chunk
+ids; in calls of few chunks and (by lists) of more than a thousand, which use another build.  Whole bytes: exact."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import zc_oracle as o
+from paper_2508_19263_amd import zc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+FORMATS = [zc.FMT_BF16, zc.FMT_FP8_E4M3, zc.FMT_FP8_E4M3_BYTES, zc.FMT_FP8_E5M2]
+
+
+def fields(kind, n, rng, top):
+    if kind == "geometric":                                     # codes of 1, 2, 3, ... bits, the longest as long as the limit allows
+        return np.minimum(rng.geometric(0.5, n) - 1, top - 1)
+    if kind == "wide":                                          # a few short codes and many long ones: pairs seldom fit the index
+        return np.where(rng.random(n) < 0.3, 0, rng.integers(0, top, n))
+    if kind == "uniform":
+        return rng.integers(0, top, n)
+    if kind == "lanes":                                         # lanes that only ever see the longest codes, beside lanes of the shortest
+        v = np.minimum(rng.geometric(0.5, n) - 1, top - 1)
+        return np.where((np.arange(n) // 16) % 64 == 5, top - 1, np.where((np.arange(n) // 16) % 64 == 6, 0, v))
+    return np.full(n, 1 % top)
+
+
+def tensor(fmt, n, exp_kind, sm_kind, seed):
+    rng = np.random.default_rng(seed)
+    eb, mb = {zc.FMT_BF16: (8, 7), zc.FMT_FP8_E5M2: (5, 2)}.get(fmt, (4, 3))
+    e, s = fields(exp_kind, n, rng, 1 << eb), fields(sm_kind, n, rng, 2 << mb)
+    v = ((s >> mb) << (eb + mb)) | (e << mb) | (s & ((1 << mb) - 1))
+    return torch.from_numpy(v.astype(np.uint16).view(np.int16) if fmt == zc.FMT_BF16 else v.astype(np.uint8))
+
+
+def decode(fmt, x, base, cb, tag, L=(0, 0, 0), policy=zc.POLICY_HUFF_ALL, lists=True):
+    n = x.numel()
+    print("case", tag, "fmt", fmt, "n", n, "chunk", cb, "L", L, "policy", policy, flush=True)
+    raw = x.view(torch.uint8).reshape(-1)
+    braw = None if base is None else base.view(torch.uint8).reshape(-1)
+    c = torch.from_numpy(o.compress(raw.numpy(), n, o.params(fmt, cb, L, 64, policy), xor_base=None if braw is None else braw.numpy())).to(DEV)
+    info = zc.read_info(c, check_index=True)
+    b = None if base is None else base.to(DEV)
+    out = torch.full((raw.numel() + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+    zc.decompress(c, info, out=out, xor_base=b)
+    assert torch.equal(out[:raw.numel()].cpu(), raw), tag
+    assert bool((out[raw.numel():] == 0x5A).all()), tag        # nothing behind the tensor
+    if not lists:
+        return info
+    rng = np.random.default_rng(n)
+    for n_ids in (5, 1200):
+        ids = rng.integers(0, info.n_chunks + 1, n_ids).astype(np.int32)      # repeated, and some out of range
+        got, _ = zc.decompress_chunks(c, info, torch.from_numpy(ids).to(DEV), out=torch.full((n_ids * cb,), 0x5A, dtype=torch.uint8, device=DEV), xor_base=b)
+        got = got.cpu().reshape(n_ids, cb)
+        for i in list(range(min(n_ids, 40))) + [n_ids - 1]:
+            want = raw[int(ids[i]) * cb:(int(ids[i]) + 1) * cb] if ids[i] < info.n_chunks else raw[:0]
+            assert torch.equal(got[i][:want.numel()], want) and bool((got[i][want.numel():] == 0x5A).all()), (tag, n_ids, i)
+    return info
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_fields_and_periods(fmt):
+    size = 2 if fmt == zc.FMT_BF16 else 1
+    limits = {zc.FMT_FP8_E4M3: (4, 6, 8, 12)}.get(fmt, (8, 11, 12, 16))
+    for i, (e, s) in enumerate((("geometric", "uniform"), ("geometric", "geometric"), ("wide", "wide"), ("lanes", "lanes"), ("uniform", "geometric"), ("geometric", "constant"))):
+        for L in limits:
+            n = (9 * 2048 + (0, 2, 514, 1024, 1026, 2046)[i]) // size
+            decode(fmt, tensor(fmt, n, e, s, 100 * i + L), None, 2048, "%s/%s" % (e, s), L=(L, L, 0), policy=i & 1)
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_rows_ends_and_deltas(fmt):
+    size = 2 if fmt == zc.FMT_BF16 else 1
+    for i, nbytes in enumerate((2, 16, 30, 1022, 1024, 1026, 2048, 3 * 1024 + 8, 5 * 1024, 6 * 1024 + 1000, 7 * 1024, 9 * 1024 + 16, 65536 + 2, 3 * 65536 - 2)):
+        x, b = tensor(fmt, nbytes // size, "geometric", "uniform", i), tensor(fmt, nbytes // size, "wide", "geometric", i + 50)
+        decode(fmt, x, None, 65536, "rows", lists=False)
+        decode(fmt, x, b, 65536, "delta", lists=False)
+    x, b = tensor(fmt, 20 * 4096 // size + 9, "geometric", "uniform", 3), tensor(fmt, 20 * 4096 // size + 9, "geometric", "geometric", 4)
+    decode(fmt, x, b, 4096, "delta lists")
+    decode(fmt, x, None, 3088, "chunks of three rows and one run")
+
+
+def test_flat_three_bit_code_of_e5m2():
+    # exactly equal counts of the eight sign+mantissa values, every number of whole rows modulo four before the last one
+    rng = np.random.default_rng(11)
+    for rows in range(6):
+        for extra in (0, 16, 200, 1008):
+            n = (rows * 1024 + extra) // 8 * 8
+            if n == 0:
+                continue
+            sm = rng.permutation(np.repeat(np.arange(8), n // 8))
+            e = np.minimum(rng.geometric(0.4, n) - 1, 31)
+            x = torch.from_numpy((((sm >> 2) << 7) | (e << 2) | (sm & 3)).astype(np.uint8))
+            info = decode(zc.FMT_FP8_E5M2, x, None, 262144, "flat3 rows %d + %d" % (rows, extra), lists=False)
+            if n >= 64:
+                assert list(info.code_len[1][:9]) == [3] * 8 + [0]
