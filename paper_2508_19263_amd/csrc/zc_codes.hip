@@ -68,13 +68,13 @@ __device__ void build_rows(const W *lw, W *pw, W *row0, W *row1, uint32_t n, int
         const uint32_t n_pk = m / 2;
         if (tid < n_pk) pw[tid] = below[2 * tid] + below[2 * tid + 1];
         __syncthreads();
-        // Both searches of a thread advance together, a fixed nine halving steps each (rows hold fewer than
-        // 512 items): the packages strictly cheaper than leaf `tid` go before it, the leaves that cost no
-        // more than package `tid` go before that.
+        // Both searches of a thread advance together, in halving steps from the largest power of two that either list
+        // reaches (an LDS round trip each: nine for 256 leaves, five for 16): the packages strictly cheaper than leaf `tid`
+        // go before it, the leaves that cost no more than package `tid` go before that.
         const W wl = tid < n ? lw[tid] : (W)0, wp = tid < n_pk ? pw[tid] : (W)0;
         uint32_t below_leaf = 0, below_pack = 0;
-#pragma unroll
-        for (uint32_t step = 256; step > 0; step >>= 1) {
+#pragma unroll 1
+        for (uint32_t step = 1u << (31 - __clz((int)(n > n_pk ? n : n_pk))); step > 0; step >>= 1) {
             const uint32_t a = below_leaf + step, b = below_pack + step;
             const W pa = pw[(a <= n_pk ? a : 1u) - 1], lb = lw[(b <= n ? b : 1u) - 1];
             if (a <= n_pk && pa < wl) below_leaf = a;
@@ -89,6 +89,18 @@ __device__ void build_rows(const W *lw, W *pw, W *row0, W *row1, uint32_t n, int
         m = n + n_pk;
         if (tid == 0) row_size[d] = m;
         __syncthreads();
+        // A row whose weights are those of the row below has nothing but copies of itself above it (a code that the limit does
+        // not bind: 256 nearly equally likely symbols are through after nine of sixteen rows).  Not looked for in the first rows.
+        if (limit - d >= 7 && d > 1 && row_size[d + 1] == m) {
+            bool same = true;
+            for (uint32_t i = tid; i < m; i += kCodeThreads) same = same && out[i] == below[i];
+            if (__syncthreads_and(same ? 1 : 0)) {
+                for (uint32_t i = tid; i < (uint32_t)(d - 1) * (kMaxRow / 32); i += kCodeThreads) leaf_bits[1 + i / (kMaxRow / 32)][i % (kMaxRow / 32)] = leaf_bits[d][i % (kMaxRow / 32)];
+                if (tid >= 1 && tid < (uint32_t)d) row_size[tid] = m;
+                __syncthreads();
+                return;
+            }
+        }
         below = out;
         W *const swap = out; out = other; other = swap;
     }
@@ -101,10 +113,11 @@ __global__ __launch_bounds__(kCodeThreads) void k_codes(TensorDev *descs, const 
     __shared__ unsigned long long h[256];              // the field's histogram by symbol
     __shared__ unsigned long long lw[256];             // leaf weights, cheapest first
     __shared__ unsigned long long row[2][kMaxRow];     // the row below and the row being merged
-    __shared__ unsigned long long pw[256];             // package weights of the row below
+    __shared__ __attribute__((aligned(16))) unsigned long long pw[256];      // package weights of the row below
     __shared__ uint32_t leaf_bits[17][kMaxRow / 32];   // per row: which items are leaves
+    __shared__ uint32_t leaves_before[17][kMaxRow / 32];
     __shared__ uint32_t row_size[17], leaves_in[17];
-    __shared__ uint32_t count[17], next[17];
+    __shared__ uint32_t wave_count[kCodeThreads / 64][17], next[17];
     __shared__ uint8_t order[256], len[256];
     __shared__ unsigned long long pay_s, sum_s;
     __shared__ uint32_t n_s, konst_s, flat_s, lmax_s;
@@ -119,7 +132,7 @@ __global__ __launch_bounds__(kCodeThreads) void k_codes(TensorDev *descs, const 
 
     // ---- the field's histogram
     h[tid] = 0; len[tid] = 0;
-    if (tid < 17) { row_size[tid] = 0; leaves_in[tid] = 0; count[tid] = 0; next[tid] = 0; }
+    if (tid < 17) { row_size[tid] = 0; leaves_in[tid] = 0; next[tid] = 0; }
     for (uint32_t i = tid; i < 17 * (kMaxRow / 32); i += kCodeThreads) (&leaf_bits[0][0])[i] = 0;
     if (tid == 0) { pay_s = 0; sum_s = 0; n_s = 0; konst_s = 0; flat_s = 0; lmax_s = 0; }
     __syncthreads();
@@ -157,10 +170,14 @@ __global__ __launch_bounds__(kCodeThreads) void k_codes(TensorDev *descs, const 
         h32[tid] = present ? (uint32_t)hv : 0xFFFFFFFFu;
         __syncthreads();
         const uint32_t mine = h32[tid];
+        const uint4 *h4 = reinterpret_cast<const uint4 *>(h32);
 #pragma unroll 8
-        for (uint32_t u = 0; u < A; u++) {
-            const uint32_t hu = h32[u];
-            rank += (hu < mine || (hu == mine && u < tid)) ? 1u : 0u;
+        for (uint32_t u = 0; u < A; u += 4) {
+            const uint4 q = h4[u / 4];
+            rank += (q.x < mine || (q.x == mine && u < tid)) ? 1u : 0u;
+            rank += (q.y < mine || (q.y == mine && u + 1 < tid)) ? 1u : 0u;
+            rank += (q.z < mine || (q.z == mine && u + 2 < tid)) ? 1u : 0u;
+            rank += (q.w < mine || (q.w == mine && u + 3 < tid)) ? 1u : 0u;
         }
     } else {
 #pragma unroll 8
@@ -186,23 +203,21 @@ __global__ __launch_bounds__(kCodeThreads) void k_codes(TensorDev *descs, const 
             build_rows<uint32_t>(lw32, reinterpret_cast<uint32_t *>(pw), reinterpret_cast<uint32_t *>(row[0]), reinterpret_cast<uint32_t *>(row[1]),
                                  n, limit, leaf_bits, row_size);
         } else build_rows<unsigned long long>(lw, pw, row[0], row[1], n, limit, leaf_bits, row_size);
-        // ---- walk the budget down from the top row (one wavefront: 16 mask words per row)
+        // ---- walk the budget down from the top row.  leaves_before[d][w]: leaves in the first 32 * w items of row d, so that a
+        // row costs the walk one LDS round trip
+        for (uint32_t i = tid; i < 17 * (kMaxRow / 32); i += kCodeThreads) {
+            const uint32_t d = i / (kMaxRow / 32), w = i % (kMaxRow / 32);
+            uint32_t c = 0;
+            for (uint32_t v = 0; v < w; v++) c += (uint32_t)__popc(leaf_bits[d][v]);
+            leaves_before[d][w] = c;
+        }
+        __syncthreads();
         if (tid < 64) {
             uint32_t budget = 2 * n - 2;
             for (int d = 1; d <= limit && budget > 0; d++) {
                 const uint32_t b = budget < row_size[d] ? budget : row_size[d];
-                uint32_t leaves;
-                if (d == limit) leaves = b;
-                else {
-                    uint32_t c = 0;
-                    if (tid < kMaxRow / 32) {
-                        const uint32_t lo = tid * 32;
-                        const uint32_t take = b > lo ? (b - lo >= 32 ? 0xFFFFFFFFu : (1u << (b - lo)) - 1) : 0u;
-                        c = (uint32_t)__popc(leaf_bits[d][tid] & take);
-                    }
-                    for (int o = 8; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-                    leaves = __shfl(c, 0, 64);
-                }
+                // (b is below 512: a row holds at most 2n - 1 items)
+                const uint32_t leaves = d == limit ? b : leaves_before[d][b / 32] + (uint32_t)__popc(leaf_bits[d][b / 32] & ((1u << (b % 32)) - 1));
                 if (tid == 0) leaves_in[d] = leaves;
                 budget = 2 * (b - leaves);
             }
@@ -229,9 +244,13 @@ __global__ __launch_bounds__(kCodeThreads) void k_codes(TensorDev *descs, const 
 
     // ---- canonical codes in (length, symbol) order
     const uint32_t my_len = tid < A ? len[tid] : 0u;
+    uint32_t before = 0;                               // symbols below this one with the same length: first those of the wavefront
+#pragma unroll
     for (uint32_t l = 1; l <= 16; l++) {
-        const uint32_t c = (uint32_t)__popcll(__ballot(my_len == l));
-        if ((tid & 63) == 0 && c) atomicAdd(&count[l], c);
+        const uint64_t m = __ballot(my_len == l);
+        const uint32_t c = (uint32_t)__popcll(m);
+        if (my_len == l) before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        if ((tid & 63) == 0) wave_count[tid >> 6][l] = c;
     }
     {
         const uint32_t c = (uint32_t)__popcll(__ballot(tid < A && my_len == sb));
@@ -239,15 +258,17 @@ __global__ __launch_bounds__(kCodeThreads) void k_codes(TensorDev *descs, const 
     }
     __syncthreads();
     if (tid == 0) {
-        uint32_t code = 0;
-        for (int l = 1; l <= 16; l++) { code = (code + (l > 1 ? count[l - 1] : 0u)) << 1; next[l] = code; }
+        uint32_t code = 0, below = 0;
+        for (int l = 1; l <= 16; l++) {
+            code = (code + below) << 1;
+            below = wave_count[0][l] + wave_count[1][l] + wave_count[2][l] + wave_count[3][l];
+            next[l] = code;
+        }
     }
     __syncthreads();
     uint32_t code = 0;
     if (my_len) {
-        uint32_t before = 0;
-#pragma unroll 8
-        for (uint32_t u = 0; u < tid; u++) before += len[u] == my_len ? 1u : 0u;
+        for (uint32_t w = 0; w < tid >> 6; w++) before += wave_count[w][my_len];
         code = next[my_len] + before;
     }
 
