@@ -486,12 +486,15 @@ private:
     // The tail of every call that reads sizes back.  When every destination can hold the worst case, the sizes
     // need not be known on the host first: the encoder is queued right behind the scan and the sizes are read back
     // meanwhile.  Otherwise the host waits for the sizes and checks them before anything is written.  `landing`:
-    // page-locked, first the ScanOut of every tensor, then extra_bytes copied from d_extra.
-    zc_status encode_and_read_sizes(LandingLease &landing, const void *d_extra, uint64_t extra_bytes)
+    // page-locked, first the ScanOut of every tensor, then, when with_blobs, the tensors' blobs (one copy where the scan
+    // kernel has placed every tensor: the sizes then come at the end of the blobs).
+    zc_status encode_and_read_sizes(LandingLease &landing, bool with_blobs)
     {
         const uint64_t scan_bytes = (uint64_t)T * sizeof(ScanOut);
-        HIP_TRY(hipMemcpyAsync(landing.ptr, ws + w.scan, scan_bytes, hipMemcpyDeviceToHost, hs));
-        if (extra_bytes) HIP_TRY(hipMemcpyAsync(landing.ptr + scan_bytes, d_extra, extra_bytes, hipMemcpyDeviceToHost, hs));
+        static_assert(kHeaderBytes + 3 * 256 + sizeof(ScanOut) <= kBlobBytes, "header, tables and sizes of a tensor fit its blob");
+        const bool one_copy = with_blobs && !q.chained;
+        if (!one_copy) HIP_TRY(hipMemcpyAsync(landing.ptr, ws + w.scan, scan_bytes, hipMemcpyDeviceToHost, hs));
+        if (with_blobs) HIP_TRY(hipMemcpyAsync(landing.ptr + scan_bytes, ws + w.blobs, (uint64_t)T * kBlobBytes, hipMemcpyDeviceToHost, hs));
         if (roomy) {
             // wait for the copies only, not for the encoder queued behind them
             hipEvent_t copied;
@@ -503,6 +506,9 @@ private:
             if (s1) return s1;
             if (e2 != hipSuccess) return ZC_ERR_DEVICE;
         } else HIP_TRY(hipStreamSynchronize(hs));
+        if (one_copy)
+            for (uint32_t t = 0; t < T; t++)
+                std::memcpy(landing.ptr + (uint64_t)t * sizeof(ScanOut), landing.ptr + scan_bytes + (uint64_t)(t + 1) * kBlobBytes - sizeof(ScanOut), sizeof(ScanOut));
         const ScanOut *scan = reinterpret_cast<const ScanOut *>(landing.ptr);
         for (uint32_t t = 0; t < T; t++) {
             if (scan[t].total_units == 0xFFFFFFFFu) return ZC_ERR_DEVICE;      // a workgroup of the one-pass kernel gave up waiting in its chain
@@ -683,7 +689,7 @@ private:
         if (no_sync) return queue_encoders_without_sizes();
         LandingLease landing((uint64_t)T * (sizeof(ScanOut) + kBlobBytes));
         if (!landing.ptr) return ZC_ERR_DEVICE;
-        st = encode_and_read_sizes(landing, ws + w.blobs, (uint64_t)T * kBlobBytes);
+        st = encode_and_read_sizes(landing, true);
         // what the device decided, for the caller's zc_info
         const uint8_t *got = landing.ptr + (uint64_t)T * sizeof(ScanOut);
         for (uint32_t t = 0; t < T; t++) {
@@ -843,7 +849,7 @@ private:
         if (no_sync) return queue_encoders_without_sizes();
         LandingLease scan_landing((uint64_t)T * sizeof(ScanOut));
         if (!scan_landing.ptr) return ZC_ERR_DEVICE;
-        st = encode_and_read_sizes(scan_landing, nullptr, 0);
+        st = encode_and_read_sizes(scan_landing, false);
         for (uint32_t t = 0; t < T; t++) tensors[t].info.total_bytes = tensors[t].out_bytes;
         return st;
     }

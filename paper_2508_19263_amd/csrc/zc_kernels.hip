@@ -451,7 +451,7 @@ int launch_encode(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_d
 // the container (when there is one), and the per-field totals for the host.
 
 __global__ __launch_bounds__(1024) void k_scan(const TensorDev *descs, int n_fields, int reversed, int skip_routes, const uint32_t *units, ScanOut *out,
-                                               const uint8_t *blobs, uint32_t blob_bytes)
+                                               uint8_t *blobs, uint32_t blob_bytes)
 {
     __shared__ uint32_t wave_sum[16];
     __shared__ uint32_t carry_s;
@@ -516,12 +516,14 @@ __global__ __launch_bounds__(1024) void k_scan(const TensorDev *descs, int n_fie
         for (int f = 0; f < n_fields; f++) o.field_units[f] = field_units[f];
         o.total_units = carry_s;
         out[blockIdx.x] = o;
+        // at the end of the blob too (its last bytes are never used): a caller that reads the blobs back has the sizes with them
+        if (blobs) *reinterpret_cast<ScanOut *>(blobs + (uint64_t)blockIdx.x * blob_bytes + blob_bytes - sizeof(ScanOut)) = o;
         if (d.comp) *reinterpret_cast<uint64_t *>(d.comp + 48) = d.payload_off + 16ull * carry_s;
     }
 }
 
 int launch_scan(const TensorDev *d_descs, uint32_t n_tensors, int n_fields, bool reversed, int skip_routes, const uint32_t *d_units, ScanOut *d_out,
-                const uint8_t *d_blobs, uint32_t blob_bytes, void *stream)
+                uint8_t *d_blobs, uint32_t blob_bytes, void *stream)
 {
     if (n_tensors == 0) return 0;
     hipLaunchKernelGGL(k_scan, dim3(n_tensors), dim3(1024), 0, (hipStream_t)stream, d_descs, n_fields, reversed ? 1 : 0, skip_routes, d_units, d_out, d_blobs,
