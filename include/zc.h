@@ -347,7 +347,7 @@ typedef struct {
     uint32_t tail_kernel;                       /* the second work list (chunks that are not whole rows, id lists with 64 lanes):
                                                    0 generic kernel, 1 the 64-lane kernel's build for such chunks (two-field formats),
                                                    2 = 1 leaving whole chunks to the FP8 kernel's build for id lists, 3 the kernels
-                                                   that look up two symbols at a time */
+                                                   that look up two symbols at a time, 4 the kernel for FP4's short last chunks */
     uint64_t fast_work_offset, work_offset;     /* byte offsets of the two work lists in d_ws */
 } zc_batch_plan;
 zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors, void *d_ws, uint64_t ws_bytes,

@@ -230,6 +230,115 @@ int launch_decode_s64_tail(uint32_t fmt, bool xor_delta, const TensorDev *d_desc
 }
 
 // ---------------------------------------------------------------------------------------
+// The short last chunk of an FP4 tensor whose element fields are stored plainly (what FP4 elements come to), with 64 lanes: its
+// rows do not depend on each other, so fifteen wavefronts take them in turn while the first decodes the block scales.  Bound by
+// the latency of the scales' chain.  One chunk per work item.
+constexpr uint32_t kFp4TailWaves = 16;
+template <int FMT, bool XOR>
+__global__ __launch_bounds__(64 * kFp4TailWaves) void k_decode_fp4_tail(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single, uint32_t first_slot)
+{
+    using F_ = Fmt<FMT>;
+    static_assert(F_::NF == 3, "element fields and block scales");
+    constexpr int SB = F_::SB, G = F_::G;
+    __shared__ __attribute__((aligned(16))) uint32_t ring[kRing2Words];
+    __shared__ FieldTab tab;
+    __shared__ TensorDev dsh;
+    WorkItem it;
+    if (use_single) { it.tensor = 0; it.first = first_slot; }
+    else it = work[blockIdx.x];
+    if (threadIdx.x == 0) dsh = use_single ? single : descs[it.tensor];
+    __syncthreads();
+    const TensorDev &d = dsh;
+    const uint32_t kind0 = uniform32(d.kind[0]), kind1 = uniform32(d.kind[1]), kind2 = uniform32(d.kind[2]);
+    const uint32_t chunk = uniform32(it.first), cb = uniform32(d.chunk_bytes);
+    const uint64_t E = (uint64_t)cb * 2, before = (uint64_t)chunk * E, n_elems = uniform64(d.n_elems);
+    // whole workgroup; the host never asks for these
+    if (kind0 == KIND_HUFF || kind1 == KIND_HUFF || uniform32(d.streams) != 64 || d.ids || chunk >= uniform32(d.n_chunks) || n_elems <= before) return;
+    if (kind2 == KIND_HUFF) build_field_tab(tab, d.comp + d.table_off[2], 256, d.lmax[2]);
+    const uint32_t n = (uint32_t)(n_elems - before < E ? n_elems - before : E), nbytes = (n + 1) / 2;
+    const uint8_t *comp = reinterpret_cast<const uint8_t *>(uniform64((uint64_t)d.comp));
+    const uint64_t payload = uniform64(d.payload_off), total = uniform64(d.total_bytes);
+    const uint8_t *sp[3];
+    uint32_t sb[3];
+#pragma unroll
+    for (int f = 0; f < 3; f++)
+        if (!stream_range(d, comp, f, chunk, payload, total, sp[f], sb[f])) return;      // damaged index: leave the chunk alone
+    const uint32_t lane = threadIdx.x & 63, wave = uniform32(threadIdx.x >> 6);
+    if (wave == 0) {
+        // block scales: 16 per run, rows of 1024, the last row incomplete
+        const uint32_t ns = n / F_::SCALE, whole = ns / 1024, tail_at = whole * 1024 + lane * 16;
+        const uint32_t tail = ns > tail_at ? (ns - tail_at < 16u ? ns - tail_at : 16u) : 0u;
+        uint8_t *const out = reinterpret_cast<uint8_t *>(uniform64((uint64_t)d.scales_out)) + (uint64_t)chunk * (E / F_::SCALE);
+        const __amdgpu_buffer_rsrc_t r2 = make_rsrc(sp[2], sb[2]);
+        const uint32_t p2 = uniform32(d.period[2]);
+        const uint64_t K2 = splat(uniform32(d.konst[2]), 8);
+        HuffStream H;
+        if (kind2 == KIND_HUFF) huff_open(H, tab, r2, reinterpret_cast<char *>(ring), lane, kRing2Words, whole > 0 || tail > 0);
+        for (uint32_t row = 0; row < whole; row++) {
+            uint64_t P0 = 0, P1 = 0;
+            if (kind2 == KIND_HUFF) huff_run<8, 16>(H, tab, p2, P0, P1, lane, 16u, row + 1 == whole ? tail : 16u);
+            else plain_run<8, 16>(kind2, r2, row, lane, K2, P0, P1);
+            store_run(out + row * 1024 + lane * 16, make_uint4((uint32_t)P0, (uint32_t)(P0 >> 32), (uint32_t)P1, (uint32_t)(P1 >> 32)), 16);
+        }
+        if (ns % 1024) {
+            uint64_t P0 = 0, P1 = 0;
+            if (kind2 == KIND_HUFF) huff_run<8, 16>(H, tab, p2, P0, P1, lane, tail, 0u);
+            else plain_tail<8, 16>(kind2, r2, whole, lane, tail, K2, P0, P1);
+            if (tail) store_run(out + tail_at, make_uint4((uint32_t)P0, (uint32_t)(P0 >> 32), (uint32_t)P1, (uint32_t)(P1 >> 32)), tail);
+        }
+        return;
+    }
+    const uint32_t rows = nbytes / 1024;
+    const __amdgpu_buffer_rsrc_t r0 = make_rsrc(sp[0], sb[0]), r1 = make_rsrc(sp[1], sb[1]);
+    const uint64_t K0 = splat(uniform32(d.konst[0]), SB), K1 = splat(uniform32(d.konst[1]), SB);
+    uint8_t *const dst = reinterpret_cast<uint8_t *>(uniform64((uint64_t)d.dst)) + (uint64_t)chunk * cb;
+    const uint8_t *const base = XOR ? reinterpret_cast<const uint8_t *>(uniform64((uint64_t)d.base)) + (uint64_t)chunk * cb : nullptr;
+    for (uint32_t row = wave - 1; row < rows; row += kFp4TailWaves - 1) {
+        uint64_t P0 = 0, P1 = 0, Q = 0;
+        plain_run<SB, G>(kind0, r0, row, lane, K0, P0, Q);
+        plain_run<SB, G>(kind1, r1, row, lane, K1, P1, Q);
+        uint4 v = join_run4<FMT>(P0, 0, P1, 0);
+        if (XOR) v = xor4(v, load_run(base + row * 1024 + lane * 16, 16));
+        store_run(dst + row * 1024 + lane * 16, v, 16);
+    }
+    if (wave == kFp4TailWaves - 1 && nbytes % 1024) {
+        const uint32_t at = rows * 1024 + lane * 16, mine = nbytes > at ? (nbytes - at < 16u ? nbytes - at : 16u) : 0u;
+        const uint32_t nel = mine ? (n - at * 2 < 32u ? n - at * 2 : 32u) : 0u, nsym = (nel + F_::GRP - 1) / F_::GRP;
+        uint64_t P0 = 0, P1 = 0, Q = 0;
+        plain_tail<SB, G>(kind0, r0, rows, lane, nsym, K0, P0, Q);
+        plain_tail<SB, G>(kind1, r1, rows, lane, nsym, K1, P1, Q);
+        if (mine) {
+            uint4 v = join_run4<FMT>(P0, 0, P1, 0);
+            if (XOR) v = xor4(v, load_run(base + at, mine));
+            store_run(dst + at, v, mine);
+        }
+    }
+}
+
+// single: one tensor, its chunk first_slot (n_work 1)
+int launch_decode_fp4_tail(uint32_t fmt, bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev *single, uint32_t first_slot,
+                           void *stream)
+{
+    if (n_work == 0) return 0;
+    hipStream_t st = (hipStream_t)stream;
+    const TensorDev s = single ? *single : TensorDev{};
+    const int use_single = single ? 1 : 0;
+    const dim3 grid(n_work), block(64 * kFp4TailWaves);
+#define ZC_TAIL(F) \
+    if (xor_delta) hipLaunchKernelGGL((k_decode_fp4_tail<F, true>), grid, block, 0, st, d_descs, d_work, s, use_single, first_slot); \
+    else hipLaunchKernelGGL((k_decode_fp4_tail<F, false>), grid, block, 0, st, d_descs, d_work, s, use_single, first_slot); \
+    break
+    switch (fmt) {
+    case ZC_FMT_FP4_E2M1_MX: ZC_TAIL(ZC_FMT_FP4_E2M1_MX);
+    case ZC_FMT_FP4_E2M1_MX_BYTES: ZC_TAIL(ZC_FMT_FP4_E2M1_MX_BYTES);
+    case ZC_FMT_FP4_E2M1_NV: ZC_TAIL(ZC_FMT_FP4_E2M1_NV);
+    default: return 1;
+    }
+#undef ZC_TAIL
+    return (int)hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------
 // BF16 with 64 lanes per chunk and whole chunks, exponent field table decoded and the sign+mantissa field either
 // table decoded on the same refill period (checkpoint deltas, Sec. 3.1 / 4.1) or stored plainly (weights): the
 // same streams and rings as above with the per-symbol work cut down for this format.

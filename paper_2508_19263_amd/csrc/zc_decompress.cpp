@@ -236,6 +236,8 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         // the formats of two fields), geometries no specialised kernel takes
         const uint32_t n_work = (slots - first_slot + cpi - 1) / cpi;
         if (pairs) LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, kWavesPerGroup, nullptr, nullptr, n_work, &d, first_slot, stream));
+        else if (info.n_fields == 3 && !by_ids && s64_split_ok(info) && slots - first_slot == 1)
+            LAUNCH_TRY(launch_decode_fp4_tail(info.format, info.xor_delta != 0, nullptr, nullptr, 1, &d, first_slot, stream));
         else if (s64_tail_ok(info)) LAUNCH_TRY(launch_decode_s64_tail(info.format, info.xor_delta != 0, nullptr, nullptr, n_work, &d, first_slot, false, stream));
         else LAUNCH_TRY(launch_decode(info.format, nullptr, nullptr, n_work, cpi, &d, first_slot, stream));
     }
@@ -409,6 +411,8 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     if (plan->tail_kernel && fk.ok && plan->scattered) plan->tail_kernel = 2;
     // short last chunks of tensors whose code suits them: the kernels that look up two symbols at a time
     else if (plan->tail_kernel && pair_fields) { plan->tail_kernel = 3; plan->fast_sm_kind |= pair_fields << 8; }
+    // FP4 sets whose whole chunks went to the 64-lane kernel's shared build: what is left is a short last chunk per tensor
+    if (split && is_fp4(fmt) && !plan->scattered) plan->tail_kernel = 4;
     plan->fast_work_offset = descs_bytes; plan->work_offset = descs_bytes + fast_bytes;
     return ZC_OK;
 }
@@ -438,7 +442,10 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
         LAUNCH_TRY(launch_decode_bf16_sub(plan->streams, plan->xor_delta != 0, (const TensorDev *)ws,
                                           (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, plan->n_rings, stream));
     else if (plan->n_fast_work) return ZC_ERR_INVALID_ARG;
-    if (plan->n_work && plan->tail_kernel == 3 && plan->streams == 64)
+    if (plan->n_work && plan->tail_kernel == 4 && plan->streams == 64)
+        LAUNCH_TRY(launch_decode_fp4_tail(plan->format, plan->xor_delta != 0, (const TensorDev *)ws, (const WorkItem *)(ws + plan->work_offset), plan->n_work,
+                                          nullptr, 0, stream));
+    else if (plan->n_work && plan->tail_kernel == 3 && plan->streams == 64)
         LAUNCH_TRY(launch_decode_pairs(plan->format, plan->fast_sm_kind >> 8 == 2, plan->xor_delta != 0, kWavesPerGroup, (const TensorDev *)ws,
                                        (const WorkItem *)(ws + plan->work_offset), plan->n_work, nullptr, 0, stream));
     else if (plan->n_work && (plan->tail_kernel == 1 || plan->tail_kernel == 2) && plan->streams == 64)
