@@ -100,7 +100,7 @@ TensorLists device_code_lists(const Geometry &g, const CompressShape &sh, uint64
     if (fast_shape) L.fast = {0, whole_chunks, sh.fast_step};
     if (sh.whole_shape) L.whole = {0, whole_chunks, sh.whole_step};
     else if (fast_shape) L.other = {0, whole_chunks, sh.cpi};
-    L.slow = {(fast_shape || sh.whole_shape) ? whole_chunks : 0u, (uint32_t)nc, sh.split_rest ? 1u : sh.cpi};
+    L.slow = {(fast_shape || sh.whole_shape) ? whole_chunks : 0u, (uint32_t)nc, (sh.split_rest || sh.fp4_tails) ? 1u : sh.cpi};
     return L;
 }
 
@@ -112,6 +112,7 @@ CompressShape compress_shape(const Geometry &g, bool device_codes, uint64_t all_
     sh.whole_shape = g.S == 64 && g.chunk_bytes % 1024 == 0;
     sh.split_all = g.S == 64 && g.nf == 2 && g.chunk_bytes >= kSplitChunkBytes && all_chunks <= split_chunk_limit(g.fmt, delta);
     sh.split_rest = sh.split_all || (sh.whole_shape && g.nf == 2);      // (what is left over is a tensor's short last chunk)
+    sh.fp4_tails = sh.whole_shape && g.nf == 3;
     sh.lanes = device_codes && !sh.split_all && lane_counts_shape(g);
     sh.lanes8 = device_codes && !sh.split_all && lane_counts8_shape(g);
     sh.lanes_e5m2 = device_codes && !sh.split_all && lane_counts_e5m2_shape(g);
@@ -177,7 +178,8 @@ zc_status CompressQueue::queue_sizes_and_scan() const
     LAUNCH_TRY(launch_sizes(g.fmt, 0, 0x6, d_descs(), d_list(w.other_work), n_other, d_enc(), d_units(), stream));
     // what the whole-chunk kernels leave over: with 64 lanes and chunks of whole rows only a tensor's short last chunk, and
     // every chunk of a call of few, sixteen wavefronts each; otherwise every chunk, walked by the generic size pass
-    if (sh.split_rest) LAUNCH_TRY(launch_sizes_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
+    if (sh.fp4_tails) LAUNCH_TRY(launch_fp4_tails(g.fmt, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
+    else if (sh.split_rest) LAUNCH_TRY(launch_sizes_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
     else LAUNCH_TRY(launch_sizes(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
     // the chained kernel has placed and written the tensors of its route (FP8: 1, BF16: 2) itself
     LAUNCH_TRY(launch_scan(d_descs(), T, (int)g.nf, g.reversed, chained ? (sh.bf16 ? 0x4 : 0x2) : 0, d_units(), (ScanOut *)(ws + w.scan), stats_only ? nullptr : ws + w.blobs,
@@ -194,7 +196,8 @@ zc_status CompressQueue::queue_encoders() const
     LAUNCH_TRY(launch_encode(g.fmt, sh.whole_mode, 0x6, d_descs(), d_list(w.whole_work), n_whole, d_enc(), stream));
     if (sh.rows8) LAUNCH_TRY(launch_encode_bf16(g.fmt, d_descs(), d_list(w.whole_work), n_whole, d_enc(), stream));
     LAUNCH_TRY(launch_encode(g.fmt, 0, 0x6, d_descs(), d_list(w.other_work), n_other, d_enc(), stream));
-    if (sh.split_rest) LAUNCH_TRY(launch_encode_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
+    if (sh.fp4_tails) LAUNCH_TRY(launch_fp4_tails(g.fmt, 1, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), nullptr, stream));
+    else if (sh.split_rest) LAUNCH_TRY(launch_encode_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
     else LAUNCH_TRY(launch_encode(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
     return ZC_OK;
 }
@@ -823,7 +826,7 @@ private:
             const uint32_t n_whole = (descs[t].route != 1 && sh.whole_shape) ? (uint32_t)whole_chunks : 0;
             append(fast_work, t, {0, n_fast, chained ? chained_step() : sh.fast_step});
             append(whole_work, t, {0, n_whole, sh.whole_step});
-            append(slow_work, t, {n_fast + n_whole, (uint32_t)ncs[t], sh.split_rest ? 1u : sh.cpi});
+            append(slow_work, t, {n_fast + n_whole, (uint32_t)ncs[t], (sh.split_rest || sh.fp4_tails) ? 1u : sh.cpi});
         }
         if (codes_out) *codes_out = codes;
         if (!chained) order_for_xcds(fast_work);                   // the chain runs through the items in the list's order

@@ -101,6 +101,7 @@ struct CompressShape {
     bool whole_shape;           // 64 lanes, chunks of whole 1 KiB rows: the generic encoder's whole-chunk build
     bool split_rest;            // 64 lanes, two fields: what the whole-chunk kernels leave over goes through the kernels that give a chunk sixteen wavefronts
     bool split_all;             // so few chunks that all of them do (then no other chunk list and no counts per lane)
+    bool fp4_tails;             // FP4, 64 lanes, chunks of whole rows: what is left over is a tensor's short last chunk, for k_encode_fp4_tail
     int whole_mode;             // 2: one whole chunk per work item, shared by its four wavefronts
     uint32_t whole_step, fast_step, cpi;    // chunks per work item of the whole-chunk list, the fast list, the generic kernels
 };

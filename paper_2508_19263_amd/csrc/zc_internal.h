@@ -137,6 +137,7 @@ int launch_copy_chunked(const void *d_src, void *d_dst, uint64_t bytes, uint32_t
 // by the workgroup's four wavefronts
 int launch_sizes(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                  const uint32_t *d_enc_tables, uint32_t *d_units, void *stream);
+int launch_fp4_tails(uint32_t fmt, int write, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream);
 // d_blobs: per tensor the header and code-length tables to put at the start of its container (blob_bytes apart), or null
 // (whose last sizeof(ScanOut) bytes it fills as it does d_out)
 int launch_scan(const TensorDev *d_descs, uint32_t n_tensors, int n_fields, bool reversed, int skip_routes, const uint32_t *d_units, ScanOut *d_out, uint8_t *d_blobs,

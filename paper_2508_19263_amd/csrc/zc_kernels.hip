@@ -278,6 +278,8 @@ __global__ __launch_bounds__(256) void k_encode(const TensorDev *descs, const Wo
     const WorkItem it = work[blockIdx.x];
     // whole workgroup: these chunks belong to a specialised kernel (bit r of skip_routes: leave tensors of route r alone)
     if ((skip_routes >> descs[it.tensor].route) & 1) return;
+    // whole workgroup: short last chunks that k_encode_fp4_tail takes (what shared_chunk asks of the build for any chunks)
+    if (!WHOLE && F_::NF == 3 && shared_chunk && descs[it.tensor].kind[0] != 0 && descs[it.tensor].kind[1] != 0) return;
     if (threadIdx.x == 0) dsh = descs[it.tensor];
     for (uint32_t i = threadIdx.x; i < 3 * 256; i += 256) (&enc[0][0])[i] = enc_tables[(uint64_t)it.tensor * 768 + i];
     __syncthreads();
@@ -408,11 +410,109 @@ __global__ __launch_bounds__(256) void k_encode(const TensorDev *descs, const Wo
     }
 }
 
+// The short last chunk of an FP4 tensor whose element fields are stored plainly (flat code, raw, constant), with 64 lanes: its
+// rows do not depend on each other, so fifteen wavefronts take them in turn while the first codes the block scales; the size
+// pass needs no element data at all.  One chunk per work item; tensors with a table-coded element field are left to
+// k_encode.
+constexpr uint32_t kFp4TailWaves = 16;
+constexpr int kFp4Tails = 3;            // launch_encode_f's `whole`: any chunks, but for those
+template <int FMT, bool WRITE>
+__global__ __launch_bounds__(WRITE ? 64 * kFp4TailWaves : 64) void k_encode_fp4_tail(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, uint32_t *units)
+{
+    using F_ = Fmt<FMT>;
+    static_assert(F_::NF == 3, "element fields and block scales");
+    constexpr int SB = F_::SB, kPerWord = 32 / SB;
+    __shared__ uint32_t enc[256];
+    __shared__ TensorDev dsh;
+    const WorkItem it = work[blockIdx.x];
+    if (descs[it.tensor].kind[0] == 0 || descs[it.tensor].kind[1] == 0 || descs[it.tensor].streams != 64) return;       // whole workgroup: not this kernel's
+    if (threadIdx.x == 0) dsh = descs[it.tensor];
+    for (uint32_t i = threadIdx.x; i < 256; i += blockDim.x) enc[i] = enc_tables[(uint64_t)it.tensor * 768 + 512 + i];
+    __syncthreads();
+    const TensorDev &d = dsh;
+    const Lanes L = make_lanes(64);
+    const uint32_t lane = L.lane, wave = threadIdx.x >> 6, chunk = it.first;
+    const uint64_t E = (uint64_t)d.chunk_bytes * 2, first = (uint64_t)chunk * E;
+    if (chunk >= d.n_chunks || first >= d.n_elems) return;
+    const uint32_t n = (uint32_t)(d.n_elems - first < E ? d.n_elems - first : E), nbytes = (n + 1) / 2;
+    const uint32_t rows = nbytes / 1024, nsyms = (n + F_::GRP - 1) / F_::GRP;
+    // what the lane owns of the row after the whole ones
+    const uint32_t tail_at = rows * 1024 + lane * 16, tail_bytes = nbytes > tail_at ? (nbytes - tail_at < 16u ? nbytes - tail_at : 16u) : 0u;
+    const uint32_t tail_el = tail_bytes ? (n - tail_at * 2 < 32u ? n - tail_at * 2 : 32u) : 0u, tail_sym = (tail_el + F_::GRP - 1) / F_::GRP;
+    uint8_t *stream[3] = {nullptr, nullptr, nullptr};
+    for (int f = 0; f < 3 && WRITE; f++) stream[f] = d.comp + d.payload_off + 16ull * reinterpret_cast<const uint32_t *>(d.comp + d.index_off[f])[chunk];
+    if (wave == 0) {
+        EncField S = {0, 0, 0, 0, 0, 0, 0};
+        const uint32_t ns = n / F_::SCALE, srows = (ns + 1023) / 1024, m2 = d.mode[2];
+        const uint8_t *sc = d.scales + (uint64_t)chunk * (E / F_::SCALE);
+        for (uint32_t i = 0; i < srows; i++) {
+            const uint32_t run = i * 64 + lane, done = run * 16, nsym = ns > done ? (ns - done < 16u ? ns - done : 16u) : 0u;
+            uint64_t P = 0, Q = 0;
+            if (nsym) {
+                const uint4 v = load_run(sc + (uint64_t)run * 16, nsym);
+                P = (uint64_t)v.x | ((uint64_t)v.y << 32); Q = (uint64_t)v.z | ((uint64_t)v.w << 32);
+            }
+            if (m2 == ZC_MODE_HUFF) {
+                if (__all(nsym == 16u)) enc_run<WRITE, 8, 16, true>(S, d.period[2], P, Q, nsym, enc, stream[2], L);
+                else enc_run<WRITE, 8, 16, false>(S, d.period[2], P, Q, nsym, enc, stream[2], L);
+            } else if (m2 == ZC_MODE_RAW && WRITE && nsym) {
+                reinterpret_cast<uint64_t *>(stream[2])[2 * run] = P;
+                reinterpret_cast<uint64_t *>(stream[2])[2 * run + 1] = Q;
+            }
+        }
+        uint32_t u2 = 0;
+        if (m2 == ZC_MODE_HUFF) u2 = enc_finish<WRITE>(S, stream[2], L);
+        else if (m2 == ZC_MODE_RAW) u2 = (ns + 15) / 16;
+        if (WRITE) return;
+        // flat: two words per whole run and one per started word of a cut one; raw: the symbols' bits
+        uint32_t words = rows * 2 + (tail_sym + kPerWord - 1) / kPerWord;
+        for (int o = 32; o > 0; o >>= 1) words += __shfl_xor(words, o, 64);
+        if (lane == 0) {
+            uint32_t *my = units + d.units_off;
+            for (int f = 0; f < 2; f++)
+                my[f * d.n_chunks + chunk] = d.mode[f] == ZC_MODE_HUFF ? (words + 3) / 4 : d.mode[f] == ZC_MODE_RAW ? (uint32_t)((((uint64_t)nsyms * SB + 7) / 8 + 15) / 16) : 0u;
+            my[2 * d.n_chunks + chunk] = u2;
+        }
+        return;
+    }
+    const uint8_t *src = d.src + (uint64_t)chunk * d.chunk_bytes, *base = d.base ? d.base + (uint64_t)chunk * d.chunk_bytes : nullptr;
+    const uint32_t mode[2] = {d.mode[0], d.mode[1]};
+    auto put = [&](uint32_t row, uint32_t valid, uint32_t nsym, bool whole) {
+        const uint32_t run = row * 64 + lane;
+        uint64_t P[2] = {0, 0};
+        if (valid) {
+            uint4 v = load_run(src + (uint64_t)run * 16, valid);
+            if (base) v = xor4(v, load_run(base + (uint64_t)run * 16, valid));
+            split_run<FMT>(v, P[0], P[1]);
+        }
+#pragma unroll
+        for (int f = 0; f < 2; f++) {
+            if (mode[f] == ZC_MODE_HUFF) {
+                uint32_t *w = reinterpret_cast<uint32_t *>(stream[f]);
+                uint32_t at = row * 128;
+#pragma unroll
+                for (int h = 0; h < 2; h++) {
+                    const bool owner = whole || (uint32_t)(h * kPerWord) < nsym;
+                    const uint64_t bm = __ballot(owner);
+                    if (owner) w[at + prefix_count(bm)] = reverse_in_groups<SB>((uint32_t)(P[f] >> (32 * h)));
+                    at += (uint32_t)__popcll(bm);
+                }
+                if (!whole && lane < ((4 - (at & 3)) & 3)) w[at + lane] = 0;             // up to a whole 16-byte unit
+            } else if (mode[f] == ZC_MODE_RAW && valid) {
+                reinterpret_cast<uint64_t *>(stream[f])[run] = P[f];
+                if (!whole && (run & 1) == 0 && tail_at + 16 >= nbytes) reinterpret_cast<uint64_t *>(stream[f])[run + 1] = 0;
+            }
+        }
+    };
+    for (uint32_t row = wave - 1; row < rows; row += kFp4TailWaves - 1) put(row, 16, F_::G, true);
+    if (wave == kFp4TailWaves - 1 && nbytes % 1024) put(rows, tail_bytes, tail_sym, false);
+}
+
 template <int FMT, bool WRITE>
 static void launch_encode_f(int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, hipStream_t st)
 {
-    if (whole) hipLaunchKernelGGL((k_encode<FMT, WRITE, true>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, whole == 2 ? 1 : 0);
-    else hipLaunchKernelGGL((k_encode<FMT, WRITE, false>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, 0);
+    if (whole == 1 || whole == 2) hipLaunchKernelGGL((k_encode<FMT, WRITE, true>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, whole == 2 ? 1 : 0);
+    else hipLaunchKernelGGL((k_encode<FMT, WRITE, false>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, whole == kFp4Tails ? 1 : 0);
 }
 
 template <bool WRITE>
@@ -430,6 +530,28 @@ static int launch_encode_t(uint32_t fmt, int whole, int skip_routes, const Tenso
     default: return 1;
     }
     return (int)hipGetLastError();
+}
+
+// FP4, 64 lanes: sizes (write 0) or encoding of tensors' short last chunks, one per work item: what k_encode_fp4_tail takes
+// through that kernel, the rest through k_encode
+int launch_fp4_tails(uint32_t fmt, int write, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream)
+{
+    if (n_work == 0) return 0;
+    hipStream_t st = (hipStream_t)stream;
+#define ZC_TAIL(F) \
+    if (write) hipLaunchKernelGGL((k_encode_fp4_tail<F, true>), dim3(n_work), dim3(64 * kFp4TailWaves), 0, st, d_descs, d_work, d_enc, d_units); \
+    else hipLaunchKernelGGL((k_encode_fp4_tail<F, false>), dim3(n_work), dim3(64), 0, st, d_descs, d_work, d_enc, d_units); \
+    break
+    switch (fmt) {
+    case ZC_FMT_FP4_E2M1_MX: ZC_TAIL(ZC_FMT_FP4_E2M1_MX);
+    case ZC_FMT_FP4_E2M1_MX_BYTES: ZC_TAIL(ZC_FMT_FP4_E2M1_MX_BYTES);
+    case ZC_FMT_FP4_E2M1_NV: ZC_TAIL(ZC_FMT_FP4_E2M1_NV);
+    default: return 1;
+    }
+#undef ZC_TAIL
+    const int e = (int)hipGetLastError();
+    if (e) return e;
+    return write ? launch_encode_t<true>(fmt, kFp4Tails, 0, d_descs, d_work, n_work, d_enc, nullptr, st) : launch_encode_t<false>(fmt, kFp4Tails, 0, d_descs, d_work, n_work, d_enc, d_units, st);
 }
 
 // whole: 1 = every work item is up to four whole chunks of a tensor with 64 lanes per chunk and chunks of whole

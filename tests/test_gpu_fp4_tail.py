@@ -1,5 +1,5 @@
-"""The decoder of an FP4 tensor's short last chunk (64 lanes, plainly stored element fields): containers of the oracle decode to
-the original bytes at the edges of rows of elements and of block scales, alone and in a set.  Whole bytes: exact."""
+"""Encoder and decoder of an FP4 tensor's short last chunk (64 lanes, plainly stored element fields): the oracle's containers, byte
+for byte, and from them the original bytes, at the edges of rows of elements and of block scales, alone and in a set.  Whole bytes: exact."""
 import numpy as np
 import pytest
 import torch
@@ -28,10 +28,13 @@ def test_short_last_chunks(fmt, policy):
         for base in (None, torch.from_numpy(rng.integers(0, 256, src.numel()).astype(np.uint8))):
             print("case fmt", fmt, "policy", policy, "n", n, "delta", base is not None, flush=True)
             want = o.compress(src.numpy(), n, po, scales=sc.numpy(), xor_base=None if base is None else base.numpy())
+            db = None if base is None else base.to(DEV)
+            got, _ = zc.compress(src.to(DEV), n, p, scales=sc.to(DEV), xor_base=db)
+            assert np.array_equal(got.cpu().numpy(), want)
             c = torch.from_numpy(want).to(DEV)
             out = torch.full((src.numel() + 32,), 0x5A, dtype=torch.uint8, device=DEV)
             sco = torch.full((sc.numel() + 32,), 0x5A, dtype=torch.uint8, device=DEV)
-            zc.decompress(c, zc.read_info(c, check_index=True), out=out, scales_out=sco, xor_base=None if base is None else base.to(DEV))
+            zc.decompress(c, zc.read_info(c, check_index=True), out=out, scales_out=sco, xor_base=db)
             assert torch.equal(out[:src.numel()].cpu(), src) and torch.equal(sco[:sc.numel()].cpu(), sc)
             assert bool((out[src.numel():] == 0x5A).all()) and bool((sco[sc.numel():] == 0x5A).all())       # nothing behind either
         held.append((src, sc, n))
