@@ -2,6 +2,7 @@
 // plan / run halves): which kernel takes which container, descriptors, work lists, launches.  See include/zc.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -86,14 +87,23 @@ uint32_t pairs_fields(const zc_info &info)
     return 1;
 }
 
+// Least bytes of FP8 chunks, and of a set's longest short last chunk next to a kernel for whole chunks, that are worth a 64 KiB table
+constexpr uint64_t kPairsBytes = 32 * 1024;
+// bytes of a tensor's short last chunk (0: it has none)
+uint64_t tail_bytes(const zc_info &info)
+{
+    return info.chunk_bytes ? (info.n_elems * (uint64_t)elem_bits(info.format) + 7) / 8 % info.chunk_bytes : 0;
+}
+
 // Chunks per workgroup of those kernels for a call of `slots` chunks, 0: another kernel is faster.  FP8 E4M3: from 1,024 chunks
 // on k_decode_fp8, bound by its traffic, is ahead (1,536 chunks: 249 against 280 us still, but with tables of 13 bits that lose
 // 10 % to those of 14 below; 2,048: 282 against 288).  Two table-decoded fields fill the compute units' LDS with 4,096
 // chunks, and a few more take a second round (4,096 and one: 723 us against 708 in k_decode_bf16_s64; 3,072: 435 | 662;
 // 6,144: 866 | 893).
-uint32_t pairs_waves(uint32_t fmt, uint32_t fields, uint64_t slots)
+// FP8 chunks below 32 KiB do not pay for the table either (500 of 16 KiB: 47 | 46 us, 900 of 4 KiB: 36 | 38).
+uint32_t pairs_waves(uint32_t fmt, uint32_t fields, uint64_t slots, uint32_t chunk_bytes)
 {
-    if (fmt == ZC_FMT_FP8_E4M3) return slots <= 1024 ? 4 : 0;
+    if (fmt == ZC_FMT_FP8_E4M3) return slots <= 1024 && chunk_bytes >= kPairsBytes ? 4 : 0;
     if (fmt == ZC_FMT_BF16 && fields == 2 && slots > 3072 && slots <= 5120) return 0;
     return slots <= 1024 ? 4 : 8;
 }
@@ -208,8 +218,8 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         if (info.format == ZC_FMT_BF16) LAUNCH_TRY(launch_decode_bf16_sub(info.streams, info.xor_delta != 0, nullptr, nullptr, (n_fast + spg - 1) / spg, &d, spg, stream));
         else LAUNCH_TRY(launch_decode_fp8_sub(info.streams, info.xor_delta != 0, by_ids, nullptr, nullptr, (n_fast + spg - 1) / spg, &d, spg, stream));
         first_slot = n_fast;
-    } else if (pairs && pairs_waves(info.format, pairs, slots)) {
-        const uint32_t waves = pairs_waves(info.format, pairs, slots);
+    } else if (pairs && pairs_waves(info.format, pairs, slots, info.chunk_bytes)) {
+        const uint32_t waves = pairs_waves(info.format, pairs, slots, info.chunk_bytes);
         LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, waves, nullptr, nullptr, (slots + waves - 1) / waves, &d, 0, stream));
         first_slot = slots;
     } else if ((fk.ok || rings) && !by_ids) {
@@ -235,7 +245,8 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         // what is left: chunks that are not whole rows and id lists with 64 lanes (the 64-lane kernel's build for those, for
         // the formats of two fields), geometries no specialised kernel takes
         const uint32_t n_work = (slots - first_slot + cpi - 1) / cpi;
-        if (pairs) LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, kWavesPerGroup, nullptr, nullptr, n_work, &d, first_slot, stream));
+        if (pairs && info.chunk_bytes % 1024 == 0 && !by_ids && (info.format != ZC_FMT_FP8_E4M3 || tail_bytes(info) >= kPairsBytes))
+            LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, kWavesPerGroup, nullptr, nullptr, n_work, &d, first_slot, stream));
         else if (info.n_fields == 3 && !by_ids && s64_split_ok(info) && slots - first_slot == 1)
             LAUNCH_TRY(launch_decode_fp4_tail(info.format, info.xor_delta != 0, nullptr, nullptr, 1, &d, first_slot, stream));
         else if (s64_tail_ok(info)) LAUNCH_TRY(launch_decode_s64_tail(info.format, info.xor_delta != 0, nullptr, nullptr, n_work, &d, first_slot, false, stream));
@@ -348,7 +359,7 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
         if (k == 0 || tensors[t].info.xor_delta != tensors[0].info.xor_delta) pair_fields = 0;
         else if (k > pair_fields) pair_fields = k;
     }
-    const uint32_t pair_waves = pair_fields ? pairs_waves(fmt, pair_fields, all_slots) : 0;
+    const uint32_t pair_waves = pair_fields ? pairs_waves(fmt, pair_fields, all_slots, tensors[0].info.chunk_bytes) : 0;
     const uint32_t spg = pair_waves ? pair_waves : sub ? sub_slots_per_group(S, all_slots) : split ? 1u : kWavesPerGroup;
     std::vector<TensorDev> descs(n_tensors);
     std::vector<WorkItem> fast_work, work;
@@ -407,10 +418,16 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     plan->tail_kernel = 1;
     for (uint32_t t = 0; t < n_tensors && plan->tail_kernel; t++)
         if (tensors[t].info.n_elems && (!s64_tail_ok(tensors[t].info) || tensors[t].info.xor_delta != tensors[0].info.xor_delta)) plan->tail_kernel = 0;
+    uint64_t longest_tail = 0;
+    bool only_tails = plan->scattered == 0;                    // the second list is short last chunks and nothing else
+    for (uint32_t t = 0; t < n_tensors; t++) {
+        longest_tail = std::max(longest_tail, tail_bytes(tensors[t].info));
+        only_tails = only_tails && tensors[t].info.chunk_bytes % 1024 == 0;
+    }
     // lists over containers the FP8 kernel takes: that kernel has the whole chunks of the second list
     if (plan->tail_kernel && fk.ok && plan->scattered) plan->tail_kernel = 2;
     // short last chunks of tensors whose code suits them: the kernels that look up two symbols at a time
-    else if (plan->tail_kernel && pair_fields) { plan->tail_kernel = 3; plan->fast_sm_kind |= pair_fields << 8; }
+    else if (plan->tail_kernel && fast && only_tails && pair_fields && (fmt != ZC_FMT_FP8_E4M3 || longest_tail >= kPairsBytes)) { plan->tail_kernel = 3; plan->fast_sm_kind |= pair_fields << 8; }
     // FP4 sets whose whole chunks went to the 64-lane kernel's shared build: what is left is a short last chunk per tensor
     if (split && is_fp4(fmt) && !plan->scattered) plan->tail_kernel = 4;
     plan->fast_work_offset = descs_bytes; plan->work_offset = descs_bytes + fast_bytes;
