@@ -228,14 +228,14 @@ def other_workloads(torch, wl, zc, dev, extras, copy_gbps):
             compress_kernels="k_hist_fp8_lanes + k_codes + k_sizes_fp8_counts + k_scan + k_encode_fp8")
         del chunk_ids
         ragged = [t[:t.numel() - 4096 - 7 * 16] for t in set2]
-        run("c2_fp8_ragged_tails", zc.FMT_FP8_E4M3, ragged, [t.numel() for t in ragged], 262144, 64, decode_kernel="k_decode_fp8 + k_decode_s64<TAIL> (last chunks)", compress_kernels="k_hist_fp8_lanes + k_hist + k_codes + k_sizes_fp8_counts + k_sizes_tail (last chunks) + k_scan + k_encode_fp8 + k_encode (last chunks)")
+        run("c2_fp8_ragged_tails", zc.FMT_FP8_E4M3, ragged, [t.numel() for t in ragged], 262144, 64, decode_kernel="k_decode_fp8 + k_decode_pairs (last chunks)", compress_kernels="k_hist_fp8_lanes + k_hist + k_codes + k_sizes_fp8_counts + k_sizes_tail (last chunks) + k_scan + k_encode_fp8 + k_encode (last chunks)")
         del set2, ragged
         set2 = [t for _, t in wl.fp8_weight_set(32, device=dev, e5m2=True)]
         run("c2_shapes_in_fp8_e5m2", zc.FMT_FP8_E5M2, set2, [t.numel() for t in set2], 262144, 64, decode_kernel=S64, compress_kernels="k_hist_fp8_lanes<E5M2> + k_codes + k_sizes_e5m2_counts + k_scan + k_encode_bf16<E5M2>")
         run("c2_shapes_in_fp8_e5m2_limit_8", zc.FMT_FP8_E5M2, set2, [t.numel() for t in set2], 262144, 64, limit=(8, 8, 0), decode_kernel=S64, compress_kernels="k_hist_fp8_lanes<E5M2> + k_codes + k_sizes_e5m2_counts + k_scan + k_encode_bf16<E5M2>")
         del set2
     x = wl.bf16_weight(1 << 20, device=dev, seed=0)
-    run("c1_bf16_1M", zc.FMT_BF16, [x], [1 << 20], 65536, 64, limit=(16, 16, 0), decode_kernel="k_decode_bf16_s64", compress_kernels="k_hist + k_codes + k_encode (sizes) + k_scan + k_encode_bf16")
+    run("c1_bf16_1M", zc.FMT_BF16, [x], [1 << 20], 65536, 64, limit=(16, 16, 0), decode_kernel="k_decode_pairs", compress_kernels="k_hist + k_codes + k_sizes_split + k_scan + k_encode_split")
     mats = [wl.mxfp4_weight(8192, 28672, device=dev, seed=300 + i) for i in range(3)]
     run("c3_mxfp4_70b_mlp", zc.FMT_FP4_E2M1_MX, [m[0] for m in mats], [8192 * 28672] * 3, 262144, 64, scales=[m[1] for m in mats],
         decode_kernel="k_decode_s64 (chunk shared by four wavefronts)", compress_kernels="k_hist x2 + k_codes + k_encode (sizes) + k_scan + k_encode")
@@ -253,11 +253,11 @@ def other_workloads(torch, wl, zc, dev, extras, copy_gbps):
     w0, w1 = [q[0] for q in pairs], [q[1] for q in pairs]
     bf16_c = "k_hist + k_codes + k_encode (sizes) + k_scan + k_encode_bf16"
     bf16_lanes_c = "k_hist_rows8_lanes + k_codes + k_sizes_rows8_counts + k_scan + k_encode_bf16"       # 256 KiB chunks: sizes from counts per lane
-    run("c4_bf16_checkpoint_w1", zc.FMT_BF16, w1, [4096 * 16384] * 16, 262144, 64, limit=(16, 16, 0), decode_kernel="k_decode_bf16_s64", compress_kernels=bf16_lanes_c)
-    run("c4_bf16_checkpoint_xor_delta", zc.FMT_BF16, w1, [4096 * 16384] * 16, 262144, 64, bases=w0, limit=(16, 16, 0), decode_kernel="k_decode_bf16_s64", compress_kernels=bf16_lanes_c)
+    run("c4_bf16_checkpoint_w1", zc.FMT_BF16, w1, [4096 * 16384] * 16, 262144, 64, limit=(16, 16, 0), decode_kernel="k_decode_pairs", compress_kernels=bf16_lanes_c)
+    run("c4_bf16_checkpoint_xor_delta", zc.FMT_BF16, w1, [4096 * 16384] * 16, 262144, 64, bases=w0, limit=(16, 16, 0), decode_kernel="k_decode_pairs", compress_kernels=bf16_lanes_c)
     if extras:
-        run("c4_bf16_checkpoint_xor_delta_limit_11", zc.FMT_BF16, w1, [4096 * 16384] * 16, 262144, 64, bases=w0, limit=(11, 11, 0), decode_kernel="k_decode_bf16_s64", compress_kernels=bf16_lanes_c)
-        run("c4_bf16_checkpoint_xor_delta_64KiB_chunks", zc.FMT_BF16, w1, [4096 * 16384] * 16, 65536, 64, bases=w0, limit=(16, 16, 0), decode_kernel="k_decode_bf16_s64", compress_kernels=bf16_c)
+        run("c4_bf16_checkpoint_xor_delta_limit_11", zc.FMT_BF16, w1, [4096 * 16384] * 16, 262144, 64, bases=w0, limit=(11, 11, 0), decode_kernel="k_decode_pairs", compress_kernels=bf16_lanes_c)
+        run("c4_bf16_checkpoint_xor_delta_64KiB_chunks", zc.FMT_BF16, w1, [4096 * 16384] * 16, 65536, 64, bases=w0, limit=(16, 16, 0), decode_kernel="k_decode_pairs", compress_kernels=bf16_c)
     del pairs, w0, w1
     kv = []
     for layer in range(32):
