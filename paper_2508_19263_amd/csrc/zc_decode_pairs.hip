@@ -670,7 +670,7 @@ __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, c
     if (n_elems <= before) return;
     const uint32_t n = (uint32_t)(n_elems - before < E ? n_elems - before : E);
     ChunkOut o;
-    o.nbytes = n * F_::EB / 8;
+    o.nbytes = (uint32_t)((uint64_t)n * F_::EB / 8);         // (n * EB passes 32 bits from chunks of 512 MiB on)
     o.whole_rows = o.nbytes / 1024;
     const uint32_t tail_at = o.whole_rows * 1024 + lane * 16;
     o.tail_bytes = o.nbytes > tail_at ? (o.nbytes - tail_at < 16u ? o.nbytes - tail_at : 16u) : 0u;

@@ -50,15 +50,15 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
         }
     }
     const uint32_t cb = uniform32(d.chunk_bytes);
-    const uint32_t E = cb * 8 / F_::EB;
+    const uint64_t E = (uint64_t)cb * 8 / F_::EB;             // (the product passes 32 bits from chunks of 512 MiB on)
     const uint64_t n_elems = uniform64(d.n_elems);
     const uint32_t n_full = (uint32_t)(n_elems / E);
     if (TAIL ? chunk >= uniform32(d.n_chunks) : chunk >= n_full) return;
     if (TAIL && skip_whole && chunk < n_full && cb % 1024 == 0) return;        // a specialised kernel took the whole chunks of this launch
     // this chunk's elements and bytes: all of cb unless it is the tensor's short last chunk
     const uint64_t before = (uint64_t)chunk * E;
-    const uint32_t n = (!TAIL || n_elems - before >= E) ? E : (uint32_t)(n_elems - before);
-    const uint32_t nbytes = n * F_::EB / 8;                   // two-field formats have whole bytes per element
+    const uint64_t n = (!TAIL || n_elems - before >= E) ? E : n_elems - before;
+    const uint32_t nbytes = (uint32_t)(n * F_::EB / 8);                   // two-field formats have whole bytes per element
     if (TAIL && n_elems <= before) return;
     const uint8_t *comp = reinterpret_cast<const uint8_t *>(uniform64((uint64_t)d.comp));
     const uint64_t payload = uniform64(d.payload_off), total = uniform64(d.total_bytes);
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
     const uint32_t rows = TAIL ? whole_rows : cb / 1024;      // 64 lanes x 16 bytes per row
     if (split && (kind[0] == KIND_HUFF || kind[1] == KIND_HUFF)) return;          // the host never asks for this
     uint32_t row_begin = 0, row_end = rows;
-    if (split) shared_chunk_rows(rows, F_::NF == 3 ? E / F_::SCALE / 1024 : 0u, wave, row_begin, row_end);
+    if (split) shared_chunk_rows(rows, F_::NF == 3 ? (uint32_t)(E / F_::SCALE / 1024) : 0u, wave, row_begin, row_end);
     // what a row takes from global memory besides its stream words (plainly stored fields, the base of a delta) is asked
     // for one row ahead
     constexpr int WPR = F_::G * F_::SB / 32;
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
     if (F_::NF == 3 && !(split && wave != 0)) {
         // block scales: one byte per 32 elements, 16 per run, the chunk's E/32 scales in rows of 1024
         constexpr int F2 = F_::NF - 1;
-        const uint32_t n_sc = E / F_::SCALE;
+        const uint32_t n_sc = (uint32_t)(E / F_::SCALE);
         const __amdgpu_buffer_rsrc_t r2 = make_rsrc(sp[F2], sb[F2]);
         const __amdgpu_buffer_rsrc_t ss = make_rsrc(reinterpret_cast<uint8_t *>(uniform64((uint64_t)d.scales_out)) + (uint64_t)chunk * n_sc, n_sc);
         const uint32_t p2 = uniform32(d.period[F2]);
