@@ -682,9 +682,10 @@ __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, c
 #pragma unroll
     for (int f = 0; f < 2; f++)
         if (!stream_range(d, comp, f, chunk, payload, total, sp[f], sb[f])) return;      // damaged index: leave the chunk alone
-    // a plainly stored sign+mantissa field takes 512 bytes per row, and its rows are addressed through the scalar offset, which
-    // is not range checked: a stream shorter than that (a damaged index) must not be read at all
-    if (FMT != ZC_FMT_FP8_E5M2 && (kind1 == KIND_FLAT || kind1 == KIND_RAW) && sb[1] < o.whole_rows * 512) return;
+    // a plainly stored sign+mantissa field takes 512 bytes per row (E5M2's three bits per value 384): a shorter stream (a damaged
+    // index) leaves the chunk alone.  It must not be read either: but for E5M2's, rows are addressed through the scalar offset,
+    // which is not range checked
+    if ((kind1 == KIND_FLAT || kind1 == KIND_RAW || FMT == ZC_FMT_FP8_E5M2) && sb[1] < o.whole_rows * (FMT == ZC_FMT_FP8_E5M2 ? 384u : 512u)) return;
     o.dst = reinterpret_cast<uint8_t *>(uniform64((uint64_t)d.dst)) + (uint64_t)slot * cb;
     o.base = XOR ? reinterpret_cast<const uint8_t *>(uniform64((uint64_t)d.base)) + (uint64_t)chunk * cb : comp;
     o.r1 = make_rsrc(sp[1], sb[1]);

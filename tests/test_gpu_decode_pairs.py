@@ -95,3 +95,21 @@ def test_flat_three_bit_code_of_e5m2():
             info = decode(zc.FMT_FP8_E5M2, x, None, 262144, "flat3 rows %d + %d" % (rows, extra), lists=False)
             if n >= 64:
                 assert list(info.code_len[1][:9]) == [3] * 8 + [0]
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_too_short_a_plain_stream_leaves_its_chunk_alone(fmt):
+    # the index says that the last chunk's sign+mantissa stream ends before its rows do: the other chunks decode, that one's place
+    # in the output keeps what it held (17 units: E5M2's stream has a word per lane, 16 units, that the decoder never uses)
+    size, cb, chunks = (2 if fmt == zc.FMT_BF16 else 1), 65536, 5
+    x = tensor(fmt, chunks * cb // size, "geometric", "uniform", 21)
+    c = torch.from_numpy(o.compress(x.view(torch.uint8).numpy(), x.numel(), o.params(fmt, cb, (0, 0, 0), 64, zc.POLICY_AUTO))).to(DEV)
+    info = zc.read_info(c, check_index=True)
+    assert info.mode[1] == zc.MODE_RAW or len(set(info.code_len[1][:16 if fmt != zc.FMT_FP8_E5M2 else 8])) == 1
+    end = info.index_offset[1] + 4 * chunks
+    last = c[end:end + 4].view(torch.int32)
+    last -= 17
+    out = torch.full((chunks * cb,), 0x5A, dtype=torch.uint8, device=DEV)
+    zc.decompress(c, info, out=out)
+    got, want = out.cpu(), x.view(torch.uint8).reshape(-1)
+    assert torch.equal(got[:-cb], want[:-cb]) and bool((got[-cb:] == 0x5A).all())
