@@ -66,6 +66,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
 
+// A lane's 16 bytes of a row (64 runs) of the output; POLICY: 2 = with the non-temporal hint.  The row goes into the vector operand:
+// with a scalar offset the compiler takes the data registers as free at once, and the instruction after such a store has been seen
+// to overwrite the last lanes' first word before the store had read it (gfx950).
+template <int POLICY>
+__device__ __forceinline__ void store_row(const u32x4 &v, __amdgpu_buffer_rsrc_t out, uint32_t lane, uint32_t row)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, out, (int)(lane * 16 + row * 1024), 0, POLICY);
+}
+
 // (x & 0xFF) << sh in one instruction (byte select on the shifted operand); sh lives in a VGPR
 __device__ __forceinline__ uint32_t byte0_shl(uint32_t x, uint32_t sh)
 {

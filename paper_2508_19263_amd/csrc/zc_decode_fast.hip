@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void k_decode_fp8(const TensorDev *descs, cons
         u32x4 v = {o[0], o[1], o[2], o[3]};
         if (XOR) v ^= __builtin_amdgcn_raw_buffer_load_b128(bs, (int)(lane * 16), (int)(row * 1024), 0);
         // (whole cache lines written once: the non-temporal hint keeps them from displacing the streams' lines in the L2; 1.3 % on the weight set)
-        __builtin_amdgcn_raw_buffer_store_b128(v, ds, (int)(lane * 16), (int)(row * 1024), 2);
+        store_row<2>(v, ds, lane, row);
     }
 }
 

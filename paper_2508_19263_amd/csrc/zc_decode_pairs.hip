@@ -505,16 +505,13 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
         for (int i = 0; i < 4; i++) v[i] = (ew[i] & EX) | (mw[i] & ~EX);
         return v;
     };
-    // (the row's place in the vector operand: with a scalar offset the compiler takes the data registers as free at once, and the
-    // instruction after such a store has been seen to overwrite the last lanes' first word before the store had read it)
-    auto store = [&](uint32_t row, u32x4 v) { __builtin_amdgcn_raw_buffer_store_b128(v, o.ds, (int)(lane * 16 + row * 1024), 0, 2); };
     auto fast_row = [&](auto service, uint32_t row, const RowAhead &f, const RowAhead &even) {      // even: the pair of rows' three words (E5M2)
         uint32_t ea[NP], eb[NP], mw[4];
         pair_run<FMT, R, TWO, RW, false, decltype(service)::value>(A, B, C, lane, ea, eb, 0, 0);
         sm_words(row, SM == kSmFlat3 ? even.m : f.m, eb, mw);
         u32x4 v = merge(ea, mw);
         if (XOR) v ^= f.base;
-        store(row, v);
+        store_row<2>(v, o.ds, lane, row);
     };
     const bool ragged = o.nbytes % 1024 != 0;
     // ---- rows that need care: the first, until no lane is in the state of the start; the last before an incomplete one
@@ -527,7 +524,7 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
         sm_words(row, f.m, eb, mw);
         u32x4 v = merge(ea, mw);
         if (XOR) v ^= f.base;
-        store(row, v);
+        store_row<2>(v, o.ds, lane, row);
     };
     uint32_t row = 0;
     const uint32_t fast_end = ragged && rows ? rows - 1 : rows;

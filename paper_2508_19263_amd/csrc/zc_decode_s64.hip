@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
         u32x4 v = {j.x, j.y, j.z, j.w};
         if (XOR) v ^= base;
         // (a whole row of the output, written once: stored with the non-temporal hint so that it does not displace the streams' lines in the L2)
-        __builtin_amdgcn_raw_buffer_store_b128(v, ds, (int)(lane * 16), (int)(row * 1024), 2);
+        store_row<2>(v, ds, lane, row);
     }
     if (TAIL && nbytes % 1024) {
         uint64_t P0 = 0, P1 = 0, Q0 = 0, Q1 = 0;
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
             if (kind[F2] == KIND_HUFF) huff_run<8, 16>(H2, tab[F2], p2, P0, P1, lane);
             else plain_run<8, 16>(kind[F2], r2, row, lane, K2, P0, P1);
             const u32x4 v = {(uint32_t)P0, (uint32_t)(P0 >> 32), (uint32_t)P1, (uint32_t)(P1 >> 32)};
-            __builtin_amdgcn_raw_buffer_store_b128(v, ss, (int)(lane * 16), (int)(row * 1024), 0);
+            store_row<0>(v, ss, lane, row);
         }
     }
 }
@@ -542,7 +542,7 @@ __device__ __forceinline__ void bf16_rows(const FieldTab *tab, uint32_t kind1, u
 #pragma unroll
         for (int i = 0; i < 4; i++) v[i] = bfi(kExpMask2, ea[i], mb[i]);
         if (XOR) v ^= base;
-        __builtin_amdgcn_raw_buffer_store_b128(v, ds, (int)(lane * 16), (int)(row * 1024), 2);
+        store_row<2>(v, ds, lane, row);
     }
 }
 

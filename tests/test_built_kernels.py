@@ -1,0 +1,50 @@
+"""The instructions of the built library's kernels.  A buffer store of more than 8 bytes per lane whose offset is partly in a scalar
+register, followed at once by an instruction that overwrites its data registers, has stored the new values on gfx950, and the
+compiler inserts no wait there: no kernel may have such a store.  (Whether a wait is there depends on what follows the store, and
+that changes with any edit; with the whole offset in a vector register the compiler waits where it has to.)"""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2508_19263_amd import zc
+
+LLVM = "/opt/rocm/llvm/bin"
+STORE = re.compile(r"^\s*buffer_store_(?:dwordx[34]|format_xyzw?) ([^/]*)")
+
+
+def wide_scalar_offset_stores(listing):
+    """Lines of a listing that hold a store as described: data, vector offset, resource, then the scalar offset."""
+    hits = []
+    for line in listing:
+        m = STORE.match(line)
+        if m:
+            soffset = m.group(1).split(", ")[3].split()[0]
+            if not re.fullmatch(r"0|0x0|null", soffset):
+                hits.append(line.strip())
+    return hits
+
+
+def test_the_pattern_finds_what_it_looks_for():
+    assert wide_scalar_offset_stores(["\tbuffer_store_dwordx4 v[2:5], v9, s[4:7], s20 offen nt  // 00001234: E07E1000"])
+    assert wide_scalar_offset_stores(["\tbuffer_store_dwordx4 v[2:5], off, s[4:7], m0  // 0"])
+    assert not wide_scalar_offset_stores(["\tbuffer_store_dwordx4 v[2:5], v9, s[4:7], 0 offen offset:1024 nt  // 00001234: E07E1000",
+                                          "\tbuffer_store_dwordx2 v[2:3], v9, s[4:7], s20 offen  // 0", "\tbuffer_load_dwordx4 v[2:5], v9, s[4:7], s20 offen"])
+
+
+def test_no_wide_store_with_a_scalar_offset(tmp_path):
+    if not os.path.exists(LLVM + "/llvm-objdump"):
+        pytest.skip("llvm-objdump not found")
+    zc.lib()                                                   # (fails if the library is not built)
+    shutil.copy(os.path.join(os.path.dirname(zc.__file__), "libzc.so"), str(tmp_path))
+    subprocess.run([LLVM + "/llvm-objdump", "--offloading", "libzc.so"], cwd=str(tmp_path), check=True, capture_output=True)
+    objects = [f for f in os.listdir(str(tmp_path)) if f.endswith("gfx950")]
+    assert objects
+    stores, hits = 0, []
+    for f in objects:
+        listing = subprocess.run([LLVM + "/llvm-objdump", "-d", f], cwd=str(tmp_path), check=True, capture_output=True, text=True).stdout.splitlines()
+        stores += sum(1 for line in listing if STORE.match(line))
+        hits += wide_scalar_offset_stores(listing)
+    assert stores > 100 and not hits, (stores, len(hits), hits[:5])
