@@ -341,9 +341,10 @@ typedef struct {
                                                    5 BF16 small chunks, 6 BF16 with 64 lanes (table-decoded exponents),
                                                    7 FP8 E5M2 with 64 lanes (table-decoded exponents, flat 3-bit sign+mantissa code),
                                                    8 BF16, FP8 and FP8 in byte symbols with 64 lanes: 7 and 8 look up two symbols at
-                                                   a time and take every chunk, short last ones and id lists included */
-    uint32_t fast_exp_kind, fast_sm_kind /* bits 8 up: tail_kernel 3's table-decoded fields */,
-        n_rings /* kernels 3, 5: slots per workgroup; 7, 8: table-decoded fields * 64 + chunks per workgroup */, xor_delta;
+                                                   a time and take every chunk, short last ones and id lists included,
+                                                   9 E5M2 as 7, a symbol per lookup, whole chunks: sets of many tensors of few chunks */
+    uint32_t fast_exp_kind, fast_sm_kind, n_rings /* kernels 3, 5: slots per workgroup; 7, 8: table-decoded fields * 64 + chunks per
+                                                   workgroup, + 32 with long rings */, xor_delta;
     uint32_t scattered;                         /* some tensor decodes an id list */
     uint32_t tail_kernel;                       /* the second work list (chunks that are not whole rows, id lists with 64 lanes):
                                                    0 generic kernel, 1 the 64-lane kernel's build for such chunks (two-field formats),

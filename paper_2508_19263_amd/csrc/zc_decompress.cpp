@@ -65,6 +65,16 @@ bool e5m2_flat3(const zc_info &info)
     return true;
 }
 
+// Can the E5M2 kernel decode this container's full chunks?  64 lanes, chunks of whole rows, exponent field table
+// decoded on a refill period of 2, 4 or 8, sign+mantissa field coded with the flat 3-bit code.
+bool e5m2_s64_ok(const zc_info &info)
+{
+    if (info.format != ZC_FMT_FP8_E5M2 || !s64_rings(info)) return false;
+    const TensorDev d = make_desc(info);
+    if (d.kind[0] != 0 || (d.period[0] != 2 && d.period[0] != 4 && d.period[0] != 8)) return false;
+    return e5m2_flat3(info);
+}
+
 // Can the 64-lane kernel's build for chunks that are not whole rows decode this container's chunks (a short last chunk,
 // or every chunk when the chunk size is not a multiple of 1 KiB)?  64 lanes, a format of two fields, no empty field.
 bool s64_tail_ok(const zc_info &info)
@@ -87,25 +97,68 @@ uint32_t pairs_fields(const zc_info &info)
     return 1;
 }
 
-// Least bytes of FP8 chunks, and of a set's longest short last chunk next to a kernel for whole chunks, that are worth a 64 KiB table
-constexpr uint64_t kPairsBytes = 32 * 1024;
 // bytes of a tensor's short last chunk (0: it has none)
 uint64_t tail_bytes(const zc_info &info)
 {
     return info.chunk_bytes ? (info.n_elems * (uint64_t)elem_bits(info.format) + 7) / 8 % info.chunk_bytes : 0;
 }
 
-// Chunks per workgroup of those kernels for a call of `slots` chunks, 0: another kernel is faster.  FP8 E4M3: from 1,024 chunks
-// on k_decode_fp8, bound by its traffic, is ahead (1,536 chunks: 249 against 280 us still, but with tables of 13 bits that lose
-// 10 % to those of 14 below; 2,048: 282 against 288).  Two table-decoded fields fill the compute units' LDS with 4,096
-// chunks, and a few more take a second round (4,096 and one: 723 us against 708 in k_decode_bf16_s64; 3,072: 435 | 662;
-// 6,144: 866 | 893).
-// FP8 chunks below 32 KiB do not pay for the table either (500 of 16 KiB: 47 | 46 us, 900 of 4 KiB: 36 | 38).
-uint32_t pairs_waves(uint32_t fmt, uint32_t fields, uint64_t slots, uint32_t chunk_bytes)
+// What a call decodes, as far as the choice of those kernels asks: its chunks, the workgroups they make four to each (a workgroup has
+// chunks of one tensor), tensors with any, the most chunks of a tensor, bytes of the largest whole chunk and of the longest short last
+// one (0: no such chunk; short ones are not looked for where an id list says what is decoded).
+struct CallChunks {
+    uint64_t slots = 0, groups = 0, tensors = 0, most = 0, whole = 0, tail = 0;
+    bool lists = false;
+    void add(const zc_info &info, uint64_t n, bool by_ids)
+    {
+        if (n == 0) return;
+        slots += n; groups += (n + 3) / 4; tensors++;
+        most = std::max(most, n);
+        lists = lists || by_ids;
+        if (info.n_elems >= (uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(info.format)) whole = std::max<uint64_t>(whole, info.chunk_bytes);
+        if (!by_ids) tail = std::max(tail, tail_bytes(info));
+    }
+};
+constexpr uint64_t kComputeUnits = 256;
+// Least bytes of an FP8 E4M3 tensor's short last chunk that pay for a 64 KiB table, against k_decode_s64's build for such chunks
+// (16 tensors of 12,000 bytes: 27 | 25 us, 16,000: 30 | 30, 24,000: 35 | 41)
+constexpr uint64_t kPairsTailBytes = 16 * 1024;
+
+// How those kernels take a call: chunks per workgroup, and whether with the long rings (four chunks then); chunks 0: another kernel is
+// faster.  Measured on MI355X, these kernels | the others, in us.
+//  - Long rings leave a compute unit one workgroup (byte symbols with one table-decoded field, whose table is small: two), so they
+//    are for calls of one round of workgroups.  300 BF16 tensors of 100,000 bytes, a workgroup each: 184 with long rings, 110 with short.
+//  - FP8 E4M3 has tables of 64 KiB and comes here with long rings only; beyond a round, k_decode_fp8, bound by its traffic, is ahead.
+//    Its table pays for whole chunks from 96 KiB on (16 of 64 KiB: 70 | 70, 256: 74 | 71; 96 KiB: 94 | 98 and 83 | 99; 192 KiB: 149 | 183),
+//    and sooner where it saves the second launch that a short last chunk needs beside k_decode_fp8 (64 chunks of 32 KiB and one of
+//    64 bytes: 41 | 50, of 16 KiB: 41 | 72).
+//  - With short rings a workgroup's rings are as many as its chunks, so that more workgroups fit a compute unit where tensors have few
+//    (room for eight | for as many as there are: 1,500 BF16 tensors of one chunk of 100,000 bytes 321 | 213, 3,000 of two chunks
+//    1,538 | 883, 600 of three 520 | 329; with room for four, 600 of six: BF16 632 | 641, E5M2 580 | 752).
+//  - A table for each of many workgroups of few chunks costs more than it saves once they take a second round, unless the other
+//    kernels need a second launch for short last chunks of some length.  E5M2, one whole chunk of 64 KiB each: 1,000 tensors 100 | 139,
+//    1,500 206 | 154; four of 16 KiB: 600 tensors 45 | 54, 1,000 70 | 61; three such and a short one, 1,500 tensors: 90 | 128; one short
+//    chunk of 4,000 bytes, 1,500 tensors: 43 | 37.  BF16, two of 64 KiB, 1,500 tensors: 164 | 155; one short chunk of 6,000 bytes:
+//    42 | 49.  Byte symbols, whose tables are small, are ahead throughout (3,000 chunks of 2 KiB: 25 | 37).
+//  - Two table-decoded fields fill the compute units with 4,096 chunks, and a few more take a second round: whole BF16 chunks, 256 KiB:
+//    4,096: 536 | 667 in k_decode_bf16_s64, 4,097: 744 | 718, 5,120: 792 | 745, 5,400: 800 | 820; 128 KiB: 4,097: 390 | 383, 5,100: 413 | 397;
+//    64 KiB: 4,097: 201 | 216.  With a short last chunk, which is a second launch there: 4,300: 770 | 870; from an id list: 669 | 931.
+struct PairsShape { uint32_t chunks; bool long_rings; };
+PairsShape pairs_shape(uint32_t fmt, uint32_t fields, const CallChunks &c)
 {
-    if (fmt == ZC_FMT_FP8_E4M3) return slots <= 1024 && chunk_bytes >= kPairsBytes ? 4 : 0;
-    if (fmt == ZC_FMT_BF16 && fields == 2 && slots > 3072 && slots <= 5120) return 0;
-    return slots <= 1024 ? 4 : 8;
+    const bool one_round = c.groups <= kComputeUnits * (fmt == ZC_FMT_FP8_E4M3_BYTES && fields == 1 ? 2 : 1);
+    if (fmt == ZC_FMT_FP8_E4M3) {
+        const bool pays = c.whole ? c.whole >= 96 * 1024 || (c.whole >= 32 * 1024 && c.tail) : c.tail >= kPairsTailBytes;
+        return {one_round && pays ? 4u : 0u, true};
+    }
+    if (fmt == ZC_FMT_BF16 && fields == 2 && c.slots > 4096 && c.slots <= 5120 && c.whole >= 128 * 1024 && c.tail == 0 && !c.lists) return {0, false};
+    if (one_round) return {4, true};
+    const bool few_each = c.slots <= 4 * c.tensors;
+    if (fmt != ZC_FMT_FP8_E4M3_BYTES && few_each && !c.lists && c.groups > kComputeUnits * (c.most <= 2 ? 4 : 3) &&
+        (c.whole ? c.tail == 0 : c.tail <= (fmt == ZC_FMT_FP8_E5M2 ? 8192 : 4096)))
+        return {0, false};
+    // (one or two chunks to a workgroup only where no tensor has more: the work list is then no longer than with four)
+    return {c.most <= 1 ? 1u : c.most <= 2 ? 2u : few_each ? 4u : 8u, false};
 }
 
 // Are both element fields stored plainly (flat code, raw, constant)?  Then the rows of a chunk do not depend on
@@ -209,6 +262,9 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
     const FastKind fk = fast_kind(info);
     uint32_t first_slot = 0;
     const uint32_t rings = s64_rings(info), pairs = pairs_fields(info);
+    CallChunks call;
+    call.add(info, slots, by_ids);
+    const PairsShape pairs_as = pairs ? pairs_shape(info.format, pairs, call) : PairsShape{0, false};
     const uint64_t elems_per_chunk = (uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(info.format);
     if (sub_ok(info, need) && (!by_ids || info.n_elems % elems_per_chunk == 0)) {
         // small chunks (pages): several per wavefront.  An id list may name a short last chunk, which
@@ -218,15 +274,16 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         if (info.format == ZC_FMT_BF16) LAUNCH_TRY(launch_decode_bf16_sub(info.streams, info.xor_delta != 0, nullptr, nullptr, (n_fast + spg - 1) / spg, &d, spg, stream));
         else LAUNCH_TRY(launch_decode_fp8_sub(info.streams, info.xor_delta != 0, by_ids, nullptr, nullptr, (n_fast + spg - 1) / spg, &d, spg, stream));
         first_slot = n_fast;
-    } else if (pairs && pairs_waves(info.format, pairs, slots, info.chunk_bytes)) {
-        const uint32_t waves = pairs_waves(info.format, pairs, slots, info.chunk_bytes);
-        LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, waves, nullptr, nullptr, (slots + waves - 1) / waves, &d, 0, stream));
+    } else if (pairs_as.chunks) {
+        LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, pairs_as.chunks, pairs_as.long_rings, nullptr, nullptr,
+                                       (uint32_t)(((uint64_t)slots + pairs_as.chunks - 1) / pairs_as.chunks), &d, 0, stream));
         first_slot = slots;
     } else if ((fk.ok || rings) && !by_ids) {
         // full chunks through a specialised kernel, a short last chunk through the generic one
         const uint32_t n_full = (uint32_t)(info.n_elems / ((uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(info.format)));
         const uint32_t n_fast = (n_full + kWavesPerGroup - 1) / kWavesPerGroup;
         if (fk.ok) LAUNCH_TRY(launch_decode_fp8_fast(fk.exp_kind, fk.sm_kind, info.xor_delta != 0, false, nullptr, nullptr, n_fast, &d, stream));
+        else if (e5m2_s64_ok(info)) LAUNCH_TRY(launch_decode_e5m2(info.xor_delta != 0, nullptr, nullptr, n_fast, &d, stream));
         else if (bf16_s64_rings(info)) LAUNCH_TRY(launch_decode_bf16_s64(bf16_s64_rings(info), info.xor_delta != 0, nullptr, nullptr, n_fast, &d, stream));
         else {
             const bool split = s64_split_ok(info);
@@ -245,8 +302,8 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         // what is left: chunks that are not whole rows and id lists with 64 lanes (the 64-lane kernel's build for those, for
         // the formats of two fields), geometries no specialised kernel takes
         const uint32_t n_work = (slots - first_slot + cpi - 1) / cpi;
-        if (pairs && info.chunk_bytes % 1024 == 0 && !by_ids && (info.format != ZC_FMT_FP8_E4M3 || tail_bytes(info) >= kPairsBytes))
-            LAUNCH_TRY(launch_decode_pairs(info.format, pairs == 2, info.xor_delta != 0, kWavesPerGroup, nullptr, nullptr, n_work, &d, first_slot, stream));
+        if (info.format == ZC_FMT_FP8_E4M3 && pairs && info.chunk_bytes % 1024 == 0 && !by_ids && call.tail >= kPairsTailBytes)
+            LAUNCH_TRY(launch_decode_pairs(info.format, false, info.xor_delta != 0, 4, true, nullptr, nullptr, n_work, &d, first_slot, stream));
         else if (info.n_fields == 3 && !by_ids && s64_split_ok(info) && slots - first_slot == 1)
             LAUNCH_TRY(launch_decode_fp4_tail(info.format, info.xor_delta != 0, nullptr, nullptr, 1, &d, first_slot, stream));
         else if (s64_tail_ok(info)) LAUNCH_TRY(launch_decode_s64_tail(info.format, info.xor_delta != 0, nullptr, nullptr, n_work, &d, first_slot, false, stream));
@@ -342,6 +399,8 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     }
     bool split = rings != 0;
     for (uint32_t t = 0; t < n_tensors && split; t++) split = s64_split_ok(tensors[t].info);
+    bool e5m2 = rings != 0;
+    for (uint32_t t = 0; t < n_tensors && e5m2; t++) e5m2 = e5m2_s64_ok(tensors[t].info);
     // BF16 sets whose every tensor has the shape of the BF16 kernel go there instead
     uint32_t bf16_rings = rings ? 1 : 0;
     for (uint32_t t = 0; t < n_tensors && bf16_rings; t++) {
@@ -349,8 +408,8 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
         bf16_rings = r == 0 ? 0 : (r > bf16_rings ? r : bf16_rings);
     }
     const bool fast = fk.ok || rings != 0 || sub;
-    uint64_t all_slots = 0;
-    for (uint32_t t = 0; t < n_tensors; t++) all_slots += tensors[t].d_chunk_ids ? tensors[t].n_chunk_ids : tensors[t].info.n_chunks;
+    CallChunks call;
+    for (uint32_t t = 0; t < n_tensors; t++) call.add(tensors[t].info, tensors[t].d_chunk_ids ? tensors[t].n_chunk_ids : tensors[t].info.n_chunks, tensors[t].d_chunk_ids != nullptr);
     // the kernels that look up two symbols at a time, when every tensor with any chunks qualifies: they take all chunks there are
     uint32_t pair_fields = 1;
     for (uint32_t t = 0; t < n_tensors && pair_fields; t++) {
@@ -359,8 +418,8 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
         if (k == 0 || tensors[t].info.xor_delta != tensors[0].info.xor_delta) pair_fields = 0;
         else if (k > pair_fields) pair_fields = k;
     }
-    const uint32_t pair_waves = pair_fields ? pairs_waves(fmt, pair_fields, all_slots, tensors[0].info.chunk_bytes) : 0;
-    const uint32_t spg = pair_waves ? pair_waves : sub ? sub_slots_per_group(S, all_slots) : split ? 1u : kWavesPerGroup;
+    const PairsShape pairs_as = pair_fields ? pairs_shape(fmt, pair_fields, call) : PairsShape{0, false};
+    const uint32_t spg = pairs_as.chunks ? pairs_as.chunks : sub ? sub_slots_per_group(S, call.slots) : split ? 1u : kWavesPerGroup;
     std::vector<TensorDev> descs(n_tensors);
     std::vector<WorkItem> fast_work, work;
     for (uint32_t t = 0; t < n_tensors; t++) {
@@ -378,7 +437,7 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
         const uint32_t slots = x.d_chunk_ids ? x.n_chunk_ids : info.n_chunks;
         uint32_t first_generic = 0;
         const uint64_t per_chunk = (uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(fmt);
-        if (pair_waves) {
+        if (pairs_as.chunks) {
             for (uint32_t c = 0; c < slots; c += spg) fast_work.push_back({t, c});
             first_generic = slots;
         } else if (fast && (sub || !x.d_chunk_ids)) {
@@ -409,8 +468,8 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     plan->format = fmt; plan->streams = S; plan->n_tensors = n_tensors;
     plan->n_fast_work = (uint32_t)fast_work.size(); plan->n_work = (uint32_t)work.size();
     plan->fast_exp_kind = (uint32_t)fk.exp_kind; plan->fast_sm_kind = (uint32_t)fk.sm_kind; plan->xor_delta = tensors[0].info.xor_delta;
-    plan->fast_kernel = pair_waves ? (fmt == ZC_FMT_FP8_E5M2 ? 7u : 8u) : fk.ok ? 1u : (rings ? (bf16_rings ? 6u : split ? 4u : 2u) : (sub ? (fmt == ZC_FMT_BF16 ? 5u : 3u) : 0u));
-    plan->n_rings = pair_waves ? pair_fields * 64 + pair_waves : sub ? spg : (bf16_rings ? bf16_rings : rings);
+    plan->fast_kernel = pairs_as.chunks ? (fmt == ZC_FMT_FP8_E5M2 ? 7u : 8u) : fk.ok ? 1u : (rings ? (e5m2 ? 9u : bf16_rings ? 6u : split ? 4u : 2u) : (sub ? (fmt == ZC_FMT_BF16 ? 5u : 3u) : 0u));
+    plan->n_rings = pairs_as.chunks ? pair_fields * 64 + (pairs_as.long_rings ? 32 : 0) + pairs_as.chunks : sub ? spg : (bf16_rings ? bf16_rings : rings);
     plan->scattered = 0;
     for (uint32_t t = 0; t < n_tensors; t++) if (tensors[t].d_chunk_ids) plan->scattered = 1;
     // the second list (chunks that are not whole rows, id lists with 64 lanes) goes through the 64-lane kernel's build for
@@ -418,16 +477,13 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     plan->tail_kernel = 1;
     for (uint32_t t = 0; t < n_tensors && plan->tail_kernel; t++)
         if (tensors[t].info.n_elems && (!s64_tail_ok(tensors[t].info) || tensors[t].info.xor_delta != tensors[0].info.xor_delta)) plan->tail_kernel = 0;
-    uint64_t longest_tail = 0;
     bool only_tails = plan->scattered == 0;                    // the second list is short last chunks and nothing else
-    for (uint32_t t = 0; t < n_tensors; t++) {
-        longest_tail = std::max(longest_tail, tail_bytes(tensors[t].info));
-        only_tails = only_tails && tensors[t].info.chunk_bytes % 1024 == 0;
-    }
+    for (uint32_t t = 0; t < n_tensors; t++) only_tails = only_tails && tensors[t].info.chunk_bytes % 1024 == 0;
     // lists over containers the FP8 kernel takes: that kernel has the whole chunks of the second list
     if (plan->tail_kernel && fk.ok && plan->scattered) plan->tail_kernel = 2;
-    // short last chunks of tensors whose code suits them: the kernels that look up two symbols at a time
-    else if (plan->tail_kernel && fast && only_tails && pair_fields && (fmt != ZC_FMT_FP8_E4M3 || longest_tail >= kPairsBytes)) { plan->tail_kernel = 3; plan->fast_sm_kind |= pair_fields << 8; }
+    // FP8 sets of more chunks than the kernels that look up two symbols at a time take: those kernels for the short last chunks, where
+    // these are long enough for their tables and one round of workgroups (1,500 of 100,000 bytes: 579 us against 184 without)
+    else if (plan->tail_kernel && fast && only_tails && pair_fields && fmt == ZC_FMT_FP8_E4M3 && call.tail >= kPairsTailBytes && work.size() <= kComputeUnits) plan->tail_kernel = 3;
     // FP4 sets whose whole chunks went to the 64-lane kernel's shared build: what is left is a short last chunk per tensor
     if (split && is_fp4(fmt) && !plan->scattered) plan->tail_kernel = 4;
     plan->fast_work_offset = descs_bytes; plan->work_offset = descs_bytes + fast_bytes;
@@ -441,7 +497,7 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
     if (!d_ws || !elem_bits(plan->format) || plan->streams == 0 || plan->streams > 64 || (plan->streams & (plan->streams - 1))) return ZC_ERR_INVALID_ARG;
     const uint8_t *ws = (const uint8_t *)d_ws;
     if (plan->n_fast_work && plan->fast_kernel == 1)
-        LAUNCH_TRY(launch_decode_fp8_fast((int)plan->fast_exp_kind, (int)(plan->fast_sm_kind & 255u), plan->xor_delta != 0, plan->scattered != 0, (const TensorDev *)ws,
+        LAUNCH_TRY(launch_decode_fp8_fast((int)plan->fast_exp_kind, (int)plan->fast_sm_kind, plan->xor_delta != 0, plan->scattered != 0, (const TensorDev *)ws,
                                           (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
     else if (plan->n_fast_work && (plan->fast_kernel == 2 || plan->fast_kernel == 4))
         LAUNCH_TRY(launch_decode_s64(plan->format, plan->n_rings, plan->xor_delta != 0, plan->fast_kernel == 4, (const TensorDev *)ws,
@@ -449,8 +505,10 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
     else if (plan->n_fast_work && plan->fast_kernel == 6)
         LAUNCH_TRY(launch_decode_bf16_s64(plan->n_rings, plan->xor_delta != 0, (const TensorDev *)ws,
                                           (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
+    else if (plan->n_fast_work && plan->fast_kernel == 9)
+        LAUNCH_TRY(launch_decode_e5m2(plan->xor_delta != 0, (const TensorDev *)ws, (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
     else if (plan->n_fast_work && (plan->fast_kernel == 8 || plan->fast_kernel == 7))
-        LAUNCH_TRY(launch_decode_pairs(plan->format, plan->n_rings / 64 == 2, plan->xor_delta != 0, plan->n_rings % 64, (const TensorDev *)ws,
+        LAUNCH_TRY(launch_decode_pairs(plan->format, plan->n_rings / 64 == 2, plan->xor_delta != 0, plan->n_rings % 32, (plan->n_rings & 32) != 0, (const TensorDev *)ws,
                                        (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, 0, stream));
     else if (plan->n_fast_work && plan->fast_kernel == 3)
         LAUNCH_TRY(launch_decode_fp8_sub(plan->streams, plan->xor_delta != 0, plan->scattered != 0, (const TensorDev *)ws,
@@ -463,7 +521,7 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
         LAUNCH_TRY(launch_decode_fp4_tail(plan->format, plan->xor_delta != 0, (const TensorDev *)ws, (const WorkItem *)(ws + plan->work_offset), plan->n_work,
                                           nullptr, 0, stream));
     else if (plan->n_work && plan->tail_kernel == 3 && plan->streams == 64)
-        LAUNCH_TRY(launch_decode_pairs(plan->format, plan->fast_sm_kind >> 8 == 2, plan->xor_delta != 0, kWavesPerGroup, (const TensorDev *)ws,
+        LAUNCH_TRY(launch_decode_pairs(plan->format, false, plan->xor_delta != 0, 4, true, (const TensorDev *)ws,
                                        (const WorkItem *)(ws + plan->work_offset), plan->n_work, nullptr, 0, stream));
     else if (plan->n_work && (plan->tail_kernel == 1 || plan->tail_kernel == 2) && plan->streams == 64)
         LAUNCH_TRY(launch_decode_s64_tail(plan->format, plan->xor_delta != 0, (const TensorDev *)ws, (const WorkItem *)(ws + plan->work_offset), plan->n_work,
