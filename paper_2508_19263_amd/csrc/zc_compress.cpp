@@ -110,8 +110,10 @@ CompressShape compress_shape(const Geometry &g, bool device_codes, uint64_t all_
     sh.cpi = chunks_per_work_item(g.S);
     sh.bf16 = g.fmt == ZC_FMT_BF16;
     sh.whole_shape = g.S == 64 && g.chunk_bytes % 1024 == 0;
-    sh.split_all = g.S == 64 && g.nf == 2 && g.chunk_bytes >= kSplitChunkBytes && all_chunks <= split_chunk_limit(g.fmt, delta);
-    sh.split_rest = sh.split_all || (sh.whole_shape && g.nf == 2);      // (what is left over is a tensor's short last chunk)
+    // (those kernels address a stream by 31 bits: not chunks whose stream can be longer, codes of 16 bits and all)
+    const bool split_can = g.S == 64 && g.nf == 2 && g.elems_per_chunk / (uint64_t)group_of(g.fmt) * 2 < 0x7FFFF000ull;
+    sh.split_all = split_can && g.chunk_bytes >= kSplitChunkBytes && all_chunks <= split_chunk_limit(g.fmt, delta);
+    sh.split_rest = sh.split_all || (split_can && sh.whole_shape);      // (what is left over is a tensor's short last chunk)
     sh.fp4_tails = sh.whole_shape && g.nf == 3;
     sh.lanes = device_codes && !sh.split_all && lane_counts_shape(g);
     sh.lanes8 = device_codes && !sh.split_all && lane_counts8_shape(g);

@@ -44,3 +44,23 @@ def test_one_chunk_of_fp4():
     zc.decompress(c, info, out=out, scales_out=scales)
     for got, want in ((out, x), (scales, sc)):
         assert torch.equal(got[:want.numel()], want) and bool((got[want.numel():] == 0x5A).all())
+
+
+def test_a_stream_of_more_than_2_gib_is_written():
+    # a dictionary whose longest code, all ones, is fifteen bits long, over a chunk of 1.25 GiB that has nothing but that symbol
+    n = 5 * HALF_GIB // 2
+    e = torch.zeros(1 << 16, dtype=torch.uint8)
+    for s in range(1, 16):                                      # symbol s half as often as s - 1
+        e[: 1 << (16 - s)] = s
+    e[0] = 15
+    p = zc.params(zc.FMT_FP8_E4M3, n, (15, 4, 0), streams=64)
+    code = zc.train_code((e << 3).to(DEV), e.numel(), p)
+    assert max(code.code_len[0]) == 15 and code.code_len[0][15] == 15
+    x = torch.full((n,), 15 << 3, dtype=torch.uint8, device=DEV)
+    dst = torch.full((zc.compress_bound(n, p),), 0x5A, dtype=torch.uint8, device=DEV)
+    c, info = zc.compress_with_code(x, n, p, code, dst=dst)
+    stream = c[info.payload_offset:info.payload_offset + (n // 8 * 15)]
+    assert info.n_chunks == 1 and stream.numel() > 1 << 31
+    # every word of the stream but the last ones of its 64 lanes is full of ones
+    written = bool((stream[:-4096] == 0xFF).all())
+    assert written
