@@ -111,6 +111,7 @@ def test_a_few_chunks_more_than_fill_the_gpu_with_two_table_decoded_fields():
     p = zc.params(BF16, chunk, streams=64)
     whole = [kinds[i % 2] for i in range(100)]                  # 4,100 chunks
     assert decode_set(whole, p).fast_kernel == 6
+    assert decode_set([torch.cat(whole)], p).fast_kernel == 6   # (and one tensor alone)
     for xs, ids in ((whole[:99] + [kinds[0][:kinds[0].numel() - 512]], None), (whole[:99], None), (whole, [np.arange(41) for _ in whole])):
         plan = decode_set(xs, p, ids)
         assert plan.fast_kernel == 8 and plan.n_rings == 128 + 8 and plan.n_work == 0
