@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
         kind[f] = uniform32(d.kind[f]);
         if (kind[f] == KIND_HUFF && !(SPLIT && f < 2)) build_field_tab(tab[f], d.comp + d.table_off[f], 1 << (f == 2 ? 8 : F_::SB), d.lmax[f]);
     }
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63, wave = uniform32(threadIdx.x >> 6);       // (uniform: so are the rows, their loop and the stores' places)
     const uint32_t slot = uniform32(it.first + (split ? 0u : wave));
     uint32_t chunk = slot;
     if (TAIL) {
@@ -52,12 +52,12 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
     const uint32_t cb = uniform32(d.chunk_bytes);
     const uint64_t E = (uint64_t)cb * 8 / F_::EB;             // (the product passes 32 bits from chunks of 512 MiB on)
     const uint64_t n_elems = uniform64(d.n_elems);
-    const uint32_t n_full = (uint32_t)(n_elems / E);
-    if (TAIL ? chunk >= uniform32(d.n_chunks) : chunk >= n_full) return;
-    if (TAIL && skip_whole && chunk < n_full && cb % 1024 == 0) return;        // a specialised kernel took the whole chunks of this launch
-    // this chunk's elements and bytes: all of cb unless it is the tensor's short last chunk
     const uint64_t before = (uint64_t)chunk * E;
-    const uint64_t n = (!TAIL || n_elems - before >= E) ? E : n_elems - before;
+    const bool whole = before + E <= n_elems;
+    if (TAIL ? chunk >= uniform32(d.n_chunks) : !whole) return;
+    if (TAIL && skip_whole && whole && cb % 1024 == 0) return;        // a specialised kernel took the whole chunks of this launch
+    // this chunk's elements and bytes: all of cb unless it is the tensor's short last chunk
+    const uint64_t n = (!TAIL || whole) ? E : n_elems - before;
     const uint32_t nbytes = (uint32_t)(n * F_::EB / 8);                   // two-field formats have whole bytes per element
     if (TAIL && n_elems <= before) return;
     const uint8_t *comp = reinterpret_cast<const uint8_t *>(uniform64((uint64_t)d.comp));
@@ -107,8 +107,25 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
         if (SPLIT || kind[1] != KIND_HUFF) plain_fetch<F_::SB, F_::G>(kind[1], r1, row_begin, lane, w1_next);
         if (XOR) base_next = __builtin_amdgcn_raw_buffer_load_b128(bs, (int)(lane * 16), (int)(row_begin * 1024), 0);
     }
+    // (0x0F70: vector memory operations only.  With nothing in flight on the way into the loop, the wait for a row's words inside it need
+    // not be one for the store behind them as well)
+    if (SPLIT) __builtin_amdgcn_s_waitcnt(0x0F70);
     for (uint32_t row = row_begin; row < row_end; row++) {
         uint64_t P0 = 0, P1 = 0, Q0 = 0, Q1 = 0;       // Q: symbols 8..15 of a run of 16 symbols of 8 bits
+        if constexpr (SPLIT) {
+            // (the next row's words come into the registers this row's have just left: with copies instead, what waits for the words
+            // before the copies waits for this row's store too)
+            plain_finish<F_::SB, F_::G>(kind[0], w0_next, K0, P0, Q0);
+            plain_finish<F_::SB, F_::G>(kind[1], w1_next, K1, P1, Q1);
+            const uint4 j = join_run4<FMT>(P0, Q0, P1, Q1);
+            u32x4 v = {j.x, j.y, j.z, j.w};
+            if (XOR) v ^= base_next;
+            plain_fetch<F_::SB, F_::G>(kind[0], r0, row + 1, lane, w0_next);
+            plain_fetch<F_::SB, F_::G>(kind[1], r1, row + 1, lane, w1_next);
+            if (XOR) base_next = __builtin_amdgcn_raw_buffer_load_b128(bs, (int)(lane * 16), (int)((row + 1 < rows ? row + 1 : row) * 1024), 0);
+            store_row<2>(v, ds, lane, row);
+            continue;
+        }
         uint32_t w0[WPR], w1[WPR];
 #pragma unroll
         for (int h = 0; h < WPR; h++) { w0[h] = w0_next[h]; w1[h] = w1_next[h]; }

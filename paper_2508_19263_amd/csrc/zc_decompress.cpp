@@ -126,8 +126,9 @@ constexpr uint64_t kPairsTailBytes = 16 * 1024;
 
 // How those kernels take a call: chunks per workgroup, and whether with the long rings (four chunks then); chunks 0: another kernel is
 // faster.  Measured on MI355X, these kernels | the others, in us.
-//  - Long rings leave a compute unit one workgroup (byte symbols with one table-decoded field, whose table is small: two), so they
-//    are for calls of one round of workgroups.  300 BF16 tensors of 100,000 bytes, a workgroup each: 184 with long rings, 110 with short.
+//  - Long rings leave a compute unit one workgroup, so they are for calls of one round of workgroups.  300 BF16 tensors of 100,000 bytes,
+//    a workgroup each: 184 with long rings, 110 with short.  (Byte symbols with one table-decoded field, whose table is small: two
+//    workgroups, but from 1,025 chunks on only the largest gain: 1,500 chunks of 16 KiB 29 | 27, 64 KiB 72 | 70, 256 KiB 255 | 278.)
 //  - FP8 E4M3 has tables of 64 KiB and comes here with long rings only; beyond a round, k_decode_fp8, bound by its traffic, is ahead.
 //    Its table pays for whole chunks from 96 KiB on (16 of 64 KiB: 70 | 70, 256: 74 | 71; 96 KiB: 94 | 98 and 83 | 99; 192 KiB: 149 | 183),
 //    and sooner where it saves the second launch that a short last chunk needs beside k_decode_fp8 (64 chunks of 32 KiB and one of
@@ -146,7 +147,7 @@ constexpr uint64_t kPairsTailBytes = 16 * 1024;
 struct PairsShape { uint32_t chunks; bool long_rings; };
 PairsShape pairs_shape(uint32_t fmt, uint32_t fields, const CallChunks &c)
 {
-    const bool one_round = c.groups <= kComputeUnits * (fmt == ZC_FMT_FP8_E4M3_BYTES && fields == 1 ? 2 : 1);
+    const bool one_round = c.groups <= kComputeUnits || (fmt == ZC_FMT_FP8_E4M3_BYTES && fields == 1 && c.slots <= 1024 && c.groups <= 2 * kComputeUnits);
     if (fmt == ZC_FMT_FP8_E4M3) {
         const bool pays = c.whole ? c.whole >= 96 * 1024 || (c.whole >= 32 * 1024 && c.tail) : c.tail >= kPairsTailBytes;
         return {one_round && pays ? 4u : 0u, true};

@@ -65,6 +65,7 @@ CASES = [
     (E5M2, 300, 2 * 4096 + 2048, 4096, 7, 64 + 4, None),
     (BYTES, 400, 4096, 256 * KIB, 8, LONG, None),               # small tables: two workgroups on a compute unit
     (BYTES, 600, 4096, 256 * KIB, 8, 64 + 1, None),
+    (BYTES, 1, 1100 * 2048, 2048, 8, 64 + 8, None),
     (BYTES, 1100, 2 * 2048, 2048, 8, 64 + 2, None),
     (BF16, 1100, 2 * 2048, 2048, 6, None, None),                # many tensors of few whole chunks
     (BF16, 800, 3 * 2048, 2048, 6, None, None),
