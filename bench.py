@@ -215,8 +215,8 @@ def other_workloads(torch, wl, zc, dev, extras, copy_gbps):
         # config 2 again with byte-grouped symbols (two exponents per symbol; the flat sign+mantissa field raw)
         set2 = [t for _, t in wl.fp8_weight_set(32, device=dev)]
         n2 = [t.numel() for t in set2]
-        run("c2_fp8_byte_symbols", zc.FMT_FP8_E4M3_BYTES, set2, n2, 262144, 64, policy=zc.POLICY_AUTO, decode_kernel=S64, compress_kernels="k_hist_rows8_lanes + k_codes + k_sizes_rows8_counts + k_scan + k_encode_bf16<BYTES>")
-        run("c2_fp8_byte_symbols_limit_11", zc.FMT_FP8_E4M3_BYTES, set2, n2, 262144, 64, limit=(11, 11, 0), policy=zc.POLICY_AUTO, decode_kernel=S64, compress_kernels="k_hist_rows8_lanes + k_codes + k_sizes_rows8_counts + k_scan + k_encode_bf16<BYTES>")
+        run("c2_fp8_byte_symbols", zc.FMT_FP8_E4M3_BYTES, set2, n2, 262144, 64, policy=zc.POLICY_AUTO, decode_kernel="k_decode_pairs", compress_kernels="k_hist_rows8_lanes + k_codes + k_sizes_rows8_counts + k_scan + k_encode_bf16<BYTES>")
+        run("c2_fp8_byte_symbols_limit_11", zc.FMT_FP8_E4M3_BYTES, set2, n2, 262144, 64, limit=(11, 11, 0), policy=zc.POLICY_AUTO, decode_kernel="k_decode_pairs", compress_kernels="k_hist_rows8_lanes + k_codes + k_sizes_rows8_counts + k_scan + k_encode_bf16<BYTES>")
         run("c2_fp8_plain_symbols_auto", zc.FMT_FP8_E4M3, set2, n2, 262144, 64, policy=zc.POLICY_AUTO, decode_kernel="k_decode_fp8", compress_kernels="k_hist_fp8_lanes + k_codes + k_sizes_fp8_counts + k_scan + k_encode_fp8")
         # the generic paths beside their specialised neighbours: a chunk size that is not whole rows of 1 KiB takes the
         # chunks that are not whole rows: the generic encoder, the 64-lane decoder's build for such chunks
@@ -224,15 +224,15 @@ def other_workloads(torch, wl, zc, dev, extras, copy_gbps):
         run("c2_fp8_chunks_of_48KiB_specialised_kernels", zc.FMT_FP8_E4M3, set2, n2, 48 * 1024, 64, decode_kernel="k_decode_fp8", compress_kernels="k_hist + k_codes + k_sizes_fp8 + k_scan + k_encode_fp8")
         # random access to the chunks of weights (Sec. 3.1): a seeded quarter of every tensor's 256 KiB chunks, in random order
         chunk_ids = [wl.page_sample(t.numel() // 262144, 0.25, device=dev, seed=900 + i) for i, t in enumerate(set2)]
-        run("c2_fp8_chunk_list", zc.FMT_FP8_E4M3, set2, n2, 262144, 64, ids=chunk_ids, decode_kernel="k_decode_fp8; the list: k_decode_s64<TAIL>",
+        run("c2_fp8_chunk_list", zc.FMT_FP8_E4M3, set2, n2, 262144, 64, ids=chunk_ids, decode_kernel="k_decode_fp8; the list: its build for lists",
             compress_kernels="k_hist_fp8_lanes + k_codes + k_sizes_fp8_counts + k_scan + k_encode_fp8")
         del chunk_ids
         ragged = [t[:t.numel() - 4096 - 7 * 16] for t in set2]
-        run("c2_fp8_ragged_tails", zc.FMT_FP8_E4M3, ragged, [t.numel() for t in ragged], 262144, 64, decode_kernel="k_decode_fp8 + k_decode_pairs (last chunks)", compress_kernels="k_hist_fp8_lanes + k_hist + k_codes + k_sizes_fp8_counts + k_sizes_tail (last chunks) + k_scan + k_encode_fp8 + k_encode (last chunks)")
+        run("c2_fp8_ragged_tails", zc.FMT_FP8_E4M3, ragged, [t.numel() for t in ragged], 262144, 64, decode_kernel="k_decode_fp8 + k_decode_pairs (last chunks)", compress_kernels="k_hist_fp8_lanes + k_hist + k_codes + k_sizes_fp8_counts + k_sizes_split (last chunks) + k_scan + k_encode_fp8 + k_encode_split (last chunks)")
         del set2, ragged
         set2 = [t for _, t in wl.fp8_weight_set(32, device=dev, e5m2=True)]
-        run("c2_shapes_in_fp8_e5m2", zc.FMT_FP8_E5M2, set2, [t.numel() for t in set2], 262144, 64, decode_kernel=S64, compress_kernels="k_hist_fp8_lanes<E5M2> + k_codes + k_sizes_e5m2_counts + k_scan + k_encode_bf16<E5M2>")
-        run("c2_shapes_in_fp8_e5m2_limit_8", zc.FMT_FP8_E5M2, set2, [t.numel() for t in set2], 262144, 64, limit=(8, 8, 0), decode_kernel=S64, compress_kernels="k_hist_fp8_lanes<E5M2> + k_codes + k_sizes_e5m2_counts + k_scan + k_encode_bf16<E5M2>")
+        run("c2_shapes_in_fp8_e5m2", zc.FMT_FP8_E5M2, set2, [t.numel() for t in set2], 262144, 64, decode_kernel="k_decode_pairs", compress_kernels="k_hist_fp8_lanes<E5M2> + k_codes + k_sizes_e5m2_counts + k_scan + k_encode_bf16<E5M2>")
+        run("c2_shapes_in_fp8_e5m2_limit_8", zc.FMT_FP8_E5M2, set2, [t.numel() for t in set2], 262144, 64, limit=(8, 8, 0), decode_kernel="k_decode_pairs", compress_kernels="k_hist_fp8_lanes<E5M2> + k_codes + k_sizes_e5m2_counts + k_scan + k_encode_bf16<E5M2>")
         del set2
     x = wl.bf16_weight(1 << 20, device=dev, seed=0)
     run("c1_bf16_1M", zc.FMT_BF16, [x], [1 << 20], 65536, 64, limit=(16, 16, 0), decode_kernel="k_decode_pairs", compress_kernels="k_hist + k_codes + k_sizes_split + k_scan + k_encode_split")

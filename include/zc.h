@@ -96,8 +96,8 @@ typedef struct {
 /* Choosing the geometry.  Every geometry above gives a valid container; these give the fast kernels:
  *   - 64 lanes: chunk_bytes a multiple of 1024 (whole rows of 16 bytes per lane).  Other chunk sizes are compressed
  *     by the generic kernels (1.25 x slower) and decode about 1.35 x slower on MI355X (48 KiB + 16 against 48 KiB);
- *     the short last chunk of a tensor costs a compress call, and a decode of more than 1,024 FP8 chunks, a second, small
- *     launch; other decodes take it along.
+ *     the short last chunk of a tensor costs a compress call, and a decode of FP4 or of more than 1,024 FP8 chunks, a second,
+ *     small launch; other decodes mostly take it along.
  *   - chunks below 16 KiB (K/V pages, Sec. 3.3): 4 to 32 lanes with chunk_bytes a multiple of 16 * lanes.  A
  *     wavefront then decodes 64 / lanes chunks at once; with 64 lanes it decodes one small chunk at a time (a 2 KiB
  *     page: 2.3 x slower from an id list) and every lane's look-ahead words eat the gain (ratio 1.00 against 0.86).

@@ -3,7 +3,8 @@
 // on the same period or stored plainly (flat code, raw, constant; E5M2: its flat 3-bit code).
 //
 // A chunk is one wavefront's serial chain: window, lookups, refill (whose word depends on how many lanes take one), window.
-// Every link is an LDS round trip of about 90 cycles, and a call of few chunks takes as long as one chunk's chain.  So
+// Every link is an LDS round trip with the arithmetic that gives its address, about 140 cycles, and a call of few chunks takes as long
+// as one chunk's chain.  So
 //   - exponents are looked up in pairs: the next 13 stream bits give the next TWO symbols, which halves the lookups and their
 //     address and shift instructions.  An entry already is the pair's part of an output word.  (Sign+mantissa codes and byte
 //     symbols are too long for pairs: singles, by 12 bits.)
