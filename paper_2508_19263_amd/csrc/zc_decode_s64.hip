@@ -693,16 +693,14 @@ __device__ __forceinline__ void e5m2_rows(const FieldTab &T, __amdgpu_buffer_rsr
 }
 
 template <bool XOR>
-__global__ __launch_bounds__(256) void k_decode_e5m2(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single)
+__global__ __launch_bounds__(256) void k_decode_e5m2(const TensorDev *descs, const WorkItem *work)
 {
     __shared__ __attribute__((aligned(16))) uint32_t rings[kWavesPerGroup * kRing2Words];
     __shared__ FieldTab tab;
     __shared__ TensorDev dsh;
     __shared__ uint32_t flat3;
-    WorkItem it;
-    if (use_single) { it.tensor = 0; it.first = blockIdx.x * kWavesPerGroup; }
-    else it = work[blockIdx.x];
-    if (threadIdx.x == 0) { dsh = use_single ? single : descs[it.tensor]; flat3 = 1; }
+    const WorkItem it = work[blockIdx.x];
+    if (threadIdx.x == 0) { dsh = descs[it.tensor]; flat3 = 1; }
     __syncthreads();
     const TensorDev &d = dsh;
     const uint32_t p0 = uniform32(d.period[0]);
@@ -738,14 +736,12 @@ __global__ __launch_bounds__(256) void k_decode_e5m2(const TensorDev *descs, con
     else e5m2_rows<8, false, XOR>(tab, r0, r1, ds, bs, ring, rows, lane);
 }
 
-int launch_decode_e5m2(bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev *single, void *stream)
+int launch_decode_e5m2(bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, void *stream)
 {
     if (n_work == 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-    const TensorDev s = single ? *single : TensorDev{};
-    const int use_single = single ? 1 : 0;
-    if (xor_delta) hipLaunchKernelGGL((k_decode_e5m2<true>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, s, use_single);
-    else hipLaunchKernelGGL((k_decode_e5m2<false>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, s, use_single);
+    if (xor_delta) hipLaunchKernelGGL((k_decode_e5m2<true>), dim3(n_work), dim3(256), 0, st, d_descs, d_work);
+    else hipLaunchKernelGGL((k_decode_e5m2<false>), dim3(n_work), dim3(256), 0, st, d_descs, d_work);
     return (int)hipGetLastError();
 }
 

@@ -284,7 +284,6 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         const uint32_t n_full = (uint32_t)(info.n_elems / ((uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(info.format)));
         const uint32_t n_fast = (n_full + kWavesPerGroup - 1) / kWavesPerGroup;
         if (fk.ok) LAUNCH_TRY(launch_decode_fp8_fast(fk.exp_kind, fk.sm_kind, info.xor_delta != 0, false, nullptr, nullptr, n_fast, &d, stream));
-        else if (e5m2_s64_ok(info)) LAUNCH_TRY(launch_decode_e5m2(info.xor_delta != 0, nullptr, nullptr, n_fast, &d, stream));
         else if (bf16_s64_rings(info)) LAUNCH_TRY(launch_decode_bf16_s64(bf16_s64_rings(info), info.xor_delta != 0, nullptr, nullptr, n_fast, &d, stream));
         else {
             const bool split = s64_split_ok(info);
@@ -507,7 +506,7 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
         LAUNCH_TRY(launch_decode_bf16_s64(plan->n_rings, plan->xor_delta != 0, (const TensorDev *)ws,
                                           (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
     else if (plan->n_fast_work && plan->fast_kernel == 9)
-        LAUNCH_TRY(launch_decode_e5m2(plan->xor_delta != 0, (const TensorDev *)ws, (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
+        LAUNCH_TRY(launch_decode_e5m2(plan->xor_delta != 0, (const TensorDev *)ws, (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, stream));
     else if (plan->n_fast_work && (plan->fast_kernel == 8 || plan->fast_kernel == 7))
         LAUNCH_TRY(launch_decode_pairs(plan->format, plan->n_rings / 64 == 2, plan->xor_delta != 0, plan->n_rings % 32, (plan->n_rings & 32) != 0, (const TensorDev *)ws,
                                        (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, 0, stream));

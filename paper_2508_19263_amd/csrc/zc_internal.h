@@ -169,7 +169,7 @@ int launch_decode_bf16_s64(uint32_t n_rings, bool xor_delta, const TensorDev *d_
                            const TensorDev *single, void *stream);
 // FP8 E5M2, 64 lanes per chunk, full chunks, exponent field table decoded (refill period 2, 4 or 8), sign+mantissa field
 // coded with the flat 3-bit code over the values 0..7 (zc_decode_s64.hip)
-int launch_decode_e5m2(bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev *single, void *stream);
+int launch_decode_e5m2(bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, void *stream);
 // BF16, FP8 (E4M3, E5M2, byte symbols), 64 lanes, any chunks and lists of them, two symbols per lookup; two: some tensor's
 // sign+mantissa field is table decoded too; chunks: per work item, 4 with long rings (FP8 E4M3: always), else 1, 2, 4 or 8;
 // first_slot: where a single tensor's items start

@@ -125,3 +125,11 @@ def test_id_lists_of_fp8():
         ids = np.random.default_rng(1).integers(0, 31 if tail else 30, 50)
         ids[7] = 30 if tail else 29
         assert decode_set([x, x], zc.params(FP8, chunk, streams=64), [ids, ids[:9]]).fast_kernel == kernel
+
+
+@pytest.mark.parametrize("longest", [4, 8, 12])                 # refill periods of 8, 4 and 2
+@pytest.mark.parametrize("delta", [False, True])
+def test_many_e5m2_tensors_of_few_whole_chunks(longest, delta):
+    print("case", longest, delta, flush=True)
+    x, w = [tensor(E5M2, 2 * 2048, s, longest) for s in range(3)], torch.zeros(4096, dtype=torch.uint8, device=DEV)
+    assert decode_set([x[i % 3] for i in range(1100)], zc.params(E5M2, 2048, streams=64), bases=[w] * 1100 if delta else None).fast_kernel == 9
