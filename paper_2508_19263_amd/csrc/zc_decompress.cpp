@@ -105,7 +105,8 @@ uint64_t tail_bytes(const zc_info &info)
 
 // What a call decodes, as far as the choice of those kernels asks: its chunks, the workgroups they make four to each (a workgroup has
 // chunks of one tensor), tensors with any, the most chunks of a tensor, bytes of the largest whole chunk and of the longest short last
-// one (0: no such chunk; short ones are not looked for where an id list says what is decoded).
+// one (0: no such chunk; short ones are not looked for where an id list says what is decoded).  Chunks that are not whole rows count as
+// short ones: the other kernels take them the same way.
 struct CallChunks {
     uint64_t slots = 0, groups = 0, tensors = 0, most = 0, whole = 0, tail = 0;
     bool lists = false;
@@ -115,7 +116,10 @@ struct CallChunks {
         slots += n; groups += (n + 3) / 4; tensors++;
         most = std::max(most, n);
         lists = lists || by_ids;
-        if (info.n_elems >= (uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(info.format)) whole = std::max<uint64_t>(whole, info.chunk_bytes);
+        if (info.n_elems >= (uint64_t)info.chunk_bytes * 8 / (uint64_t)elem_bits(info.format)) {
+            uint64_t &kind = info.chunk_bytes % 1024 == 0 ? whole : tail;
+            kind = std::max<uint64_t>(kind, info.chunk_bytes);
+        }
         if (!by_ids) tail = std::max(tail, tail_bytes(info));
     }
 };

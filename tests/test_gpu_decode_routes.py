@@ -80,6 +80,10 @@ CASES = [
     (FP8, 5, 12 * KIB, 256 * KIB, 1, None, 1),                  # short ones alone from 16 KiB,
     (FP8, 5, 20 * KIB, 256 * KIB, 8, LONG, None),
     (FP8, 300, 20 * KIB, 256 * KIB, 1, None, 1),                # one round of workgroups
+    (FP8, 1, 20 * (20 * KIB + 16), 20 * KIB + 16, 8, LONG, None),        # chunks that are not whole rows: as short ones
+    (FP8, 1, 20 * (12 * KIB + 16), 12 * KIB + 16, 0, None, 1),
+    (E5M2, 1100, 2 * 9232, 9232, 7, 64 + 2, None),
+    (BF16, 1100, 2 * 9232, 9232, 8, 64 + 2, None),
     (FP8, 1, 1024 * 96 * KIB + 16, 96 * KIB, 1, None, 1),
     (FP8, 1, 1025 * 32 * KIB + 20 * KIB, 32 * KIB, 1, None, 3),
     (FP8, 100, 12 * 32 * KIB + 20 * KIB, 32 * KIB, 1, None, 3),
