@@ -140,9 +140,9 @@ bool compress_fast_shape(const Geometry &g, uint64_t n_elems, uint64_t bound_byt
 }
 
 // field split + histogram (a1-a3)
-zc_status CompressQueue::queue_histogram() const
+zc_status CompressQueue::queue_histogram(bool cleared) const
 {
-    LAUNCH_TRY(launch_zero(d_hist(), (uint64_t)T * 3 * 256, stream));
+    if (!cleared) LAUNCH_TRY(launch_zero(d_hist(), (uint64_t)T * 3 * 256, stream));
     LAUNCH_TRY(launch_hist(g.fmt, d_descs(), d_list(w.hist_work), n_hist, 0, d_hist(), stream));
     if (sh.lanes8) LAUNCH_TRY(launch_hist_rows8_lanes(g.fmt, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), (uint32_t *)d_lane_counts(), stream));
     else LAUNCH_TRY(launch_hist_fp8_lanes(sh.lanes_e5m2, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), d_lane_counts(), stream));
@@ -498,8 +498,9 @@ private:
         const uint64_t scan_bytes = (uint64_t)T * sizeof(ScanOut);
         static_assert(kHeaderBytes + 3 * 256 + sizeof(ScanOut) <= kBlobBytes, "header, tables and sizes of a tensor fit its blob");
         const bool one_copy = with_blobs && !q.chained;
-        if (!one_copy) HIP_TRY(hipMemcpyAsync(landing.ptr, ws + w.scan, scan_bytes, hipMemcpyDeviceToHost, hs));
-        if (with_blobs) HIP_TRY(hipMemcpyAsync(landing.ptr + scan_bytes, ws + w.blobs, (uint64_t)T * kBlobBytes, hipMemcpyDeviceToHost, hs));
+        zc_status got = one_copy ? ZC_OK : read_back(landing.ptr, ws + w.scan, scan_bytes, stream);
+        if (got == ZC_OK && with_blobs) got = read_back(landing.ptr + scan_bytes, ws + w.blobs, (uint64_t)T * kBlobBytes, stream);
+        if (got) return got;
         if (roomy) {
             // wait for the copies only, not for the encoder queued behind them
             hipEvent_t copied;
@@ -683,9 +684,9 @@ private:
                               {w.whole_work, whole_work.data(), whole_work.size() * sizeof(WorkItem)},
                               {w.other_work, other_work.data(), other_work.size() * sizeof(WorkItem)},
                               {w.blobs, blobs.data(), blobs.size()}};
-        zc_status st = stage_upload(ws, w.descs, w.enc, all, 9, stream);
+        zc_status st = stage_upload(ws, w.descs, w.enc, all, 9, stream, q.d_hist(), (uint64_t)T * 3 * 256);
         if (st) return st;
-        st = q.queue_histogram();
+        st = q.queue_histogram(true);
         if (st) return st;
         st = q.queue_codes(params->policy);
         if (st) return st;

@@ -662,6 +662,25 @@ __global__ __launch_bounds__(256) void k_zero(uint64_t *p, uint64_t n)
     if (i < n) p[i] = 0;
 }
 
+// What the host hands a small call, read from its page-locked buffer by the GPU itself, and words to be cleared, in one launch; and
+// what the host reads back from one, written there.  A copy through the runtime is a launch of its own with a gap of about 5 us on either
+// side: seven FP8 tensors compressed 230 | 219 us, 2^20 BF16 values 90 | 88, nine FP8 layers 1,250 | 1,236.  Bound by the launch.
+__global__ __launch_bounds__(256) void k_hand_over(const uint8_t *src, uint8_t *dst, uint32_t bytes, uint64_t *zero, uint32_t n_zero)
+{
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x, n16 = bytes / 16;
+    if (i < n16) reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
+    if (i < bytes % 16) dst[n16 * 16 + i] = src[n16 * 16 + i];
+    if (i < n_zero) zero[i] = 0;
+    __threadfence_system();                                      // (the destination may be the host's)
+}
+
+int launch_hand_over(const void *src, void *dst, uint64_t bytes, uint64_t *d_zero, uint64_t n_zero, void *stream)
+{
+    const uint64_t n = bytes / 16 + 16 > n_zero ? bytes / 16 + 16 : n_zero;
+    hipLaunchKernelGGL(k_hand_over, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, (const uint8_t *)src, (uint8_t *)dst, (uint32_t)bytes, d_zero, (uint32_t)n_zero);
+    return (int)hipGetLastError();
+}
+
 int launch_zero(uint64_t *d_words, uint64_t n_words, void *stream)
 {
     if (n_words == 0) return 0;

@@ -15,6 +15,10 @@ namespace zc {
 
 namespace {
 
+// Bytes up to which the GPU fetches and delivers by itself (k_hand_over); a larger transfer is worth the runtime's copy, whose launch it
+// hides.
+constexpr uint64_t kHandOver = 256 * 1024;
+
 // ---- uploads -----------------------------------------------------------------------------------
 // A few buffers used in turn: the pieces of an upload are packed into one at their workspace offsets and leave in
 // a single asynchronous copy.  A buffer's next user waits for the event of the copy that last left it, so calls
@@ -23,9 +27,9 @@ namespace {
 // other threads wait for each other only when they are dealt the same buffer.
 class HostStage {
 public:
-    zc_status upload(uint8_t *d_ws, uint64_t lo, uint64_t hi, const Piece *pieces, int n, hipStream_t hs)
+    zc_status upload(uint8_t *d_ws, uint64_t lo, uint64_t hi, const Piece *pieces, int n, hipStream_t hs, uint64_t *d_zero, uint64_t n_zero)
     {
-        if (hi <= lo) return ZC_OK;
+        if (hi <= lo) { LAUNCH_TRY(launch_zero(d_zero, n_zero, hs)); return ZC_OK; }
         int mine;
         {
             std::lock_guard<std::mutex> deal(m_);
@@ -47,7 +51,11 @@ public:
         if (!k.ev && hipEventCreateWithFlags(&k.ev, hipEventDisableTiming) != hipSuccess) return ZC_ERR_DEVICE;
         for (int i = 0; i < n; i++)
             if (pieces[i].bytes) std::memcpy(k.buf + (pieces[i].off - lo), pieces[i].src, pieces[i].bytes);
-        HIP_TRY(hipMemcpyAsync(d_ws + lo, k.buf, need, hipMemcpyHostToDevice, hs));
+        if (need <= kHandOver && (uintptr_t)(d_ws + lo) % 16 == 0) LAUNCH_TRY(launch_hand_over(k.buf, d_ws + lo, need, d_zero, n_zero, hs));
+        else {
+            HIP_TRY(hipMemcpyAsync(d_ws + lo, k.buf, need, hipMemcpyHostToDevice, hs));
+            LAUNCH_TRY(launch_zero(d_zero, n_zero, hs));
+        }
         HIP_TRY(hipEventRecord(k.ev, hs));
         k.pending = true;
         return ZC_OK;
@@ -120,9 +128,19 @@ HostLanding &host_landing() { static HostLanding s; return s; }
 
 }  // namespace
 
-zc_status stage_upload(uint8_t *d_ws, uint64_t lo, uint64_t hi, const Piece *pieces, int n, void *stream)
+zc_status stage_upload(uint8_t *d_ws, uint64_t lo, uint64_t hi, const Piece *pieces, int n, void *stream, uint64_t *d_zero, uint64_t n_zero)
 {
-    return host_stage().upload(d_ws, lo, hi, pieces, n, (hipStream_t)stream);
+    return host_stage().upload(d_ws, lo, hi, pieces, n, (hipStream_t)stream, d_zero, n_zero);
+}
+
+zc_status read_back(uint8_t *landing, const uint8_t *d_src, uint64_t bytes, void *stream)
+{
+    if (bytes && bytes <= kHandOver && (uintptr_t)landing % 16 == 0 && (uintptr_t)d_src % 16 == 0) {
+        LAUNCH_TRY(launch_hand_over(d_src, landing, bytes, nullptr, 0, stream));
+        return ZC_OK;
+    }
+    HIP_TRY(hipMemcpyAsync(landing, d_src, bytes, hipMemcpyDeviceToHost, (hipStream_t)stream));
+    return ZC_OK;
 }
 
 LandingLease::LandingLease(uint64_t bytes) { if (bytes) ptr = host_landing().acquire(bytes, &cap); }
