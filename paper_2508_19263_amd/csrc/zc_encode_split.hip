@@ -20,7 +20,11 @@ namespace zc {
 
 namespace {
 
-constexpr uint32_t kSplitWaves = 16;
+// Wavefronts per chunk: sixteen, of which a compute unit holds two workgroups, 512 chunks in all; eight in calls of more, which would
+// leave the second round nearly empty.  Whole calls over chunks of 256 KiB, sixteen | eight, us: FP8 520: 223 | 202, 600: 234 | 215,
+// 768: 238 | 231; BF16 520: 235 | 216, 768: 246 | 235; not E5M2 (520: 292 | 299) and byte symbols (600: 280 | 289), whose chunks are worth
+// more instructions.
+inline uint32_t split_waves(uint32_t fmt, uint32_t n_work) { return n_work > 512 && (fmt == ZC_FMT_FP8_E4M3 || fmt == ZC_FMT_BF16) ? 8 : 16; }
 // places of the (up to two) words a wavefront finds asked for and not complete at its first row; as byte offsets they lie
 // beyond every stream, so the range check of the buffer store drops them
 constexpr uint32_t kSeam0 = 0xFFFFFFFEu, kSeam1 = 0xFFFFFFFFu;
@@ -250,15 +254,15 @@ __device__ __forceinline__ void load_tables(const TensorDev *dp, const uint32_t 
 
 }  // namespace
 
-// Stream sizes of the chunks of a work list, one chunk per item.  Sixteen wavefronts add up the code lengths of a sixteenth
-// of the rows each; the closed form above, taken at a lane's last step, gives the lane's words.
-template <int FMT>
-__global__ __launch_bounds__(64 * kSplitWaves) void k_sizes_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, uint32_t *units)
+// Stream sizes of the chunks of a work list, one chunk per item.  W wavefronts add up the code lengths of a W-th of the rows
+// each; the closed form above, taken at a lane's last step, gives the lane's words.
+template <int FMT, uint32_t W>
+__global__ __launch_bounds__(64 * W) void k_sizes_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, uint32_t *units)
 {
     using F_ = Fmt<FMT>;
     static_assert(F_::NF == 2 && (F_::SB == 4 || F_::SB == 8) && F_::G * F_::SB <= 128, "two fields of 4- or 8-bit symbols, at most two 64-bit words per run");
     __shared__ uint32_t enc[2][256], tab[2][256];
-    __shared__ uint32_t part[kSplitWaves][2][64];
+    __shared__ uint32_t part[W][2][64];
     const WorkItem it = work[blockIdx.x];
     const TensorDev *dp = descs + it.tensor;
     const uint32_t lane = threadIdx.x & 63, wave = uni32(threadIdx.x >> 6);
@@ -274,11 +278,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_sizes_split(const TensorDe
     uint32_t bits[2] = {0, 0};
     if (walk) {
         constexpr uint32_t kDepth = 4;
-        for (uint32_t r0 = wave; r0 < C.rows; r0 += kSplitWaves * kDepth) {
+        for (uint32_t r0 = wave; r0 < C.rows; r0 += W * kDepth) {
             u32x4 v[kDepth];
 #pragma unroll
             for (uint32_t i = 0; i < kDepth; i++) {
-                const uint32_t run = (r0 + i * kSplitWaves) * 64 + lane;
+                const uint32_t run = (r0 + i * W) * 64 + lane;
                 v[i] = u32x4{0, 0, 0, 0};
                 if (run + 64 < C.runs) {
                     v[i] = *reinterpret_cast<const u32x4 *>(C.src + (uint64_t)run * 16);
@@ -287,7 +291,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_sizes_split(const TensorDe
             }
 #pragma unroll
             for (uint32_t i = 0; i < kDepth; i++) {
-                const uint32_t run = (r0 + i * kSplitWaves) * 64 + lane;
+                const uint32_t run = (r0 + i * W) * 64 + lane;
                 if (run + 64 >= C.runs) continue;
                 uint32_t w[2][4], last;
                 split_words<FMT>(v[i], w);
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_sizes_split(const TensorDe
             if (fkind == 1) before = (steps - 1) * R * F_::SB;
             else {
 #pragma unroll
-                for (uint32_t wv = 0; wv < kSplitWaves; wv++) before += part[wv][f][lane];
+                for (uint32_t wv = 0; wv < W; wv++) before += part[wv][f][lane];
                 uint32_t w[2][4], x[4];
                 split_words<FMT>(C.run_of(row, lane), w);
 #pragma unroll
@@ -339,17 +343,17 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_sizes_split(const TensorDe
 // FP8 chunks where one wavefront each takes 157 us, 54 us for BF16 deltas (both fields table coded), and 36 us for a set's
 // short last chunks instead of 435 - 500 us in the generic encoder.  Its size pass: 11 - 17 us (15 - 52 us before it asked for
 // four rows at a time).
-template <int FMT>
-__global__ __launch_bounds__(64 * kSplitWaves) void k_encode_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables)
+template <int FMT, uint32_t W>
+__global__ __launch_bounds__(64 * W) void k_encode_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables)
 {
     using F_ = Fmt<FMT>;
     constexpr int SB = F_::SB, G = F_::G, WPR = G * SB / 32;     // WPR: words of a plainly stored field per run
     static_assert(F_::NF == 2 && (SB == 4 || SB == 8) && (WPR == 2 || WPR == 4), "two fields of 4- or 8-bit symbols, at most two 64-bit words per run");
     __shared__ uint32_t enc[2][256], tab[2][256];
-    __shared__ uint32_t seg_bits[kSplitWaves][2][64], seg_last[kSplitWaves][2][64];     // a segment's bits and those of its last period
-    __shared__ uint32_t seam[2][kSplitWaves][2][64];             // see SplitStream
-    __shared__ uint32_t end_lo[2][kSplitWaves][64], end_p0[2][kSplitWaves][64], end_p1[2][kSplitWaves][64];
-    __shared__ uint8_t n_seam[2][kSplitWaves][64], end_owed[2][64];
+    __shared__ uint32_t seg_bits[W][2][64], seg_last[W][2][64];     // a segment's bits and those of its last period
+    __shared__ uint32_t seam[2][W][2][64];             // see SplitStream
+    __shared__ uint32_t end_lo[2][W][64], end_p0[2][W][64], end_p1[2][W][64];
+    __shared__ uint8_t n_seam[2][W][64], end_owed[2][64];
     __shared__ uint32_t end_words[2];
     const WorkItem it = work[blockIdx.x];
     const TensorDev *dp = descs + it.tensor;
@@ -375,7 +379,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_encode_split(const TensorD
     const bool flat[2] = {mode[0] == ZC_MODE_HUFF && !table[0], mode[1] == ZC_MODE_HUFF && !table[1]};
     const char *lut[2] = {reinterpret_cast<const char *>(tab[0]), reinterpret_cast<const char *>(tab[1])};
 
-    const uint32_t per_wave = (C.rows + kSplitWaves - 1) / kSplitWaves, segments = (C.rows + per_wave - 1) / per_wave;
+    const uint32_t per_wave = (C.rows + W - 1) / W, segments = (C.rows + per_wave - 1) / per_wave;
     const uint32_t row_begin = wave * per_wave < C.rows ? wave * per_wave : C.rows;
     const uint32_t row_end = row_begin + per_wave < C.rows ? row_begin + per_wave : C.rows;
     // ---- bits of every segment but the last (whose rows may be incomplete, and whose bits nobody asks for)
@@ -508,12 +512,19 @@ int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d
 {
     if (n_work == 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid(n_work), block(64 * kSplitWaves);
+    const uint32_t waves = split_waves(fmt, n_work);
+    const dim3 grid(n_work), block(64 * waves);
     switch (fmt) {
-    case ZC_FMT_BF16: hipLaunchKernelGGL(k_sizes_split<ZC_FMT_BF16>, grid, block, 0, st, d_descs, d_work, d_enc, d_units); break;
-    case ZC_FMT_FP8_E4M3: hipLaunchKernelGGL(k_sizes_split<ZC_FMT_FP8_E4M3>, grid, block, 0, st, d_descs, d_work, d_enc, d_units); break;
-    case ZC_FMT_FP8_E4M3_BYTES: hipLaunchKernelGGL(k_sizes_split<ZC_FMT_FP8_E4M3_BYTES>, grid, block, 0, st, d_descs, d_work, d_enc, d_units); break;
-    case ZC_FMT_FP8_E5M2: hipLaunchKernelGGL(k_sizes_split<ZC_FMT_FP8_E5M2>, grid, block, 0, st, d_descs, d_work, d_enc, d_units); break;
+    case ZC_FMT_BF16:
+        if (waves == 8) hipLaunchKernelGGL((k_sizes_split<ZC_FMT_BF16, 8>), grid, block, 0, st, d_descs, d_work, d_enc, d_units);
+        else hipLaunchKernelGGL((k_sizes_split<ZC_FMT_BF16, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units);
+        break;
+    case ZC_FMT_FP8_E4M3:
+        if (waves == 8) hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3, 8>), grid, block, 0, st, d_descs, d_work, d_enc, d_units);
+        else hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units);
+        break;
+    case ZC_FMT_FP8_E4M3_BYTES: hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3_BYTES, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units); break;
+    case ZC_FMT_FP8_E5M2: hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E5M2, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units); break;
     default: return 1;
     }
     return (int)hipGetLastError();
@@ -523,12 +534,19 @@ int launch_encode_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *
 {
     if (n_work == 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid(n_work), block(64 * kSplitWaves);
+    const uint32_t waves = split_waves(fmt, n_work);
+    const dim3 grid(n_work), block(64 * waves);
     switch (fmt) {
-    case ZC_FMT_BF16: hipLaunchKernelGGL(k_encode_split<ZC_FMT_BF16>, grid, block, 0, st, d_descs, d_work, d_enc); break;
-    case ZC_FMT_FP8_E4M3: hipLaunchKernelGGL(k_encode_split<ZC_FMT_FP8_E4M3>, grid, block, 0, st, d_descs, d_work, d_enc); break;
-    case ZC_FMT_FP8_E4M3_BYTES: hipLaunchKernelGGL(k_encode_split<ZC_FMT_FP8_E4M3_BYTES>, grid, block, 0, st, d_descs, d_work, d_enc); break;
-    case ZC_FMT_FP8_E5M2: hipLaunchKernelGGL(k_encode_split<ZC_FMT_FP8_E5M2>, grid, block, 0, st, d_descs, d_work, d_enc); break;
+    case ZC_FMT_BF16:
+        if (waves == 8) hipLaunchKernelGGL((k_encode_split<ZC_FMT_BF16, 8>), grid, block, 0, st, d_descs, d_work, d_enc);
+        else hipLaunchKernelGGL((k_encode_split<ZC_FMT_BF16, 16>), grid, block, 0, st, d_descs, d_work, d_enc);
+        break;
+    case ZC_FMT_FP8_E4M3:
+        if (waves == 8) hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3, 8>), grid, block, 0, st, d_descs, d_work, d_enc);
+        else hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3, 16>), grid, block, 0, st, d_descs, d_work, d_enc);
+        break;
+    case ZC_FMT_FP8_E4M3_BYTES: hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3_BYTES, 16>), grid, block, 0, st, d_descs, d_work, d_enc); break;
+    case ZC_FMT_FP8_E5M2: hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E5M2, 16>), grid, block, 0, st, d_descs, d_work, d_enc); break;
     default: return 1;
     }
     return (int)hipGetLastError();
