@@ -130,8 +130,9 @@ int launch_codes(TensorDev *d_descs, uint32_t n_tensors, const uint64_t *d_hist,
 int launch_hist(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                 int scales_view, uint64_t *d_hist, void *stream);
 int launch_zero(uint64_t *d_words, uint64_t n_words, void *stream);
-// between a page-locked host buffer and device memory, either way (both aligned to 16 bytes); clears n_zero words at d_zero too
-int launch_hand_over(const void *src, void *dst, uint64_t bytes, uint64_t *d_zero, uint64_t n_zero, void *stream);
+// between a page-locked host buffer and device memory, either way (both aligned to 16 bytes; to_host: the host waits for what is
+// written); clears n_zero words at d_zero too
+int launch_hand_over(const void *src, void *dst, uint64_t bytes, bool to_host, uint64_t *d_zero, uint64_t n_zero, void *stream);
 int launch_copy(const void *d_src, void *d_dst, uint64_t bytes, void *stream);
 int launch_copy_chunked(const void *d_src, void *d_dst, uint64_t bytes, uint32_t chunk_bytes, void *stream);
 // skip_routes: bit r set = leave tensors of route r to the specialised kernel that takes their whole chunks

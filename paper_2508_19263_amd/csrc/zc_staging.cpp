@@ -1,7 +1,7 @@
 // Page-locked host memory of the library: what the host sends to a workspace (descriptors, work lists, tables)
 // and what it reads back between kernels (histograms, stream sizes, headers).  A copy to or from pageable
 // memory is staged by the runtime in pieces and makes the caller wait; from page-locked memory it is one
-// asynchronous transfer.  The buffers are allocated on first use and kept until zc_release_host_buffers() or
+// asynchronous transfer, or for small ones a kernel that reads or writes the buffer.  The buffers are allocated on first use and kept until zc_release_host_buffers() or
 // the end of the process.
 #include <hip/hip_runtime.h>
 
@@ -16,14 +16,15 @@ namespace zc {
 namespace {
 
 // Bytes up to which the GPU fetches and delivers by itself (k_hand_over); a larger transfer is worth the runtime's copy, whose launch it
-// hides.
+// hides.  (Decode plans, that kernel | the runtime's copy, us: 1 FP8 tensor of 16 KiB 21.2 | 21.3, 64 of them 23.4 | 23.1, from 100 on, more than 16
+// KiB to send, 23.4 | 39.0.)
 constexpr uint64_t kHandOver = 256 * 1024;
 
 // ---- uploads -----------------------------------------------------------------------------------
 // A few buffers used in turn: the pieces of an upload are packed into one at their workspace offsets and leave in
-// a single asynchronous copy.  A buffer's next user waits for the event of the copy that last left it, so calls
-// queued back to back block only when more than kSlots uploads are still ahead of the device.  Every buffer has a
-// lock of its own, held while its user waits for that event, fills the buffer and queues the copy: callers on
+// a single asynchronous transfer (k_hand_over, or above kHandOver a copy).  A buffer's next user waits for the event behind
+// the transfer that last left it, so calls queued back to back block only when more than kSlots uploads are still ahead of the device.  Every
+// buffer has a lock of its own, held while its user waits for that event, fills the buffer and queues the transfer: callers on
 // other threads wait for each other only when they are dealt the same buffer.
 class HostStage {
 public:
@@ -51,7 +52,7 @@ public:
         if (!k.ev && hipEventCreateWithFlags(&k.ev, hipEventDisableTiming) != hipSuccess) return ZC_ERR_DEVICE;
         for (int i = 0; i < n; i++)
             if (pieces[i].bytes) std::memcpy(k.buf + (pieces[i].off - lo), pieces[i].src, pieces[i].bytes);
-        if (need <= kHandOver && (uintptr_t)(d_ws + lo) % 16 == 0) LAUNCH_TRY(launch_hand_over(k.buf, d_ws + lo, need, d_zero, n_zero, hs));
+        if (need <= kHandOver && (uintptr_t)(d_ws + lo) % 16 == 0) LAUNCH_TRY(launch_hand_over(k.buf, d_ws + lo, need, false, d_zero, n_zero, hs));
         else {
             HIP_TRY(hipMemcpyAsync(d_ws + lo, k.buf, need, hipMemcpyHostToDevice, hs));
             LAUNCH_TRY(launch_zero(d_zero, n_zero, hs));
@@ -60,7 +61,7 @@ public:
         k.pending = true;
         return ZC_OK;
     }
-    // waits for the copies still in flight, then frees every buffer
+    // waits for the transfers still in flight, then frees every buffer
     zc_status release()
     {
         zc_status st = ZC_OK;
@@ -136,7 +137,7 @@ zc_status stage_upload(uint8_t *d_ws, uint64_t lo, uint64_t hi, const Piece *pie
 zc_status read_back(uint8_t *landing, const uint8_t *d_src, uint64_t bytes, void *stream)
 {
     if (bytes && bytes <= kHandOver && (uintptr_t)landing % 16 == 0 && (uintptr_t)d_src % 16 == 0) {
-        LAUNCH_TRY(launch_hand_over(d_src, landing, bytes, nullptr, 0, stream));
+        LAUNCH_TRY(launch_hand_over(d_src, landing, bytes, true, nullptr, 0, stream));
         return ZC_OK;
     }
     HIP_TRY(hipMemcpyAsync(landing, d_src, bytes, hipMemcpyDeviceToHost, (hipStream_t)stream));

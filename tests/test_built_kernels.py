@@ -1,7 +1,9 @@
 """The instructions of the built library's kernels.  A buffer store of more than 8 bytes per lane whose offset is partly in a scalar
 register, followed at once by an instruction that overwrites its data registers, has stored the new values on gfx950, and the
 compiler inserts no wait there: no kernel may have such a store.  (Whether a wait is there depends on what follows the store, and
-that changes with any edit; with the whole offset in a vector register the compiler waits where it has to.)"""
+that changes with any edit; with the whole offset in a vector register the compiler waits where it has to.)
+
+And what else is to be seen there: a kernel that writes device memory only does not write its caches back to the system."""
 import os
 import re
 import shutil
@@ -48,3 +50,25 @@ def test_no_wide_store_with_a_scalar_offset(tmp_path):
         stores += sum(1 for line in listing if STORE.match(line))
         hits += wide_scalar_offset_stores(listing)
     assert stores > 100 and not hits, (stores, len(hits), hits[:5])
+
+
+def listing_of(tmp_path, symbol):
+    """The instructions of the kernel whose symbol starts like that (of all files of the library's: the one that has it)."""
+    shutil.copy(os.path.join(os.path.dirname(zc.__file__), "libzc.so"), str(tmp_path))
+    subprocess.run([LLVM + "/llvm-objdump", "--offloading", "libzc.so"], cwd=str(tmp_path), check=True, capture_output=True)
+    for f in sorted(f for f in os.listdir(str(tmp_path)) if f.endswith("gfx950")):
+        names = subprocess.run([LLVM + "/llvm-readelf", "-s", "--wide", f], cwd=str(tmp_path), check=True, capture_output=True, text=True).stdout.split()
+        found = [n for n in names if n.startswith(symbol) and "." not in n]
+        if found:
+            return subprocess.run([LLVM + "/llvm-objdump", "-d", "--no-show-raw-insn", "--disassemble-symbols=" + found[0], f], cwd=str(tmp_path), check=True,
+                                  capture_output=True, text=True).stdout
+    return ""
+
+
+@pytest.mark.parametrize("to_host", [False, True])
+def test_only_what_the_host_reads_is_written_back_to_the_system(tmp_path, to_host):
+    if not os.path.exists(LLVM + "/llvm-objdump"):
+        pytest.skip("llvm-objdump not found")
+    zc.lib()
+    listing = listing_of(tmp_path, "_ZN2zc11k_hand_overILb%d" % to_host)
+    assert "global_store" in listing and ("buffer_wbl2" in listing) == to_host
