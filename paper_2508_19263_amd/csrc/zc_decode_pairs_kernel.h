@@ -524,9 +524,10 @@ template <int FMT, int F, uint32_t RW> constexpr bool kSure = Entries<FMT, F, RW
 template <int FMT, int F, uint32_t RW>
 __device__ __forceinline__ bool unresolved(uint32_t e) { return !kSure<FMT, F, RW> && (Entries<FMT, F, RW>::kPair ? (int)e < 0 : e == 0); }
 
-// The same where an entry does not resolve in some lane; a0: the first entry, as look_up found it (in every lane the right one)
-template <int FMT, int F, int N, uint32_t RW>
-__device__ __forceinline__ uint32_t look_up_slowly(const PairStream &S, const PairCanon &C, uint32_t c, uint32_t x, uint32_t a0, uint32_t e[N])
+// The same where an entry does not resolve in some lane; e[0]: as look_up found it (in every lane the right one); FOUND: and the others,
+// which are right in the lanes where those before them resolved (looked up again: byte symbols, 1,500 chunks of 256 KiB 287 | 276 us)
+template <int FMT, int F, int N, uint32_t RW, bool FOUND>
+__device__ __forceinline__ uint32_t look_up_slowly(const PairStream &S, const PairCanon &C, uint32_t c, uint32_t x, uint32_t e[N])
 {
     typedef Entries<FMT, F, RW> P;
     constexpr uint32_t K = P::kBits;
@@ -534,8 +535,9 @@ __device__ __forceinline__ uint32_t look_up_slowly(const PairStream &S, const Pa
     else {
 #pragma unroll
     for (int i = 0; i < N; i++) {
-        uint32_t a = i == 0 ? a0 : entry_at<FMT, F, 0, RW>(x), len;
+        uint32_t a = e[i], len;
         if (P::kPair) {
+            if (i > 0) a = entry_at<FMT, F, 0, RW>(x);
             // both symbols one after the other in every lane
             uint32_t l1 = first_len(a, P::kLen1), s1 = a & P::kFirst;
             uint32_t b = entry_at<FMT, F, 0, RW>(x >> l1);
@@ -551,9 +553,13 @@ __device__ __forceinline__ uint32_t look_up_slowly(const PairStream &S, const Pa
             a = s1 | (s2 << P::kSecond);
             len = l1 + l2;
         } else {
+            if (i > 0 && !FOUND) a = entry_at<FMT, F, 0, RW>(x);
             len = first_len(a, P::kLen);
             a &= P::kFirst;
-            if (__ballot(len == 0) != 0) { if (len == 0) a = P::put(long_symbol<K>(S, C, x, len)) & P::kFirst; }
+            if (len == 0) {
+                a = P::put(long_symbol<K>(S, C, x, len)) & P::kFirst;
+                if (FOUND && i + 1 < N) e[i + 1] = entry_at<FMT, F, 0, RW>(x >> len);
+            }
         }
         e[i] = a;
         c += len;
@@ -611,11 +617,11 @@ __device__ __forceinline__ void pair_run(PairStream &A, PairStream &B, const Pai
         Refill ra = ask<RW, CAREFUL, Entries<FMT, 0, RW>::kNoise>(A, ta, owner), rb;
         if (TWO) rb = ask<RW, CAREFUL, Entries<FMT, 1, RW>::kNoise>(B, tb, owner);
         if (__builtin_expect(__any(unresolved<FMT, 0, RW>(a[NA - 1])), 0)) {
-            ta = look_up_slowly<FMT, 0, NA, RW>(A, C[0], A.c, xa, a[0], a);
+            ta = look_up_slowly<FMT, 0, NA, RW, true>(A, C[0], A.c, xa, a);
             ra = ask<RW, CAREFUL, Entries<FMT, 0, RW>::kNoise>(A, ta, owner);
         }
         if (TWO && __builtin_expect(__any(unresolved<FMT, 1, RW>(b[NB - 1])), 0)) {
-            tb = look_up_slowly<FMT, 1, NB, RW>(B, C[1], B.c, xb, b[0], b);
+            tb = look_up_slowly<FMT, 1, NB, RW, true>(B, C[1], B.c, xb, b);
             rb = ask<RW, CAREFUL, Entries<FMT, 1, RW>::kNoise>(B, tb, owner);
         }
         take<CAREFUL>(A, ra);
@@ -758,7 +764,8 @@ __device__ __forceinline__ void late_again(Late &next, const Late &L, const Pair
     }
     late_settle<TWICE>(next);
     const uint32_t x = __builtin_amdgcn_alignbit(next.hi, next.lo, next.c);
-    next.c = look_up_slowly<FMT, F, N, RW>(S, C, next.c, x, entry_at<FMT, F, 0, RW>(x), e) & 63u;
+    e[0] = entry_at<FMT, F, 0, RW>(x);
+    next.c = look_up_slowly<FMT, F, N, RW, false>(S, C, next.c, x, e) & 63u;
     if (TWICE) {
         // (nothing is owed after it: its codes may be longer than the index)
         late_ask<RW>(next, S.ring);
