@@ -53,7 +53,8 @@ template <int B> __device__ __forceinline__ uint32_t shr_byte(uint32_t v, uint32
 // KiB), short with eight wavefronts per workgroup and several workgroups per compute unit
 constexpr uint32_t kLongRing = 1024, kLongRingTwo = 512 + 0x8000, kLongRingSingles = kLongRing + 0x10000, kLongRingWeights = 2048, kShortRing = 512, kShortRingLate = kShortRing + 0x10000;
 // (kLongRingTwo: long rings where two streams of a chunk share one; kLongRingSingles, kLongRingWeights: other tables for the same launches;
-// kShortRingLate: see pair_rows)
+// kShortRingLate: see pair_rows; a kernel of its own, which takes 20 registers more: in one with short rings' others, 600 tensors of a
+// delta, four chunks of 16 KiB each, 49 | 42 us)
 template <uint32_t RW> constexpr uint32_t kRing = RW & 0x7FFFu;
 template <uint32_t RW> constexpr bool kInFours = kRing<RW> == 1024;
 
@@ -1042,7 +1043,10 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
 
 }  // namespace
 
-struct PairShared { TensorDev d; PairCanon canon[2]; uint32_t wave_count[4][17], flat3; LongCodes longs; };
+// (longs: only where there are whole tables)
+struct PairShared { TensorDev d; PairCanon canon[2]; uint32_t wave_count[4][17], flat3; };
+struct FewShared : PairShared { LongCodes longs; };
+template <uint32_t RW> constexpr uint32_t kSharedBytes = RW == kShortRing || RW == kShortRingLate ? sizeof(PairShared) : sizeof(FewShared);
 
 // One wavefront per chunk, `chunks` of them per workgroup (whose wavefronts build the tables together) around one copy of the tables;
 // RW: which tables and rings.
@@ -1059,7 +1063,7 @@ __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, c
     // all LDS in one piece, sized by the host, with field 0's table at its start (so that its entries need no base address);
     // then field 1's table where it has one, the rings, and what the workgroup shares besides
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    PairShared &sh = *reinterpret_cast<PairShared *>(lds + lds_tables_and_rings);
+    FewShared &sh = *reinterpret_cast<FewShared *>(lds + lds_tables_and_rings);              // (short rings: a PairShared)
     PairCanon *const canon = sh.canon;
     uint32_t(*const wave_count)[17] = sh.wave_count;
     WorkItem it;
@@ -1082,10 +1086,9 @@ __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, c
     if (FMT == ZC_FMT_FP8_E4M3 && ((kind1 != KIND_FLAT && kind1 != KIND_RAW) || p0 == 8)) return;
     build_canon(canon[0], wave_count, d.comp + d.table_off[0], kAlphabet);
     if (two) build_canon(canon[1], wave_count, d.comp + d.table_off[1], kAlphabet);
-    // other tables: FP8 exponent codes of more than eight bits; two fields, sign+mantissa codes of at most 12 (short rings: a workgroup per
-    // compute unit)
-    const bool other = FMT == ZC_FMT_FP8_E4M3 ? p0 == 2 : FMT == ZC_FMT_BF16 && two && (RW == kLongRingTwo ? uniform32(canon[1].limit[12]) >= 65536u : RW == kShortRing && gridDim.x <= 256);
-    constexpr uint32_t OW = FMT == ZC_FMT_FP8_E4M3 ? kLongRingSingles : FMT == ZC_FMT_BF16 && RW == kLongRingTwo ? kLongRingWeights : FMT == ZC_FMT_BF16 && RW == kShortRing ? kShortRingLate : RW;
+    // other tables: FP8 exponent codes of more than eight bits; two fields, sign+mantissa codes of at most 12
+    const bool other = FMT == ZC_FMT_FP8_E4M3 ? p0 == 2 : FMT == ZC_FMT_BF16 && two && RW == kLongRingTwo && uniform32(canon[1].limit[12]) >= 65536u;
+    constexpr uint32_t OW = FMT == ZC_FMT_FP8_E4M3 ? kLongRingSingles : FMT == ZC_FMT_BF16 && RW == kLongRingTwo ? kLongRingWeights : RW;
     if (OW != RW && other) {
         build_entries<FMT, 0, OW>(lds, canon[0], sh.longs);
         if (two) build_entries<FMT, 1, OW>(lds + kTableBytes<FMT, 0, OW>, canon[1], sh.longs);
@@ -1174,11 +1177,11 @@ template <int FMT, uint32_t RW>
 static int launch_pairs_x(bool two, bool xor_delta, uint32_t chunks, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev &s, int use_single,
                           uint32_t first_slot, hipStream_t st)
 {
-    const uint32_t lds = rings_at<FMT, RW>(two) + chunks * (two ? 2u : 1u) * kRing<RW> * 4, all = lds + (uint32_t)sizeof(PairShared);
+    const uint32_t lds = rings_at<FMT, RW>(two) + chunks * (two ? 2u : 1u) * kRing<RW> * 4, all = lds + kSharedBytes<RW>;
     static_assert(RW != kLongRingTwo || rings_at<ZC_FMT_BF16, kLongRingWeights>(true) + 8 * kRing<kLongRingWeights> * 4 <= rings_at<ZC_FMT_BF16, RW>(true), "the other tables and their rings fit");
     // (with short rings eight wavefronts build the tables, four where a call has more workgroups than the compute units hold of eight:
     // 1,500 BF16 tensors of one chunk of 100,000 bytes: 255 | 213 us)
-    const dim3 grid(n_work), block(RW != kShortRing ? 1024 : chunks > 4 || n_work <= 4 * 256 ? 512 : 256);
+    const dim3 grid(n_work), block(RW != kShortRing && RW != kShortRingLate ? 1024 : chunks > 4 || n_work <= 4 * 256 ? 512 : 256);
     if (xor_delta) hipLaunchKernelGGL((k_decode_pairs<FMT, true, RW>), grid, block, all, st, d_descs, d_work, s, use_single, first_slot, chunks, lds);
     else hipLaunchKernelGGL((k_decode_pairs<FMT, false, RW>), grid, block, all, st, d_descs, d_work, s, use_single, first_slot, chunks, lds);
     return (int)hipGetLastError();

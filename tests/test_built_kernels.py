@@ -72,3 +72,18 @@ def test_only_what_the_host_reads_is_written_back_to_the_system(tmp_path, to_hos
     zc.lib()
     listing = listing_of(tmp_path, "_ZN2zc11k_hand_overILb%d" % to_host)
     assert "global_store" in listing and ("buffer_wbl2" in listing) == to_host
+
+
+def test_registers_of_the_decoder_whose_workgroups_share_a_compute_unit(tmp_path):
+    """BF16 deltas with short rings: seven wavefronts per SIMD (85 registers and five of them made sets of small deltas 5 - 15 % slower)."""
+    if not os.path.exists(LLVM + "/llvm-objdump"):
+        pytest.skip("llvm-objdump not found")
+    zc.lib()
+    listing_of(tmp_path, "_ZN2zc14k_decode_pairsILi1ELb1E")    # (leaves the files' code objects there)
+    counts = []
+    for f in sorted(f for f in os.listdir(str(tmp_path)) if f.endswith("gfx950")):
+        notes = subprocess.run([LLVM + "/llvm-readelf", "--notes", f], cwd=str(tmp_path), check=True, capture_output=True, text=True).stdout
+        for kernel in notes.split("- .agpr_count")[1:]:
+            if re.search(r"\.name: +_ZN2zc14k_decode_pairsILi1ELb1ELj512E", kernel):
+                counts.append(int(re.search(r"\.vgpr_count: +(\d+)", kernel).group(1)))
+    assert counts and max(counts) <= 72, counts
