@@ -51,11 +51,12 @@ template <int B> __device__ __forceinline__ uint32_t shr_byte(uint32_t v, uint32
 
 // Words of a stream's ring: long where a workgroup has a compute unit to itself (calls of one round: the table takes 128 of its 160
 // KiB), short with eight wavefronts per workgroup and several workgroups per compute unit
-constexpr uint32_t kLongRing = 1024, kLongRingTwo = 512 + 0x8000, kLongRingSingles = kLongRing + 0x10000, kLongRingWeights = 2048, kShortRing = 512, kShortRingLate = kShortRing + 0x10000;
+constexpr uint32_t kLongRing = 1024, kLongRingTwo = 512 + 0x8000, kLongRingSingles = kLongRing + 0x10000, kLongRingWeights = 2048, kShortRing = 512, kShortRingLate = kShortRing + 0x10000, kLongRingSmall = 2048 + 0x8000;
 // (kLongRingTwo: long rings where two streams of a chunk share one; kLongRingSingles, kLongRingWeights: other tables for the same launches;
 // kShortRingLate: see pair_rows; a kernel of its own, which takes 20 registers more: in one with short rings' others, 600 tensors of a
 // delta, four chunks of 16 KiB each, 49 | 42 us)
 template <uint32_t RW> constexpr uint32_t kRing = RW & 0x7FFFu;
+// (kLongRingSmall: byte symbols with small tables, four chunks to a workgroup, of which several fit a compute unit)
 template <uint32_t RW> constexpr bool kInFours = kRing<RW> == 1024;
 
 // How the table entries of field F of format FMT are laid out.  kBits: stream bits a lookup goes by; kBytes: of an entry.  put: a
@@ -878,7 +879,7 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
     constexpr bool TWO = SM == kSmTable;
     // (With several wavefronts per SIMD it is the number of instructions alone: 2,048 BF16 chunks 200 | 257 us.  Two fields and two
     // wavefronts: 1,526 chunks of a delta 314 | 303, but 3,052, three of them, 436 | 454.)
-    constexpr bool kLate = RW != kShortRing;
+    constexpr bool kLate = RW != kShortRing && RW != kLongRingSmall;
     constexpr int NA = kLookups<FMT, 0, R, RW>, NB = kLookups<FMT, 1, R, RW>;
     constexpr uint32_t EX = kExponentBits<FMT>;
     const uint32_t rows = o.whole_rows;
@@ -1181,7 +1182,7 @@ static int launch_pairs_x(bool two, bool xor_delta, uint32_t chunks, const Tenso
     static_assert(RW != kLongRingTwo || rings_at<ZC_FMT_BF16, kLongRingWeights>(true) + 8 * kRing<kLongRingWeights> * 4 <= rings_at<ZC_FMT_BF16, RW>(true), "the other tables and their rings fit");
     // (with short rings eight wavefronts build the tables, four where a call has more workgroups than the compute units hold of eight:
     // 1,500 BF16 tensors of one chunk of 100,000 bytes: 255 | 213 us)
-    const dim3 grid(n_work), block(RW != kShortRing && RW != kShortRingLate ? 1024 : chunks > 4 || n_work <= 4 * 256 ? 512 : 256);
+    const dim3 grid(n_work), block(RW == kLongRingSmall ? 256 : RW != kShortRing && RW != kShortRingLate ? 1024 : chunks > 4 || n_work <= 4 * 256 ? 512 : 256);
     if (xor_delta) hipLaunchKernelGGL((k_decode_pairs<FMT, true, RW>), grid, block, all, st, d_descs, d_work, s, use_single, first_slot, chunks, lds);
     else hipLaunchKernelGGL((k_decode_pairs<FMT, false, RW>), grid, block, all, st, d_descs, d_work, s, use_single, first_slot, chunks, lds);
     return (int)hipGetLastError();

@@ -131,8 +131,9 @@ constexpr uint64_t kPairsTailBytes = 16 * 1024;
 // How those kernels take a call: chunks per workgroup, and whether with the long rings (four chunks then); chunks 0: another kernel is
 // faster.  Measured on MI355X, these kernels | the others, in us.
 //  - Long rings leave a compute unit one workgroup, so they are for calls of one round of workgroups.  300 BF16 tensors of 100,000 bytes,
-//    a workgroup each: 184 with long rings, 110 with short.  (Byte symbols with one table-decoded field, whose table is small: two
-//    workgroups, but from 1,025 chunks on only the largest gain: 1,500 chunks of 16 KiB 29 | 27, 64 KiB 72 | 70, 256 KiB 255 | 278.)
+//    a workgroup each: 184 with long rings, 110 with short.  (Byte symbols with one table-decoded field: up to 512 workgroups, which have small
+//    tables from 257 on, so that two fit a compute unit: 300 tensors of 4 KiB 19 with whole ones, 11 with small, of 256 KiB 243 | 230; but from
+//    1,025 chunks on only the largest gain, short rings | these: 1,500 chunks of 16 KiB 29 | 27, 64 KiB 72 | 70, 256 KiB 255 | 278.)
 //  - FP8 E4M3 has a table of 128 KiB and comes here with long rings only; beyond a round, k_decode_fp8, bound by its traffic, is ahead.
 //    The line at 96 KiB is where a table of 64 KiB with checked lookups paid (16 of 64 KiB: 70 | 70; 96 KiB: 94 | 98), and sooner where it
 //    saves the second launch that a short last chunk needs beside k_decode_fp8 (64 chunks of 32 KiB and one of 64 bytes: 41 | 50, of 16
