@@ -22,10 +22,10 @@ int launch_decode_pairs(uint32_t fmt, bool two, bool xor_delta, uint32_t chunks,
     switch (fmt) {
     case ZC_FMT_BF16: return launch_pairs_bf16(two, xor_delta, chunks, long_rings, d_descs, d_work, n_work, s, use_single, first_slot, st);
     case ZC_FMT_FP8_E4M3_BYTES: return launch_pairs_bytes(two, xor_delta, chunks, long_rings, d_descs, d_work, n_work, s, use_single, first_slot, st);
-    case ZC_FMT_FP8_E4M3: return long_rings ? launch_pairs_x<ZC_FMT_FP8_E4M3, kLongRing>(two, xor_delta, chunks, d_descs, d_work, n_work, s, use_single, first_slot, st) : 1;       // (only calls of few chunks come here)
+    case ZC_FMT_FP8_E4M3: return long_rings ? launch_pairs_x<ZC_FMT_FP8_E4M3, kFew>(two, xor_delta, chunks, d_descs, d_work, n_work, s, use_single, first_slot, st) : 1;       // (only calls of few chunks come here)
     case ZC_FMT_FP8_E5M2:
-        if (!long_rings) return launch_pairs_x<ZC_FMT_FP8_E5M2, kShortRing>(two, xor_delta, chunks, d_descs, d_work, n_work, s, use_single, first_slot, st);
-        return launch_pairs_x<ZC_FMT_FP8_E5M2, kLongRing>(two, xor_delta, chunks, d_descs, d_work, n_work, s, use_single, first_slot, st);
+        if (!long_rings) return launch_pairs_x<ZC_FMT_FP8_E5M2, kMany>(two, xor_delta, chunks, d_descs, d_work, n_work, s, use_single, first_slot, st);
+        return launch_pairs_x<ZC_FMT_FP8_E5M2, kFew>(two, xor_delta, chunks, d_descs, d_work, n_work, s, use_single, first_slot, st);
     default: return 1;
     }
 }

@@ -26,6 +26,11 @@
 
 namespace zc {
 
+// What a launch is for: calls of one round of workgroups (kFew; kFewTwo: some tensor's sign+mantissa field is table decoded too), whose
+// workgroups have a compute unit to themselves, with tables of up to 136 KiB; all others; of those, two fields and up to 256 workgroups (a
+// kernel of its own: it takes 20 registers more).
+enum Launch { kFew, kFewTwo, kMany, kManyTwo };
+
 namespace {
 
 // canonical code of a field: limit[l] = left-aligned (16 bits) exclusive upper bound of the codes of length <= l, rebase[l] =
@@ -49,143 +54,129 @@ template <int B> __device__ __forceinline__ uint32_t shr_byte(uint32_t v, uint32
     return r;
 }
 
-// Words of a stream's ring: long where a workgroup has a compute unit to itself (calls of one round: the table takes 128 of its 160
-// KiB), short with eight wavefronts per workgroup and several workgroups per compute unit
-constexpr uint32_t kLongRing = 1024, kLongRingTwo = 512 + 0x8000, kLongRingSingles = kLongRing + 0x10000, kLongRingWeights = 2048, kShortRing = 512, kShortRingLate = kShortRing + 0x10000, kLongRingSmall = 2048 + 0x8000;
-// (kLongRingTwo: long rings where two streams of a chunk share one; kLongRingSingles, kLongRingWeights: other tables for the same launches;
-// kShortRingLate: see pair_rows; a kernel of its own, which takes 20 registers more: in one with short rings' others, 600 tensors of a
-// delta, four chunks of 16 KiB each, 49 | 42 us)
-template <uint32_t RW> constexpr uint32_t kRing = RW & 0x7FFFu;
-// (kLongRingSmall: byte symbols with small tables, four chunks to a workgroup, of which several fit a compute unit)
-template <uint32_t RW> constexpr bool kInFours = kRing<RW> == 1024;
+// A field's table, by the stream bits a lookup goes by: whole ones by 16, which every code (kWholePairs: every pair of codes of at most
+// eight bits) fits, so that nothing is ever unresolved; pairs by 11 - 13 bits; singles by 12.
+enum Table { kNone = 32, kPairs11 = 11, kPairs12 = 12, kPairs13 = 13, kSingles12 = 32 + 12, kWhole = 64 + 16, kWholePairs = 96 + 16 };
+constexpr bool in_pairs(Table t) { return t < 32 || t == kWholePairs; }
+constexpr bool is_whole(Table t) { return t == kWhole || t == kWholePairs; }
+constexpr uint32_t index_bits(Table t) { return t % 32; }
+constexpr uint32_t entry_bytes(Table t) { return t < 32 ? 4 : 2; }
 
-// How the table entries of field F of format FMT are laid out.  kBits: stream bits a lookup goes by; kBytes: of an entry.  put: a
-// symbol at its place in an output word (kFirst: the bits it can take).  The length (a pair's, or a single's) lies in bits the
-// output's two fields leave to each other; it is added by the byte it lies in where it has one: a symbol's bit above it leaves the
-// low 7 bits of a sum alone (kNoise).
-// kWhole: 16-bit entries by 16 bits, which every code (every pair of FP8 exponents, of at most 8 bits each) fits, with the length
-// less one (kLow: the length); nothing is ever unresolved.  Else an entry that does not resolve has length 0, so that the lookups after it in the
-// period do not resolve either and the last one tells:
-// kPair: 32-bit entries of two symbols, the second kSecond bits above the first; kUnresolved (the sign bit) where the pair does
+// When the words that a period's lanes ask for at its end come in: before the next one begins; or at
+// the next one's end (where a period is one lookup: another one later), while that goes well, then behind the first entry.  See late_run.
+enum Loop { kWait, kLate };
+
+// How a chunk is decoded: words of a stream's ring, tables of the two fields
+template <uint32_t RING, Loop LOOP, Table T0, Table T1 = kNone> struct Build {
+    static constexpr uint32_t kRing = RING;
+    static constexpr Loop kLoop = LOOP;
+    static constexpr bool kInFours = RING >= 1024 && LOOP != kWait;      // see fours_service
+    template <int F> static constexpr Table kTable = F == 0 ? T0 : T1;
+};
+
+// How the table entries of field F of format FMT are laid out.  put: a symbol at its place in an output word (kFirst: the bits it can
+// take).  The length (a pair's, or a single's) lies in bits the output's two fields leave to each other; it is added by the byte it
+// lies in where it has one: a symbol's bit above it leaves the low 7 bits of a sum alone (kNoise).
+// Whole tables: 16-bit entries with the length less one (kLow: the length, in the low bits).  Else an entry that does not resolve has
+// length 0, so that the lookups after it in the period do not resolve either and the last one tells:
+// kPairs*: 32-bit entries of two symbols, the second kSecond bits above the first; kUnresolved (the sign bit) where the pair does
 // not fit the index, which has the first symbol alone, its length at kLen1 (0 there: longer than the index).
-// Else 16-bit entries, 0 for a code longer than the index.
+// kSingles12: 16-bit entries, 0 for a code longer than the index.
 //
 // Chance that one of 64 lanes finds a pair unresolved, for weights of the kinds the codec is meant for: BF16 exponents 16 % by 12
 // bits, E5M2 (a wide spread of exponents) 22 % by 13; singles by 12 bits 19 % (deltas' sign+mantissa) to 42 % (byte symbols).  Each
 // costs its wavefront 600 cycles, three periods' worth; hence the whole tables where there is the LDS for them.
 constexpr uint32_t kUnresolved = 0x80000000u;
-template <int FMT, int F> struct ShortEntries;
-struct OfWholeTable {
-    static constexpr bool kPair = false, kWhole = true, kNoise = false, kLow = false;
-    static constexpr uint32_t kBits = 16, kBytes = 2;
-    static constexpr int kSecond = 16, kLen1 = 0;
-};
-template <> struct ShortEntries<ZC_FMT_BF16, 0> {
-    static constexpr bool kPair = true, kWhole = false, kNoise = true, kLow = false;
-    static constexpr uint32_t kFirst = 0x7F80u, kBits = 12, kBytes = 4;
+template <int FMT, int F, Table T> struct Layout;
+template <Table T> struct Layout<ZC_FMT_BF16, 0, T> {            // pairs
+    static constexpr bool kNoise = true, kLow = false;
+    static constexpr uint32_t kFirst = 0x7F80u;
     static constexpr int kSecond = 16, kLen = 0, kLen1 = 16;
     static __device__ __forceinline__ uint32_t put(uint32_t s) { return s << 7; }
     static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return add_byte<0>(c, e); }
     static __device__ __forceinline__ uint32_t shift(uint32_t x, uint32_t e) { return shr_byte<0>(x, e); }
 };
-template <> struct ShortEntries<ZC_FMT_BF16, 1> {
-    static constexpr bool kPair = false, kWhole = false, kNoise = true, kLow = false;
-    static constexpr uint32_t kFirst = 0x807Fu, kBits = 12, kBytes = 2;
+template <Table T> struct Layout<ZC_FMT_BF16, 1, T> {            // singles and whole
+    static constexpr bool kNoise = true, kLow = false;
+    static constexpr uint32_t kFirst = 0x807Fu;
     static constexpr int kSecond = 16, kLen = 8, kLen1 = 0;
     static __device__ __forceinline__ uint32_t put(uint32_t s) { return ((s & 0x80u) << 8) | (s & 0x7Fu); }
     static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return add_byte<1>(c, e); }
     static __device__ __forceinline__ uint32_t shift(uint32_t x, uint32_t e) { return shr_byte<1>(x, e); }
 };
 // one value per byte: the pair in bytes 0 and 1, its length in byte 2, the first symbol's in byte 3
-template <> struct ShortEntries<ZC_FMT_FP8_E5M2, 0> {
-    static constexpr bool kPair = true, kWhole = false, kNoise = false, kLow = false;
-    static constexpr uint32_t kFirst = 0xFFu, kBits = 13, kBytes = 4;
+template <Table T> struct Layout<ZC_FMT_FP8_E5M2, 0, T> {
+    static constexpr bool kNoise = false, kLow = false;
+    static constexpr uint32_t kFirst = 0xFFu;
     static constexpr int kSecond = 8, kLen = 16, kLen1 = 24;
     static __device__ __forceinline__ uint32_t put(uint32_t s) { return (s << 2) & 0x7Cu; }
     static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return add_byte<2>(c, e); }
     static __device__ __forceinline__ uint32_t shift(uint32_t x, uint32_t e) { return shr_byte<2>(x, e); }
 };
-template <> struct ShortEntries<ZC_FMT_FP8_E4M3, 0> : OfWholeTable {};                          // (never with short rings)
-template <> struct ShortEntries<ZC_FMT_FP8_E4M3, 1> : ShortEntries<ZC_FMT_BF16, 1> {};          // (never table decoded here)
-template <> struct ShortEntries<ZC_FMT_FP8_E5M2, 1> : ShortEntries<ZC_FMT_BF16, 1> {};
+template <Table T> struct Layout<ZC_FMT_FP8_E4M3, 1, T> : Layout<ZC_FMT_BF16, 1, T> {};      // (never table decoded here)
+template <Table T> struct Layout<ZC_FMT_FP8_E5M2, 1, T> : Layout<ZC_FMT_BF16, 1, T> {};
 // byte symbols: a symbol is two values, half an output word (exponent bits 0x78 of every byte, sign+mantissa bits 0x87)
-template <> struct ShortEntries<ZC_FMT_FP8_E4M3_BYTES, 0> {
-    static constexpr bool kPair = false, kWhole = false, kNoise = false, kLow = false;
-    static constexpr uint32_t kFirst = 0x7878u, kBits = 12, kBytes = 2;
+template <Table T> struct Layout<ZC_FMT_FP8_E4M3_BYTES, 0, T> {
+    static constexpr bool kNoise = false, kLow = false;
+    static constexpr uint32_t kFirst = 0x7878u;
     static constexpr int kSecond = 16, kLen = 7, kLen1 = 0;
     static __device__ __forceinline__ uint32_t put(uint32_t s) { return ((s & 15u) << 3) | ((s & 0xF0u) << 7); }
     static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return c + ((e >> 7) & 15u); }
     static __device__ __forceinline__ uint32_t shift(uint32_t x, uint32_t e) { return x >> ((e >> 7) & 15u); }
 };
-template <> struct ShortEntries<ZC_FMT_FP8_E4M3_BYTES, 1> {
-    static constexpr bool kPair = false, kWhole = false, kNoise = false, kLow = false;
-    static constexpr uint32_t kFirst = 0x8787u, kBits = 12, kBytes = 2;
+template <Table T> struct Layout<ZC_FMT_FP8_E4M3_BYTES, 1, T> {
+    static constexpr bool kNoise = false, kLow = false;
+    static constexpr uint32_t kFirst = 0x8787u;
     static constexpr int kSecond = 16, kLen = 3, kLen1 = 0;
     static __device__ __forceinline__ uint32_t put(uint32_t s) { return (s & 7u) | ((s & 8u) << 4) | ((s & 0x70u) << 4) | ((s & 0x80u) << 8); }
     static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return c + ((e >> 3) & 15u); }
     static __device__ __forceinline__ uint32_t shift(uint32_t x, uint32_t e) { return x >> ((e >> 3) & 15u); }
 };
-
-template <int FMT, int F, uint32_t RW> struct Entries : ShortEntries<FMT, F> {};
 // FP8 exponents in whole pairs, in bytes 0 and 1 of half an output word
-template <> struct Entries<ZC_FMT_FP8_E4M3, 0, kLongRing> : OfWholeTable {
-    static constexpr bool kPair = true;
+template <> struct Layout<ZC_FMT_FP8_E4M3, 0, kWholePairs> {
+    static constexpr bool kNoise = false, kLow = false;
     static constexpr uint32_t kFirst = 0x78u;
-    static constexpr int kSecond = 8, kLen = 7;
+    static constexpr int kSecond = 8, kLen = 7, kLen1 = 0;
     static __device__ __forceinline__ uint32_t put(uint32_t s) { return (s << 3) & 0x78u; }
     static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return c + ((e >> 7) & 15u); }
     static __device__ __forceinline__ uint32_t shift(uint32_t x, uint32_t e) { return x >> ((e >> 7) & 15u); }
 };
 // the length in the low bits, above which a symbol's in a sum of entries are left alone
-struct OfWholeTableLow : OfWholeTable {
+struct LengthLow {
     static constexpr bool kNoise = true, kLow = true;
-    static constexpr int kLen = 0;
+    static constexpr int kLen = 0, kLen1 = 0;
     static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return c + e; }
     static __device__ __forceinline__ uint64_t shift(uint64_t x, uint32_t e) { return x >> (e & 63u); }
 };
-template <int FMT> struct OneByte : OfWholeTableLow {             // a symbol in byte 1
+template <int FMT> struct OneByte : LengthLow {                  // a symbol in byte 1
     static constexpr uint32_t kFirst = 0xFF00u;
     static constexpr int kSecond = 8;
     static __device__ __forceinline__ uint32_t put(uint32_t s) { return (FMT == ZC_FMT_FP8_E4M3 ? (s << 3) & 0x78u : (s << 2) & 0x7Cu) << 8; }
 };
-template <> struct Entries<ZC_FMT_FP8_E4M3, 0, kLongRingSingles> : OneByte<ZC_FMT_FP8_E4M3> {};
-template <> struct Entries<ZC_FMT_FP8_E5M2, 0, kLongRing> : OneByte<ZC_FMT_FP8_E5M2> {};
-template <> struct Entries<ZC_FMT_BF16, 0, kLongRing> : OfWholeTableLow {
+template <> struct Layout<ZC_FMT_FP8_E4M3, 0, kWhole> : OneByte<ZC_FMT_FP8_E4M3> {};
+template <> struct Layout<ZC_FMT_FP8_E5M2, 0, kWhole> : OneByte<ZC_FMT_FP8_E5M2> {};
+template <> struct Layout<ZC_FMT_BF16, 0, kWhole> : LengthLow {
     static constexpr uint32_t kFirst = 0x7F80u;
+    static constexpr int kSecond = 16;
     static __device__ __forceinline__ uint32_t put(uint32_t s) { return s << 7; }
 };
-template <> struct Entries<ZC_FMT_FP8_E4M3_BYTES, 0, kLongRing> : OfWholeTable {
-    static constexpr uint32_t kFirst = 0x7878u;
-    static constexpr int kLen = 7;
-    static __device__ __forceinline__ uint32_t put(uint32_t s) { return ShortEntries<ZC_FMT_FP8_E4M3_BYTES, 0>::put(s); }
-    static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return c + ((e >> 7) & 15u); }
-    static __device__ __forceinline__ uint32_t shift(uint32_t x, uint32_t e) { return x >> ((e >> 7) & 15u); }
-};
-// Two fields: a delta's exponents take 1.1 bits each, so pairs by 11 bits are unresolved in 1.5 % of the periods and leave the LDS to
-// the other field.  Where that has codes of at most 12 bits (small tensors of weights, whose pairs by 11 bits are unresolved in 39 %),
-// pairs by 13 bits and longer rings.
-template <> struct Entries<ZC_FMT_BF16, 0, kLongRingWeights> : ShortEntries<ZC_FMT_BF16, 0> { static constexpr uint32_t kBits = 13; };
-template <> struct Entries<ZC_FMT_BF16, 0, kLongRingTwo> : ShortEntries<ZC_FMT_BF16, 0> { static constexpr uint32_t kBits = 11; };
-template <> struct Entries<ZC_FMT_BF16, 1, kLongRingTwo> : OfWholeTable {
-    static constexpr bool kNoise = true;
-    static constexpr uint32_t kFirst = 0x807Fu;
-    static constexpr int kLen = 8;
-    static __device__ __forceinline__ uint32_t put(uint32_t s) { return ShortEntries<ZC_FMT_BF16, 1>::put(s); }
-    static __device__ __forceinline__ uint32_t add(uint32_t c, uint32_t e) { return add_byte<1>(c, e); }
-    static __device__ __forceinline__ uint32_t shift(uint32_t x, uint32_t e) { return shr_byte<1>(x, e); }
+template <int FMT, int F, class W> struct Entries : Layout<FMT, F, W::template kTable<F>> {
+    static constexpr Table kTable = W::template kTable<F>;
+    static constexpr bool kPair = in_pairs(kTable), kWhole = is_whole(kTable);
+    static constexpr uint32_t kBits = index_bits(kTable), kBytes = entry_bytes(kTable);
 };
 __device__ __forceinline__ uint32_t first_len(uint32_t e, int shift) { return (e >> shift) & 15u; }
 // lookups of a period of R symbols
-template <int FMT, int F, int R, uint32_t RW> constexpr int kLookups = Entries<FMT, F, RW>::kPair ? R / 2 : R;
+template <int FMT, int F, int R, class W> constexpr int kLookups = Entries<FMT, F, W>::kPair ? R / 2 : R;
 // bits of an output word that come from the exponent entries
 template <int FMT> constexpr uint32_t kExponentBits = FMT == ZC_FMT_BF16 ? 0x7F807F80u : FMT == ZC_FMT_FP8_E5M2 ? 0x7C7C7C7Cu : 0x78787878u;
 // bytes of a field's table
-template <int FMT, int F, uint32_t RW> constexpr uint32_t kTableBytes = Entries<FMT, F, RW>::kBytes << Entries<FMT, F, RW>::kBits;
+template <int F, class W> constexpr uint32_t kTableBytes = entry_bytes(W::template kTable<F>) << index_bits(W::template kTable<F>);
 // where the rings start: every ring at a multiple of its size, so that a place in it is or-ed to its start
-template <int FMT, uint32_t RW> constexpr uint32_t rings_at(bool two)
+template <class W> constexpr uint32_t rings_at(bool two)
 {
-    constexpr uint32_t ring = kRing<RW> * 4;
-    return (kTableBytes<FMT, 0, RW> + (two ? kTableBytes<FMT, 1, RW> : 0u) + ring - 1) / ring * ring;
+    constexpr uint32_t ring = W::kRing * 4;
+    return (kTableBytes<0, W> + (two ? kTableBytes<1, W> : 0u) + ring - 1) / ring * ring;
 }
 
 // all threads of the workgroup (at least 256)
@@ -241,10 +232,10 @@ __device__ __forceinline__ uint32_t code_symbol(const PairCanon &C, uint32_t w, 
 // once (a pair's first code has at most eight: then only the second one differs); the few indices with longer codes are dealt out
 // to all threads.
 struct LongCodes { uint32_t n; uint16_t at[1024]; };
-template <int FMT, int F, uint32_t RW>
+template <int FMT, int F, class W>
 __device__ __forceinline__ void build_whole(uint16_t *table, const PairCanon &C, const uint32_t (&limit)[17], LongCodes &longs)
 {
-    typedef Entries<FMT, F, RW> P;
+    typedef Entries<FMT, F, W> P;
     const uint32_t tid = threadIdx.x;
     constexpr uint32_t less = P::kLow ? 0 : 1;
     if (tid == 0) longs.n = 0;
@@ -280,10 +271,10 @@ __device__ __forceinline__ void build_whole(uint16_t *table, const PairCanon &C,
     __syncthreads();
 }
 
-template <int FMT, int F, uint32_t RW>
+template <int FMT, int F, class W>
 __device__ __forceinline__ void build_entries(char *table, const PairCanon &C, LongCodes &longs)
 {
-    typedef Entries<FMT, F, RW> P;
+    typedef Entries<FMT, F, W> P;
     constexpr uint32_t K = P::kBits, entries = 1u << K;
     const uint32_t lane = threadIdx.x & 63, mine = lane < 17 ? C.limit[lane] : 0u;
     uint32_t limit[K + 1];
@@ -291,7 +282,7 @@ __device__ __forceinline__ void build_entries(char *table, const PairCanon &C, L
     for (uint32_t l = 1; l <= K; l++) limit[l] = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)l);
     uint32_t *const pairs = reinterpret_cast<uint32_t *>(table);
     uint16_t *const singles = reinterpret_cast<uint16_t *>(table);
-    if constexpr (P::kWhole) { build_whole<FMT, F, RW>(singles, C, limit, longs); return; }
+    if constexpr (P::kWhole) { build_whole<FMT, F, W>(singles, C, limit, longs); return; }
     // A thread's entries have the low eight bits of their index in common, so a code of at most eight bits can be looked up once for
     // all of them: 1,000 E5M2 tensors of 2 KB 24.5 -> 21.5 us.  The other formats have longer codes in some lane of nearly every
     // wavefront, which would make it 3 - 5 % slower for small chunks.
@@ -340,7 +331,7 @@ struct PairStream {
     __amdgpu_buffer_rsrc_t rs;
 };
 
-// Ring of RW words per wavefront and field, refilled SEG = RW / 4 words at a time; see ring_service in zc_decode_s64.hip
+// Ring of W words per wavefront and field, refilled SEG = W / 4 words at a time; see ring_service in zc_decode_s64.hip
 template <uint32_t B>
 __device__ __forceinline__ void ring_write(uint32_t at, const u32x4 &v)
 {
@@ -361,16 +352,16 @@ __device__ __forceinline__ u32x4 segment_load(__amdgpu_buffer_rsrc_t rs, uint32_
 }
 
 // A segment of SEG words: pieces of 64 * B words, B of them per lane and load
-template <uint32_t RW> struct Segment {
-    static constexpr uint32_t kWords = kRing<RW> / 4, B = kWords >= 256 ? 4 : kWords / 64, kPieces = kWords / (64 * B);
+template <class W> struct Segment {
+    static constexpr uint32_t kWords = W::kRing / 4, B = kWords >= 256 ? 4 : kWords / 64, kPieces = kWords / (64 * B);
     static_assert((B == 1 || B == 2 || B == 4) && kPieces >= 1 && kPieces <= 4, "whole loads");
 };
 
-template <uint32_t RW>
+template <class W>
 __device__ __forceinline__ void pair_open(PairStream &S, uint32_t lane, bool owner)
 {
-    constexpr uint32_t B = Segment<RW>::B;
-    constexpr uint32_t kLoads = kRing<RW> / (64 * B), kAtOnce = kLoads < 8 ? kLoads : 8;
+    constexpr uint32_t B = Segment<W>::B;
+    constexpr uint32_t kLoads = W::kRing / (64 * B), kAtOnce = kLoads < 8 ? kLoads : 8;
 #pragma unroll 1
     for (uint32_t q = 0; q < kLoads; q += kAtOnce) {
         u32x4 v[kAtOnce];
@@ -384,31 +375,31 @@ __device__ __forceinline__ void pair_open(PairStream &S, uint32_t lane, bool own
     S.hi = lds_word(S.ring + prefix_count64(takers) * 4);
     S.lo = S.hi;
     S.c = 32; S.wpos = (uint32_t)__popcll(takers); S.wbase = 0; S.pslot = 0; S.pending = false; S.on = 0;
-    if (kInFours<RW>) S.wbase = S.pslot = kRing<RW>;
+    if (W::kInFours) S.wbase = S.pslot = W::kRing;
 #pragma unroll
     for (int i = 0; i < 4; i++) S.pv[i] = u32x4{0, 0, 0, 0};
 }
 
 // the segment on its way, when there is one, into its place
-template <uint32_t RW>
+template <class W>
 __device__ __forceinline__ void pair_settle(PairStream &S, uint32_t lane)
 {
-    constexpr uint32_t B = Segment<RW>::B;
+    constexpr uint32_t B = Segment<W>::B;
     if (S.pending) {
 #pragma unroll
-        for (uint32_t q = 0; q < Segment<RW>::kPieces; q++) ring_write<B>(S.ring + (S.pslot + (q * 64 + lane) * B) * 4, S.pv[q]);
+        for (uint32_t q = 0; q < Segment<W>::kPieces; q++) ring_write<B>(S.ring + (S.pslot + (q * 64 + lane) * B) * 4, S.pv[q]);
     }
 }
 
-template <uint32_t RW>
+template <class W>
 __device__ __forceinline__ void pair_service(PairStream &S, uint32_t lane)
 {
-    constexpr uint32_t SEG = Segment<RW>::kWords, B = Segment<RW>::B;
+    constexpr uint32_t SEG = Segment<W>::kWords, B = Segment<W>::B;
     if (S.wpos - S.wbase >= SEG) {
-        pair_settle<RW>(S, lane);
+        pair_settle<W>(S, lane);
 #pragma unroll
-        for (uint32_t q = 0; q < Segment<RW>::kPieces; q++) S.pv[q] = segment_load<B>(S.rs, (S.wbase + kRing<RW> + (q * 64 + lane) * B) * 4);
-        S.pslot = S.wbase & (kRing<RW> - 1);
+        for (uint32_t q = 0; q < Segment<W>::kPieces; q++) S.pv[q] = segment_load<B>(S.rs, (S.wbase + W::kRing + (q * 64 + lane) * B) * 4);
+        S.pslot = S.wbase & (W::kRing - 1);
         S.wbase += SEG;
         S.pending = true;
     }
@@ -419,41 +410,41 @@ __device__ __forceinline__ void pair_service(PairStream &S, uint32_t lane)
 // ring, each of the four into registers of its own.  (With one segment at a time a wait for it is a wait for what the row before
 // has asked for.)
 // wbase: words that are in the ring, pslot: words asked for, pv[i], on: the pieces on their way
-template <uint32_t RW> constexpr uint32_t kPiece = kRing<RW> / 8;
+template <class W> constexpr uint32_t kPiece = W::kRing / 8;
 constexpr uint32_t kGuard = 256;                                 // (a period takes 64 words at most, and four are what a guard is for)
-template <uint32_t RW>
+template <class W>
 __device__ __forceinline__ void fours_write(PairStream &S, uint32_t i, uint32_t lane)
 {
-    constexpr uint32_t B = kPiece<RW> / 64;
+    constexpr uint32_t B = kPiece<W> / 64;
     if (S.on & (1u << i)) {
-        ring_write<B>(S.ring + ((S.wbase & (kRing<RW> - 1)) + lane * B) * 4, S.pv[i]);
-        S.wbase += kPiece<RW>;
+        ring_write<B>(S.ring + ((S.wbase & (W::kRing - 1)) + lane * B) * 4, S.pv[i]);
+        S.wbase += kPiece<W>;
     }
 }
-template <uint32_t RW, uint32_t ROW>
+template <class W, uint32_t ROW>
 __device__ __forceinline__ void fours_service(PairStream &S, uint32_t lane)
 {
-    constexpr uint32_t B = kPiece<RW> / 64;
-    fours_write<RW>(S, ROW, lane);
+    constexpr uint32_t B = kPiece<W> / 64;
+    fours_write<W>(S, ROW, lane);
     S.on &= ~(1u << ROW);
-    if (S.pslot + kPiece<RW> - S.wpos <= kRing<RW>) {
+    if (S.pslot + kPiece<W> - S.wpos <= W::kRing) {
         S.pv[ROW] = segment_load<B>(S.rs, (S.pslot + lane * B) * 4);
-        S.pslot += kPiece<RW>;
+        S.pslot += kPiece<W>;
         S.on |= 1u << ROW;
     }
 }
 // what is on its way (the oldest of it after row ROW's) into the ring, then as much as it holds: there has to be a guard's worth
-template <uint32_t RW, uint32_t ROW>
+template <class W, uint32_t ROW>
 __device__ __forceinline__ void fours_guard(PairStream &S, uint32_t lane)
 {
-    constexpr uint32_t B = kPiece<RW> / 64;
+    constexpr uint32_t B = kPiece<W> / 64;
     if (__builtin_expect(S.wbase - S.wpos >= kGuard, 1)) return;
 #pragma unroll
-    for (uint32_t k = 1; k <= 4; k++) fours_write<RW>(S, (ROW + k) & 3u, lane);
+    for (uint32_t k = 1; k <= 4; k++) fours_write<W>(S, (ROW + k) & 3u, lane);
     S.on = 0;
-    while (S.wbase + kPiece<RW> - S.wpos <= kRing<RW>) {
-        ring_write<B>(S.ring + ((S.wbase & (kRing<RW> - 1)) + lane * B) * 4, segment_load<B>(S.rs, (S.wbase + lane * B) * 4));
-        S.wbase += kPiece<RW>;
+    while (S.wbase + kPiece<W> - S.wpos <= W::kRing) {
+        ring_write<B>(S.ring + ((S.wbase & (W::kRing - 1)) + lane * B) * 4, segment_load<B>(S.rs, (S.wbase + lane * B) * 4));
+        S.wbase += kPiece<W>;
     }
     S.pslot = S.wbase;
 }
@@ -471,83 +462,82 @@ __device__ __forceinline__ uint32_t long_symbol(const PairStream &S, const PairC
 }
 
 // The entry at the window x, which lies SCALE bits up (where it is scaled by an entry's size, masked it is an address)
-template <int FMT, int F, int SCALE, uint32_t RW>
+template <int FMT, int F, int SCALE, class W>
 __device__ __forceinline__ uint32_t entry_at(uint32_t x)
 {
-    typedef Entries<FMT, F, RW> P;
+    typedef Entries<FMT, F, W> P;
     constexpr int size = P::kBytes == 4 ? 2 : 1;
-    constexpr uint32_t mask = ((1u << P::kBits) - 1) << size, table = F == 0 ? 0u : kTableBytes<FMT, 0, RW>;
+    constexpr uint32_t mask = ((1u << P::kBits) - 1) << size, table = F == 0 ? 0u : kTableBytes<0, W>;
     const uint32_t at = ((x << (size - SCALE)) & mask) + table;
     if (P::kBytes == 4) return lds_word(at);
     return *reinterpret_cast<const LdsHalf *>(at);
 }
 // Bits a period's window is scaled by: where the bits this costs at its top are no lookup's.  (In a whole table's period, with its
 // lengths less one, the shift past a code leaves the window scaled by one; kLow: a window of 64 bits.)
-template <int FMT, int F, int N, uint32_t RW>
-constexpr int kScale = Entries<FMT, F, RW>::kLow ? 1 : Entries<FMT, F, RW>::kWhole || N * (int)Entries<FMT, F, RW>::kBits + (Entries<FMT, F, RW>::kPair ? 2 : 1) > 32 ? 0 : Entries<FMT, F, RW>::kPair ? 2 : 1;
+template <int FMT, int F, int N, class W>
+constexpr int kScale = Entries<FMT, F, W>::kLow ? 1 : Entries<FMT, F, W>::kWhole || N * (int)Entries<FMT, F, W>::kBits + (Entries<FMT, F, W>::kPair ? 2 : 1) > 32 ? 0 : Entries<FMT, F, W>::kPair ? 2 : 1;
 
-// the entries of a period after the first, e[0], which was found at x (scaled)
-template <int FMT, int F, int N, uint32_t RW>
+// the entries of a period from FROM on, where the one before it was found at the window (scaled)
+template <int FMT, int F, int N, class W, int FROM>
 __device__ __forceinline__ void look_on(uint64_t window, uint32_t e[N])
 {
-    typedef Entries<FMT, F, RW> P;
+    typedef Entries<FMT, F, W> P;
     uint32_t x = (uint32_t)window;
 #pragma unroll
-    for (int i = 1; i < N; i++) {
+    for (int i = FROM; i < N; i++) {
         if constexpr (P::kLow) {
             window = P::shift(window, e[i - 1]);
-            e[i] = entry_at<FMT, F, 1, RW>((uint32_t)window);
+            e[i] = entry_at<FMT, F, 1, W>((uint32_t)window);
             continue;
         }
         const uint32_t y = (uint32_t)P::shift(x, e[i - 1]);
-        e[i] = entry_at<FMT, F, P::kWhole ? 1 : kScale<FMT, F, N, RW>, RW>(y);
+        e[i] = entry_at<FMT, F, P::kWhole ? 1 : kScale<FMT, F, N, W>, W>(y);
         x = P::kWhole ? y >> 1 : y;
     }
 }
 // c: bits used before a period's entries, returns them after it (in the low 7 bits)
-template <int FMT, int F, int N, uint32_t RW>
+template <int FMT, int F, int N, class W>
 __device__ __forceinline__ uint32_t add_up(uint32_t c, const uint32_t e[N])
 {
-    if (Entries<FMT, F, RW>::kWhole && !Entries<FMT, F, RW>::kLow) c += N;
+    if (Entries<FMT, F, W>::kWhole && !Entries<FMT, F, W>::kLow) c += N;
 #pragma unroll
-    for (int i = 0; i < N; i++) c = Entries<FMT, F, RW>::add(c, e[i]);
+    for (int i = 0; i < N; i++) c = Entries<FMT, F, W>::add(c, e[i]);
     return c;
 }
 // a period's entries, N of them, from window x
-template <int FMT, int F, int N, uint32_t RW>
+template <int FMT, int F, int N, class W>
 __device__ __forceinline__ uint32_t look_up(uint32_t c, uint32_t x, uint32_t e[N])
 {
-    const uint64_t window = (uint64_t)x << kScale<FMT, F, N, RW>;
-    e[0] = entry_at<FMT, F, kScale<FMT, F, N, RW>, RW>((uint32_t)window);
-    look_on<FMT, F, N, RW>(window, e);
-    return add_up<FMT, F, N, RW>(c, e);
+    const uint64_t window = (uint64_t)x << kScale<FMT, F, N, W>;
+    e[0] = entry_at<FMT, F, kScale<FMT, F, N, W>, W>((uint32_t)window);
+    look_on<FMT, F, N, W, 1>(window, e);
+    return add_up<FMT, F, N, W>(c, e);
 }
-template <int FMT, int F, uint32_t RW> constexpr bool kSure = Entries<FMT, F, RW>::kWhole || (F == 1 && RW == kLongRingWeights);       // (no code is longer than the index)
-template <int FMT, int F, uint32_t RW>
-__device__ __forceinline__ bool unresolved(uint32_t e) { return !kSure<FMT, F, RW> && (Entries<FMT, F, RW>::kPair ? (int)e < 0 : e == 0); }
+template <int FMT, int F, class W>
+__device__ __forceinline__ bool unresolved(uint32_t e) { return !Entries<FMT, F, W>::kWhole && (Entries<FMT, F, W>::kPair ? (int)e < 0 : e == 0); }
 
 // The same where an entry does not resolve in some lane; e[0]: as look_up found it (in every lane the right one); FOUND: and the others,
-// which are right in the lanes where those before them resolved (looked up again: byte symbols, 1,500 chunks of 256 KiB 287 | 276 us)
-template <int FMT, int F, int N, uint32_t RW, bool FOUND>
+// which are right in the lanes where those before them resolved
+template <int FMT, int F, int N, class W, bool FOUND>
 __device__ __forceinline__ uint32_t look_up_slowly(const PairStream &S, const PairCanon &C, uint32_t c, uint32_t x, uint32_t e[N])
 {
-    typedef Entries<FMT, F, RW> P;
+    typedef Entries<FMT, F, W> P;
     constexpr uint32_t K = P::kBits;
-    if constexpr (P::kWhole) return look_up<FMT, F, N, RW>(c, x, e);
+    if constexpr (P::kWhole) return look_up<FMT, F, N, W>(c, x, e);
     else {
 #pragma unroll
     for (int i = 0; i < N; i++) {
         uint32_t a = e[i], len;
         if (P::kPair) {
-            if (i > 0) a = entry_at<FMT, F, 0, RW>(x);
+            if (i > 0) a = entry_at<FMT, F, 0, W>(x);
             // both symbols one after the other in every lane
             uint32_t l1 = first_len(a, P::kLen1), s1 = a & P::kFirst;
-            uint32_t b = entry_at<FMT, F, 0, RW>(x >> l1);
+            uint32_t b = entry_at<FMT, F, 0, W>(x >> l1);
             uint32_t l2 = first_len(b, P::kLen1), s2 = b & P::kFirst;
             if (__builtin_expect(__ballot(l1 == 0 || l2 == 0) != 0, 0)) {
                 if (l1 == 0) {
                     s1 = P::put(long_symbol<K>(S, C, x, l1)) & P::kFirst;
-                    b = entry_at<FMT, F, 0, RW>(x >> l1);
+                    b = entry_at<FMT, F, 0, W>(x >> l1);
                     l2 = first_len(b, P::kLen1); s2 = b & P::kFirst;
                 }
                 if (l2 == 0) s2 = P::put(long_symbol<K>(S, C, x >> l1, l2)) & P::kFirst;
@@ -555,12 +545,12 @@ __device__ __forceinline__ uint32_t look_up_slowly(const PairStream &S, const Pa
             a = s1 | (s2 << P::kSecond);
             len = l1 + l2;
         } else {
-            if (i > 0 && !FOUND) a = entry_at<FMT, F, 0, RW>(x);
+            if (i > 0 && !FOUND) a = entry_at<FMT, F, 0, W>(x);
             len = first_len(a, P::kLen);
             a &= P::kFirst;
             if (len == 0) {
                 a = P::put(long_symbol<K>(S, C, x, len)) & P::kFirst;
-                if (FOUND && i + 1 < N) e[i + 1] = entry_at<FMT, F, 0, RW>(x >> len);
+                if (FOUND && i + 1 < N) e[i + 1] = entry_at<FMT, F, 0, W>(x >> len);
             }
         }
         e[i] = a;
@@ -575,7 +565,7 @@ __device__ __forceinline__ uint32_t look_up_slowly(const PairStream &S, const Pa
 // t: bits used so far, in its low 7 bits.  CAREFUL: owner says which lanes own a symbol at the step the words are for, and
 // lanes whose every period took 32 bits are looked after.
 struct Refill { bool need; uint32_t t, w, taken; };
-template <uint32_t RW, bool CAREFUL, bool NOISE>
+template <class W, bool CAREFUL, bool NOISE>
 __device__ __forceinline__ Refill ask(const PairStream &S, uint32_t t, bool owner)
 {
     Refill r;
@@ -583,7 +573,7 @@ __device__ __forceinline__ Refill ask(const PairStream &S, uint32_t t, bool owne
     r.need = r.t > 31u && (!CAREFUL || owner);
     const uint64_t bm = __ballot(r.need);
     const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(bm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bm, S.wpos));
-    r.w = lds_word_now(S.ring + (pos & (kRing<RW> - 1)) * 4);          // (its latency covers the check of the entries)
+    r.w = lds_word_now(S.ring + (pos & (W::kRing - 1)) * 4);          // (its latency covers the check of the entries)
     r.taken = (uint32_t)__popcll(bm);
     return r;
 }
@@ -598,33 +588,33 @@ __device__ __forceinline__ void take(PairStream &S, const Refill &r)
 
 // One run of G symbols of the exponent field (A) and, when TWO, of the sign+mantissa field (B): their entries in ea, eb.  CAREFUL: nsym is
 // what this lane owns of its symbols, nsym_next of the one's after it
-template <int FMT, int R, bool TWO, uint32_t RW, bool CAREFUL, bool SERVICE>
+template <int FMT, int R, bool TWO, class W, bool CAREFUL, bool SERVICE>
 __device__ __forceinline__ void pair_run(PairStream &A, PairStream &B, const PairCanon *C, uint32_t lane, uint32_t ea[], uint32_t eb[],
                                             uint32_t nsym, uint32_t nsym_next)
 {
-    constexpr int G = Fmt<FMT>::G, NA = kLookups<FMT, 0, R, RW>, NB = kLookups<FMT, 1, R, RW>;
-    constexpr uint32_t kPerService = kRing<RW> / 4 / 64;                // refill steps between two looks at the ring
+    constexpr int G = Fmt<FMT>::G, NA = kLookups<FMT, 0, R, W>, NB = kLookups<FMT, 1, R, W>;
+    constexpr uint32_t kPerService = W::kRing / 4 / 64;                // refill steps between two looks at the ring
 #pragma unroll
     for (int g = 0; g < G / R; g++) {
-        if (kInFours<RW>) {
-            if (g % 4 == 0) { fours_guard<RW, 3>(A, lane); if (TWO) fours_guard<RW, 3>(B, lane); }
+        if (W::kInFours) {
+            if (g % 4 == 0) { fours_guard<W, 3>(A, lane); if (TWO) fours_guard<W, 3>(B, lane); }
         } else if (SERVICE && (uint32_t)g % kPerService == 0) {
-            pair_service<RW>(A, lane);
-            if (TWO) pair_service<RW>(B, lane);
+            pair_service<W>(A, lane);
+            if (TWO) pair_service<W>(B, lane);
         }
         const uint32_t xa = __builtin_amdgcn_alignbit(A.hi, A.lo, A.c), xb = TWO ? __builtin_amdgcn_alignbit(B.hi, B.lo, B.c) : 0u;
         const bool owner = !CAREFUL || (g + 1 < G / R ? (uint32_t)((g + 1) * R) < nsym : nsym_next > 0);
         uint32_t *const a = ea + g * NA, *const b = eb + g * NB;
-        uint32_t ta = look_up<FMT, 0, NA, RW>(A.c, xa, a), tb = TWO ? look_up<FMT, 1, NB, RW>(B.c, xb, b) : 0u;
-        Refill ra = ask<RW, CAREFUL, Entries<FMT, 0, RW>::kNoise>(A, ta, owner), rb;
-        if (TWO) rb = ask<RW, CAREFUL, Entries<FMT, 1, RW>::kNoise>(B, tb, owner);
-        if (__builtin_expect(__any(unresolved<FMT, 0, RW>(a[NA - 1])), 0)) {
-            ta = look_up_slowly<FMT, 0, NA, RW, true>(A, C[0], A.c, xa, a);
-            ra = ask<RW, CAREFUL, Entries<FMT, 0, RW>::kNoise>(A, ta, owner);
+        uint32_t ta = look_up<FMT, 0, NA, W>(A.c, xa, a), tb = TWO ? look_up<FMT, 1, NB, W>(B.c, xb, b) : 0u;
+        Refill ra = ask<W, CAREFUL, Entries<FMT, 0, W>::kNoise>(A, ta, owner), rb;
+        if (TWO) rb = ask<W, CAREFUL, Entries<FMT, 1, W>::kNoise>(B, tb, owner);
+        if (__builtin_expect(__any(unresolved<FMT, 0, W>(a[NA - 1])), 0)) {
+            ta = look_up_slowly<FMT, 0, NA, W, true>(A, C[0], A.c, xa, a);
+            ra = ask<W, CAREFUL, Entries<FMT, 0, W>::kNoise>(A, ta, owner);
         }
-        if (TWO && __builtin_expect(__any(unresolved<FMT, 1, RW>(b[NB - 1])), 0)) {
-            tb = look_up_slowly<FMT, 1, NB, RW, true>(B, C[1], B.c, xb, b);
-            rb = ask<RW, CAREFUL, Entries<FMT, 1, RW>::kNoise>(B, tb, owner);
+        if (TWO && __builtin_expect(__any(unresolved<FMT, 1, W>(b[NB - 1])), 0)) {
+            tb = look_up_slowly<FMT, 1, NB, W, true>(B, C[1], B.c, xb, b);
+            rb = ask<W, CAREFUL, Entries<FMT, 1, W>::kNoise>(B, tb, owner);
         }
         take<CAREFUL>(A, ra);
         if (TWO) take<CAREFUL>(B, rb);
@@ -637,7 +627,9 @@ __device__ __forceinline__ void pair_run(PairStream &A, PairStream &B, const Pai
 // alone, and the refill (the count of the lanes that take a word, an address, an LDS read) runs beside them.  Zeros come into a
 // window that runs out of bits; an entry found there is still the right one as long as its codes' bits were there, so a period
 // has gone wrong only in lanes that wait for a word and are already past the next 32 bits (2.6 % of the periods of FP8 E4M3 weights
-// and byte symbols, 0.7 % of deltas' sign+mantissa fields, hardly any where a period is one lookup), and is done once more.
+// and byte symbols, 0.7 % of deltas' sign+mantissa fields, hardly any where a period is one lookup), and is done once more.  Where
+// codes are so long that two periods often take more than 32 bits (wide) that would be nearly every period.  There the word comes in
+// behind the period's first entry (INSIDE), which costs six more instructions and goes wrong only where one code is that long.
 // What is not the chain stands where LDS reads are waited for anyway, masks are read late, and there is one branch per period.
 // x: the window, scaled for a lookup; e: the entry found there; c: bits used of (hi, lo) once what is owed has come in; need, w: lanes
 // that asked at the end of the last period, and the words; owed, v: at the end of the one before it (kTwice only).
@@ -657,19 +649,19 @@ struct Late {
     }
 };
 // one pair per period: no lane asks twice within two periods (31 bits, a pair of at most 15, again one: no 64)
-template <int FMT, int F, int N, uint32_t RW> constexpr bool kTwice = N == 1 && Entries<FMT, F, RW>::kPair && !Entries<FMT, F, RW>::kWhole;
+template <int FMT, int F, int N, class W> constexpr bool kTwice = N == 1 && Entries<FMT, F, W>::kPair && !Entries<FMT, F, W>::kWhole;
 __device__ __forceinline__ void in_order() { __builtin_amdgcn_sched_barrier(0); }
 
 // what the lanes look up next at bit t of (hi, lo)
-template <int FMT, int F, int N, uint32_t RW>
+template <int FMT, int F, int N, class W>
 __device__ __forceinline__ void late_window(Late &S, uint32_t t)
 {
     const uint64_t w = ((uint64_t)S.hi << 32 | S.lo) >> (t & 63u);
-    S.x = Entries<FMT, F, RW>::kLow ? w << 1 : (uint32_t)w << kScale<FMT, F, N, RW>;
-    S.e = entry_at<FMT, F, kScale<FMT, F, N, RW>, RW>((uint32_t)S.x);
+    S.x = Entries<FMT, F, W>::kLow ? w << 1 : (uint32_t)w << kScale<FMT, F, N, W>;
+    S.e = entry_at<FMT, F, kScale<FMT, F, N, W>, W>((uint32_t)S.x);
 }
 // the word they ask for
-template <uint32_t RW>
+template <class W>
 __device__ __forceinline__ void late_ask(Late &S, uint32_t ring)
 {
     S.need = S.c > 31u;
@@ -689,6 +681,22 @@ __device__ __forceinline__ void late_take(Late &S, bool lanes, uint32_t word)
     S.lo = lanes ? S.hi : S.lo;
     S.hi = lanes ? word : S.hi;
 }
+// The period's entries; INSIDE: the word that is out comes in (into next) behind the first of them
+template <int FMT, int F, int N, class W, bool INSIDE>
+__device__ __forceinline__ void late_look(Late &next, const Late &L, uint32_t e[N])
+{
+    typedef Entries<FMT, F, W> P;
+    e[0] = L.e;
+    if constexpr (INSIDE) {
+        static_assert(N > 1, "a second lookup");
+        next = L;
+        late_take(next, L.need, L.w);
+        const uint32_t second = P::add((L.c & 31u) + (P::kWhole && !P::kLow ? 1u : 0u), e[0]) & 63u;
+        const uint64_t w = ((uint64_t)next.hi << 32 | next.lo) >> second, x = P::kLow ? w << 1 : (uint32_t)w << kScale<FMT, F, N, W>;
+        e[1] = entry_at<FMT, F, kScale<FMT, F, N, W>, W>((uint32_t)x);
+        look_on<FMT, F, N, W, 2>(x, e);
+    } else look_on<FMT, F, N, W, 1>(L.x, e);
+}
 // everything asked for comes in
 template <bool TWICE>
 __device__ __forceinline__ void late_settle(Late &S)
@@ -698,14 +706,14 @@ __device__ __forceinline__ void late_settle(Late &S)
     S.c &= 31u;
     S.need = S.owed = false; S.asked = S.asked_before = 0;
 }
-template <int FMT, int F, int N, uint32_t RW>
+template <int FMT, int F, int N, class W>
 __device__ __forceinline__ void late_open(Late &L, const PairStream &S)
 {
     L.lo = S.lo; L.hi = S.hi; L.c = S.c; L.wpos = L.taken = S.wpos;
     L.need = L.owed = false; L.asked = L.asked_before = 0; L.w = L.v = 0;
-    L.wrap = (kRing<RW> - 1) * 4;
+    L.wrap = (W::kRing - 1) * 4;
     asm("" : "+v"(L.wpos), "+v"(L.wrap));
-    late_window<FMT, F, N, RW>(L, L.c);
+    late_window<FMT, F, N, W>(L, L.c);
 }
 template <bool TWICE>
 __device__ __forceinline__ void late_close(Late &L, PairStream &S)
@@ -715,37 +723,45 @@ __device__ __forceinline__ void late_close(Late &L, PairStream &S)
 }
 // The rest of the period: what was out comes in, the next window is looked up, the next word asked for.  t: the bit the next window
 // starts at, c: bits used as they are counted for the next word (at t, less 32 in the lanes whose word is not in yet)
-template <int FMT, int F, int N, uint32_t RW>
+template <int FMT, int F, int N, class W, bool INSIDE>
 __device__ __forceinline__ void late_go_on(Late &next, const Late &L, const PairStream &S, uint32_t t, uint32_t c)
 {
-    if (kTwice<FMT, F, N, RW>) {
+    if (kTwice<FMT, F, N, W>) {
         late_take(next, L.owed, L.v);
-        late_window<FMT, F, N, RW>(next, t);
+        late_window<FMT, F, N, W>(next, t);
         next.owed = L.need; next.asked_before = L.asked; next.v = L.w;
     } else {
-        late_take(next, L.need, L.w);
-        late_window<FMT, F, N, RW>(next, t);
+        if (!INSIDE) late_take(next, L.need, L.w);
+        late_window<FMT, F, N, W>(next, t);
     }
     in_order();                                                  // (the chain goes through the entry: its read first)
-    next.c = Entries<FMT, F, RW>::kNoise ? c & 63u : c;
-    late_ask<RW>(next, S.ring);
+    next.c = Entries<FMT, F, W>::kNoise ? c & 63u : c;
+    late_ask<W>(next, S.ring);
 }
 // the period from L on as it should go; returns the lanes in which it did not.  c: bits used after its entries
-template <int FMT, int F, int N, uint32_t RW>
+template <int FMT, int F, int N, class W, bool INSIDE>
 __device__ __forceinline__ uint64_t late_period(Late &next, const Late &L, const PairStream &S, const uint32_t e[N], uint32_t c)
 {
-    constexpr bool TWICE = kTwice<FMT, F, N, RW>;
-    const uint64_t open = __ballot(unresolved<FMT, F, RW>(e[N - 1]));
+    constexpr bool TWICE = kTwice<FMT, F, N, W>;
+    if constexpr (INSIDE) {
+        // (an entry that did not resolve because its bits were not there: the ones after it may.  All in one sign.)
+        int sign = 64 - (int)(Entries<FMT, F, W>::add(L.c + (Entries<FMT, F, W>::kWhole && !Entries<FMT, F, W>::kLow ? 1u : 0u), e[0]) & 127u);
+        if (!Entries<FMT, F, W>::kWhole) sign |= Entries<FMT, F, W>::kPair ? (int)(e[0] | e[N - 1]) : ((int)e[0] - 1) | ((int)e[N - 1] - 1);
+        const uint64_t amiss = __ballot(sign < 0);
+        late_go_on<FMT, F, N, W, true>(next, L, S, c, c);
+        return amiss;
+    }
+    const uint64_t open = __ballot(unresolved<FMT, F, W>(e[N - 1]));
     next = L;
-    late_go_on<FMT, F, N, RW>(next, L, S, TWICE ? Entries<FMT, F, RW>::add(L.c, e[0]) : c, c);
+    late_go_on<FMT, F, N, W, false>(next, L, S, TWICE ? Entries<FMT, F, W>::add(L.c, e[0]) : c, c);
     return open | (next.asked & (TWICE ? L.asked_before : L.asked));
 }
 // The period once more, where it went wrong in some lane
-template <int FMT, int F, int N, uint32_t RW>
+template <int FMT, int F, int N, class W>
 __device__ __forceinline__ void late_again(Late &next, const Late &L, const PairStream &S, const PairCanon &C, uint32_t e[N])
 {
-    typedef Entries<FMT, F, RW> P;
-    constexpr bool TWICE = kTwice<FMT, F, N, RW>;
+    typedef Entries<FMT, F, W> P;
+    constexpr bool TWICE = kTwice<FMT, F, N, W>;
     constexpr uint32_t K = P::kBits;
     uint64_t amiss = 1;
     uint32_t l1 = 0, l2 = 0, b = 0;
@@ -753,7 +769,7 @@ __device__ __forceinline__ void late_again(Late &next, const Late &L, const Pair
         // some lanes' second symbols have to be looked up by themselves: that is all, unless a code is longer than the index, a
         // lane's words are late, or it takes so many bits that the next period's index might not be there
         l1 = first_len(e[0], P::kLen1);
-        b = entry_at<FMT, F, kScale<FMT, F, N, RW>, RW>((uint32_t)L.x >> l1);
+        b = entry_at<FMT, F, kScale<FMT, F, N, W>, W>((uint32_t)L.x >> l1);
         l2 = first_len(b, P::kLen1);
         const int room = (int)((L.owed ? 32u : 63u - K) - (L.c + l1 + l2)), shorter = (int)(l1 < l2 ? l1 : l2) - 1;
         amiss = __ballot((room | shorter) < 0) | (next.asked & L.asked_before);
@@ -761,59 +777,65 @@ __device__ __forceinline__ void late_again(Late &next, const Late &L, const Pair
     next = L;
     if (TWICE && amiss == 0) {
         e[0] = (e[0] & P::kFirst) | ((b & P::kFirst) << P::kSecond);
-        late_go_on<FMT, F, N, RW>(next, L, S, L.c + l1 + l2, (L.c & 31u) + l1 + l2);
+        late_go_on<FMT, F, N, W, false>(next, L, S, L.c + l1 + l2, (L.c & 31u) + l1 + l2);
         return;
     }
     late_settle<TWICE>(next);
     const uint32_t x = __builtin_amdgcn_alignbit(next.hi, next.lo, next.c);
-    e[0] = entry_at<FMT, F, 0, RW>(x);
-    next.c = look_up_slowly<FMT, F, N, RW, false>(S, C, next.c, x, e) & 63u;
+    e[0] = entry_at<FMT, F, 0, W>(x);
+    next.c = look_up_slowly<FMT, F, N, W, false>(S, C, next.c, x, e) & 63u;
     if (TWICE) {
         // (nothing is owed after it: its codes may be longer than the index)
-        late_ask<RW>(next, S.ring);
+        late_ask<W>(next, S.ring);
         late_settle<TWICE>(next);
-        late_window<FMT, F, N, RW>(next, next.c);
+        late_window<FMT, F, N, W>(next, next.c);
         asm volatile("" : "+v"(next.e));                         // (waited for here, or the way on would wait for all that is out)
     } else {
-        late_window<FMT, F, N, RW>(next, next.c);
+        late_window<FMT, F, N, W>(next, next.c);
         in_order();
-        late_ask<RW>(next, S.ring);
+        late_ask<W>(next, S.ring);
     }
 }
 
+// Periods there have been, less kAgain times those in which a word came too late; rows up to which words come in late (none if that was often)
+struct LateRoom { static constexpr int kAgain = 12; int room; uint32_t end; };
+
 // fill(g): what there is to do while the entries of period g are on their way
-template <int FMT, int R, bool TWO, uint32_t RW, bool SERVICE, uint32_t ROW, class Fill>
-__device__ __forceinline__ void late_run(Late &LA, Late &LB, PairStream &A, PairStream &B, const PairCanon *C, uint32_t lane, uint32_t ea[], uint32_t eb[], Fill fill)
+template <int FMT, int R, bool TWO, class W, bool SERVICE, uint32_t ROW, bool INSIDE, class Fill>
+__device__ __forceinline__ void late_run(Late &LA, Late &LB, PairStream &A, PairStream &B, const PairCanon *C, uint32_t lane, uint32_t ea[], uint32_t eb[], LateRoom &late, Fill fill)
 {
-    constexpr int G = Fmt<FMT>::G, NA = kLookups<FMT, 0, R, RW>, NB = kLookups<FMT, 1, R, RW>;
-    constexpr uint32_t kPerService = kRing<RW> / 4 / 64;         // refill steps between two looks at the ring
+    constexpr int G = Fmt<FMT>::G, NA = kLookups<FMT, 0, R, W>, NB = kLookups<FMT, 1, R, W>;
+    constexpr bool inside_a = INSIDE && NA > 1, inside_b = INSIDE && NB > 1;
+    constexpr uint32_t kPerService = W::kRing / 4 / 64;         // refill steps between two looks at the ring
 #pragma unroll
     for (int g = 0; g < G / R; g++) {
-        if (kInFours<RW>) {
+        if (W::kInFours) {
             A.wpos = LA.taken;
             if (TWO) B.wpos = LB.taken;
-            if (g == 0) { fours_service<RW, ROW>(A, lane); if (TWO) fours_service<RW, ROW>(B, lane); }
-            if (g % 4 == 0) { fours_guard<RW, ROW>(A, lane); if (TWO) fours_guard<RW, ROW>(B, lane); }
+            if (g == 0) { fours_service<W, ROW>(A, lane); if (TWO) fours_service<W, ROW>(B, lane); }
+            if (g % 4 == 0) { fours_guard<W, ROW>(A, lane); if (TWO) fours_guard<W, ROW>(B, lane); }
         } else if (SERVICE && (uint32_t)g % kPerService == 0) {
-            A.wpos = LA.taken; pair_service<RW>(A, lane);
-            if (TWO) { B.wpos = LB.taken; pair_service<RW>(B, lane); }
+            A.wpos = LA.taken; pair_service<W>(A, lane);
+            if (TWO) { B.wpos = LB.taken; pair_service<W>(B, lane); }
         }
         uint32_t *const a = ea + g * NA, *const b = eb + g * NB;
-        a[0] = LA.e;
-        look_on<FMT, 0, NA, RW>(LA.x, a);
-        if (TWO) {
-            b[0] = LB.e;
-            look_on<FMT, 1, NB, RW>(LB.x, b);
-        }
+        Late nextA, nextB;
+        late_look<FMT, 0, NA, W, inside_a>(nextA, LA, a);
+        if (TWO) late_look<FMT, 1, NB, W, inside_b>(nextB, LB, b);
         in_order();                                              // (nothing that waits for the words before this)
         fill(g, G / R);
         in_order();
-        const uint32_t ca = add_up<FMT, 0, NA, RW>(LA.c & 31u, a), cb = TWO ? add_up<FMT, 1, NB, RW>(LB.c & 31u, b) : 0u;
-        Late nextA, nextB;
-        const uint64_t wrong_a = late_period<FMT, 0, NA, RW>(nextA, LA, A, a, ca), wrong_b = TWO ? late_period<FMT, 1, NB, RW>(nextB, LB, B, b, cb) : 0u;
+        const uint32_t ca = add_up<FMT, 0, NA, W>(LA.c & 31u, a), cb = TWO ? add_up<FMT, 1, NB, W>(LB.c & 31u, b) : 0u;
+        const uint64_t wrong_a = late_period<FMT, 0, NA, W, inside_a>(nextA, LA, A, a, ca);
+        const uint64_t wrong_b = TWO ? late_period<FMT, 1, NB, W, inside_b>(nextB, LB, B, b, cb) : 0u;
         if (__builtin_expect((wrong_a | wrong_b) != 0, 0)) {
-            if (!TWO || wrong_a != 0) late_again<FMT, 0, NA, RW>(nextA, LA, A, C[0], a);
-            if (TWO && wrong_b != 0) late_again<FMT, 1, NB, RW>(nextB, LB, B, C[1], b);
+            const bool late_a = !kTwice<FMT, 0, NA, W> && (nextA.asked & LA.asked) != 0, late_b = TWO && !kTwice<FMT, 1, NB, W> && (nextB.asked & LB.asked) != 0;
+            if (!INSIDE && (late_a || late_b)) {
+                late.room -= LateRoom::kAgain;
+                if (late.room < 0) late.end = 0;
+            }
+            if (!TWO || wrong_a != 0) late_again<FMT, 0, NA, W>(nextA, LA, A, C[0], a);
+            if (TWO && wrong_b != 0) late_again<FMT, 1, NB, W>(nextB, LB, B, C[1], b);
         }
         LA = nextA;
         if (TWO) LB = nextB;
@@ -821,11 +843,11 @@ __device__ __forceinline__ void late_run(Late &LA, Late &LB, PairStream &A, Pair
 }
 
 // output word i of a run from its entries of field F
-template <int FMT, int F, uint32_t RW>
+template <int FMT, int F, class W>
 __device__ __forceinline__ uint32_t entry_word(const uint32_t e[], int i)
 {
     // a word is one pair, two singles or two pairs that take half of it each (the low halves of both), or four singles of a byte
-    typedef Entries<FMT, F, RW> P;
+    typedef Entries<FMT, F, W> P;
     constexpr bool one = P::kPair && P::kSecond == 16, four = !P::kPair && P::kSecond == 8;
     if (one) return e[i];
     if (four)
@@ -872,15 +894,15 @@ struct ChunkOut {
     uint32_t konst1;                                         // the constant symbol in every place of a word
 };
 
-template <int FMT, int R, int SM, bool XOR, uint32_t RW>
+template <int FMT, int R, int SM, bool XOR, class W>
 __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const PairCanon *C, const ChunkOut &o, uint32_t lane)
 {
     constexpr int NP = Fmt<FMT>::G;                              // entries of a run, at most
     constexpr bool TWO = SM == kSmTable;
     // (With several wavefronts per SIMD it is the number of instructions alone: 2,048 BF16 chunks 200 | 257 us.  Two fields and two
     // wavefronts: 1,526 chunks of a delta 314 | 303, but 3,052, three of them, 436 | 454.)
-    constexpr bool kLate = RW != kShortRing && RW != kLongRingSmall;
-    constexpr int NA = kLookups<FMT, 0, R, RW>, NB = kLookups<FMT, 1, R, RW>;
+    constexpr bool kAhead = W::kLoop != kWait;
+    constexpr int NA = kLookups<FMT, 0, R, W>, NB = kLookups<FMT, 1, R, W>;
     constexpr uint32_t EX = kExponentBits<FMT>;
     const uint32_t rows = o.whole_rows;
     Late LA, LB;
@@ -907,7 +929,7 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
     // word i of a row's output, without the base; m: its sign+mantissa words (E5M2: its pair of rows' three)
     auto out_word = [&](uint32_t row, const uint32_t m[4], const uint32_t ea[], const uint32_t eb[], int i) {
         uint32_t mw;
-        if (SM == kSmTable) mw = entry_word<FMT, 1, RW>(eb, i);
+        if (SM == kSmTable) mw = entry_word<FMT, 1, W>(eb, i);
         else if (SM == kSmFlat3) {
             // an even row's 48 bits start at bit 0 of the three words, an odd one's at bit 48
             const uint32_t lo = (row & 1) ? __builtin_amdgcn_alignbit(m[2], m[1], 16) : m[0];
@@ -919,7 +941,7 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
             // (byte symbols are coded as bytes, most significant bit first, and their nibbles are in order then)
             mw = plain_word<FMT>(flat ? reverse_in_groups<SB>(m[0]) : m[0], flat ? reverse_in_groups<SB>(m[1]) : m[1], i);
         }
-        return (entry_word<FMT, 0, RW>(ea, i) & EX) | (mw & ~EX);
+        return (entry_word<FMT, 0, W>(ea, i) & EX) | (mw & ~EX);
     };
     auto put_row = [&](uint32_t row, const uint32_t m[4], const uint32_t ea[], const uint32_t eb[], const u32x4 &base) {
         u32x4 v;
@@ -936,7 +958,7 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
     auto careful_row = [&](uint32_t row) {
         fetch(row, f[3]);
         if (SM == kSmFlat3) fetch_flat3(row / 2, f[2]);
-        pair_run<FMT, R, TWO, RW, true, true>(A, B, C, lane, ea[1], eb[1], (uint32_t)Fmt<FMT>::G, (ragged && row + 1 == rows) ? o.tail_sym : 1u);
+        pair_run<FMT, R, TWO, W, true, true>(A, B, C, lane, ea[1], eb[1], (uint32_t)Fmt<FMT>::G, (ragged && row + 1 == rows) ? o.tail_sym : 1u);
         put_row(row, SM == kSmFlat3 ? f[2].m : f[3].m, ea[1], eb[1], f[3].base);
     };
     uint32_t row = 0;
@@ -951,24 +973,25 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
     // for what is in flight).  The rings are looked at every kRows rows.  A segment's words go into the ring only when the next one
     // is asked for, and what waits for them waits for everything that was asked for before them: the rows in between are what
     // they have to arrive.
-    constexpr uint32_t kRows = kRing<RW> / 4 / 64 / (Fmt<FMT>::G / R) >= 4 ? 4 : kRing<RW> / 4 / 64 / (Fmt<FMT>::G / R) >= 2 ? 2 : 1;
+    constexpr uint32_t kRows = W::kRing / 4 / 64 / (Fmt<FMT>::G / R) >= 4 ? 4 : W::kRing / 4 / 64 / (Fmt<FMT>::G / R) >= 2 ? 2 : 1;
     if (row + 4 <= fast_end) {
-        if (!kInFours<RW>) { pair_settle<RW>(A, lane); A.pending = false; }
-        if (TWO) { pair_settle<RW>(B, lane); B.pending = false; }
-        if (kLate) {
-            late_open<FMT, 0, NA, RW>(LA, A);
-            if (TWO) late_open<FMT, 1, NB, RW>(LB, B);
+        if (!W::kInFours) { pair_settle<W>(A, lane); A.pending = false; }
+        if (TWO) { pair_settle<W>(B, lane); B.pending = false; }
+        if (kAhead) {
+            late_open<FMT, 0, NA, W>(LA, A);
+            if (TWO) late_open<FMT, 1, NB, W>(LB, B);
         }
-        // (kLate: the row before the first is stored once more, from the same registers: it is what the first one's waits are filled with)
+        // (kAhead: the row before the first is stored once more, from the same registers: it is what the first one's waits are filled with)
 #pragma unroll
-        for (uint32_t i = 0; i < (kLate ? 3 : 4); i++) {
+        for (uint32_t i = 0; i < (kAhead ? 3 : 4); i++) {
             fetch(row + i, f[i]);
-            if (SM == kSmFlat3 && i % 2 == 0 && (i == 0 || !kLate)) fetch_flat3((row + i) / 2, f[i]);
+            if (SM == kSmFlat3 && i % 2 == 0 && (i == 0 || !kAhead)) fetch_flat3((row + i) / 2, f[i]);
         }
-        auto block_row = [&](auto index) {
+        LateRoom late = {4 * LateRoom::kAgain, fast_end};
+        auto block_row = [&](auto index, auto inside) {
             constexpr uint32_t i = decltype(index)::value, last = (i + 3) & 3;
-            if (!kLate) {
-                pair_run<FMT, R, TWO, RW, false, i % kRows == 0>(A, B, C, lane, ea[0], eb[0], 0, 0);
+            if (!kAhead) {
+                pair_run<FMT, R, TWO, W, false, i % kRows == 0>(A, B, C, lane, ea[0], eb[0], 0, 0);
                 put_row(row + i, SM == kSmFlat3 ? f[i & 2].m : f[i].m, ea[0], eb[0], f[i].base);
                 if (SM == kSmFlat3 && i % 2 == 1) fetch_flat3((row + i + 3) / 2, f[i & 2]);
                 fetch(row + i + 4, f[i]);
@@ -976,7 +999,7 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
             }
             const uint32_t prev = row + i - 1;
             u32x4 v;
-            late_run<FMT, R, TWO, RW, i % kRows == 0, i>(LA, LB, A, B, C, lane, ea[i & 1], eb[i & 1], [&](int g, int periods) {
+            late_run<FMT, R, TWO, W, i % kRows == 0, i, decltype(inside)::value>(LA, LB, A, B, C, lane, ea[i & 1], eb[i & 1], late, [&](int g, int periods) {
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
                     if (k * periods / 4 != g) continue;
@@ -990,17 +1013,27 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
             if (SM == kSmFlat3 && last % 2 == 1) fetch_flat3((prev + 3) / 2, f[last & 2]);
             fetch(prev + 4, f[last]);
         };
+        auto block = [&](auto inside) {
+            block_row(std::integral_constant<uint32_t, 0>(), inside);
+            block_row(std::integral_constant<uint32_t, 1>(), inside);
+            block_row(std::integral_constant<uint32_t, 2>(), inside);
+            block_row(std::integral_constant<uint32_t, 3>(), inside);
+            row += 4;
+        };
+        if constexpr (W::kLoop == kLate) {
+            // as long as one period in twelve goes wrong at most, but for a few at first
 #pragma unroll 1
-        for (; row + 4 <= fast_end; row += 4) {
-            block_row(std::integral_constant<uint32_t, 0>());
-            block_row(std::integral_constant<uint32_t, 1>());
-            block_row(std::integral_constant<uint32_t, 2>());
-            block_row(std::integral_constant<uint32_t, 3>());
+            while (row + 4 <= late.end) {
+                block(std::false_type());
+                late.room = late.room + 4 * Fmt<FMT>::G / R < 8 * LateRoom::kAgain ? late.room + 4 * Fmt<FMT>::G / R : 8 * LateRoom::kAgain;
+            }
         }
-        if (kLate) {
+#pragma unroll 1
+        while (row + 4 <= fast_end) block(std::true_type());
+        if (kAhead) {
             put_row(row - 1, SM == kSmFlat3 ? f[2].m : f[3].m, ea[1], eb[1], f[3].base);
-            late_close<kTwice<FMT, 0, NA, RW>>(LA, A);
-            if (TWO) late_close<kTwice<FMT, 1, NB, RW>>(LB, B);
+            late_close<kTwice<FMT, 0, NA, W>>(LA, A);
+            if (TWO) late_close<kTwice<FMT, 1, NB, W>>(LB, B);
         }
     }
 #pragma unroll 1
@@ -1008,7 +1041,7 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
     if (!ragged) return;
     // ---- the incomplete last row: a lane owns a whole run, part of one or nothing
     uint32_t m[4] = {o.konst1, o.konst1, 0, 0};
-    pair_run<FMT, R, TWO, RW, true, true>(A, B, C, lane, ea[0], eb[0], o.tail_sym, 0u);
+    pair_run<FMT, R, TWO, W, true, true>(A, B, C, lane, ea[0], eb[0], o.tail_sym, 0u);
     if (SM == kSmFlat3) {
         // Steps of eight codes, 24 bits, two per row.  Lanes in step ask for words 0 .. 4 at steps 0 .. 4 and then at all but
         // every fourth step, so of the two words a row's 48 bits lie in, the first has been asked for by every lane before the
@@ -1042,21 +1075,63 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
     }
 }
 
+template <class... W> struct Choice {};
+template <int FMT, Launch L> struct Builds;
+// FP8 E4M3: codes of at most eight bits, longer ones
+template <> struct Builds<ZC_FMT_FP8_E4M3, kFew> { typedef Choice<Build<1024, kLate, kWholePairs>, Build<1024, kLate, kWhole>> All; };
+template <> struct Builds<ZC_FMT_FP8_E5M2, kFew> { typedef Choice<Build<1024, kLate, kWhole>> All; };
+template <> struct Builds<ZC_FMT_FP8_E5M2, kMany> { typedef Choice<Build<512, kWait, kPairs13>> All; };
+template <> struct Builds<ZC_FMT_BF16, kFew> { typedef Choice<Build<1024, kLate, kWhole>> All; };
+// BF16 with two fields: the other field's codes of more than 12 bits, shorter ones
+template <> struct Builds<ZC_FMT_BF16, kFewTwo> { typedef Choice<Build<512, kLate, kPairs11, kWhole>, Build<2048, kLate, kPairs13, kSingles12>> All; };
+template <> struct Builds<ZC_FMT_BF16, kMany> { typedef Choice<Build<512, kWait, kPairs12, kSingles12>> All; };
+template <> struct Builds<ZC_FMT_BF16, kManyTwo> { typedef Choice<Build<512, kLate, kPairs12, kSingles12>> All; };
+template <> struct Builds<ZC_FMT_FP8_E4M3_BYTES, kFew> { typedef Choice<Build<1024, kLate, kWhole>> All; };
+template <> struct Builds<ZC_FMT_FP8_E4M3_BYTES, kFewTwo> { typedef Choice<Build<2048, kWait, kSingles12, kSingles12>> All; };
+template <> struct Builds<ZC_FMT_FP8_E4M3_BYTES, kMany> { typedef Choice<Build<512, kWait, kSingles12, kSingles12>> All; };
+
+// Refill periods and sign+mantissa fields that a launch's build I is for
+template <int FMT, Launch L> constexpr bool is_for(uint32_t I, int R, int SM)
+{
+    if (FMT == ZC_FMT_FP8_E5M2) return SM == kSmFlat3;
+    if (FMT == ZC_FMT_FP8_E4M3) return (SM == kSmFlat || SM == kSmRaw) && R == (I == 0 ? 4 : 2);
+    if (SM == kSmFlat3 || (L == kFew && SM == kSmTable)) return false;
+    if (FMT == ZC_FMT_FP8_E4M3_BYTES || L == kMany || L == kManyTwo) return true;
+    if (L == kFew) return true;
+    return I == 0 || SM == kSmTable;
+}
+template <int FMT, Launch L>
+__device__ __forceinline__ uint32_t choose_build(const PairCanon *C, uint32_t R, bool two)
+{
+    if (FMT == ZC_FMT_FP8_E4M3) return R == 2;
+    // deltas' exponents take 1.1 bits each: pairs by 11 bits leave the LDS to the other field's long codes
+    if (FMT == ZC_FMT_BF16 && L == kFewTwo) return two && uniform32(C[1].limit[12]) >= 65536u;
+    return 0;
+}
+
 }  // namespace
 
 // (longs: only where there are whole tables)
 struct PairShared { TensorDev d; PairCanon canon[2]; uint32_t wave_count[4][17], flat3; };
 struct FewShared : PairShared { LongCodes longs; };
-template <uint32_t RW> constexpr uint32_t kSharedBytes = RW == kShortRing || RW == kShortRingLate ? sizeof(PairShared) : sizeof(FewShared);
+template <Launch L> constexpr uint32_t kSharedBytes = L == kFew || L == kFewTwo ? sizeof(FewShared) : sizeof(PairShared);
 
 // One wavefront per chunk, `chunks` of them per workgroup (whose wavefronts build the tables together) around one copy of the tables;
-// RW: which tables and rings.
+// W: which tables and rings.
 // Bound by the instructions of a chunk's chain up to about a thousand chunks (one wavefront per SIMD), then by all instructions, and
 // from BF16's eight thousand on by HBM.  MI355X, GPU time, us, 200 chunks of 256 KiB, with tables by 12 - 14 bits and every period's word
 // waited for | now: FP8 182 | 134 (1,020 cycles per row of 1 KiB, 192 instructions), BF16 129 | 118, E5M2 296 | 232, byte symbols 232 | 128,
 // BF16 deltas 267 | 194; chunks of 16 KiB: E5M2 38 | 24, deltas 38 | 26, byte symbols 25 | 17.  A single chunk of BF16 weights
 // whose sign+mantissa codes differ in length is no faster (64 KiB: 66 | 69, 256 KiB: 196 | 197).
-template <int FMT, bool XOR, uint32_t RW>
+// Build I of a launch's and its number, for f
+template <int FMT, Launch L, uint32_t I, class F, class W, class... Rest>
+__device__ __forceinline__ void with_build(Choice<W, Rest...>, uint32_t which, const F &f)
+{
+    if constexpr (sizeof...(Rest) == 0) f(W(), std::integral_constant<uint32_t, I>());
+    else if (which == I) f(W(), std::integral_constant<uint32_t, I>());
+    else with_build<FMT, L, I + 1>(Choice<Rest...>(), which, f);
+}
+template <int FMT, bool XOR, Launch L>
 __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single, uint32_t first_slot,
                                                        uint32_t chunks, uint32_t lds_tables_and_rings)
 {
@@ -1064,7 +1139,7 @@ __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, c
     // all LDS in one piece, sized by the host, with field 0's table at its start (so that its entries need no base address);
     // then field 1's table where it has one, the rings, and what the workgroup shares besides
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    FewShared &sh = *reinterpret_cast<FewShared *>(lds + lds_tables_and_rings);              // (short rings: a PairShared)
+    FewShared &sh = *reinterpret_cast<FewShared *>(lds + lds_tables_and_rings);              // (kMany, kManyTwo: a PairShared)
     PairCanon *const canon = sh.canon;
     uint32_t(*const wave_count)[17] = sh.wave_count;
     WorkItem it;
@@ -1082,21 +1157,18 @@ __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, c
     }
     const bool two = FMT != ZC_FMT_FP8_E5M2 && kind1 == KIND_HUFF;
     // whole workgroup; the host never asks for these
-    if (uniform32(d.kind[0]) != KIND_HUFF || (p0 != 2 && p0 != 4 && p0 != 8) || (two && (p1 != p0 || RW == kLongRing))) return;
+    if (uniform32(d.kind[0]) != KIND_HUFF || (p0 != 2 && p0 != 4 && p0 != 8) || (two && (p1 != p0 || L == kFew))) return;
     if (FMT == ZC_FMT_FP8_E5M2 && (uniform32(d.mode[1]) != ZC_MODE_HUFF || !sh.flat3)) return;
     if (FMT == ZC_FMT_FP8_E4M3 && ((kind1 != KIND_FLAT && kind1 != KIND_RAW) || p0 == 8)) return;
     build_canon(canon[0], wave_count, d.comp + d.table_off[0], kAlphabet);
     if (two) build_canon(canon[1], wave_count, d.comp + d.table_off[1], kAlphabet);
-    // other tables: FP8 exponent codes of more than eight bits; two fields, sign+mantissa codes of at most 12
-    const bool other = FMT == ZC_FMT_FP8_E4M3 ? p0 == 2 : FMT == ZC_FMT_BF16 && two && RW == kLongRingTwo && uniform32(canon[1].limit[12]) >= 65536u;
-    constexpr uint32_t OW = FMT == ZC_FMT_FP8_E4M3 ? kLongRingSingles : FMT == ZC_FMT_BF16 && RW == kLongRingTwo ? kLongRingWeights : RW;
-    if (OW != RW && other) {
-        build_entries<FMT, 0, OW>(lds, canon[0], sh.longs);
-        if (two) build_entries<FMT, 1, OW>(lds + kTableBytes<FMT, 0, OW>, canon[1], sh.longs);
-    } else {
-        build_entries<FMT, 0, RW>(lds, canon[0], sh.longs);
-        if (two) build_entries<FMT, 1, RW>(lds + kTableBytes<FMT, 0, RW>, canon[1], sh.longs);
-    }
+    const uint32_t which = choose_build<FMT, L>(canon, p0, two);
+    typedef typename Builds<FMT, L>::All All;
+    with_build<FMT, L, 0>(All(), which, [&](auto build, auto) __attribute__((always_inline)) {
+        typedef decltype(build) W;
+        build_entries<FMT, 0, W>(lds, canon[0], sh.longs);
+        if (FMT != ZC_FMT_FP8_E5M2 && FMT != ZC_FMT_FP8_E4M3 && L != kFew && two) build_entries<FMT, 1, W>(lds + kTableBytes<0, W>, canon[1], sh.longs);
+    });
 
     const uint32_t lane = threadIdx.x & 63, wave = uniform32(threadIdx.x >> 6);
     if (wave >= chunks) return;
@@ -1137,13 +1209,12 @@ __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, c
     o.bs = make_rsrc(o.base, XOR ? o.nbytes : 0);
     o.konst1 = (uint32_t)splat(uniform32(d.konst[1]), F_::SB);
     const bool first = o.whole_rows > 0 || o.tail_sym > 0;       // does this lane own a symbol at step 0?
-    // W: the tables and rings there are
-    auto decode = [&](auto tables) __attribute__((always_inline)) {
-        constexpr uint32_t W = decltype(tables)::value;
+    with_build<FMT, L, 0>(All(), which, [&](auto build, auto number) __attribute__((always_inline)) {
+        typedef decltype(build) W;
         PairStream A, B;
-        const uint32_t rings = rings_at<FMT, W>(two) + wave * (two ? 2 : 1) * kRing<W> * 4;
+        const uint32_t rings = rings_at<W>(two) + wave * (two ? 2 : 1) * W::kRing * 4;               // (two: there is a second table)
         A.ring = rings; A.rs = make_rsrc(sp[0], sb[0]);
-        B.ring = rings + kRing<W> * 4; B.rs = o.r1;
+        B.ring = rings + W::kRing * 4; B.rs = o.r1;
         constexpr uint32_t KA = Entries<FMT, 0, W>::kBits, KB = Entries<FMT, 1, W>::kBits;
 #pragma unroll
         for (uint32_t i = 0; i < 4; i++) {
@@ -1152,39 +1223,39 @@ __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, c
         }
         pair_open<W>(A, lane, first);
         if (two) pair_open<W>(B, lane, first);
-#define ZC_ROWS(R, SM) case (R) * 8 + (SM): pair_rows<FMT, R, SM, XOR, W>(A, B, canon, o, lane); break
-        if constexpr (FMT == ZC_FMT_FP8_E5M2) {
-            switch (p0 * 8 + kSmFlat3) { ZC_ROWS(2, kSmFlat3); ZC_ROWS(4, kSmFlat3); ZC_ROWS(8, kSmFlat3); }
-        } else if constexpr (FMT == ZC_FMT_FP8_E4M3) {
-            constexpr int R = W == RW ? 4 : 2;
-            switch (R * 8 + kind1) { ZC_ROWS(R, kSmFlat); ZC_ROWS(R, kSmRaw); }
-        } else {
-            if constexpr (W == RW) switch (p0 * 8 + kind1) {
-                ZC_ROWS(2, kSmFlat); ZC_ROWS(4, kSmFlat); ZC_ROWS(8, kSmFlat);
-                ZC_ROWS(2, kSmRaw); ZC_ROWS(4, kSmRaw); ZC_ROWS(8, kSmRaw);
-                ZC_ROWS(2, kSmConst); ZC_ROWS(4, kSmConst); ZC_ROWS(8, kSmConst);
-            }
-            if constexpr (W != kLongRing) switch (p0 * 8 + kind1) { ZC_ROWS(2, kSmTable); ZC_ROWS(4, kSmTable); ZC_ROWS(8, kSmTable); }
+        const uint32_t sm = FMT == ZC_FMT_FP8_E5M2 ? (uint32_t)kSmFlat3 : kind1;
+#define ZC_ROWS(R, SM) case (R) * 8 + (SM): if constexpr (is_for<FMT, L>(decltype(number)::value, R, SM)) pair_rows<FMT, R, SM, XOR, W>(A, B, canon, o, lane); break
+        switch (p0 * 8 + sm) {
+            ZC_ROWS(2, kSmTable); ZC_ROWS(4, kSmTable); ZC_ROWS(8, kSmTable);
+            ZC_ROWS(2, kSmFlat); ZC_ROWS(4, kSmFlat); ZC_ROWS(8, kSmFlat);
+            ZC_ROWS(2, kSmRaw); ZC_ROWS(4, kSmRaw); ZC_ROWS(8, kSmRaw);
+            ZC_ROWS(2, kSmConst); ZC_ROWS(4, kSmConst); ZC_ROWS(8, kSmConst);
+            ZC_ROWS(2, kSmFlat3); ZC_ROWS(4, kSmFlat3); ZC_ROWS(8, kSmFlat3);
         }
 #undef ZC_ROWS
-    };
-    if constexpr (OW != RW) {
-        if (other) { decode(std::integral_constant<uint32_t, OW>()); return; }
-    }
-    decode(std::integral_constant<uint32_t, RW>());
+    });
 }
 
-template <int FMT, uint32_t RW>
+// LDS that a launch's tables and rings take: its largest build's
+template <class... W> constexpr uint32_t most_lds(Choice<W...>, bool two, uint32_t chunks)
+{
+    uint32_t most = 0;
+    for (const uint32_t n : {(two && W::template kTable<1> != kNone ? rings_at<W>(true) + chunks * 2 * W::kRing * 4 : rings_at<W>(false) + chunks * W::kRing * 4) ...}) most = n > most ? n : most;
+    return most;
+}
+template <int FMT, Launch L>
 static int launch_pairs_x(bool two, bool xor_delta, uint32_t chunks, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev &s, int use_single,
                           uint32_t first_slot, hipStream_t st)
 {
-    const uint32_t lds = rings_at<FMT, RW>(two) + chunks * (two ? 2u : 1u) * kRing<RW> * 4, all = lds + kSharedBytes<RW>;
-    static_assert(RW != kLongRingTwo || rings_at<ZC_FMT_BF16, kLongRingWeights>(true) + 8 * kRing<kLongRingWeights> * 4 <= rings_at<ZC_FMT_BF16, RW>(true), "the other tables and their rings fit");
-    // (with short rings eight wavefronts build the tables, four where a call has more workgroups than the compute units hold of eight:
-    // 1,500 BF16 tensors of one chunk of 100,000 bytes: 255 | 213 us)
-    const dim3 grid(n_work), block(RW == kLongRingSmall ? 256 : RW != kShortRing && RW != kShortRingLate ? 1024 : chunks > 4 || n_work <= 4 * 256 ? 512 : 256);
-    if (xor_delta) hipLaunchKernelGGL((k_decode_pairs<FMT, true, RW>), grid, block, all, st, d_descs, d_work, s, use_single, first_slot, chunks, lds);
-    else hipLaunchKernelGGL((k_decode_pairs<FMT, false, RW>), grid, block, all, st, d_descs, d_work, s, use_single, first_slot, chunks, lds);
+    typedef typename Builds<FMT, L>::All All;
+    const uint32_t lds = most_lds(All(), two, chunks), all = lds + kSharedBytes<L>;
+    static_assert(L == kMany || L == kManyTwo || most_lds(All(), L == kFewTwo, 4) + kSharedBytes<L> <= 160 * 1024, "a compute unit's LDS");
+    // (whole tables by 1,024 threads; small ones by eight wavefronts, four where a call has more workgroups than the compute units hold
+    // of eight: 1,500 BF16 tensors of one chunk of 100,000 bytes: 255 | 213 us)
+    const uint32_t few = FMT == ZC_FMT_FP8_E4M3_BYTES && L == kFewTwo ? 256 : 1024;
+    const dim3 grid(n_work), block(L == kFew || L == kFewTwo ? few : chunks > 4 || n_work <= 4 * 256 ? 512 : 256);
+    if (xor_delta) hipLaunchKernelGGL((k_decode_pairs<FMT, true, L>), grid, block, all, st, d_descs, d_work, s, use_single, first_slot, chunks, lds);
+    else hipLaunchKernelGGL((k_decode_pairs<FMT, false, L>), grid, block, all, st, d_descs, d_work, s, use_single, first_slot, chunks, lds);
     return (int)hipGetLastError();
 }
 

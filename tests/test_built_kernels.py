@@ -84,6 +84,6 @@ def test_registers_of_the_decoder_whose_workgroups_share_a_compute_unit(tmp_path
     for f in sorted(f for f in os.listdir(str(tmp_path)) if f.endswith("gfx950")):
         notes = subprocess.run([LLVM + "/llvm-readelf", "--notes", f], cwd=str(tmp_path), check=True, capture_output=True, text=True).stdout
         for kernel in notes.split("- .agpr_count")[1:]:
-            if re.search(r"\.name: +_ZN2zc14k_decode_pairsILi1ELb1ELj512E", kernel):
+            if re.search(r"\.name: +_ZN2zc14k_decode_pairsILi1ELb1ELNS_6LaunchE2E", kernel):
                 counts.append(int(re.search(r"\.vgpr_count: +(\d+)", kernel).group(1)))
     assert counts and max(counts) <= 72, counts
