@@ -55,16 +55,16 @@ template <int B> __device__ __forceinline__ uint32_t shr_byte(uint32_t v, uint32
 }
 
 // A field's table, by the stream bits a lookup goes by: whole ones by 16, which every code (kWholePairs: every pair of codes of at most
-// eight bits) fits, so that nothing is ever unresolved; pairs by 11 - 13 bits; singles by 12.
-enum Table { kNone = 32, kPairs11 = 11, kPairs12 = 12, kPairs13 = 13, kSingles12 = 32 + 12, kWhole = 64 + 16, kWholePairs = 96 + 16 };
+// eight bits) fits, so that nothing is ever unresolved; pairs by 11 - 15 bits; singles by 12.
+enum Table { kNone = 32, kPairs11 = 11, kPairs12 = 12, kPairs13 = 13, kPairs15 = 15, kSingles12 = 32 + 12, kWhole = 64 + 16, kWholePairs = 96 + 16 };
 constexpr bool in_pairs(Table t) { return t < 32 || t == kWholePairs; }
 constexpr bool is_whole(Table t) { return t == kWhole || t == kWholePairs; }
 constexpr uint32_t index_bits(Table t) { return t % 32; }
 constexpr uint32_t entry_bytes(Table t) { return t < 32 ? 4 : 2; }
 
-// When the words that a period's lanes ask for at its end come in: before the next one begins; or at
+// When the words that a period's lanes ask for at its end come in: before the next one begins; behind the next one's first entry; or at
 // the next one's end (where a period is one lookup: another one later), while that goes well, then behind the first entry.  See late_run.
-enum Loop { kWait, kLate };
+enum Loop { kWait, kInside, kLate };
 
 // How a chunk is decoded: words of a stream's ring, tables of the two fields
 template <uint32_t RING, Loop LOOP, Table T0, Table T1 = kNone> struct Build {
@@ -271,6 +271,26 @@ __device__ __forceinline__ void build_whole(uint16_t *table, const PairCanon &C,
     __syncthreads();
 }
 
+// Pairs by 15 bits of codes of at most eight, by 1,024 threads: only two of eight bits each do not fit
+template <int FMT, int F, class W>
+__device__ __forceinline__ void build_pairs(uint32_t *table, const PairCanon &C, const uint32_t (&limit)[16], LongCodes &longs)
+{
+    typedef Entries<FMT, F, W> P;
+    const uint32_t tid = threadIdx.x;
+    if (tid < 256) {
+        const uint32_t w = __brev(tid) >> 16, len = code_length<15>(w, limit);
+        longs.at[tid] = (uint16_t)(code_symbol(C, w, len) | (len < 9 ? len : 8u) << 8);
+    }
+    __syncthreads();
+    const uint32_t a = longs.at[tid & 255u], l1 = a >> 8;
+#pragma unroll 8
+    for (uint32_t j = 0; j < 32; j++) {
+        const uint32_t i = tid + j * 1024, b = longs.at[(i >> l1) & 255u], l2 = b >> 8;
+        table[i] = P::put(a & 255u) | l1 << P::kLen1 | (l1 + l2 < 16 ? P::put(b & 255u) << P::kSecond | (l1 + l2) << P::kLen : kUnresolved);
+    }
+    __syncthreads();
+}
+
 template <int FMT, int F, class W>
 __device__ __forceinline__ void build_entries(char *table, const PairCanon &C, LongCodes &longs)
 {
@@ -283,6 +303,7 @@ __device__ __forceinline__ void build_entries(char *table, const PairCanon &C, L
     uint32_t *const pairs = reinterpret_cast<uint32_t *>(table);
     uint16_t *const singles = reinterpret_cast<uint16_t *>(table);
     if constexpr (P::kWhole) { build_whole<FMT, F, W>(singles, C, limit, longs); return; }
+    if constexpr (P::kTable == kPairs15) { build_pairs<FMT, F, W>(pairs, C, limit, longs); return; }
     // A thread's entries have the low eight bits of their index in common, so a code of at most eight bits can be looked up once for
     // all of them: 1,000 E5M2 tensors of 2 KB 24.5 -> 21.5 us.  The other formats have longer codes in some lane of nearly every
     // wavefront, which would make it 3 - 5 % slower for small chunks.
@@ -629,7 +650,7 @@ __device__ __forceinline__ void pair_run(PairStream &A, PairStream &B, const Pai
 // has gone wrong only in lanes that wait for a word and are already past the next 32 bits (2.6 % of the periods of FP8 E4M3 weights
 // and byte symbols, 0.7 % of deltas' sign+mantissa fields, hardly any where a period is one lookup), and is done once more.  Where
 // codes are so long that two periods often take more than 32 bits (wide) that would be nearly every period.  There the word comes in
-// behind the period's first entry (INSIDE), which costs six more instructions and goes wrong only where one code is that long.
+// behind the period's first entry (kInside), which costs six more instructions and goes wrong only where one code is that long.
 // What is not the chain stands where LDS reads are waited for anyway, masks are read late, and there is one branch per period.
 // x: the window, scaled for a lookup; e: the entry found there; c: bits used of (hi, lo) once what is owed has come in; need, w: lanes
 // that asked at the end of the last period, and the words; owed, v: at the end of the one before it (kTwice only).
@@ -1079,9 +1100,10 @@ template <class... W> struct Choice {};
 template <int FMT, Launch L> struct Builds;
 // FP8 E4M3: codes of at most eight bits, longer ones
 template <> struct Builds<ZC_FMT_FP8_E4M3, kFew> { typedef Choice<Build<1024, kLate, kWholePairs>, Build<1024, kLate, kWhole>> All; };
-template <> struct Builds<ZC_FMT_FP8_E5M2, kFew> { typedef Choice<Build<1024, kLate, kWhole>> All; };
+// E5M2, BF16: codes of more than eight bits, all others
+template <> struct Builds<ZC_FMT_FP8_E5M2, kFew> { typedef Choice<Build<1024, kLate, kWhole>, Build<1024, kInside, kPairs15>> All; };
 template <> struct Builds<ZC_FMT_FP8_E5M2, kMany> { typedef Choice<Build<512, kWait, kPairs13>> All; };
-template <> struct Builds<ZC_FMT_BF16, kFew> { typedef Choice<Build<1024, kLate, kWhole>> All; };
+template <> struct Builds<ZC_FMT_BF16, kFew> { typedef Choice<Build<1024, kLate, kWhole>, Build<1024, kInside, kPairs15>> All; };
 // BF16 with two fields: the other field's codes of more than 12 bits, shorter ones
 template <> struct Builds<ZC_FMT_BF16, kFewTwo> { typedef Choice<Build<512, kLate, kPairs11, kWhole>, Build<2048, kLate, kPairs13, kSingles12>> All; };
 template <> struct Builds<ZC_FMT_BF16, kMany> { typedef Choice<Build<512, kWait, kPairs12, kSingles12>> All; };
@@ -1093,17 +1115,18 @@ template <> struct Builds<ZC_FMT_FP8_E4M3_BYTES, kMany> { typedef Choice<Build<5
 // Refill periods and sign+mantissa fields that a launch's build I is for
 template <int FMT, Launch L> constexpr bool is_for(uint32_t I, int R, int SM)
 {
-    if (FMT == ZC_FMT_FP8_E5M2) return SM == kSmFlat3;
+    if (FMT == ZC_FMT_FP8_E5M2) return SM == kSmFlat3 && (L == kMany || (I == 0) == (R == 2));
     if (FMT == ZC_FMT_FP8_E4M3) return (SM == kSmFlat || SM == kSmRaw) && R == (I == 0 ? 4 : 2);
     if (SM == kSmFlat3 || (L == kFew && SM == kSmTable)) return false;
     if (FMT == ZC_FMT_FP8_E4M3_BYTES || L == kMany || L == kManyTwo) return true;
-    if (L == kFew) return true;
+    if (L == kFew) return (I == 0) == (R == 2);
     return I == 0 || SM == kSmTable;
 }
 template <int FMT, Launch L>
 __device__ __forceinline__ uint32_t choose_build(const PairCanon *C, uint32_t R, bool two)
 {
     if (FMT == ZC_FMT_FP8_E4M3) return R == 2;
+    if (FMT == ZC_FMT_FP8_E5M2 || (FMT == ZC_FMT_BF16 && L == kFew)) return L == kFew && R != 2;
     // deltas' exponents take 1.1 bits each: pairs by 11 bits leave the LDS to the other field's long codes
     if (FMT == ZC_FMT_BF16 && L == kFewTwo) return two && uniform32(C[1].limit[12]) >= 65536u;
     return 0;

@@ -57,6 +57,13 @@ def test_wide_codes(fmt, narrow, wide, limit):
     assert b < limit * a
 
 
+def test_codes_of_few_symbols():
+    """BF16 exponents with codes of at most eight bits, in pairs: 45 us where longer ones take 63 (64 when one at a time)."""
+    a, b = (decode_us([spread(BF16, 8 * 128 * KIB, w)], BF16, 128 * KIB) for w in (1.0, 0.3))
+    print("us", a, b, flush=True)
+    assert b < 0.9 * a
+
+
 def test_byte_symbol_tensors_beyond_a_compute_unit_each():
     """11 us for 256 and for 300 (19)."""
     x = wl.fp8_weight(4096, DEV, 1)
