@@ -3,12 +3,6 @@
 
 namespace zc {
 
-// zc_decode_pairs_bf16.hip, zc_decode_pairs_bytes.hip
-int launch_pairs_bf16(bool two, bool xor_delta, uint32_t chunks, bool long_rings, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
-                      const TensorDev &s, int use_single, uint32_t first_slot, hipStream_t st);
-int launch_pairs_bytes(bool two, bool xor_delta, uint32_t chunks, bool long_rings, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
-                       const TensorDev &s, int use_single, uint32_t first_slot, hipStream_t st);
-
 // two: some tensor's sign+mantissa field is table decoded too; chunks: per work item, 4 with long rings, else 1, 2, 4 or 8; first_slot:
 // where a single tensor's first work item starts
 int launch_decode_pairs(uint32_t fmt, bool two, bool xor_delta, uint32_t chunks, bool long_rings, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,

@@ -8,9 +8,9 @@
 // LDS read, 16 where a scalar instruction reads a mask just written by a vector one, 30 for a branch taken: what a period takes is
 // its instructions, with the waits beside them.  So
 //   - calls of one round of workgroups have tables by 16 bits, in 128 of a compute unit's 160 KiB of LDS: every code fits, no
-//     lookup has to be checked, and FP8 exponents (codes of at most 8 bits) come in pairs.  In the others the tables are small:
-//     exponents in pairs by 11 - 13 bits, which halves the lookups, other symbols by 12 bits, and what does not resolve sends the
-//     wavefront through the period once more.
+//     lookup has to be checked, and FP8 E4M3 exponents (codes of at most 8 bits) come in pairs; or pairs by 15 bits, for other exponents with
+//     such codes.  In the others the tables are small: exponents in pairs by 12 or 13 bits, which halves the lookups, other symbols by 12
+//     bits, and what does not resolve sends the wavefront through the period once more.
 //   - in calls of one round a period does not wait for the words asked for before it (late_run), and a row is put together and stored
 //     while the next one's entries are looked up.
 //   - two table-decoded fields go through the chain side by side.
@@ -30,6 +30,12 @@ namespace zc {
 // workgroups have a compute unit to themselves, with tables of up to 136 KiB; all others; of those, two fields and up to 256 workgroups (a
 // kernel of its own: it takes 20 registers more).
 enum Launch { kFew, kFewTwo, kMany, kManyTwo };
+
+// builds by format: zc_decode_pairs_bf16.hip, zc_decode_pairs_bytes.hip
+int launch_pairs_bf16(bool two, bool xor_delta, uint32_t chunks, bool long_rings, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
+                      const TensorDev &s, int use_single, uint32_t first_slot, hipStream_t st);
+int launch_pairs_bytes(bool two, bool xor_delta, uint32_t chunks, bool long_rings, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
+                       const TensorDev &s, int use_single, uint32_t first_slot, hipStream_t st);
 
 namespace {
 
@@ -55,10 +61,11 @@ template <int B> __device__ __forceinline__ uint32_t shr_byte(uint32_t v, uint32
 }
 
 // A field's table, by the stream bits a lookup goes by: whole ones by 16, which every code (kWholePairs: every pair of codes of at most
-// eight bits) fits, so that nothing is ever unresolved; pairs by 11 - 15 bits; singles by 12.
-enum Table { kNone = 32, kPairs11 = 11, kPairs12 = 12, kPairs13 = 13, kPairs15 = 15, kSingles12 = 32 + 12, kWhole = 64 + 16, kWholePairs = 96 + 16 };
+// eight bits) fits, so that nothing is ever unresolved; pairs by 11 - 15 bits; singles by 12 (kShort12: of codes no longer than that).
+enum Table { kNone = 32, kPairs11 = 11, kPairs12 = 12, kPairs13 = 13, kPairs15 = 15, kSingles12 = 32 + 12, kWhole = 64 + 16, kWholePairs = 96 + 16, kShort12 = 128 + 12 };
 constexpr bool in_pairs(Table t) { return t < 32 || t == kWholePairs; }
 constexpr bool is_whole(Table t) { return t == kWhole || t == kWholePairs; }
+constexpr bool is_sure(Table t) { return is_whole(t) || t == kShort12; }
 constexpr uint32_t index_bits(Table t) { return t % 32; }
 constexpr uint32_t entry_bytes(Table t) { return t < 32 ? 4 : 2; }
 
@@ -85,7 +92,7 @@ template <uint32_t RING, Loop LOOP, Table T0, Table T1 = kNone> struct Build {
 //
 // Chance that one of 64 lanes finds a pair unresolved, for weights of the kinds the codec is meant for: BF16 exponents 16 % by 12
 // bits, E5M2 (a wide spread of exponents) 22 % by 13; singles by 12 bits 19 % (deltas' sign+mantissa) to 42 % (byte symbols).  Each
-// costs its wavefront 600 cycles, three periods' worth; hence the whole tables where there is the LDS for them.
+// sends its wavefront through the period again; hence the whole tables where there is the LDS for them.
 constexpr uint32_t kUnresolved = 0x80000000u;
 template <int FMT, int F, Table T> struct Layout;
 template <Table T> struct Layout<ZC_FMT_BF16, 0, T> {            // pairs
@@ -162,7 +169,7 @@ template <> struct Layout<ZC_FMT_BF16, 0, kWhole> : LengthLow {
 };
 template <int FMT, int F, class W> struct Entries : Layout<FMT, F, W::template kTable<F>> {
     static constexpr Table kTable = W::template kTable<F>;
-    static constexpr bool kPair = in_pairs(kTable), kWhole = is_whole(kTable);
+    static constexpr bool kPair = in_pairs(kTable), kWhole = is_whole(kTable), kSure = is_sure(kTable);
     static constexpr uint32_t kBits = index_bits(kTable), kBytes = entry_bytes(kTable);
 };
 __device__ __forceinline__ uint32_t first_len(uint32_t e, int shift) { return (e >> shift) & 15u; }
@@ -535,7 +542,7 @@ __device__ __forceinline__ uint32_t look_up(uint32_t c, uint32_t x, uint32_t e[N
     return add_up<FMT, F, N, W>(c, e);
 }
 template <int FMT, int F, class W>
-__device__ __forceinline__ bool unresolved(uint32_t e) { return !Entries<FMT, F, W>::kWhole && (Entries<FMT, F, W>::kPair ? (int)e < 0 : e == 0); }
+__device__ __forceinline__ bool unresolved(uint32_t e) { return !Entries<FMT, F, W>::kSure && (Entries<FMT, F, W>::kPair ? (int)e < 0 : e == 0); }
 
 // The same where an entry does not resolve in some lane; e[0]: as look_up found it (in every lane the right one); FOUND: and the others,
 // which are right in the lanes where those before them resolved
@@ -767,7 +774,7 @@ __device__ __forceinline__ uint64_t late_period(Late &next, const Late &L, const
     if constexpr (INSIDE) {
         // (an entry that did not resolve because its bits were not there: the ones after it may.  All in one sign.)
         int sign = 64 - (int)(Entries<FMT, F, W>::add(L.c + (Entries<FMT, F, W>::kWhole && !Entries<FMT, F, W>::kLow ? 1u : 0u), e[0]) & 127u);
-        if (!Entries<FMT, F, W>::kWhole) sign |= Entries<FMT, F, W>::kPair ? (int)(e[0] | e[N - 1]) : ((int)e[0] - 1) | ((int)e[N - 1] - 1);
+        if (!Entries<FMT, F, W>::kSure) sign |= Entries<FMT, F, W>::kPair ? (int)(e[0] | e[N - 1]) : ((int)e[0] - 1) | ((int)e[N - 1] - 1);
         const uint64_t amiss = __ballot(sign < 0);
         late_go_on<FMT, F, N, W, true>(next, L, S, c, c);
         return amiss;
@@ -1104,8 +1111,11 @@ template <> struct Builds<ZC_FMT_FP8_E4M3, kFew> { typedef Choice<Build<1024, kL
 template <> struct Builds<ZC_FMT_FP8_E5M2, kFew> { typedef Choice<Build<1024, kLate, kWhole>, Build<1024, kInside, kPairs15>> All; };
 template <> struct Builds<ZC_FMT_FP8_E5M2, kMany> { typedef Choice<Build<512, kWait, kPairs13>> All; };
 template <> struct Builds<ZC_FMT_BF16, kFew> { typedef Choice<Build<1024, kLate, kWhole>, Build<1024, kInside, kPairs15>> All; };
-// BF16 with two fields: the other field's codes of more than 12 bits, shorter ones
-template <> struct Builds<ZC_FMT_BF16, kFewTwo> { typedef Choice<Build<512, kLate, kPairs11, kWhole>, Build<2048, kLate, kPairs13, kSingles12>> All; };
+// BF16 with two fields: see choose_build; the last two are for a tensor with one among others with two
+template <> struct Builds<ZC_FMT_BF16, kFewTwo> {
+    typedef Choice<Build<512, kLate, kPairs11, kWhole>, Build<512, kLate, kWhole, kShort12>, Build<512, kLate, kWhole, kSingles12>, Build<512, kInside, kPairs15, kShort12>,
+                   Build<1024, kLate, kWhole>, Build<1024, kInside, kPairs15>> All;
+};
 template <> struct Builds<ZC_FMT_BF16, kMany> { typedef Choice<Build<512, kWait, kPairs12, kSingles12>> All; };
 template <> struct Builds<ZC_FMT_BF16, kManyTwo> { typedef Choice<Build<512, kLate, kPairs12, kSingles12>> All; };
 template <> struct Builds<ZC_FMT_FP8_E4M3_BYTES, kFew> { typedef Choice<Build<1024, kLate, kWhole>> All; };
@@ -1120,15 +1130,25 @@ template <int FMT, Launch L> constexpr bool is_for(uint32_t I, int R, int SM)
     if (SM == kSmFlat3 || (L == kFew && SM == kSmTable)) return false;
     if (FMT == ZC_FMT_FP8_E4M3_BYTES || L == kMany || L == kManyTwo) return true;
     if (L == kFew) return (I == 0) == (R == 2);
-    return I == 0 || SM == kSmTable;
+    return (I < 4) == (SM == kSmTable) && (I == 3 || I == 5) == (R != 2);
 }
 template <int FMT, Launch L>
 __device__ __forceinline__ uint32_t choose_build(const PairCanon *C, uint32_t R, bool two)
 {
     if (FMT == ZC_FMT_FP8_E4M3) return R == 2;
     if (FMT == ZC_FMT_FP8_E5M2 || (FMT == ZC_FMT_BF16 && L == kFew)) return L == kFew && R != 2;
-    // deltas' exponents take 1.1 bits each: pairs by 11 bits leave the LDS to the other field's long codes
-    if (FMT == ZC_FMT_BF16 && L == kFewTwo) return two && uniform32(C[1].limit[12]) >= 65536u;
+    if (FMT == ZC_FMT_BF16 && L == kFewTwo) {
+        if (!two) return R != 2 ? 5 : 4;
+        if (R != 2) return 3;
+        // The exponents have the whole table, but where the other field has codes of more than 12 bits and they have one of a single bit
+        // (deltas): then they take so few bits that pairs by 11 are unresolved in 1.5 % of the periods (weights: 39 %), and leave the LDS to
+        // the other field.  Eight chunks of 128 KiB, exponents in pairs by 11 or 13 bits | the whole table, us: weights, whose sign+mantissa
+        // codes have nine bits, 64 KiB 70 | 58, 200 tensors of 256 KiB 205 | 201; exponents spread with scale 8, signs+mantissas with scale 60:
+        // 264 | 107, with scale 2, codes of 16 bits: 268 | 114.  A tensor with one such field beside those: pairs by 11 bits | as on its own:
+        // 8 MiB 173 | 117.
+        if (uniform32(C[1].limit[12]) >= 65536u) return 1;
+        return uniform32(C[0].limit[1]) != 0 ? 0 : 2;
+    }
     return 0;
 }
 
@@ -1139,13 +1159,6 @@ struct PairShared { TensorDev d; PairCanon canon[2]; uint32_t wave_count[4][17],
 struct FewShared : PairShared { LongCodes longs; };
 template <Launch L> constexpr uint32_t kSharedBytes = L == kFew || L == kFewTwo ? sizeof(FewShared) : sizeof(PairShared);
 
-// One wavefront per chunk, `chunks` of them per workgroup (whose wavefronts build the tables together) around one copy of the tables;
-// W: which tables and rings.
-// Bound by the instructions of a chunk's chain up to about a thousand chunks (one wavefront per SIMD), then by all instructions, and
-// from BF16's eight thousand on by HBM.  MI355X, GPU time, us, 200 chunks of 256 KiB, with tables by 12 - 14 bits and every period's word
-// waited for | now: FP8 182 | 134 (1,020 cycles per row of 1 KiB, 192 instructions), BF16 129 | 118, E5M2 296 | 232, byte symbols 232 | 128,
-// BF16 deltas 267 | 194; chunks of 16 KiB: E5M2 38 | 24, deltas 38 | 26, byte symbols 25 | 17.  A single chunk of BF16 weights
-// whose sign+mantissa codes differ in length is no faster (64 KiB: 66 | 69, 256 KiB: 196 | 197).
 // Build I of a launch's and its number, for f
 template <int FMT, Launch L, uint32_t I, class F, class W, class... Rest>
 __device__ __forceinline__ void with_build(Choice<W, Rest...>, uint32_t which, const F &f)
@@ -1154,6 +1167,12 @@ __device__ __forceinline__ void with_build(Choice<W, Rest...>, uint32_t which, c
     else if (which == I) f(W(), std::integral_constant<uint32_t, I>());
     else with_build<FMT, L, I + 1>(Choice<Rest...>(), which, f);
 }
+// One wavefront per chunk, `chunks` of them per workgroup (whose wavefronts build the tables together) around one copy of the tables.
+// Bound by the instructions of a chunk's chain up to about a thousand chunks (one wavefront per SIMD), then by all instructions, and
+// from BF16's eight thousand on by HBM.  MI355X, GPU time, us, 200 chunks of 256 KiB, with tables by 12 - 14 bits and every period's word
+// waited for | now: FP8 182 | 134 (201 instructions per row of 1 KiB, the table's construction included), BF16 129 | 118, E5M2 296 | 232 (307
+// instructions), byte symbols 232 | 128, BF16 deltas 267 | 194; chunks of 16 KiB: E5M2 38 | 24, deltas 38 | 26, byte symbols 25 | 17; a single
+// chunk of BF16 weights whose sign+mantissa codes differ in length: 64 KiB: 66 | 58, 256 KiB: 197 | 192.
 template <int FMT, bool XOR, Launch L>
 __global__ __launch_bounds__(1024) void k_decode_pairs(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single, uint32_t first_slot,
                                                        uint32_t chunks, uint32_t lds_tables_and_rings)

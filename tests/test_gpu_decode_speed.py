@@ -49,6 +49,7 @@ def decode_us(xs, fmt, chunk, policy=zc.POLICY_HUFF_ALL):
     (E5M2, (1.0, None), (8.0, None), 1.2),                       # 120 and 84 us (206)
     (BF16, (1.0, None), (40.0, None), 1.25),                     # 63 and 68 us (92)
     (BF16, (1.0, 8.0), (1.0, 60.0), 1.1),                        # 119 and 104 us (150)
+    (BF16, (1.0, 8.0), (16.0, 2.0), 1.4),                        # 119 and 117 us (305)
 ])
 def test_wide_codes(fmt, narrow, wide, limit):
     nbytes = 8 * 128 * KIB
@@ -62,6 +63,14 @@ def test_codes_of_few_symbols():
     a, b = (decode_us([spread(BF16, 8 * 128 * KIB, w)], BF16, 128 * KIB) for w in (1.0, 0.3))
     print("us", a, b, flush=True)
     assert b < 0.9 * a
+
+
+def test_a_small_tensor_with_two_table_decoded_fields_beside_a_large_one_with_one():
+    """117 us either way (173 for the two)."""
+    large, small = spread(BF16, 8 << 20, 1.0), spread(BF16, 8192, 1.0, 60.0)
+    a, b = decode_us([large], BF16, 256 * KIB), decode_us([large, small], BF16, 256 * KIB)
+    print("us", a, b, flush=True)
+    assert b < 1.2 * a
 
 
 def test_byte_symbol_tensors_beyond_a_compute_unit_each():
