@@ -698,9 +698,9 @@ private:
         st = encode_and_read_sizes(landing, true);
         // what the device decided, for the caller's zc_info
         const uint8_t *got = landing.ptr + (uint64_t)T * sizeof(ScanOut);
+        FieldCode fc[3] = {};                                    // (of 8 KiB: cleared once; a field's bytes beyond its symbols stay clear)
         for (uint32_t t = 0; t < T; t++) {
             const uint8_t *blob = got + (uint64_t)t * kBlobBytes;
-            FieldCode fc[3] = {};
             for (uint32_t f = 0; f < g.nf; f++) {
                 fc[f].mode = blob[32 + 4 * f]; fc[f].lmax = blob[34 + 4 * f]; fc[f].konst = blob[35 + 4 * f];
                 std::memcpy(fc[f].len, blob + descs[t].table_off[f], (size_t)1 << sym_bits(g.fmt, (int)f));
