@@ -70,8 +70,9 @@ constexpr uint32_t index_bits(Table t) { return t % 32; }
 constexpr uint32_t entry_bytes(Table t) { return t < 32 ? 4 : 2; }
 
 // When the words that a period's lanes ask for at its end come in: before the next one begins; behind the next one's first entry; or at
-// the next one's end (where a period is one lookup: another one later), while that goes well, then behind the first entry.  See late_run.
-enum Loop { kWait, kInside, kLate };
+// the next one's end (where a period is one lookup: another one later), while that goes well, then behind the first entry; or always
+// there (codes too short to be late: a second loop in the kernel costs such calls 1 - 2 %).  See late_run.
+enum Loop { kWait, kInside, kLate, kSteady };
 
 // How a chunk is decoded: words of a stream's ring, tables of the two fields
 template <uint32_t RING, Loop LOOP, Table T0, Table T1 = kNone> struct Build {
@@ -858,7 +859,7 @@ __device__ __forceinline__ void late_run(Late &LA, Late &LB, PairStream &A, Pair
         const uint64_t wrong_b = TWO ? late_period<FMT, 1, NB, W, inside_b>(nextB, LB, B, b, cb) : 0u;
         if (__builtin_expect((wrong_a | wrong_b) != 0, 0)) {
             const bool late_a = !kTwice<FMT, 0, NA, W> && (nextA.asked & LA.asked) != 0, late_b = TWO && !kTwice<FMT, 1, NB, W> && (nextB.asked & LB.asked) != 0;
-            if (!INSIDE && (late_a || late_b)) {
+            if (!INSIDE && W::kLoop == kLate && (late_a || late_b)) {
                 late.room -= LateRoom::kAgain;
                 if (late.room < 0) late.end = 0;
             }
@@ -1048,7 +1049,10 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
             block_row(std::integral_constant<uint32_t, 3>(), inside);
             row += 4;
         };
-        if constexpr (W::kLoop == kLate) {
+        if constexpr (W::kLoop == kSteady) {
+#pragma unroll 1
+            while (row + 4 <= fast_end) block(std::false_type());
+        } else if constexpr (W::kLoop == kLate) {
             // as long as one period in twelve goes wrong at most, but for a few at first
 #pragma unroll 1
             while (row + 4 <= late.end) {
@@ -1056,8 +1060,10 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
                 late.room = late.room + 4 * Fmt<FMT>::G / R < 8 * LateRoom::kAgain ? late.room + 4 * Fmt<FMT>::G / R : 8 * LateRoom::kAgain;
             }
         }
+        if constexpr (W::kLoop != kSteady) {
 #pragma unroll 1
-        while (row + 4 <= fast_end) block(std::true_type());
+            while (row + 4 <= fast_end) block(std::true_type());
+        }
         if (kAhead) {
             put_row(row - 1, SM == kSmFlat3 ? f[2].m : f[3].m, ea[1], eb[1], f[3].base);
             late_close<kTwice<FMT, 0, NA, W>>(LA, A);
@@ -1106,9 +1112,9 @@ __device__ __forceinline__ void pair_rows(PairStream &A, PairStream &B, const Pa
 template <class... W> struct Choice {};
 template <int FMT, Launch L> struct Builds;
 // FP8 E4M3: codes of at most eight bits, longer ones
-template <> struct Builds<ZC_FMT_FP8_E4M3, kFew> { typedef Choice<Build<1024, kLate, kWholePairs>, Build<1024, kLate, kWhole>> All; };
-// E5M2, BF16: codes of more than eight bits, all others
-template <> struct Builds<ZC_FMT_FP8_E5M2, kFew> { typedef Choice<Build<1024, kLate, kWhole>, Build<1024, kInside, kPairs15>> All; };
+template <> struct Builds<ZC_FMT_FP8_E4M3, kFew> { typedef Choice<Build<1024, kLate, kWholePairs>, Build<1024, kSteady, kWhole>> All; };
+// E5M2, BF16: codes of more than eight bits, all others.  (Two of E5M2's 32 symbols take ten bits at most in the mean, two of FP8's sixteen eight.)
+template <> struct Builds<ZC_FMT_FP8_E5M2, kFew> { typedef Choice<Build<1024, kSteady, kWhole>, Build<1024, kInside, kPairs15>> All; };
 template <> struct Builds<ZC_FMT_FP8_E5M2, kMany> { typedef Choice<Build<512, kWait, kPairs13>> All; };
 template <> struct Builds<ZC_FMT_BF16, kFew> { typedef Choice<Build<1024, kLate, kWhole>, Build<1024, kInside, kPairs15>> All; };
 // BF16 with two fields: see choose_build; the last two are for a tensor with one among others with two
