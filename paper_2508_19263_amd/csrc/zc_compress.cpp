@@ -179,7 +179,7 @@ zc_status CompressQueue::queue_sizes_and_scan() const
         LAUNCH_TRY(launch_sizes(g.fmt, sh.whole_mode, sh.lanes8 ? 0x6 : 0x2, d_descs(), d_list(w.whole_work), n_whole, d_enc(), d_units(), stream));
     LAUNCH_TRY(launch_sizes(g.fmt, 0, 0x6, d_descs(), d_list(w.other_work), n_other, d_enc(), d_units(), stream));
     // what the whole-chunk kernels leave over: with 64 lanes and chunks of whole rows only a tensor's short last chunk, and
-    // every chunk of a call of few, sixteen wavefronts each; otherwise every chunk, walked by the generic size pass
+    // every chunk of a call of few, sixteen or eight wavefronts each; otherwise every chunk, walked by the generic size pass
     if (sh.fp4_tails) LAUNCH_TRY(launch_fp4_tails(g.fmt, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
     else if (sh.split_rest) LAUNCH_TRY(launch_sizes_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
     else LAUNCH_TRY(launch_sizes(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));

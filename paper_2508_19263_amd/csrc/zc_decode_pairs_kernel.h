@@ -655,10 +655,10 @@ __device__ __forceinline__ void pair_run(PairStream &A, PairStream &B, const Pai
 // before the last one come in during it, else those asked for at the end of the last one.  So the chain of a period is its lookups
 // alone, and the refill (the count of the lanes that take a word, an address, an LDS read) runs beside them.  Zeros come into a
 // window that runs out of bits; an entry found there is still the right one as long as its codes' bits were there, so a period
-// has gone wrong only in lanes that wait for a word and are already past the next 32 bits (2.6 % of the periods of FP8 E4M3 weights
-// and byte symbols, 0.7 % of deltas' sign+mantissa fields, hardly any where a period is one lookup), and is done once more.  Where
+// has gone wrong only in lanes that wait for a word and are already past the next 32 bits (3.6 % of the periods of FP8 E4M3 weights,
+// 2.1 % of byte symbols, 1.0 % of deltas, hardly any where a period is one lookup), and is done once more.  Where
 // codes are so long that two periods often take more than 32 bits (wide) that would be nearly every period.  There the word comes in
-// behind the period's first entry (kInside), which costs six more instructions and goes wrong only where one code is that long.
+// behind the period's first entry (kInside), which costs two to three more instructions and goes wrong only where one code is that long.
 // What is not the chain stands where LDS reads are waited for anyway, masks are read late, and there is one branch per period.
 // x: the window, scaled for a lookup; e: the entry found there; c: bits used of (hi, lo) once what is owed has come in; need, w: lanes
 // that asked at the end of the last period, and the words; owed, v: at the end of the one before it (kTwice only).

@@ -125,7 +125,8 @@ struct CallChunks {
 };
 constexpr uint64_t kComputeUnits = 256;
 // Least bytes of an FP8 E4M3 tensor's short last chunk that go there; it is where a table of 64 KiB paid, against k_decode_s64's build for
-// such chunks (16 tensors of 12,000 bytes: 27 | 25 us, 16,000: 30 | 30, 24,000: 35 | 41)
+// such chunks.  (With the table of now, 16 tensors of 1,500 bytes: 11.4 | 10.6 us, 4,000: 12.1 | 12.8, 12,000: 16 | 24, 24,000: 22 | 41.  The line has only
+// been kept, as the one at 96 KiB below.)
 constexpr uint64_t kPairsTailBytes = 16 * 1024;
 
 // How those kernels take a call: chunks per workgroup, and whether with the long rings (four chunks then); chunks 0: another kernel is
@@ -135,10 +136,10 @@ constexpr uint64_t kPairsTailBytes = 16 * 1024;
 //    tables from 257 on, so that two fit a compute unit: 300 tensors of 4 KiB 19 with whole ones, 11 with small, of 256 KiB 243 | 230; but from
 //    1,025 chunks on only the largest gain, short rings | these: 1,500 chunks of 16 KiB 29 | 27, 64 KiB 72 | 70, 256 KiB 255 | 278.)
 //  - FP8 E4M3 has a table of 128 KiB and comes here with long rings only; beyond a round, k_decode_fp8, bound by its traffic, is ahead.
-//    The line at 96 KiB is where a table of 64 KiB with checked lookups paid (16 of 64 KiB: 70 | 70; 96 KiB: 94 | 98), and sooner where it
-//    saves the second launch that a short last chunk needs beside k_decode_fp8 (64 chunks of 32 KiB and one of 64 bytes: 41 | 50, of 16
-//    KiB: 41 | 72).  The table of now pays from 2 KiB on (16 chunks of 64 KiB 42 | 70, of 4 KiB 13 | 17): the line has only been kept, with
-//    the tests that hold calls on either side of it to their kernels.
+//    The line at 96 KiB is where a table of 64 KiB with checked lookups paid, and sooner where it saves the second launch that a short last
+//    chunk needs beside k_decode_fp8 (64 chunks of 32 KiB and one of 64 bytes: 27 | 50).  The table of now pays from 2 KiB on (16, 256 and 1,024
+//    chunks of 2 KiB 11 | 15, of 4 KiB 12 - 13 | 17, of 16 KiB 19 | 28, of 64 KiB 42 - 44 | 70 - 71, of 96 KiB 57 | 98): the line has only been kept,
+//    with the tests that hold calls on either side of it to their kernels.
 //  - With short rings a workgroup's rings are as many as its chunks, so that more workgroups fit a compute unit where tensors have few
 //    (room for eight | for as many as there are: 1,500 BF16 tensors of one chunk of 100,000 bytes 321 | 213, 3,000 of two chunks
 //    1,538 | 883, 600 of three 520 | 329; with room for four, 600 of six: BF16 632 | 641, E5M2 580 | 752).

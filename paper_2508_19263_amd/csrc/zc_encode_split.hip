@@ -1,4 +1,4 @@
-// Stream sizes and encoder of 64-lane chunks that are walked by sixteen wavefronts at once instead of one (a5, a7 for the
+// Stream sizes and encoder of 64-lane chunks that are walked by sixteen wavefronts (or eight, see split_waves) at once instead of one (a5, a7 for the
 // two-field formats): a tensor's short last chunk, chunks that are not whole rows, and every chunk of a call that has too
 // few of them to fill the GPU with one wavefront each.
 //
@@ -20,10 +20,13 @@ namespace zc {
 
 namespace {
 
-// Wavefronts per chunk: sixteen, of which a compute unit holds two workgroups, 512 chunks in all; eight in calls of more, which would
-// leave the second round nearly empty.  Whole calls over chunks of 256 KiB, sixteen | eight, us: FP8 520: 223 | 202, 600: 234 | 215,
+// Wavefronts per chunk: sixteen, of which a compute unit holds two workgroups, 512 chunks in all; eight in launches of more, which would
+// leave the last round nearly empty.  Whole calls over chunks of 256 KiB, sixteen | eight, us: FP8 520: 223 | 202, 600: 234 | 215,
 // 768: 238 | 231; BF16 520: 235 | 216, 768: 246 | 235; not E5M2 (520: 292 | 299) and byte symbols (600: 280 | 289), whose chunks are worth
-// more instructions.
+// more instructions.  Short last chunks, however many, are ahead with eight throughout (both kernels' GPU time; chunks of 5,000, 40,000 and
+// 200,000 bytes): 513 tensors of FP8 25 | 15, 39 | 30, 113 | 93, of BF16 27 | 15, 52 | 40, 163 | 139, of deltas 27 | 16, 51 | 39, 169 | 146; 1,100:
+// FP8 42 | 24, 67 | 49, 185 | 148, deltas 48 | 27, 86 | 63, 280 | 229; 3,000: FP8 94 | 45, 152 | 97, 433 | 323, BF16 106 | 56, 195 | 130, 625 | 481,
+// deltas 109 | 57, 196 | 131, 666 | 506.
 inline uint32_t split_waves(uint32_t fmt, uint32_t n_work) { return n_work > 512 && (fmt == ZC_FMT_FP8_E4M3 || fmt == ZC_FMT_BF16) ? 8 : 16; }
 // places of the (up to two) words a wavefront finds asked for and not complete at its first row; as byte offsets they lie
 // beyond every stream, so the range check of the buffer store drops them

@@ -69,7 +69,7 @@ uint32_t sub_slots_per_group(uint32_t streams, uint64_t slots);
 // ---- page-locked staging (zc_staging.cpp) ---------------------------------------------------
 struct Piece { uint64_t off; const void *src; uint64_t bytes; };
 // Copies pieces (all inside [lo, hi) of the workspace) to d_ws + lo .. d_ws + hi on `stream`, through one of a few
-// page-locked buffers of the library's that are used in turn: one asynchronous copy that needs no wait (the
+// page-locked buffers of the library's that are used in turn: one asynchronous transfer that needs no wait (the
 // buffer outlives the call).  Clears n_zero words at d_zero behind it.
 zc_status stage_upload(uint8_t *d_ws, uint64_t lo, uint64_t hi, const Piece *pieces, int n, void *stream, uint64_t *d_zero = nullptr, uint64_t n_zero = 0);
 // device memory into a page-locked buffer of the library's, on `stream`, for calls that queue more behind it (where the host waits for
@@ -102,7 +102,7 @@ struct CompressShape {
     bool bf16;
     bool rows8;                 // 64 lanes, whole rows, 8 or 16 symbols of 8 bits per run and field (BF16, FP8 in byte symbols, FP8 E5M2): the 64-lane encoder written for BF16
     bool whole_shape;           // 64 lanes, chunks of whole 1 KiB rows: the generic encoder's whole-chunk build
-    bool split_rest;            // 64 lanes, two fields: what the whole-chunk kernels leave over goes through the kernels that give a chunk sixteen wavefronts
+    bool split_rest;            // 64 lanes, two fields: what the whole-chunk kernels leave over goes through the kernels that give a chunk sixteen or eight wavefronts
     bool split_all;             // so few chunks that all of them do (then no other chunk list and no counts per lane)
     bool fp4_tails;             // FP4, 64 lanes, chunks of whole rows: what is left over is a tensor's short last chunk, for k_encode_fp4_tail
     int whole_mode;             // 2: one whole chunk per work item, shared by its four wavefronts

@@ -98,7 +98,7 @@ constexpr uint32_t kHistBlockBytes = 256 * 1024;
 constexpr uint32_t kWavesPerGroup = 4;
 
 // A compress call (64 lanes, two fields) of at most split_chunk_limit() chunks of at least kSplitChunkBytes (two rows per
-// wavefront) leaves all of them to the kernels that give a chunk sixteen wavefronts.  One wavefront per chunk takes as long
+// wavefront) leaves all of them to the kernels that give a chunk sixteen or eight wavefronts.  One wavefront per chunk takes as long
 // for one chunk as for a thousand; sixteen per chunk take time in proportion to the chunks from 512 (two workgroups per
 // compute unit) on, and read the source twice.  Measured on MI355X, whole calls over chunks of 256 KiB, one wavefront |
 // sixteen, in us: FP8 128: 230 | 114, 512: 252 | 192, 768: 279 | 243, 1024: 345 | 324, 1536: 413 | 468; BF16 768: 283 | 256,
@@ -195,7 +195,7 @@ int launch_sizes_e5m2_counts(const TensorDev *d_descs, const WorkItem *d_work, u
 int launch_hist_rows8_lanes(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint64_t *d_hist, uint32_t *d_lane_counts, void *stream);
 int launch_sizes_rows8_counts(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc,
                               const uint32_t *d_lane_counts, uint32_t *d_units, void *stream);
-// Two-field formats, 64 lanes, any chunks, one per work item: sixteen wavefronts to a chunk (zc_encode_split.hip)
+// Two-field formats, 64 lanes, any chunks, one per work item: sixteen or eight wavefronts to a chunk (zc_encode_split.hip)
 int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream);
 int launch_encode_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream);
 int launch_sizes_fp8_counts(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint16_t *d_lane_counts,
