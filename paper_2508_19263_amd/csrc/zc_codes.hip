@@ -324,11 +324,11 @@ __global__ __launch_bounds__(256) void k_codes_finish(TensorDev *descs, CodePara
     if (threadIdx.x == 0) d.route = fast ? 1 : bf16 ? 2 : 0;
 }
 
-int launch_codes(TensorDev *d_descs, uint32_t n_tensors, const uint64_t *d_hist, const CodeParams &cp, uint8_t *d_blobs, uint32_t *d_enc, void *stream)
+int launch_codes(TensorDev *d_descs, uint32_t n_tensors, const uint64_t *d_hist, const CodeParams &cp, uint8_t *d_blobs, uint32_t *d_enc, bool routes, void *stream)
 {
     if (n_tensors == 0) return 0;
     hipLaunchKernelGGL(k_codes, dim3(n_tensors, cp.nf), dim3(kCodeThreads), 0, (hipStream_t)stream, d_descs, d_hist, cp, d_blobs, d_enc);
-    hipLaunchKernelGGL(k_codes_finish, dim3(n_tensors), dim3(256), 0, (hipStream_t)stream, d_descs, cp, d_enc);
+    if (routes) hipLaunchKernelGGL(k_codes_finish, dim3(n_tensors), dim3(256), 0, (hipStream_t)stream, d_descs, cp, d_enc);
     return (int)hipGetLastError();
 }
 

@@ -156,7 +156,8 @@ zc_status CompressQueue::queue_codes(uint32_t policy) const
     CodeParams cp;
     cp.fmt = g.fmt; cp.policy = policy; cp.nf = g.nf; cp.blob_bytes = (uint32_t)kBlobBytes; cp.run_len = (uint32_t)run_len(g.fmt, 0);
     for (int f = 0; f < kMaxFields; f++) cp.limit[f] = f < (int)g.nf ? g.limit[f] : 0;
-    LAUNCH_TRY(launch_codes(d_descs(), T, d_hist(), cp, ws + w.blobs, d_enc(), stream));
+    // (nobody asks for routes where sixteen wavefronts take every chunk, nor for FP4, which has one)
+    LAUNCH_TRY(launch_codes(d_descs(), T, d_hist(), cp, ws + w.blobs, d_enc(), !sh.split_all && g.nf == 2, stream));
     return ZC_OK;
 }
 
@@ -185,7 +186,7 @@ zc_status CompressQueue::queue_sizes_and_scan() const
     else LAUNCH_TRY(launch_sizes(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
     // the chained kernel has placed and written the tensors of its route (FP8: 1, BF16: 2) itself
     LAUNCH_TRY(launch_scan(d_descs(), T, (int)g.nf, g.reversed, chained ? (sh.bf16 ? 0x4 : 0x2) : 0, d_units(), (ScanOut *)(ws + w.scan), stats_only ? nullptr : ws + w.blobs,
-                           (uint32_t)kBlobBytes, stream));
+                           (uint32_t)kBlobBytes, to_host, stream));
     return ZC_OK;
 }
 
@@ -489,41 +490,35 @@ private:
     }
 
     // The tail of every call that reads sizes back.  When every destination can hold the worst case, the sizes
-    // need not be known on the host first: the encoder is queued right behind the scan and the sizes are read back
-    // meanwhile.  Otherwise the host waits for the sizes and checks them before anything is written.  `landing`:
-    // page-locked, first the ScanOut of every tensor, then, when with_blobs, the tensors' blobs (one copy where the scan
-    // kernel has placed every tensor: the sizes then come at the end of the blobs).
-    zc_status encode_and_read_sizes(LandingLease &landing, bool with_blobs)
+    // need not be known on the host first: the encoder is queued right behind the scan, which leaves the sizes in
+    // q.to_host meanwhile.  Otherwise the host waits for the sizes and checks them before anything is written.
+    zc_status encode_and_read_sizes()
     {
-        const uint64_t scan_bytes = (uint64_t)T * sizeof(ScanOut);
         static_assert(kHeaderBytes + 3 * 256 + sizeof(ScanOut) <= kBlobBytes, "header, tables and sizes of a tensor fit its blob");
-        const bool one_copy = with_blobs && !q.chained;
-        zc_status got = one_copy ? ZC_OK : read_back(landing.ptr, ws + w.scan, scan_bytes, stream);
-        if (got == ZC_OK && with_blobs) got = read_back(landing.ptr + scan_bytes, ws + w.blobs, (uint64_t)T * kBlobBytes, stream);
-        if (got) return got;
-        if (roomy) {
-            // wait for the copies only, not for the encoder queued behind them
-            hipEvent_t copied;
-            HIP_TRY(hipEventCreateWithFlags(&copied, hipEventDisableTiming));
-            const hipError_t e1 = hipEventRecord(copied, hs);
-            const zc_status s1 = e1 == hipSuccess ? q.queue_encoders() : ZC_ERR_DEVICE;
-            const hipError_t e2 = e1 == hipSuccess ? hipEventSynchronize(copied) : e1;
-            (void)hipEventDestroy(copied);
-            if (s1) return s1;
-            if (e2 != hipSuccess) return ZC_ERR_DEVICE;
-        } else HIP_TRY(hipStreamSynchronize(hs));
-        if (one_copy)
-            for (uint32_t t = 0; t < T; t++)
-                std::memcpy(landing.ptr + (uint64_t)t * sizeof(ScanOut), landing.ptr + scan_bytes + (uint64_t)(t + 1) * kBlobBytes - sizeof(ScanOut), sizeof(ScanOut));
-        const ScanOut *scan = reinterpret_cast<const ScanOut *>(landing.ptr);
+        const zc_status queued = roomy ? q.queue_encoders() : ZC_OK;
+        const zc_status known = wait_for_records(q.to_host, T, stream);       // (whatever was queued: the buffer is the scan's until then)
+        if (queued || known) return queued ? queued : known;
+        return read_sizes(true);
+    }
+    // the sizes in q.to_host, and, when the encoders are not queued yet, those
+    zc_status read_sizes(bool then_encode)
+    {
+        const uint64_t stride = q.to_host.blobs ? kBlobBytes : sizeof(ScanOut);
+        std::vector<ScanOut> scan(scan_out ? T : 0);
+        zc_status st = ZC_OK;
         for (uint32_t t = 0; t < T; t++) {
-            if (scan[t].total_units == 0xFFFFFFFFu) return ZC_ERR_DEVICE;      // a workgroup of the one-pass kernel gave up waiting in its chain
-            const uint64_t total = descs[t].payload_off + 16ull * scan[t].total_units;
-            tensors[t].out_bytes = total;
-            if (!stats_only && total > tensors[t].comp_capacity) return ZC_ERR_BUFFER_TOO_SMALL;
+            ScanOut got;
+            std::memcpy(&got, q.to_host.records + (t + 1) * stride - sizeof(ScanOut), sizeof(ScanOut));
+            if (got.total_units == 0xFFFFFFFFu) return ZC_ERR_DEVICE;          // a workgroup of the one-pass kernel gave up waiting in its chain
+            tensors[t].out_bytes = descs[t].payload_off + 16ull * got.total_units;
+            if (!stats_only && tensors[t].out_bytes > tensors[t].comp_capacity) {
+                st = ZC_ERR_BUFFER_TOO_SMALL;
+                if (then_encode) return st;
+            }
+            if (scan_out) scan[t] = got;
         }
-        if (scan_out) scan_out->assign(scan, scan + T);
-        if (stats_only || roomy) return ZC_OK;
+        if (scan_out) *scan_out = std::move(scan);
+        if (!then_encode || stats_only || roomy) return st;
         return q.queue_encoders();
     }
 
@@ -538,30 +533,37 @@ private:
             if (descs[t].route != route || ncs[t] == 0 || ncs[t] > compress_pages_fused_limit() || tensors[t].n_elems % g.elems_per_chunk) return false;
         return true;
     }
+    // descriptors, one code's tables and one header go up, whatever the number of tensors: the kernel sets what a tensor's header has of its own
     zc_status run_fused_pages()
     {
+        const uint64_t blob_off = align256((uint64_t)T * sizeof(TensorDev)), enc_off = blob_off + kBlobBytes;      // (room that the lists, blobs and tables would have)
+        const Piece all[3] = {{w.descs, descs.data(), T * sizeof(TensorDev)}, {w.descs + blob_off, blobs.data(), kBlobBytes}, {w.descs + enc_off, enc.data(), 768 * 4}};
+        const zc_status up = stage_upload(ws, w.descs, w.descs + enc_off + 768 * 4, all, 3, stream);
+        if (up) return up;
+        LandingLease landing(no_sync ? 0 : LandingLease::record_bytes(T, false));
+        if (!no_sync) {
+            if (!landing.ptr) return ZC_ERR_DEVICE;
+            q.to_host = landing.records(T, false);
+        }
         uint32_t periods = 0;                                           // BF16: one build per refill period of the exponent field
         if (sh.bf16)
             for (uint32_t t = 0; t < T; t++) periods |= descs[t].period[0];
-        LAUNCH_TRY(launch_compress_pages_fused(g.S, periods, g.reversed, q.d_descs(), T, q.d_enc(), ws + w.blobs, (uint32_t)kBlobBytes, (ScanOut *)(ws + w.scan), stream));
+        LAUNCH_TRY(launch_compress_pages_fused(g.S, periods, g.reversed, q.d_descs(), T, (const uint32_t *)(ws + w.descs + enc_off), ws + w.descs + blob_off, (ScanOut *)(ws + w.scan),
+                                               q.to_host, stream));
+        return placed_by_one_kernel(T);
+    }
+    // The rest of a call whose containers one kernel has sized, placed and written (words: set when the sizes are there).  A destination below the worst case only
+    // loses what lies beyond it (the encoder's stores are range checked) and the call reports that it was too small.
+    zc_status placed_by_one_kernel(uint32_t words)
+    {
         if (no_sync) {
             for (uint32_t t = 0; t < T; t++) tensors[t].out_bytes = 0;
             return ZC_OK;
         }
-        // the sizes are known when the kernel, encoder included, is through; a destination below the worst case only
-        // loses what lies beyond it (the encoder's stores are range checked) and the call reports that it was too small
-        LandingLease landing((uint64_t)T * sizeof(ScanOut));
-        if (!landing.ptr) return ZC_ERR_DEVICE;
-        HIP_TRY(hipMemcpyAsync(landing.ptr, ws + w.scan, (uint64_t)T * sizeof(ScanOut), hipMemcpyDeviceToHost, hs));
-        HIP_TRY(hipStreamSynchronize(hs));
-        const ScanOut *scan = reinterpret_cast<const ScanOut *>(landing.ptr);
-        zc_status st = ZC_OK;
-        for (uint32_t t = 0; t < T; t++) {
-            tensors[t].out_bytes = descs[t].payload_off + 16ull * scan[t].total_units;
-            tensors[t].info.total_bytes = tensors[t].out_bytes;
-            if (tensors[t].out_bytes > tensors[t].comp_capacity) st = ZC_ERR_BUFFER_TOO_SMALL;
-        }
-        if (scan_out) scan_out->assign(scan, scan + T);
+        const zc_status known = wait_for_records(q.to_host, words, stream);
+        if (known) return known;
+        const zc_status st = read_sizes(false);
+        for (uint32_t t = 0; t < T; t++) tensors[t].info.total_bytes = tensors[t].out_bytes;
         return st;
     }
 
@@ -607,24 +609,13 @@ private:
         uint64_t *status = reinterpret_cast<uint64_t *>(ws + w.units), *counter = reinterpret_cast<uint64_t *>(ws + w.hist);
         LAUNCH_TRY(launch_compress_pages_chained(g.S, sh.bf16 ? descs[0].period[0] : 0u, chained_hold(), q.d_descs(), q.d_list(w.fast_work), q.n_fast, chained_step(), q.d_enc(),
                                                  ws + w.blobs, (uint32_t)kBlobBytes, status, counter, (ScanOut *)(ws + w.scan), stream));
-        if (no_sync) {
-            for (uint32_t t = 0; t < T; t++) tensors[t].out_bytes = 0;
-            return ZC_OK;
-        }
-        LandingLease landing((uint64_t)T * sizeof(ScanOut));
+        if (no_sync) return placed_by_one_kernel(0);
+        LandingLease landing(LandingLease::record_bytes(T, false));
         if (!landing.ptr) return ZC_ERR_DEVICE;
-        HIP_TRY(hipMemcpyAsync(landing.ptr, ws + w.scan, (uint64_t)T * sizeof(ScanOut), hipMemcpyDeviceToHost, hs));
-        HIP_TRY(hipStreamSynchronize(hs));
-        const ScanOut *scan = reinterpret_cast<const ScanOut *>(landing.ptr);
-        zc_status st = ZC_OK;
-        for (uint32_t t = 0; t < T; t++) {
-            if (scan[t].total_units == 0xFFFFFFFFu) return ZC_ERR_DEVICE;      // a workgroup gave up waiting in the chain
-            tensors[t].out_bytes = descs[t].payload_off + 16ull * scan[t].total_units;
-            tensors[t].info.total_bytes = tensors[t].out_bytes;
-            if (tensors[t].out_bytes > tensors[t].comp_capacity) st = ZC_ERR_BUFFER_TOO_SMALL;
-        }
-        if (scan_out) scan_out->assign(scan, scan + T);
-        return st;
+        q.to_host = landing.records(T, false);
+        const uint32_t bytes = (uint32_t)(T * sizeof(ScanOut)), groups = hand_over_groups(bytes);      // (a word per workgroup: no more than tensors)
+        LAUNCH_TRY(launch_hand_over(ws + w.scan, q.to_host.records, bytes, true, nullptr, 0, q.to_host.flags, stream));
+        return placed_by_one_kernel(groups);
     }
 
     // a call that waits for nothing: the sizes stay in the containers' headers
@@ -690,14 +681,18 @@ private:
         if (st) return st;
         st = q.queue_codes(params->policy);
         if (st) return st;
+        LandingLease landing(no_sync ? 0 : LandingLease::record_bytes(T, true));
+        if (!no_sync) {
+            if (!landing.ptr) return ZC_ERR_DEVICE;
+            q.to_host = landing.records(T, true);
+        }
         st = q.queue_sizes_and_scan();
         if (st) return st;
         if (no_sync) return queue_encoders_without_sizes();
-        LandingLease landing((uint64_t)T * (sizeof(ScanOut) + kBlobBytes));
-        if (!landing.ptr) return ZC_ERR_DEVICE;
-        st = encode_and_read_sizes(landing, true);
+        st = encode_and_read_sizes();
+        if (st == ZC_ERR_DEVICE) return st;
         // what the device decided, for the caller's zc_info
-        const uint8_t *got = landing.ptr + (uint64_t)T * sizeof(ScanOut);
+        const uint8_t *got = q.to_host.records;
         FieldCode fc[3] = {};                                    // (of 8 KiB: cleared once; a field's bytes beyond its symbols stay clear)
         for (uint32_t t = 0; t < T; t++) {
             const uint8_t *blob = got + (uint64_t)t * kBlobBytes;
@@ -716,30 +711,35 @@ private:
     std::vector<uint8_t> blobs;             // header + code-length tables per tensor
     const uint64_t *hist = nullptr;         // the device histograms, landed
 
+    // A dictionary call gives every tensor the same code (Sec. 3.3, 5.2: K/V pages of a decoding step): tensor t takes what tensor 0
+    // got, and only what depends on the element count is set again.
+    bool shares_code(uint32_t t) const { return dict && t > 0 && !codes_out && tensors[t].n_elems && tensors[0].n_elems && fast_shape(t) == fast_shape(0); }
+    void share_desc(uint32_t t)
+    {
+        zc_info &info = tensors[t].info;
+        info = tensors[0].info;
+        info.xor_delta = tensors[t].d_xor_base != nullptr; info.n_elems = tensors[t].n_elems; info.n_chunks = (uint32_t)ncs[t];
+        info.total_bytes = 0;
+        layout(g.fmt, ncs[t], info.table_offset, info.index_offset, &info.payload_offset);
+        TensorDev &d = descs[t];
+        const TensorDev &d0 = descs[0];
+        for (uint32_t f = 0; f < g.nf; f++) { d.mode[f] = d0.mode[f]; d.lmax[f] = d0.lmax[f]; d.konst[f] = d0.konst[f]; d.period[f] = d0.period[f]; d.kind[f] = d0.kind[f]; }
+        d.route = d0.route;
+    }
+    void share_tables(uint32_t t)
+    {
+        const zc_info &info = tensors[t].info;
+        uint8_t *blob = &blobs[(size_t)t * kBlobBytes];
+        std::memcpy(blob, &blobs[0], kBlobBytes);
+        blob[10] = (uint8_t)((info.xor_delta ? 1 : 0) | (g.reversed ? 2 : 0));
+        put64(blob + 16, info.n_elems); put32(blob + 24, info.n_chunks); put64(blob + 48, 0); put64(blob + 56, info.payload_offset);
+        std::memcpy(&enc[(size_t)t * 768], &enc[0], 768 * sizeof(uint32_t));
+    }
+
     // code construction on the host (a4), one tensor
     zc_status build_one(uint32_t t)
     {
-        // A dictionary call gives every tensor the same code (Sec. 3.3, 5.2: K/V pages of a decoding step), so what
-        // tensor 0 got is copied and only what depends on the element count is set again: for 64 tensors of a step
-        // this is a third of the call's host time.  Tensors are built in order here (one thread with a dictionary).
-        if (dict && t > 0 && !codes_out && tensors[t].n_elems && tensors[0].n_elems && fast_shape(t) == fast_shape(0)) {
-            zc_info &info = tensors[t].info;
-            info = tensors[0].info;
-            info.xor_delta = tensors[t].d_xor_base != nullptr; info.n_elems = tensors[t].n_elems; info.n_chunks = (uint32_t)ncs[t];
-            info.total_bytes = 0;
-            layout(g.fmt, ncs[t], info.table_offset, info.index_offset, &info.payload_offset);
-            uint8_t *blob = &blobs[(size_t)t * kBlobBytes];
-            std::memcpy(blob, &blobs[0], kBlobBytes);
-            blob[10] = (uint8_t)((info.xor_delta ? 1 : 0) | (g.reversed ? 2 : 0));
-            put64(blob + 16, info.n_elems); put32(blob + 24, info.n_chunks); put64(blob + 48, 0); put64(blob + 56, info.payload_offset);
-            std::memcpy(&enc[(size_t)t * 768], &enc[0], 768 * sizeof(uint32_t));
-            TensorDev &d = descs[t];
-            const TensorDev &d0 = descs[0];
-            for (uint32_t f = 0; f < g.nf; f++) { d.mode[f] = d0.mode[f]; d.lmax[f] = d0.lmax[f]; d.konst[f] = d0.konst[f]; d.period[f] = d0.period[f]; d.kind[f] = d0.kind[f]; }
-            d.route = d0.route;
-            return ZC_OK;
-        }
-        FieldCode *fc = &codes[(size_t)t * 3];
+        FieldCode *fc = &codes[dict ? 0 : (size_t)t * 3];          // (a dictionary's is not looked at again)
         const zc_status s1 = dict ? codes_from_dictionary(g, tensors[t].n_elems, *dict, fc)
                                   : build_codes(g, params->policy, tensors[t].n_elems, &hist[(size_t)t * 768], fc, train);
         if (s1) return s1;
@@ -786,19 +786,16 @@ private:
         LandingLease landing(hist_bytes);
         if (hist_bytes && !landing.ptr) return ZC_ERR_DEVICE;
         hist = reinterpret_cast<const uint64_t *>(landing.ptr);
-        auto allocate_tables = [&]() {
-            codes.resize((size_t)T * 3);
-            enc.assign((size_t)T * 768, 0);
-            blobs.assign((size_t)T * kBlobBytes, 0);
+        auto allocate_tables = [&](uint32_t n) {
+            codes.resize(dict ? 3 : (size_t)n * 3);
+            enc.resize((size_t)n * 768, 0);
+            blobs.resize((size_t)n * kBlobBytes, 0);
         };
-        // The worker threads are started once the histogram kernel is queued and before the wait for it, so that
-        // their start-up (tens of microseconds each) is hidden behind it; they sleep until run() opens the gate.
-        // With a dictionary there is nothing to wait for and little to do per tensor: one thread.
-        const uint32_t n_threads = (!dict && T >= 8) ? std::min<uint32_t>(std::min<uint32_t>(8, T / 2), std::max(1u, std::thread::hardware_concurrency())) : 1;
-        std::optional<CodeCrew> crew;
-        const auto one = [this](uint32_t t) { return build_one(t); };
         zc_status st;
         if (!dict) {
+            // The worker threads are started once the histogram kernel is queued and before the wait for it, so that
+            // their start-up (tens of microseconds each) is hidden behind it; they sleep until run() opens the gate.
+            const uint32_t n_threads = T >= 8 ? std::min<uint32_t>(std::min<uint32_t>(8, T / 2), std::max(1u, std::thread::hardware_concurrency())) : 1;
             const Piece first[3] = {{w.descs, descs.data(), T * sizeof(TensorDev)},
                                     {w.hist_work, hist_work.data(), hist_work.size() * sizeof(WorkItem)},
                                     {w.scale_work, scale_work.data(), scale_work.size() * sizeof(WorkItem)}};
@@ -808,16 +805,29 @@ private:
             st = q.queue_histogram();
             if (st) return st;
             HIP_TRY(hipMemcpyAsync(landing.ptr, q.d_hist(), hist_bytes, hipMemcpyDeviceToHost, hs));
-            crew.emplace(T, n_threads, one);
-            allocate_tables();
+            CodeCrew crew(T, n_threads, [this](uint32_t t) { return build_one(t); });
+            allocate_tables(T);
             HIP_TRY(hipStreamSynchronize(hs));
+            st = crew.run();
+            if (st) return st;
         } else {
-            crew.emplace(T, n_threads, one);
-            allocate_tables();
+            allocate_tables(1);
+            st = build_one(0);
+            if (st) return st;
+            bool all_share = true;
+            for (uint32_t t = 1; t < T; t++) {
+                if (shares_code(t)) share_desc(t);
+                else all_share = false;
+            }
+            if (all_share && pages_fit_one_workgroup()) return run_fused_pages();
+            allocate_tables(T);
+            for (uint32_t t = 1; t < T; t++) {
+                if (shares_code(t)) { share_tables(t); continue; }
+                st = build_one(t);
+                if (st) return st;
+            }
         }
-        st = crew->run();
-        if (st) return st;
-        const bool chained = !pages_fit_one_workgroup() && pages_in_one_pass();
+        const bool chained = pages_in_one_pass();
         for (uint32_t t = 0; t < T; t++) {
             // the route is known, so every chunk is listed once
             if (sh.split_all) {
@@ -848,14 +858,16 @@ private:
                               {w.enc, enc.data(), enc.size() * 4}};
         st = stage_upload(ws, w.descs, w.host_end, all, 8, stream);
         if (st) return st;
-        if (pages_fit_one_workgroup()) return run_fused_pages();
         if (chained) return run_pages_in_one_pass();
+        LandingLease sizes(no_sync ? 0 : LandingLease::record_bytes(T, false));
+        if (!no_sync) {
+            if (!sizes.ptr) return ZC_ERR_DEVICE;
+            q.to_host = sizes.records(T, false);
+        }
         st = q.queue_sizes_and_scan();
         if (st) return st;
         if (no_sync) return queue_encoders_without_sizes();
-        LandingLease scan_landing((uint64_t)T * sizeof(ScanOut));
-        if (!scan_landing.ptr) return ZC_ERR_DEVICE;
-        st = encode_and_read_sizes(scan_landing, false);
+        st = encode_and_read_sizes();
         for (uint32_t t = 0; t < T; t++) tensors[t].info.total_bytes = tensors[t].out_bytes;
         return st;
     }

@@ -7,6 +7,12 @@
 
 namespace zc {
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// A word the host waits for, set once all that this wavefront has written is on its way to memory and in front of it (and, after a
+// workgroup barrier, all that its workgroup has).  One thread: the write-back that goes with it is the compute unit's.
+__device__ __forceinline__ void tell_host(uint32_t *flag) { __hip_atomic_store(flag, kTold, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM); }
+
 // ------------------------------------------------------------------ lane helpers
 
 struct Lanes {

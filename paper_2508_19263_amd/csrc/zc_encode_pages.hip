@@ -313,8 +313,8 @@ constexpr uint32_t kFusedMaxPages = 512;
 // BF as in the page encoder: 0 = FP8, else BF16 with that refill period of the exponent field (a workgroup whose
 // tensor has another one returns at once: the host launches one build per period that occurs in the call).
 template <int S, int BF>
-__global__ __launch_bounds__(256) void k_compress_pages_fused(const TensorDev *descs, const uint32_t *enc_tables, const uint8_t *blobs, uint32_t blob_bytes,
-                                                              ScanOut *out, int reversed)
+__global__ __launch_bounds__(256) void k_compress_pages_fused(const TensorDev *descs, const uint32_t *enc_table, const uint8_t *blob, ScanOut *out, int reversed,
+                                                              HostRecords to)
 {
     constexpr uint32_t kGroups = 64 / S, kRing = 32 * S, kPerPass = kWavesPerGroup * kGroups;
     __shared__ uint32_t pair[256];
@@ -328,13 +328,21 @@ __global__ __launch_bounds__(256) void k_compress_pages_fused(const TensorDev *d
     // whole workgroup; the host sends only tensors of the page kernels' route with 1 .. kFusedMaxPages whole pages here
     if (dp->route != (BF ? 2 : 1) || (BF && dp->period[0] != BF) || nc == 0 || nc > kFusedMaxPages || !comp) return;
     if (uni64(dp->n_elems) * (BF ? 2 : 1) != (uint64_t)nc * uni32(dp->chunk_bytes)) return;
-    pair[tid] = enc_tables[(uint64_t)blockIdx.x * 768 + (BF ? 0 : 512) + tid];
+    pair[tid] = enc_table[(BF ? 0 : 512) + tid];
     const uint32_t i0 = uni32(dp->index_off[0]), i1 = uni32(dp->index_off[1]);
     {
-        // the prologue (header and code-length tables) as prepared in the blob, and zeros behind both indices
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(blobs + (uint64_t)blockIdx.x * blob_bytes);
+        // the prologue (header and code-length tables) as prepared in the blob, with what is the tensor's own in the header (words 12 and
+        // 13, the total size, come last), and zeros behind both indices
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(blob);
         uint32_t *dst = reinterpret_cast<uint32_t *>(comp);
-        for (uint32_t i = tid; i < i0 / 4; i += 256) dst[i] = src[i];
+        const uint64_t n = dp->n_elems, p = dp->payload_off;
+        const uint32_t order = (dp->base ? 1u : 0u) | (reversed ? 2u : 0u);
+        for (uint32_t i = tid; i < i0 / 4; i += 256) {
+            uint32_t v = src[i];
+            if (i == 2) v = (v & 0xFF00FFFFu) | (order << 16);
+            v = i == 4 ? (uint32_t)n : i == 5 ? (uint32_t)(n >> 32) : i == 6 ? nc : i == 14 ? (uint32_t)p : i == 15 ? (uint32_t)(p >> 32) : v;
+            if (i / 2 != 6) dst[i] = v;
+        }
         if (tid < 8) {
             const uint32_t w = nc + 1 + (tid & 3);
             if (w < ((nc + 1 + 3) & ~3u)) dst[(tid < 4 ? i0 : i1) / 4 + w] = 0;
@@ -375,35 +383,39 @@ __global__ __launch_bounds__(256) void k_compress_pages_fused(const TensorDev *d
             ScanOut o = {{idx0[nc] - idx0[0], idx1[nc] - idx1[0], 0}, total};
             out[blockIdx.x] = o;
             *reinterpret_cast<uint64_t *>(comp + 48) = uni64(dp->payload_off) + 16ull * total;
+            if (to.flags) {                                      // (the host need not wait for the encoder)
+                reinterpret_cast<ScanOut *>(to.records)[blockIdx.x] = o;
+                tell_host(to.flags + blockIdx.x);
+            }
         }
     }
     encode_pages<S, kPagesWrite, BF>(dp, 0, slots, pair, stage, pairs_of_rows, idx0, idx1, nullptr, 0);
 }
 
 template <int S>
-static void launch_fused_s(uint32_t bf16_periods, const TensorDev *d_descs, uint32_t n_tensors, const uint32_t *d_enc, const uint8_t *d_blobs, uint32_t blob_bytes,
-                           ScanOut *d_out, int rev, hipStream_t st)
+static void launch_fused_s(uint32_t bf16_periods, const TensorDev *d_descs, uint32_t n_tensors, const uint32_t *d_enc, const uint8_t *d_blob, ScanOut *d_out, int rev,
+                           const HostRecords &to, hipStream_t st)
 {
-    if (!bf16_periods) { hipLaunchKernelGGL((k_compress_pages_fused<S, 0>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blobs, blob_bytes, d_out, rev); return; }
-    if (bf16_periods & 2) hipLaunchKernelGGL((k_compress_pages_fused<S, 2>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blobs, blob_bytes, d_out, rev);
-    if (bf16_periods & 4) hipLaunchKernelGGL((k_compress_pages_fused<S, 4>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blobs, blob_bytes, d_out, rev);
-    if (bf16_periods & 8) hipLaunchKernelGGL((k_compress_pages_fused<S, 8>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blobs, blob_bytes, d_out, rev);
+    if (!bf16_periods) { hipLaunchKernelGGL((k_compress_pages_fused<S, 0>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, to); return; }
+    if (bf16_periods & 2) hipLaunchKernelGGL((k_compress_pages_fused<S, 2>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, to);
+    if (bf16_periods & 4) hipLaunchKernelGGL((k_compress_pages_fused<S, 4>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, to);
+    if (bf16_periods & 8) hipLaunchKernelGGL((k_compress_pages_fused<S, 8>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, to);
 }
 
 // streams: 4, 8, 16 or 32; one workgroup per tensor.  bf16_periods: 0 for FP8 tensors (route 1); for BF16 tensors (route 2)
 // the refill periods of the exponent field that occur among them, or-ed together (2, 4, 8): one launch per period.
 int launch_compress_pages_fused(uint32_t streams, uint32_t bf16_periods, bool reversed, const TensorDev *d_descs, uint32_t n_tensors, const uint32_t *d_enc,
-                                const uint8_t *d_blobs, uint32_t blob_bytes, ScanOut *d_out, void *stream)
+                                const uint8_t *d_blob, ScanOut *d_out, const HostRecords &to, void *stream)
 {
     const int rev = reversed ? 1 : 0;
     if (n_tensors == 0) return 0;
     if (bf16_periods & ~14u) return 1;
     hipStream_t st = (hipStream_t)stream;
     switch (streams) {
-    case 4: launch_fused_s<4>(bf16_periods, d_descs, n_tensors, d_enc, d_blobs, blob_bytes, d_out, rev, st); break;
-    case 8: launch_fused_s<8>(bf16_periods, d_descs, n_tensors, d_enc, d_blobs, blob_bytes, d_out, rev, st); break;
-    case 16: launch_fused_s<16>(bf16_periods, d_descs, n_tensors, d_enc, d_blobs, blob_bytes, d_out, rev, st); break;
-    case 32: launch_fused_s<32>(bf16_periods, d_descs, n_tensors, d_enc, d_blobs, blob_bytes, d_out, rev, st); break;
+    case 4: launch_fused_s<4>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, to, st); break;
+    case 8: launch_fused_s<8>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, to, st); break;
+    case 16: launch_fused_s<16>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, to, st); break;
+    case 32: launch_fused_s<32>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, to, st); break;
     default: return 1;
     }
     return (int)hipGetLastError();

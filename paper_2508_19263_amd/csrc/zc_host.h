@@ -72,15 +72,17 @@ struct Piece { uint64_t off; const void *src; uint64_t bytes; };
 // page-locked buffers of the library's that are used in turn: one asynchronous transfer that needs no wait (the
 // buffer outlives the call).  Clears n_zero words at d_zero behind it.
 zc_status stage_upload(uint8_t *d_ws, uint64_t lo, uint64_t hi, const Piece *pieces, int n, void *stream, uint64_t *d_zero = nullptr, uint64_t n_zero = 0);
-// device memory into a page-locked buffer of the library's, on `stream`, for calls that queue more behind it (where the host waits for
-// the stream at once the runtime's copy is no slower: one decoding step's pages 84.3 | 84.9 us)
-zc_status read_back(uint8_t *landing, const uint8_t *d_src, uint64_t bytes, void *stream);
+// waits for n words that the kernels queued on `stream` leave
+zc_status wait_for_records(const HostRecords &to, uint32_t n, void *stream);
 // a page-locked buffer for one call's read-backs, returned to the library's pool by the destructor
 struct LandingLease {
     uint8_t *ptr = nullptr;
     uint64_t cap = 0;
     explicit LandingLease(uint64_t bytes);
     ~LandingLease();
+    // the buffer as records of n tensors with their words, cleared; it has to hold record_bytes(n, blobs)
+    HostRecords records(uint32_t n, bool blobs);
+    static uint64_t record_bytes(uint32_t n, bool blobs) { return (uint64_t)n * ((blobs ? kBlobBytes : sizeof(ScanOut)) + sizeof(uint32_t)); }
     LandingLease(const LandingLease &) = delete;
     LandingLease &operator=(const LandingLease &) = delete;
 };
@@ -140,6 +142,7 @@ struct CompressQueue {
     uint32_t chain_hold = 0;                                   // words of LDS per page where that kernel keeps the exponent streams, else 0
     uint32_t chain_step = 0;
     uint64_t chain_status = 0, chain_counter = 0;
+    HostRecords to_host = {nullptr, nullptr, 0};               // what the host waits for, left by the scan
 
     TensorDev *d_descs() const { return (TensorDev *)(ws + w.descs); }
     uint64_t *d_hist() const { return (uint64_t *)(ws + w.hist); }

@@ -11,6 +11,12 @@ constexpr uint32_t kMagic = 0x0031435Au;   // "ZC1\0"
 constexpr uint32_t kHeaderBytes = 64;
 constexpr int kMaxFields = 3;
 
+#ifdef __HIPCC__
+#define ZC_HOST_DEVICE __host__ __device__
+#else
+#define ZC_HOST_DEVICE
+#endif
+
 // ---- format geometry -------------------------------------------------------
 // element format of a (possibly byte-grouped) format, and field values per coded symbol
 inline uint32_t base_format(uint32_t fmt)
@@ -76,11 +82,6 @@ struct alignas(16) TensorDev {
 
 struct WorkItem { uint32_t tensor, first; };   // `first`: first chunk / block of the item
 
-#ifdef __HIPCC__
-#define ZC_HOST_DEVICE __host__ __device__
-#else
-#define ZC_HOST_DEVICE
-#endif
 // Workgroups are handed to the 8 XCDs (each with an L2 of its own) in turn, so workgroup p runs on XCD p % 8.
 // Work lists are ordered so that every XCD walks one contiguous eighth of the list: position p of the ordered list
 // holds the item at this position of the natural list of n items.
@@ -110,6 +111,13 @@ inline uint64_t split_chunk_limit(uint32_t fmt, bool delta) { return delta ? 512
 // per-tensor scratch written by the scan kernel and read back by the host
 struct ScanOut { uint32_t field_units[kMaxFields]; uint32_t total_units; };
 
+// What a kernel leaves for a host that waits for it, in page-locked memory: one record per tensor, its ScanOut or (blobs) the
+// tensor's blob with the ScanOut in its last bytes, and behind it the tensor's word of `flags`, which the host has cleared.
+struct HostRecords { uint8_t *records; uint32_t *flags; uint32_t blobs; };
+constexpr uint32_t kTold = 1;             // what such a word is set to
+// workgroups of k_hand_over that have bytes to move (16 per thread), each of which sets a word
+ZC_HOST_DEVICE inline uint32_t hand_over_groups(uint32_t bytes) { return bytes < 4096 ? 1u : (bytes / 16 + 255) / 256; }
+
 // ---- host-side code construction (zc_codebook.cpp) --------------------------
 // Length-limited canonical Huffman code; returns false if 2^limit < used symbols.
 bool build_code_lengths(const uint64_t *hist, int alphabet, int limit, uint8_t *len_out);
@@ -123,16 +131,16 @@ struct CodeParams {
     uint32_t run_len;         // symbols per 16-byte run of an element field
 };
 // histograms (768 counters per tensor, as k_hist leaves them) -> encode tables, the code-dependent bytes of the
-// header blobs and of the descriptors (mode, lmax, konst, period, kind, route)
-int launch_codes(TensorDev *d_descs, uint32_t n_tensors, const uint64_t *d_hist, const CodeParams &cp, uint8_t *d_blobs, uint32_t *d_enc, void *stream);
+// header blobs and of the descriptors (mode, lmax, konst, period, kind, and, with routes, route and the FP8 kernels' pair table: a launch more)
+int launch_codes(TensorDev *d_descs, uint32_t n_tensors, const uint64_t *d_hist, const CodeParams &cp, uint8_t *d_blobs, uint32_t *d_enc, bool routes, void *stream);
 
 // ---- kernel launchers (zc_kernels.hip); all return a hipError_t as int ------
 int launch_hist(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                 int scales_view, uint64_t *d_hist, void *stream);
 int launch_zero(uint64_t *d_words, uint64_t n_words, void *stream);
-// between a page-locked host buffer and device memory, either way (both aligned to 16 bytes; to_host: the host waits for what is
-// written); clears n_zero words at d_zero too
-int launch_hand_over(const void *src, void *dst, uint64_t bytes, bool to_host, uint64_t *d_zero, uint64_t n_zero, void *stream);
+// between a page-locked host buffer and device memory, either way (both aligned to 16 bytes); flags: hand_over_groups(bytes) words of
+// page-locked memory, set when the bytes have been read, or (to_host) have arrived; clears n_zero words at d_zero too
+int launch_hand_over(const void *src, void *dst, uint64_t bytes, bool to_host, uint64_t *d_zero, uint64_t n_zero, uint32_t *flags, void *stream);
 int launch_copy(const void *d_src, void *d_dst, uint64_t bytes, void *stream);
 int launch_copy_chunked(const void *d_src, void *d_dst, uint64_t bytes, uint32_t chunk_bytes, void *stream);
 // skip_routes: bit r set = leave tensors of route r to the specialised kernel that takes their whole chunks
@@ -141,10 +149,10 @@ int launch_copy_chunked(const void *d_src, void *d_dst, uint64_t bytes, uint32_t
 int launch_sizes(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                  const uint32_t *d_enc_tables, uint32_t *d_units, void *stream);
 int launch_fp4_tails(uint32_t fmt, int write, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream);
-// d_blobs: per tensor the header and code-length tables to put at the start of its container (blob_bytes apart), or null
-// (whose last sizeof(ScanOut) bytes it fills as it does d_out)
-int launch_scan(const TensorDev *d_descs, uint32_t n_tensors, int n_fields, bool reversed, int skip_routes, const uint32_t *d_units, ScanOut *d_out, uint8_t *d_blobs,
-                uint32_t blob_bytes, void *stream);
+// d_blobs: per tensor the header and code-length tables to put at the start of its container (blob_bytes apart), or null;
+// to: what the host waits for (no flags: nothing)
+int launch_scan(const TensorDev *d_descs, uint32_t n_tensors, int n_fields, bool reversed, int skip_routes, const uint32_t *d_units, ScanOut *d_out, const uint8_t *d_blobs,
+                uint32_t blob_bytes, const HostRecords &to, void *stream);
 int launch_encode(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                   const uint32_t *d_enc_tables, void *stream);
 int launch_decode(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint32_t chunks_per_item,
@@ -205,8 +213,9 @@ int launch_encode_fp8(const TensorDev *d_descs, const WorkItem *d_work, uint32_t
 // work items as for the generic whole-chunk build (zc_encode_fast.hip)
 int launch_encode_bf16(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream);
 // K/V pages, 4 to 32 lanes per chunk (zc_encode_pages.hip)
+// (d_enc, d_blob: the one code's tables and the header of one of the tensors)
 int launch_compress_pages_fused(uint32_t streams, uint32_t bf16_periods, bool reversed, const TensorDev *d_descs, uint32_t n_tensors, const uint32_t *d_enc,
-                                const uint8_t *d_blobs, uint32_t blob_bytes, ScanOut *d_out, void *stream);
+                                const uint8_t *d_blob, ScanOut *d_out, const HostRecords &to, void *stream);
 uint32_t compress_pages_fused_limit();      // most pages per tensor the fused kernel takes
 // pages in one pass over the source: containers with their fields in reverse order, dictionary calls; see the kernel
 int launch_compress_pages_chained(uint32_t streams, uint32_t bf16_period, uint32_t hold, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,

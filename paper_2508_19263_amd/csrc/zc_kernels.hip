@@ -570,86 +570,147 @@ int launch_encode(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_d
 // One workgroup per tensor: exclusive scan of the stream sizes (16-byte units) in
 // field-major order, the fields in the payload's order (reversed: the last field first).  Writes the container's prologue (header and code-length tables as prepared in the
 // tensor's blob, when blobs is given), the chunk index with the zero padding behind it and the total size into
-// the container (when there is one), and the per-field totals for the host.
+// the container (when there is one), the per-field totals, and, for a host that waits (to.flags), what it waits for: a
+// record per tensor in page-locked memory, then the tensor's word there.
+//
+// Bound by latency: a chain of a descriptor, the sizes, the scan and the stores.  Up to kScanWaveChunks chunks a field is one
+// wavefront's, so that the fields are scanned side by side with one barrier in all; the prologue and the record belong to other
+// wavefronts.  Beyond that every pass takes eight chunks per thread, read and written 16 bytes at a time where they are aligned.
+// (One 2 MiB BF16 tensor: 7.2 us, a launch of 3.8 that took the sizes to the host and a gap of 5.6 behind its event -> 4.6; 8,192 chunks of a
+// delta 18.3 -> 9.4; 64 tensors of 16,384 pages 38.8 -> 21.8.)
+constexpr uint32_t kScanWaveChunks = 512;
 
 __global__ __launch_bounds__(1024) void k_scan(const TensorDev *descs, int n_fields, int reversed, int skip_routes, const uint32_t *units, ScanOut *out,
-                                               uint8_t *blobs, uint32_t blob_bytes)
+                                               const uint8_t *blobs, uint32_t blob_bytes, HostRecords to)
 {
     __shared__ uint32_t wave_sum[16];
     __shared__ uint32_t carry_s;
-    // whole workgroup: a tensor of such a route has been placed and written by another kernel (bit r: route r)
-    if ((skip_routes >> descs[blockIdx.x].route) & 1) return;
+    __shared__ ScanOut result;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = blockIdx.x;
     // copies of what is needed from the descriptor: the stores below could alias it as far as the compiler knows
-    const TensorDev &dg = descs[blockIdx.x];
+    const TensorDev &dg = descs[t];
     struct { uint8_t *comp; uint32_t n_chunks, index_off[kMaxFields]; uint64_t payload_off; } d;
     d.comp = dg.comp; d.n_chunks = dg.n_chunks; d.payload_off = dg.payload_off;
     for (int f = 0; f < kMaxFields; f++) d.index_off[f] = dg.index_off[f];
     const uint32_t *u = units + dg.units_off;
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) carry_s = 0;
-    if (d.comp && blobs) {
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(blobs + (uint64_t)blockIdx.x * blob_bytes);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(d.comp);
-        for (uint32_t i = threadIdx.x; i < d.index_off[0] / 4; i += 1024) dst[i] = src[i];
-        if (threadIdx.x < 4 * (uint32_t)n_fields) {
-            const uint32_t f = threadIdx.x / 4, w = d.n_chunks + 1 + (threadIdx.x & 3);
-            if (w < ((d.n_chunks + 1 + 3) & ~3u)) dst[d.index_off[f] / 4 + w] = 0;
+    // a tensor of such a route has been placed and written by another kernel (bit r: route r)
+    const bool placed = (skip_routes >> dg.route) & 1;
+    // the last wavefront has the host's record: the blob, 16 bytes per lane, the sizes in its last 16 bytes
+    u32x4 record = {0, 0, 0, 0};
+    if (to.flags && to.blobs && wave == 15 && lane < blob_bytes / 16) record = reinterpret_cast<const u32x4 *>(blobs + (uint64_t)t * blob_bytes)[lane];
+    if (placed) { if (threadIdx.x == 0) result = out[t]; }
+    else {
+        if (threadIdx.x == 0) carry_s = 0;
+        if (d.comp && blobs && wave >= 4) {
+            const uint32_t *src = reinterpret_cast<const uint32_t *>(blobs + (uint64_t)t * blob_bytes);
+            uint32_t *dst = reinterpret_cast<uint32_t *>(d.comp);
+            // (words 12 and 13 are the total size, written below)
+            for (uint32_t i = threadIdx.x - 256; i < d.index_off[0] / 4; i += 768) if (i / 2 != 6) dst[i] = src[i];
         }
-    }
-    __syncthreads();                                             // the total size below overwrites a word of the prologue
-    uint32_t field_units[kMaxFields] = {0, 0, 0};
-    for (int k = 0; k < n_fields; k++) {
-        const int f = reversed ? n_fields - 1 - k : k;
-        uint32_t *index = d.comp ? reinterpret_cast<uint32_t *>(d.comp + d.index_off[f]) : nullptr;
-        const uint32_t field_start = carry_s;
-        // eight consecutive chunks per thread and pass: a tensor of pages has tens of thousands of chunks, and every
-        // pass costs three workgroup barriers
+        if (d.comp && blobs && wave == 3 && lane < 4 * (uint32_t)n_fields) {
+            const uint32_t f = lane / 4, w = d.n_chunks + 1 + (lane & 3);
+            if (w < ((d.n_chunks + 1 + 3) & ~3u)) reinterpret_cast<uint32_t *>(d.comp + d.index_off[f])[w] = 0;
+        }
+        uint32_t field_units[kMaxFields] = {0, 0, 0};
         constexpr uint32_t K = 8;
-        for (uint32_t c0 = 0; c0 < d.n_chunks; c0 += 1024 * K) {
-            const uint32_t c = c0 + threadIdx.x * K;
-            uint32_t v[K], t = 0;
-#pragma unroll
-            for (uint32_t j = 0; j < K; j++) { v[j] = c + j < d.n_chunks ? u[(uint64_t)f * d.n_chunks + c + j] : 0; t += v[j]; }
-            uint32_t x = t;                                   // inclusive scan of the threads' sums inside the wave
+        auto inclusive = [&](uint32_t x) {                       // inclusive scan over the wavefront
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
                 const uint32_t y = __shfl_up(x, o, 64);
                 if (lane >= (uint32_t)o) x += y;
             }
-            if (lane == 63) wave_sum[wave] = x;
-            __syncthreads();
-            uint32_t before = carry_s;
-            for (uint32_t w = 0; w < wave; w++) before += wave_sum[w];
-            uint32_t at = before + x - t;                     // units before this thread's first chunk
-            if (index) {
+            return x;
+        };
+        auto load8 = [&](const uint32_t *p, uint32_t c, uint32_t v[K]) {
+            if (c + K <= d.n_chunks && (uintptr_t)p % 16 == 0) {
+                const u32x4 lo = *reinterpret_cast<const u32x4 *>(p + c), hi = *reinterpret_cast<const u32x4 *>(p + c + 4);
 #pragma unroll
-                for (uint32_t j = 0; j < K; j++) { if (c + j < d.n_chunks) index[c + j] = at; at += v[j]; }
+                for (uint32_t j = 0; j < 4; j++) { v[j] = lo[j]; v[4 + j] = hi[j]; }
+            } else
+#pragma unroll
+                for (uint32_t j = 0; j < K; j++) v[j] = c + j < d.n_chunks ? p[c + j] : 0;
+        };
+        auto store8 = [&](uint32_t *index, uint32_t c, uint32_t at, const uint32_t v[K]) {
+            uint32_t w[K];
+#pragma unroll
+            for (uint32_t j = 0; j < K; j++) { w[j] = at; at += v[j]; }
+            if (c + K <= d.n_chunks) {                           // (an index starts at 16 bytes)
+                *reinterpret_cast<u32x4 *>(index + c) = u32x4{w[0], w[1], w[2], w[3]};
+                *reinterpret_cast<u32x4 *>(index + c + 4) = u32x4{w[4], w[5], w[6], w[7]};
+            } else
+#pragma unroll
+                for (uint32_t j = 0; j < K; j++) if (c + j < d.n_chunks) index[c + j] = w[j];
+        };
+        if (d.n_chunks <= kScanWaveChunks) {
+            uint32_t v[K] = {0, 0, 0, 0, 0, 0, 0, 0}, sum = 0, x = 0;
+            if (wave < (uint32_t)n_fields) {
+                load8(u + (uint64_t)wave * d.n_chunks, lane * K, v);
+#pragma unroll
+                for (uint32_t j = 0; j < K; j++) sum += v[j];
+                x = inclusive(sum);
+                if (lane == 63) wave_sum[wave] = x;
             }
             __syncthreads();
-            if (threadIdx.x == 1023) carry_s = before + x;
-            __syncthreads();
+            for (int f = 0; f < n_fields; f++) field_units[f] = wave_sum[f];
+            if (wave < (uint32_t)n_fields) {
+                uint32_t start = 0;
+                for (int f = 0; f < n_fields; f++) if (reversed ? f > (int)wave : f < (int)wave) start += field_units[f];
+                if (d.comp) {
+                    uint32_t *index = reinterpret_cast<uint32_t *>(d.comp + d.index_off[wave]);
+                    store8(index, lane * K, start + x - sum, v);
+                    if (lane == 63) index[d.n_chunks] = start + x;
+                }
+            }
+        } else
+            for (int k = 0; k < n_fields; k++) {
+                __syncthreads();
+                const int f = reversed ? n_fields - 1 - k : k;
+                uint32_t *index = d.comp ? reinterpret_cast<uint32_t *>(d.comp + d.index_off[f]) : nullptr;
+                const uint32_t field_start = carry_s;
+                for (uint32_t c0 = 0; c0 < d.n_chunks; c0 += 1024 * K) {
+                    const uint32_t c = c0 + threadIdx.x * K;
+                    uint32_t v[K], sum = 0;
+                    load8(u + (uint64_t)f * d.n_chunks, c, v);
+#pragma unroll
+                    for (uint32_t j = 0; j < K; j++) sum += v[j];
+                    const uint32_t x = inclusive(sum);
+                    if (lane == 63) wave_sum[wave] = x;
+                    __syncthreads();
+                    uint32_t before = carry_s;
+                    for (uint32_t w = 0; w < wave; w++) before += wave_sum[w];
+                    if (index) store8(index, c, before + x - sum, v);
+                    __syncthreads();
+                    if (threadIdx.x == 1023) carry_s = before + x;
+                    __syncthreads();
+                }
+                if (index && threadIdx.x == 0) index[d.n_chunks] = carry_s;
+                field_units[f] = carry_s - field_start;
+            }
+        if (threadIdx.x == 0) {
+            ScanOut o = {{0, 0, 0}, 0};
+            for (int f = 0; f < n_fields; f++) { o.field_units[f] = field_units[f]; o.total_units += field_units[f]; }
+            out[t] = o;
+            result = o;
+            if (d.comp) *reinterpret_cast<uint64_t *>(d.comp + 48) = d.payload_off + 16ull * o.total_units;
         }
-        if (index && threadIdx.x == 0) index[d.n_chunks] = carry_s;
-        field_units[f] = carry_s - field_start;
-        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        ScanOut o = {{0, 0, 0}, 0};
-        for (int f = 0; f < n_fields; f++) o.field_units[f] = field_units[f];
-        o.total_units = carry_s;
-        out[blockIdx.x] = o;
-        // at the end of the blob too (its last bytes are never used): a caller that reads the blobs back has the sizes with them
-        if (blobs) *reinterpret_cast<ScanOut *>(blobs + (uint64_t)blockIdx.x * blob_bytes + blob_bytes - sizeof(ScanOut)) = o;
-        if (d.comp) *reinterpret_cast<uint64_t *>(d.comp + 48) = d.payload_off + 16ull * carry_s;
+    if (!to.flags) return;
+    __syncthreads();
+    if (wave == 15) {
+        const uint32_t n16 = to.blobs ? blob_bytes / 16 : 1;
+        if (lane == n16 - 1) record = u32x4{result.field_units[0], result.field_units[1], result.field_units[2], result.total_units};
+        if (lane < n16) reinterpret_cast<u32x4 *>(to.records)[(uint64_t)t * n16 + lane] = record;
+        if (lane == 0) tell_host(to.flags + t);
     }
 }
 
 int launch_scan(const TensorDev *d_descs, uint32_t n_tensors, int n_fields, bool reversed, int skip_routes, const uint32_t *d_units, ScanOut *d_out,
-                uint8_t *d_blobs, uint32_t blob_bytes, void *stream)
+                const uint8_t *d_blobs, uint32_t blob_bytes, const HostRecords &to, void *stream)
 {
     if (n_tensors == 0) return 0;
+    if (to.flags && to.blobs && (!d_blobs || blob_bytes % 16 || blob_bytes > 64 * 16)) return 1;      // the record is one wavefront's
     hipLaunchKernelGGL(k_scan, dim3(n_tensors), dim3(1024), 0, (hipStream_t)stream, d_descs, n_fields, reversed ? 1 : 0, skip_routes, d_units, d_out, d_blobs,
-                       blob_bytes);
+                       blob_bytes, to);
     return (int)hipGetLastError();
 }
 
@@ -662,28 +723,35 @@ __global__ __launch_bounds__(256) void k_zero(uint64_t *p, uint64_t n)
     if (i < n) p[i] = 0;
 }
 
-// What the host hands a small call, read from its page-locked buffer by the GPU itself, and words to be cleared, in one launch; and
-// what the host reads back from one, written there (TO_HOST).  A copy through the runtime is a launch of its own with a gap of about 5 us
-// on either side.  Bound by the launch, but for the system-scope write-back that makes a host destination whole: every wavefront that
-// writes has to ask for one, so only those do.  Compress calls, by the runtime's copies and a launch that clears | with a write-back in
-// every wavefront | as it is, us: 100 BF16 tensors of 5,000 bytes 150 | 156 | 125, 200 FP8 tensors of 40,000 bytes 164 | 182 | 136, one
-// FP8 tensor of 64 KiB 64 | 62 | 61.
+// What the host hands a small call, read from its page-locked buffer by the GPU itself, and words to be cleared, in one launch; and (TO_HOST)
+// what the host waits for, written there.  A workgroup that is through with its part of the bytes sets its word of `flags` in page-locked memory: the host
+// then knows that it may fill the buffer again, or that its part has arrived.  An event behind the launch, the
+// other way to know, keeps the next kernel 5.6 us from starting.  Bound by the launch, but for the system-scope write-back that makes a host
+// destination whole; one thread asks for it.  (Compress calls, by the runtime's copies and a launch that clears | by this kernel with a write-back in
+// every wavefront | in those that write, us: 100 BF16 tensors of 5,000 bytes 150 | 156 | 125, 200 FP8 tensors of 40,000 bytes 164 | 182 | 136, one
+// FP8 tensor of 64 KiB 64 | 62 | 61.)
 template <bool TO_HOST>
-__global__ __launch_bounds__(256) void k_hand_over(const uint8_t *src, uint8_t *dst, uint32_t bytes, uint64_t *zero, uint32_t n_zero)
+__global__ __launch_bounds__(256) void k_hand_over(const uint8_t *src, uint8_t *dst, uint32_t bytes, uint64_t *zero, uint32_t n_zero, uint32_t *flags)
 {
     const uint32_t i = blockIdx.x * 256 + threadIdx.x, n16 = bytes / 16;
     if (i < n16) reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
     if (i < bytes % 16) dst[n16 * 16 + i] = src[n16 * 16 + i];
     if (i < n_zero) zero[i] = 0;
-    if (TO_HOST) __threadfence_system();
+    if (blockIdx.x >= hand_over_groups(bytes)) return;
+    // what a thread has read is in its registers once its store is issued, and the barrier is behind that of every thread
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (TO_HOST) tell_host(flags + blockIdx.x);
+        else __hip_atomic_store(flags + blockIdx.x, kTold, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
-int launch_hand_over(const void *src, void *dst, uint64_t bytes, bool to_host, uint64_t *d_zero, uint64_t n_zero, void *stream)
+int launch_hand_over(const void *src, void *dst, uint64_t bytes, bool to_host, uint64_t *d_zero, uint64_t n_zero, uint32_t *flags, void *stream)
 {
-    const uint64_t n = bytes / 16 + 16 > n_zero ? bytes / 16 + 16 : n_zero;
+    const uint64_t reads = (uint64_t)hand_over_groups((uint32_t)bytes) * 256, n = reads > n_zero ? reads : n_zero;
     const dim3 grid((uint32_t)((n + 255) / 256)), block(256);
-    if (to_host) hipLaunchKernelGGL(k_hand_over<true>, grid, block, 0, (hipStream_t)stream, (const uint8_t *)src, (uint8_t *)dst, (uint32_t)bytes, d_zero, (uint32_t)n_zero);
-    else hipLaunchKernelGGL(k_hand_over<false>, grid, block, 0, (hipStream_t)stream, (const uint8_t *)src, (uint8_t *)dst, (uint32_t)bytes, d_zero, (uint32_t)n_zero);
+    if (to_host) hipLaunchKernelGGL(k_hand_over<true>, grid, block, 0, (hipStream_t)stream, (const uint8_t *)src, (uint8_t *)dst, (uint32_t)bytes, d_zero, (uint32_t)n_zero, flags);
+    else hipLaunchKernelGGL(k_hand_over<false>, grid, block, 0, (hipStream_t)stream, (const uint8_t *)src, (uint8_t *)dst, (uint32_t)bytes, d_zero, (uint32_t)n_zero, flags);
     return (int)hipGetLastError();
 }
 
