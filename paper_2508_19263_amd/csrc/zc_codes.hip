@@ -40,18 +40,6 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
     return v;
 }
 
-// symbols of field f counted in byte b of the joint histogram: up to two (FP4 holds two elements per byte)
-__device__ __forceinline__ int joint_symbols(uint32_t fmt, int f, uint32_t b, uint32_t sym[2])
-{
-    if (fmt == ZC_FMT_FP8_E4M3) { sym[0] = f == 0 ? (b >> 3) & 0xF : ((b >> 4) & 8) | (b & 7); return 1; }
-    if (fmt == ZC_FMT_FP8_E5M2) { sym[0] = f == 0 ? (b >> 2) & 0x1F : ((b >> 5) & 4) | (b & 3); return 1; }
-    for (int h = 0; h < 2; h++) {
-        const uint32_t nib = (b >> (4 * h)) & 0xF;
-        sym[h] = f == 0 ? (nib >> 1) & 3 : ((nib >> 2) & 2) | (nib & 1);
-    }
-    return 2;
-}
-
 // Rows limit-1 .. 1 of the package-merge (the row `limit` is the leaves themselves, lw[0..n) ascending): fills
 // leaf_bits and row_size.  W: the weight type; 32 bits are enough when 16 times the sum of all weights fits (an
 // item of any row holds a leaf at most once per row below it), and halve the LDS traffic of the searches.
@@ -139,17 +127,13 @@ __global__ __launch_bounds__(kCodeThreads) void k_codes(TensorDev *descs, const 
     if (f == 2) h[tid] = hist3[512 + tid];
     else if (fmt == ZC_FMT_BF16 || grouped) h[tid] = hist3[256 * f + tid];
     else {
-        uint32_t sym[2];
-        const int k = joint_symbols(fmt, (int)f, tid, sym);
-        const unsigned long long c = hist3[tid];
-        for (int i = 0; i < k; i++) atomicAdd(&h[sym[i]], c);
+        // copies of the two fields' bins, one behind the other
+        const uint32_t stride = hist_copy_stride(fmt), second = hist_second_field(fmt);
+        for (uint32_t i = tid; i < 512; i += kCodeThreads) {
+            const uint32_t at = i % stride, v = f ? at - second : at;
+            if (at >= second == (f == 1) && v < A) atomicAdd(&h[v], hist3[i]);
+        }
     }
-    __syncthreads();
-    // FP8: chunks counted by k_hist_fp8_lanes left their field histograms in the second slot (exponents at 0..15,
-    // sign+mantissa at 16..31); the byte histogram above then covers only what that kernel did not take
-    if (fmt == ZC_FMT_FP8_E4M3 && f < 2 && tid < 16) h[tid] += hist3[256 + 16 * f + tid];
-    // FP8 E5M2: likewise for k_hist_fp8_lanes<true> (exponents at 0..31, sign+mantissa symbols at 32..39)
-    if (fmt == ZC_FMT_FP8_E5M2 && f < 2 && tid < (f ? 8u : 32u)) h[tid] += hist3[256 + (f ? 32 : 0) + tid];
     __syncthreads();
 
     // ---- leaves in (frequency, symbol) order

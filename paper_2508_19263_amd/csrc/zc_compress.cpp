@@ -109,6 +109,7 @@ CompressShape compress_shape(const Geometry &g, bool device_codes, uint64_t all_
     CompressShape sh;
     sh.cpi = chunks_per_work_item(g.S);
     sh.bf16 = g.fmt == ZC_FMT_BF16;
+    sh.delta = delta;
     sh.whole_shape = g.S == 64 && g.chunk_bytes % 1024 == 0;
     // (those kernels address a stream by 31 bits: not chunks whose stream can be longer, codes of 16 bits and all)
     const bool split_can = g.S == 64 && g.nf == 2 && g.elems_per_chunk / (uint64_t)group_of(g.fmt) * 2 < 0x7FFFF000ull;
@@ -143,9 +144,13 @@ bool compress_fast_shape(const Geometry &g, uint64_t n_elems, uint64_t bound_byt
 zc_status CompressQueue::queue_histogram(bool cleared) const
 {
     if (!cleared) LAUNCH_TRY(launch_zero(d_hist(), (uint64_t)T * 3 * 256, stream));
+    if (hist_in_planes(g.fmt)) {
+        LAUNCH_TRY(launch_hist_planes(g.fmt, sh.delta, d_descs(), d_list(w.hist_work), n_hist, d_list(w.scale_work), n_scale, d_hist(), stream));
+        LAUNCH_TRY(launch_hist_fp8_lanes(sh.lanes_e5m2, sh.delta, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), d_lane_counts(), stream));
+        return ZC_OK;
+    }
     LAUNCH_TRY(launch_hist(g.fmt, d_descs(), d_list(w.hist_work), n_hist, 0, d_hist(), stream));
-    if (sh.lanes8) LAUNCH_TRY(launch_hist_rows8_lanes(g.fmt, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), (uint32_t *)d_lane_counts(), stream));
-    else LAUNCH_TRY(launch_hist_fp8_lanes(sh.lanes_e5m2, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), d_lane_counts(), stream));
+    LAUNCH_TRY(launch_hist_rows8_lanes(g.fmt, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), (uint32_t *)d_lane_counts(), stream));
     if (g.nf == 3) LAUNCH_TRY(launch_hist(g.fmt, d_descs(), d_list(w.scale_work), n_scale, (int)scale_block(g.fmt), d_hist(), stream));
     return ZC_OK;
 }
@@ -297,28 +302,12 @@ zc_status build_codes(const Geometry &g, uint32_t policy, uint64_t n_elems, cons
         FieldCode &c = fc[f];
         std::memset(&c, 0, sizeof(c));
         const int sb = sym_bits(g.fmt, (int)f), A = 1 << sb;
-        // marginals of the joint byte histogram (FP8: one element per byte, FP4: two)
-        // formats with 8-bit symbols in both fields are counted per field by the kernel
+        // 8-bit symbols in both fields: 256 bins per field; else copies of few bins (E5M2's symbols, of 8 bits too, are below 32 and 8, with clear bins behind them)
         if (g.fmt == ZC_FMT_BF16 || (group_of(g.fmt) > 1 && f < 2)) std::memcpy(c.hist, hist3 + 256 * f, 256 * 8);
-        else if (g.fmt == ZC_FMT_FP8_E4M3) {
-            for (int b = 0; b < 256; b++) {
-                const int sym = f == 0 ? (b >> 3) & 0xF : ((b >> 4) & 8) | (b & 7);
-                c.hist[sym] += hist3[b];
-            }
-        } else if (g.fmt == ZC_FMT_FP8_E5M2) {
-            for (int b = 0; b < 256; b++) {
-                const int sym = f == 0 ? (b >> 2) & 0x1F : ((b >> 5) & 4) | (b & 3);
-                c.hist[sym] += hist3[b];
-            }
-        } else if (f == 2) std::memcpy(c.hist, hist3 + 512, 256 * 8);
-        else {
-            for (int b = 0; b < 256; b++)
-                for (int h = 0; h < 2; h++) {
-                    const int nib = (b >> (4 * h)) & 0xF;
-                    const int sym = f == 0 ? (nib >> 1) & 3 : ((nib >> 2) & 2) | (nib & 1);
-                    c.hist[sym] += hist3[b];
-                }
-        }
+        else if (f == 2) std::memcpy(c.hist, hist3 + 512, 256 * 8);
+        else
+            for (uint32_t copy = 0; copy < hist_copies(g.fmt); copy++)
+                for (uint32_t v = 0; v < (f ? 16u : 32u) && v < (uint32_t)A; v++) c.hist[v] += hist3[copy * hist_copy_stride(g.fmt) + f * hist_second_field(g.fmt) + v];
         c.n_symbols = field_symbols(g.fmt, (int)f, n_elems);
         uint64_t sum = 0;
         for (int v = 0; v < A; v++) { sum += c.hist[v]; if (c.hist[v]) { c.distinct++; c.konst = (uint32_t)v; } }
@@ -664,7 +653,6 @@ private:
         order_for_xcds(whole_work);
         order_for_xcds(other_work);
         order_for_xcds(slow_work);
-        order_for_xcds(lane_hist_work);
         set_list_sizes();
         const Piece all[9] = {{w.descs, descs.data(), T * sizeof(TensorDev)},
                               {w.hist_work, hist_work.data(), hist_work.size() * sizeof(WorkItem)},

@@ -13,181 +13,7 @@ namespace zc {
 // a lane owns every 64th 16-byte run, and the number of words its stream takes follows from its bit total alone
 // (shown at k_sizes_fp8_counts).  So the histogram pass, which reads the chunk anyway, also counts the exponents
 // per lane (16 counts of 16 bits per lane, 2 KiB per chunk of 256 KiB), and once the code is known the size pass
-// reads those counts instead of the source.
-//
-// k_hist_fp8_lanes: one workgroup per whole chunk of kHistBlockBytes (= the chunk size; the host uses this kernel
-// for no other).  Thread t takes the runs t, t+256, ...: all of chunk lane t % 64, which it shares with three
-// threads of the other wavefronts.  Every chunk lane has a histogram of all 256 byte values in LDS (16-bit
-// counters, lanes l and l + 32 in the two halves of word [value][l % 32]: one atomic addition of a constant per
-// byte; each half of a wavefront falls into 32 different banks, so nothing collides, whatever the data; a lane
-// holds 4096 bytes, so nothing overflows).  At the end the lanes' histograms are folded into exponent counts
-// per lane, which go to lane_counts, and into the chunk's two field histograms, which are added to the tensor's
-// second histogram slot (exponents at 0..15, sign+mantissa at 16..31; the first slot keeps the byte histogram
-// of what k_hist counts, a short last chunk).
-// E5M2 (s eeeee mm) is counted the same way and folded differently: 32 exponent counts and 8 sign+mantissa counts per
-// lane (80 bytes, 5 KiB per chunk), field histograms at 0..31 and 32..39 of the second slot.
-template <bool E5M2>
-__global__ __launch_bounds__(256) void k_hist_fp8_lanes(const TensorDev *descs, const WorkItem *work, uint64_t *hist, uint16_t *lane_counts)
-{
-    static_assert(kHistBlockBytes / 64 < 65536, "a lane's count of one byte value fits 16 bits");
-    __shared__ uint32_t cnt[256 * 32];                            // 32 KiB
-    const WorkItem it = work[blockIdx.x];
-    const TensorDev &d = descs[it.tensor];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, quarter = tid >> 6;
-    const uint64_t start = (uint64_t)it.first * kHistBlockBytes;
-    if (d.chunk_bytes != kHistBlockBytes || start + kHistBlockBytes > d.n_elems) return;      // whole workgroup; the host never asks for this
-    for (uint32_t i = tid; i < 256 * 32; i += 256) cnt[i] = 0;
-    __syncthreads();
-    const uint8_t *p = d.src + start;
-    const uint8_t *base = d.base ? d.base + start : nullptr;
-    // byte value b of lane l: word b * 32 + l % 32, half l / 32 (the same for everything a thread counts)
-    const uint32_t l4 = (lane & 31) * 4, inc = lane < 32 ? 1u : 0x10000u;
-    char *const lds = reinterpret_cast<char *>(cnt);
-    auto count = [&](const uint4 &v) {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            atomicAdd(reinterpret_cast<uint32_t *>(lds + (((w[i] << 7) & 0x7F80u) | l4)), inc);
-            atomicAdd(reinterpret_cast<uint32_t *>(lds + (((w[i] >> 1) & 0x7F80u) | l4)), inc);
-            atomicAdd(reinterpret_cast<uint32_t *>(lds + (((w[i] >> 9) & 0x7F80u) | l4)), inc);
-            atomicAdd(reinterpret_cast<uint32_t *>(lds + (((w[i] >> 17) & 0x7F80u) | l4)), inc);
-        }
-    };
-    // eight 16-byte loads per thread in flight at a time
-    constexpr uint32_t kStep = 256 * 16, kDepth = 8;
-    static_assert(kHistBlockBytes % (kStep * kDepth) == 0, "whole rounds");
-    for (uint32_t off = tid * 16; off < kHistBlockBytes; off += kDepth * kStep) {
-        uint4 v[kDepth];
-#pragma unroll
-        for (uint32_t k = 0; k < kDepth; k++) v[k] = *reinterpret_cast<const uint4 *>(p + off + k * kStep);
-        if (base) {
-#pragma unroll
-            for (uint32_t k = 0; k < kDepth; k++) v[k] = xor4(v[k], *reinterpret_cast<const uint4 *>(base + off + k * kStep));
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < kDepth; k++) count(v[k]);
-    }
-    __syncthreads();
-    if (E5M2) {
-        // Thread (lane, quarter) folds the byte values 64*quarter .. +63 of its lane: value = s eeeee mm, so a quarter is one
-        // sign, the exponents 16 * (quarter & 1) .. + 15 and all four mantissas.
-        uint32_t c[32];
-#pragma unroll
-        for (int i = 0; i < 32; i++) c[i] = 0;
-        const uint32_t half_shift = lane < 32 ? 0u : 16u;
-#pragma unroll
-        for (int v = 0; v < 64; v++) {
-            const uint32_t n = (cnt[(quarter * 64 + v) * 32 + (lane & 31)] >> half_shift) & 0xFFFFu;
-            c[v >> 2] += n;                                      // exponent 16 * (quarter & 1) + v / 4
-            c[16 + (v & 3)] += n;                                // sign+mantissa symbol 4 * (quarter >> 1) + v % 4
-        }
-        const uint32_t e_hi = quarter & 1, sgn = quarter >> 1;
-        __syncthreads();                                         // every thread has read its part of cnt: the array is free
-        uint32_t *const part = cnt;                              // rows of 21 words against bank conflicts
-#pragma unroll
-        for (int i = 0; i < 20; i++) part[(quarter * 64 + lane) * 21 + i] = c[i];
-        // the chunk's field histograms: the wavefront's 20 counts summed over its lanes in a butterfly that halves what a
-        // lane carries at every step; lane j < 32 ends with the total of count bitrev5(j)
-#pragma unroll
-        for (int step = 0; step < 5; step++) {
-            const int n = 16 >> step;
-            const uint32_t upper = 0u - ((lane >> step) & 1u);   // all ones in the lanes that keep the upper half
-#pragma unroll
-            for (int i = 0; i < n; i++) {
-                // (bitwise, so that the counts stay in registers: a choice between two array elements becomes an
-                // element at a computed index, which the compiler looks up with a chain of compares)
-                const uint32_t a = c[i], b = c[n + i], d = (a ^ b) & upper;
-                c[i] = (a ^ d) + (uint32_t)__shfl_xor((int)(b ^ d), 1 << step, 64);      // keeps b, gives a where upper
-            }
-        }
-        c[0] += (uint32_t)__shfl_xor((int)c[0], 32, 64);
-        const uint32_t k = ((lane & 1) << 4) | ((lane & 2) << 2) | (lane & 4) | ((lane & 8) >> 2) | ((lane & 16) >> 4);
-        if (lane < 32 && k < 20 && c[0]) {
-            unsigned long long *slot = reinterpret_cast<unsigned long long *>(&hist[((uint64_t)it.tensor * 3 + 1) * 256]);
-            atomicAdd(slot + (k < 16 ? e_hi * 16 + k : 32 + sgn * 4 + (k - 16)), (unsigned long long)c[0]);
-        }
-        __syncthreads();
-        // the lane's 40 counts: quarters 0 and 1 write the exponents 0..15 and 16..31 (both signs added), quarter 2 the eight
-        // sign+mantissa symbols (both exponent halves added)
-        const uint64_t chunk_global = (uint64_t)(d.units_off / 2) + it.first;
-        uint16_t *mine = lane_counts + (chunk_global * 64 + lane) * 40;
-        if (quarter < 2) {
-            const uint32_t *pa = part + ((0 * 2 + quarter) * 64 + lane) * 21, *pb = part + ((1 * 2 + quarter) * 64 + lane) * 21;
-            uint32_t w[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) w[j] = (pa[2 * j] + pb[2 * j]) | ((pa[2 * j + 1] + pb[2 * j + 1]) << 16);
-            uint4 *out = reinterpret_cast<uint4 *>(mine + quarter * 16);
-            out[0] = make_uint4(w[0], w[1], w[2], w[3]);
-            out[1] = make_uint4(w[4], w[5], w[6], w[7]);
-        } else if (quarter == 2) {
-            uint32_t m[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const uint32_t sg = j >> 2;
-                m[j] = part[((sg * 2 + 0) * 64 + lane) * 21 + 16 + (j & 3)] + part[((sg * 2 + 1) * 64 + lane) * 21 + 16 + (j & 3)];
-            }
-            *reinterpret_cast<uint4 *>(mine + 32) = make_uint4(m[0] | (m[1] << 16), m[2] | (m[3] << 16), m[4] | (m[5] << 16), m[6] | (m[7] << 16));
-        }
-        return;
-    }
-    // Thread (lane, quarter) folds the byte values 64*quarter .. +63 of its lane: value = s eeee mmm, so a quarter
-    // is one sign, eight exponents and all eight mantissas.
-    uint32_t ce[8], cm[8];
-#pragma unroll
-    for (int i = 0; i < 8; i++) { ce[i] = 0; cm[i] = 0; }
-    const uint32_t half_shift = lane < 32 ? 0u : 16u;
-#pragma unroll
-    for (int v = 0; v < 64; v++) {
-        const uint32_t c = (cnt[(quarter * 64 + v) * 32 + (lane & 31)] >> half_shift) & 0xFFFFu;
-        ce[v >> 3] += c;
-        cm[v & 7] += c;
-    }
-    const uint32_t e0 = (quarter & 1) * 8, s = quarter >> 1;      // the quarter's first exponent and its sign
-    __syncthreads();                                             // every thread has read its part of cnt: the array is free
-    // the exponent counts of (lane, quarter), in rows of 9 words against bank conflicts
-    uint32_t *const part = cnt;
-#pragma unroll
-    for (int i = 0; i < 8; i++) part[(quarter * 64 + lane) * 9 + i] = ce[i];
-    // the chunk's field histograms: every lane of this wavefront holds partial counts of the same 16 symbols.  They are
-    // summed over the lanes in a butterfly that halves what a lane carries at every step (8, 4, 2 and 1 exchanges, then
-    // two more of the one value left), so that lane j < 16 ends with the total of symbol j.
-    {
-        uint32_t c[16];
-#pragma unroll
-        for (int i = 0; i < 8; i++) { c[i] = ce[i]; c[8 + i] = cm[i]; }
-#pragma unroll
-        for (int step = 0; step < 4; step++) {
-            const int n = 8 >> step;                             // values kept per lane after this step
-            const uint32_t upper = 0u - ((lane >> step) & 1u);   // all ones in the lanes that keep the upper half
-#pragma unroll
-            for (int i = 0; i < n; i++) {
-                // (bitwise, so that the counts stay in registers: a choice between two array elements becomes an
-                // element at a computed index, which the compiler looks up with a chain of compares)
-                const uint32_t a = c[i], b = c[n + i], d = (a ^ b) & upper;
-                c[i] = (a ^ d) + (uint32_t)__shfl_xor((int)(b ^ d), 1 << step, 64);      // keeps b, gives a where upper
-            }
-        }
-        c[0] += (uint32_t)__shfl_xor((int)c[0], 16, 64);
-        c[0] += (uint32_t)__shfl_xor((int)c[0], 32, 64);
-        // bit `step` of the lane chose the half it kept at that step, i.e. bit 3 - step of the symbol
-        const uint32_t sym = ((lane & 1) << 3) | ((lane & 2) << 1) | ((lane & 4) >> 1) | ((lane & 8) >> 3);
-        if (lane < 16 && c[0]) {
-            unsigned long long *slot = reinterpret_cast<unsigned long long *>(&hist[((uint64_t)it.tensor * 3 + 1) * 256]);
-            atomicAdd(slot + (sym < 8 ? e0 + sym : 16 + s * 8 + (sym - 8)), (unsigned long long)c[0]);
-        }
-    }
-    __syncthreads();
-    // thread t writes the counts of exponents 4*(t/64) .. +3 of lane t%64: those came from the quarters with the
-    // same exponent half (quarter & 1 == t/128), one per sign
-    {
-        const uint32_t s0 = quarter * 4, half = quarter >> 1, i0 = s0 & 7;
-        const uint32_t *pa = part + ((half + 0) * 64 + lane) * 9 + i0, *pb = part + ((half + 2) * 64 + lane) * 9 + i0;
-        const uint32_t c0 = pa[0] + pb[0], c1 = pa[1] + pb[1], c2 = pa[2] + pb[2], c3 = pa[3] + pb[3];
-        const uint64_t chunk_global = (uint64_t)(d.units_off / 2) + it.first;      // two fields: units_off counts two entries per chunk
-        const uint2 packed = make_uint2(c0 | (c1 << 16), c2 | (c3 << 16));
-        *reinterpret_cast<uint2 *>(lane_counts + (chunk_global * 64 + lane) * 16 + s0) = packed;
-    }
-}
+// reads those counts instead of the source.  (k_hist_fp8_lanes counts: zc_hist_planes.hip.)
 
 // Stream sizes of full chunks from the per-lane exponent counts.  The decoder of a lane asks for a word at a
 // refill step (every 4 symbols) when it holds k <= 32 unread bits, one word per step at most.  With B(g) the bits
@@ -246,6 +72,13 @@ __global__ __launch_bounds__(256) void k_sizes_fp8_counts(const TensorDev *descs
 // whatever the data; a lane holds 2,048 symbols of a field).  At the end the arrays go to lane_counts as they are
 // (field, symbol, word: 64 KiB at lane_counts + chunk * 16384 words), and their sums over the lanes are added to the
 // tensor's histograms, beside what k_hist counts.
+// (non-temporal: read once, and more than the caches hold.  The delta of 2^30 values: counting 979 - 1,013 us -> 865 - 893 with this and the chunks in their
+// natural order, sizes from the counts as before)
+__device__ __forceinline__ uint4 load_once(const uint8_t *p)
+{
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
 template <int FMT>
 __global__ __launch_bounds__(512) void k_hist_rows8_lanes(const TensorDev *descs, const WorkItem *work, uint64_t *hist, uint32_t *lane_counts)
 {
@@ -288,10 +121,10 @@ __global__ __launch_bounds__(512) void k_hist_rows8_lanes(const TensorDev *descs
     for (uint32_t off = tid * 16; off < kHistBlockBytes; off += kDepth * kStep) {
         uint4 v[kDepth];
 #pragma unroll
-        for (uint32_t k = 0; k < kDepth; k++) v[k] = *reinterpret_cast<const uint4 *>(p + off + k * kStep);
+        for (uint32_t k = 0; k < kDepth; k++) v[k] = load_once(p + off + k * kStep);
         if (base) {
 #pragma unroll
-            for (uint32_t k = 0; k < kDepth; k++) v[k] = xor4(v[k], *reinterpret_cast<const uint4 *>(base + off + k * kStep));
+            for (uint32_t k = 0; k < kDepth; k++) v[k] = xor4(v[k], load_once(base + off + k * kStep));
         }
 #pragma unroll
         for (uint32_t k = 0; k < kDepth; k++) count(v[k]);
@@ -347,11 +180,11 @@ __global__ __launch_bounds__(256) void k_sizes_rows8_counts(const TensorDev *des
 #pragma unroll
         for (int f = 0; f < 2; f++) {
             if (!coded[f]) continue;
-            const uint4 *rows = reinterpret_cast<const uint4 *>(lane_counts + chunk_global * (2 * 256 * 32) + f * (256 * 32)) + lane;
+            const uint8_t *rows = reinterpret_cast<const uint8_t *>(reinterpret_cast<const uint4 *>(lane_counts + chunk_global * (2 * 256 * 32) + f * (256 * 32)) + lane);
             uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll 4
             for (uint32_t i = 0; i < 32; i++) {
-                const uint4 c = rows[i * 64];                    // symbol 8 * i + lane / 8, chunk lanes 4 * (lane % 8) .. + 3 and those + 32
+                const uint4 c = load_once(rows + i * 1024);                    // symbol 8 * i + lane / 8, chunk lanes 4 * (lane % 8) .. + 3 and those + 32
                 const uint32_t len = lens[f][8 * i + (lane >> 3)];
                 const uint32_t w[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
@@ -395,14 +228,6 @@ __global__ __launch_bounds__(256) void k_sizes_rows8_counts(const TensorDev *des
         my[chunk] = u[0];
         my[nc + chunk] = u[1];
     }
-}
-
-int launch_hist_fp8_lanes(bool e5m2, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint64_t *d_hist, uint16_t *d_lane_counts, void *stream)
-{
-    if (n_work == 0) return 0;
-    if (e5m2) hipLaunchKernelGGL(k_hist_fp8_lanes<true>, dim3(n_work), dim3(256), 0, (hipStream_t)stream, d_descs, d_work, d_hist, d_lane_counts);
-    else hipLaunchKernelGGL(k_hist_fp8_lanes<false>, dim3(n_work), dim3(256), 0, (hipStream_t)stream, d_descs, d_work, d_hist, d_lane_counts);
-    return (int)hipGetLastError();
 }
 
 int launch_sizes_fp8_counts(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint16_t *d_lane_counts,

@@ -108,6 +108,13 @@ constexpr uint32_t kWavesPerGroup = 4;
 constexpr uint32_t kSplitChunkBytes = 32 * 1024;
 inline uint64_t split_chunk_limit(uint32_t fmt, bool delta) { return delta ? 512 : fmt == ZC_FMT_FP8_E5M2 ? 1024 : 768; }
 
+// The tensor's bins of the formats that are counted in bit planes: their fields have at most 40 values together, and the first two
+// thirds of the 768 bins hold copies of them, for as many workgroups at a time to add to
+ZC_HOST_DEVICE constexpr bool hist_in_planes(uint32_t fmt) { return fmt == ZC_FMT_FP8_E4M3 || fmt == ZC_FMT_FP8_E5M2 || fmt == ZC_FMT_FP4_E2M1_MX || fmt == ZC_FMT_FP4_E2M1_NV; }
+ZC_HOST_DEVICE constexpr uint32_t hist_copy_stride(uint32_t fmt) { return fmt == ZC_FMT_FP8_E5M2 ? 64u : 32u; }
+ZC_HOST_DEVICE constexpr uint32_t hist_second_field(uint32_t fmt) { return fmt == ZC_FMT_FP8_E5M2 ? 32u : 16u; }     // where a copy's sign+mantissa bins start
+ZC_HOST_DEVICE constexpr uint32_t hist_copies(uint32_t fmt) { return 512u / hist_copy_stride(fmt); }
+
 // per-tensor scratch written by the scan kernel and read back by the host
 struct ScanOut { uint32_t field_units[kMaxFields]; uint32_t total_units; };
 
@@ -137,6 +144,9 @@ int launch_codes(TensorDev *d_descs, uint32_t n_tensors, const uint64_t *d_hist,
 // ---- kernel launchers (zc_kernels.hip); all return a hipError_t as int ------
 int launch_hist(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                 int scales_view, uint64_t *d_hist, void *stream);
+// FP8 and FP4 in single symbols (hist_in_planes), blocks of elements and, FP4, of scale bytes in one launch; delta: some tensor has a base (zc_hist_planes.hip)
+int launch_hist_planes(uint32_t fmt, bool delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const WorkItem *d_scale_work, uint32_t n_scale,
+                       uint64_t *d_hist, void *stream);
 int launch_zero(uint64_t *d_words, uint64_t n_words, void *stream);
 // between a page-locked host buffer and device memory, either way (both aligned to 16 bytes); flags: hand_over_groups(bytes) words of
 // page-locked memory, set when the bytes have been read, or (to_host) have arrived; clears n_zero words at d_zero too
@@ -194,7 +204,7 @@ int launch_sizes_fp8(const TensorDev *d_descs, const WorkItem *d_work, uint32_t 
 // e5m2: the E5M2 layout instead, 32 exponent and 8 sign+mantissa counts per lane (40 u16, 5 KiB per chunk, at
 // lane_counts[(units_off / 2 + chunk) * 2560]), read by launch_sizes_e5m2_counts (work list of the generic whole-chunk
 // size pass, which it replaces for every tensor)
-int launch_hist_fp8_lanes(bool e5m2, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint64_t *d_hist, uint16_t *d_lane_counts, void *stream);
+int launch_hist_fp8_lanes(bool e5m2, bool delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint64_t *d_hist, uint16_t *d_lane_counts, void *stream);
 int launch_sizes_e5m2_counts(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint16_t *d_lane_counts,
                              uint32_t *d_units, void *stream);
 // BF16 / FP8 in byte symbols, 64 lanes, chunks of kHistBlockBytes: the same for fields of 8-bit symbols (256 counts

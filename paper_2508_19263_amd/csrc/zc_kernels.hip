@@ -21,16 +21,12 @@
 namespace zc {
 
 // ------------------------------------------------------------------------ histogram
-// One workgroup counts kHistBlockBytes of one tensor into LDS (8 replicas per bin to spread
-// same-address atomics of skewed data) and merges into the tensor's 64-bit global bins.
-// BYTES: one 256-bin histogram of the bytes (FP8: the joint (exponent, sign+mantissa)
-// histogram; FP4: joint over two elements; E8M0 scales: the field itself); the host takes
-// the marginals.  BF16: two histograms, exponent and sign+mantissa symbol.
+// Fields of 256 symbols; those of fewer are counted in bit planes (zc_hist_planes.hip).  One workgroup counts kHistBlockBytes of one tensor
+// into LDS and merges into the tensor's 64-bit global bins.
 
 // One copy of the 256 bins per LDS bank: lane l counts in copy l % 32, at word bin * 32 + l % 32, so the
 // 32 lanes of an LDS pass always hit 32 different banks whatever the data is.
-// FMT == 0: histogram of the bytes themselves (FP8 and FP4 elements, whose field histograms are marginals
-// of the byte histogram, and the FP4 scale bytes).  Otherwise a format whose two fields have 8-bit symbols
+// FMT == 0: histogram of the FP4 scale bytes.  Otherwise a format whose two fields have 8-bit symbols
 // (BF16, the byte-grouped formats): the run is split and both fields are counted in one word, field 0 in
 // the low half and field 1 in the high half: a copy is fed by 8 threads with at most 512 symbols each per
 // block, so neither half can overflow.
