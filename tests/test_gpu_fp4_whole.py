@@ -1,0 +1,34 @@
+"""Whole FP4 chunks whose rows are dealt out to several workgroups: chunks of fewer rows than wavefronts and of many, scale streams of part of a
+row to several rows, scales of one value, of few and of nearly all, element fields that are stored plainly and (few values) that are not, deltas.  Whole containers against the oracle's, and
+back: exact."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import zc_oracle as o
+from paper_2508_19263_amd import zc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+KIB = 1024
+
+
+@pytest.mark.parametrize("policy", [zc.POLICY_HUFF_ALL, zc.POLICY_AUTO])
+@pytest.mark.parametrize("chunk", [1, 3, 16, 64, 256])
+@pytest.mark.parametrize("fmt", [zc.FMT_FP4_E2M1_MX, zc.FMT_FP4_E2M1_NV, zc.FMT_FP4_E2M1_MX_BYTES])
+def test_whole_chunks(fmt, chunk, policy):
+    rng = np.random.default_rng(chunk)
+    for values, spread, delta in ((16, 1, False), (16, 6, True), (16, 120, False), (3, 3, False)):
+        nbytes = 5 * chunk * KIB + (chunk * KIB // 2)
+        n = nbytes * 2
+        print("case", fmt, chunk, policy, values, spread, delta, flush=True)
+        x = (rng.integers(0, values, nbytes) | rng.integers(0, values, nbytes) << 4).astype(np.uint8)
+        base = rng.integers(0, 256, nbytes).astype(np.uint8) if delta else None
+        scales = (100 + np.minimum(rng.geometric(1 / spread, n // zc.scale_block(fmt)), 155)).astype(np.uint8)
+        kw = {"xor_base": base} if delta else {}
+        want = o.compress(x, n, o.params(fmt, chunk * KIB, (0, 0, 0), 64, policy=o.POLICY_AUTO if policy == zc.POLICY_AUTO else o.POLICY_HUFF_ALL), scales=scales, **kw)
+        on = [None if a is None else torch.from_numpy(a).to(DEV) for a in (x, base, scales)]
+        got, info = zc.compress(on[0], n, zc.params(fmt, chunk * KIB, streams=64, policy=policy), xor_base=on[1], scales=on[2])
+        assert np.array_equal(got.cpu().numpy(), want), (values, spread)
+        out, s = zc.decompress(got, info, xor_base=on[1])
+        assert torch.equal(out, on[0]) and torch.equal(s, on[2])
