@@ -28,6 +28,13 @@ bool lane_counts_shape(const Geometry &g) { return g.fmt == ZC_FMT_FP8_E4M3 && g
 bool lane_counts8_shape(const Geometry &g) { return (g.fmt == ZC_FMT_BF16 || g.fmt == ZC_FMT_FP8_E4M3_BYTES) && g.S == 64 && g.chunk_bytes == kHistBlockBytes; }
 // and for FP8 E5M2 (k_hist_fp8_lanes<true>, k_sizes_e5m2_counts): 40 counts per chunk lane
 bool lane_counts_e5m2_shape(const Geometry &g) { return g.fmt == ZC_FMT_FP8_E5M2 && g.S == 64 && g.chunk_bytes == kHistBlockBytes; }
+// and for FP8 E4M3 pages (k_hist_pages, k_sizes_pages): as many rows as a pair's counts of 8 bits hold, and whole passes of 256 pairs to a histogram block
+bool page_counts_shape(const Geometry &g)
+{
+    if (g.fmt != ZC_FMT_FP8_E4M3 || g.S < 4 || g.S >= 64 || g.chunk_bytes % (16 * g.S)) return false;
+    const uint32_t rows = g.chunk_bytes / (16 * g.S);
+    return rows >= 1 && rows <= 16 && (rows & (rows - 1)) == 0;
+}
 
 zc_status plan_workspace(const Geometry &g, const uint64_t *n_elems, uint32_t T, Workspace *w)
 {
@@ -68,6 +75,10 @@ zc_status plan_workspace(const Geometry &g, const uint64_t *n_elems, uint32_t T,
     // FP8 E5M2, same geometry: 32 exponent and 8 sign+mantissa counts of 16 bits per chunk lane
     if (lane_counts_e5m2_shape(g)) off = align256(off + units / 2 * (64 * 40 * 2));
     w->total = off;
+    const uint64_t pairs = page_counts_shape(g) ? units / 2 * g.S : 0;
+    w->page_counts = off; off = align256(off + pairs * 16);
+    w->page_lasts = off; off = align256(off + pairs * 2);
+    w->wanted = off;
     w->n_hist_work = (uint32_t)hw; w->n_scale_work = (uint32_t)sw; w->n_chunk_work = (uint32_t)cw; w->n_units = units;
     return ZC_OK;
 }
@@ -108,6 +119,7 @@ CompressShape compress_shape(const Geometry &g, bool device_codes, uint64_t all_
 {
     CompressShape sh;
     sh.cpi = chunks_per_work_item(g.S);
+    sh.pages = device_codes && page_counts_shape(g);
     sh.bf16 = g.fmt == ZC_FMT_BF16;
     sh.delta = delta;
     sh.whole_shape = g.S == 64 && g.chunk_bytes % 1024 == 0;
@@ -144,6 +156,10 @@ bool compress_fast_shape(const Geometry &g, uint64_t n_elems, uint64_t bound_byt
 zc_status CompressQueue::queue_histogram(bool cleared) const
 {
     if (!cleared) LAUNCH_TRY(launch_zero(d_hist(), (uint64_t)T * 3 * 256, stream));
+    if (sh.pages) {
+        LAUNCH_TRY(launch_hist_pages(sh.delta, d_descs(), d_list(w.hist_work), n_hist, g.chunk_bytes / g.S * 256, d_hist(), ws + w.page_counts, ws + w.page_lasts, stream));
+        return ZC_OK;
+    }
     if (hist_in_planes(g.fmt)) {
         LAUNCH_TRY(launch_hist_planes(g.fmt, sh.delta, d_descs(), d_list(w.hist_work), n_hist, d_list(w.scale_work), n_scale, d_hist(), stream));
         LAUNCH_TRY(launch_hist_fp8_lanes(sh.lanes_e5m2, sh.delta, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), d_lane_counts(), stream));
@@ -174,6 +190,7 @@ zc_status CompressQueue::queue_sizes_and_scan() const
                                                  (uint64_t *)(ws + chain_status), (uint64_t *)(ws + chain_counter), (ScanOut *)(ws + w.scan), stream));
     else if (g.S == 64 && sh.lanes) LAUNCH_TRY(launch_sizes_fp8_counts(d_descs(), d_list(w.fast_work), n_fast, d_enc(), d_lane_counts(), d_units(), stream));
     else if (g.S == 64) LAUNCH_TRY(launch_sizes_fp8(d_descs(), d_list(w.fast_work), n_fast, d_enc(), d_units(), stream));
+    else if (sh.pages) LAUNCH_TRY(launch_sizes_pages(d_descs(), d_list(w.fast_work), n_fast, d_enc(), ws + w.page_counts, ws + w.page_lasts, d_units(), sh.fast_step, stream));
     else LAUNCH_TRY(launch_encode_fp8_sub(g.S, 0, sh.bf16, d_descs(), d_list(w.fast_work), n_fast, d_enc(), d_units(), sh.fast_step, stream));
     // generic kernels: the whole-chunk list leaves route 1 to the FP8 kernels (route 2 there is the BF16 encoder,
     // whose sizes come from this pass); the list of page-shaped tensors leaves both routes to the page kernels
@@ -461,6 +478,7 @@ private:
         bool delta = false;
         for (uint32_t t = 0; t < T; t++) delta = delta || tensors[t].d_xor_base;
         sh = compress_shape(g, uses_device_codes(), all_chunks, delta);
+        sh.pages = sh.pages && ws_bytes >= w.wanted;
         for (uint32_t t = 0; t < T; t++) {
             zc_tensor &x = tensors[t];
             const uint64_t nc = ncs[t];
@@ -628,6 +646,7 @@ private:
             items += (ncs[t] + step - 1) / step;
         }
         if (items + 1 > (uint64_t)T * 3 * 256) return;
+        sh.pages = false;                                        // (nobody asks for sizes)
         q.chained = true; q.chain_hold = chained_hold(); q.chain_step = step; q.chain_counter = w.hist; q.chain_status = w.hist + 8;
     }
 
@@ -881,7 +900,7 @@ uint64_t zc_workspace_bytes(const uint64_t *n_elems, uint32_t n_tensors, const z
     Geometry g;
     Workspace w;
     if (!n_elems || check_params(params, &g) || plan_workspace(g, n_elems, n_tensors, &w)) return 0;
-    return w.total;
+    return w.wanted;
 }
 
 zc_status zc_compress_batch(zc_tensor *tensors, uint32_t n_tensors, const zc_params *params, void *d_ws, uint64_t ws_bytes, void *stream)

@@ -31,8 +31,13 @@ template <> struct Planes<ZC_FMT_FP8_E4M3> { static constexpr int PE = 4, PM = 4
 template <> struct Planes<ZC_FMT_FP8_E5M2> { static constexpr int PE = 5, PM = 3; static constexpr bool BYTE = true; static constexpr int E[5] = {2, 3, 4, 5, 6}, M[3] = {0, 1, 7}; };
 template <> struct Planes<ZC_FMT_FP4_E2M1_MX> { static constexpr int PE = 2, PM = 2; static constexpr bool BYTE = false; static constexpr int E[2] = {1, 2}, M[2] = {0, 3}; };
 
-// (mask & x) | (~mask & y)
-__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t x, uint32_t y) { return (x & mask) | (y & ~mask); }
+// (mask & x) | (~mask & y) in one instruction (the compiler makes two of most of these)
+__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t x, uint32_t y)
+{
+    uint32_t r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(mask), "v"(x), "v"(y));
+    return r;
+}
 
 // eight words -> eight bit planes
 template <int S>
@@ -312,6 +317,161 @@ __global__ __launch_bounds__(256) void k_hist_fp8_lanes(const TensorDev *descs, 
         for (uint32_t j = 0; j < kMine; j++) out[j] = w[j];
 }
 
+// FP8 E4M3 pages (fewer than 64 lanes per chunk, page_counts_shape): a thread takes a whole (page, lane) pair at a time, so that its counts are
+// the pair's: 16 counts of 8 bits (255 stands for 256, all a pair can hold, as no other pair of counts adds up to one less than it should) and the
+// exponents of its last four symbols, from which k_sizes_pages works in place of a second read of the source: 18 bytes where the size pass
+// read 256.  2.15 GB of pages of 2 KiB: 407 us against 319 without the pairs' counts (the loads of a wavefront lie in eight pages), and 33 us for the sizes
+// against 366 - 419 for a pass over the source.
+template <bool DELTA, int NT>
+__global__ __launch_bounds__(256) void k_hist_pages(const TensorDev *descs, const WorkItem *work, uint32_t split, uint64_t *hist, u32x4 *counts, uint16_t *lasts)
+{
+    constexpr int FMT = ZC_FMT_FP8_E4M3;
+    using C = FieldCounts<FMT>;
+    __shared__ uint32_t sums[4 * (C::NE + C::NM)];
+    const uint32_t tid = threadIdx.x;
+    const WorkItem it = work[blockIdx.x / split];
+    const TensorDev &d = descs[it.tensor];
+    const uint32_t cb = uni32(d.chunk_bytes), S = uni32(d.streams), rows = cb / (16 * S), part = kHistBlockBytes / split;
+    const uint64_t n = d.n_elems, n_pages = n / cb, paged = n_pages * cb, start = (uint64_t)it.first * kHistBlockBytes + (uint64_t)(blockIdx.x % split) * part;
+    if (start >= n) return;                                      // whole workgroup: the block ends before this part
+    const uint32_t whole = start >= paged ? 0u : paged - start < part ? (uint32_t)(paged - start) : part;      // (whole pages: a part is whole passes)
+    const uint8_t *src_at = reinterpret_cast<const uint8_t *>(uni64((uint64_t)(d.src + start)));
+    const uint8_t *base_at = DELTA ? reinterpret_cast<const uint8_t *>(uni64((uint64_t)(d.base ? d.base + start : nullptr))) : nullptr;
+    const __amdgpu_buffer_rsrc_t src = rsrc_of(src_at, uni32(whole)), bas = rsrc_of(base_at, DELTA && base_at ? uni32(whole) : 0u);
+    const uint32_t lane = tid & (S - 1), page = tid / S;         // (S is a power of two)
+    const uint32_t pass_bytes = 4096 * rows, per_pass = (rows + 3) / 4;       // of 256 pairs; rounds of four rows
+    constexpr int K = 4;
+    struct Round { u32x4 x[K], y[DELTA ? K : 1]; } a, b;
+    uint32_t f_at = page * cb + lane * 16, f_row = 0;            // where the next round is fetched from
+    auto fetch = [&](Round &r) {                                 // (zeros beyond the end)
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int at = (int)(f_row + k < rows ? f_at + (f_row + k) * 16 * S : 0xFFFFFFF0u);
+            r.x[k] = __builtin_amdgcn_raw_buffer_load_b128(src, at, 0, NT);
+            if (DELTA) r.y[k] = __builtin_amdgcn_raw_buffer_load_b128(bas, at, 0, NT);
+        }
+        f_row += K;
+        if (f_row >= rows) { f_row = 0; f_at += pass_bytes; }
+    };
+    C c;
+    c.clear();
+    uint32_t all[C::NE];                                         // the exponents' counts (by sets) over all pages so far
+#pragma unroll
+    for (int i = 0; i < C::NE; i++) all[i] = 0;
+    const uint64_t first_pair = ((uint64_t)(d.units_off / 2) + start / cb) * S;      // two fields: units_off counts two entries per chunk
+    uint32_t row = 0, pair = tid;
+    auto count = [&](const Round &r) {
+        u32x4 x[K];
+#pragma unroll
+        for (int k = 0; k < K; k++) x[k] = DELTA ? r.x[k] ^ r.y[k] : r.x[k];
+#pragma unroll
+        for (int k = 0; k < K; k += 2) c.add(x[k], x[k + 1]);
+        row += K;
+        if (row < rows) return;
+        // the pair is through: its counts, and the last word of its last row
+        uint32_t v[C::NE];
+#pragma unroll
+        for (int i = 1; i < C::NE; i++) { v[i] = c.e[i]; all[i] += c.e[i]; c.e[i] = 0; }
+        v[0] = rows * 16;
+        sets_to_values<Planes<FMT>::PE>(v);
+        const uint32_t left = rows + K - row, w = left == 1 ? x[0][3] : left == 2 ? x[1][3] : left == 3 ? x[2][3] : x[3][3];
+        if (pair * 16 * rows < whole) {
+            u32x4 packed;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                uint32_t q[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) q[j] = v[4 * i + j] > 255 ? 255u : v[4 * i + j];
+                packed[i] = q[0] | q[1] << 8 | q[2] << 16 | q[3] << 24;
+            }
+            counts[first_pair + pair] = packed;
+            const uint32_t e = (w >> 3) & 0x0F0F0F0Fu, t = e | e >> 4;
+            lasts[first_pair + pair] = (uint16_t)((t & 0xFFu) | (t >> 8 & 0xFF00u));
+        }
+        row = 0;
+        pair += 256;
+    };
+    const uint32_t rounds = (whole + pass_bytes - 1) / pass_bytes * per_pass;
+    fetch(a);
+    for (uint32_t i = 0; i < rounds; i += 2) {
+        fetch(b);
+        count(a);
+        fetch(a);
+        if (i + 1 < rounds) count(b);
+    }
+#pragma unroll
+    for (int i = 1; i < C::NE; i++) c.e[i] = all[i];
+    // what is left of the tensor behind its whole pages: less than a page, at most 8 KiB
+    uint32_t rest = 0;
+    if (paged >= start && paged < start + part && paged < n) {
+        rest = (uint32_t)(n - paged);
+        for (uint32_t at = tid * 32; at < rest; at += 256 * 32) {
+            uint4 v[2] = {make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};
+#pragma unroll
+            for (uint32_t k = 0; k < 2; k++)
+                if (at + 16 * k < rest) {
+                    v[k] = load_run(src_at + whole + at + 16 * k, rest - at - 16 * k);
+                    if (DELTA && base_at) v[k] = xor4(v[k], load_run(base_at + whole + at + 16 * k, rest - at - 16 * k));
+                }
+            c.add(u32x4{v[0].x, v[0].y, v[0].z, v[0].w}, u32x4{v[1].x, v[1].y, v[1].z, v[1].w});
+        }
+    }
+    c.finish(0);
+    add_to_bins<FMT>(c, sums, whole + rest, bins_of<FMT>(hist, it.tensor));
+}
+
+// Stream sizes of whole FP8 pages from those counts, for tensors the page kernels take (route 1): a lane's words are min(steps,
+// floor((bits - bits of its last four codes) / 32) + 2) as in k_sizes_fp8_counts, its bits the counts times the code lengths, four products to an
+// instruction.  Work items of the page kernels.
+__global__ __launch_bounds__(256) void k_sizes_pages(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, const u32x4 *counts, const uint16_t *lasts,
+                                                     uint32_t *units, uint32_t slots_per_group)
+{
+    __shared__ uint32_t len16[16];
+    const WorkItem it = work[blockIdx.x];
+    const TensorDev *dp = descs + it.tensor;
+    if (dp->route != 1) return;                                  // whole workgroup: not the page kernels' tensor
+    if (threadIdx.x < 16) len16[threadIdx.x] = enc_tables[(uint64_t)it.tensor * 768 + threadIdx.x] >> 16;
+    __syncthreads();
+    const uint32_t cb = uni32(dp->chunk_bytes), S = uni32(dp->streams), symbols = cb / S, steps = symbols / 4, nc = uni32(dp->n_chunks);
+    const uint32_t n_full = (uint32_t)(uni64(dp->n_elems) / cb), first = it.first;
+    uint32_t lens[4];
+    uint64_t nibbles = 0;                                        // (lengths of at most 8)
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        lens[i] = len16[4 * i] | len16[4 * i + 1] << 8 | len16[4 * i + 2] << 16 | len16[4 * i + 3] << 24;
+#pragma unroll
+        for (int j = 0; j < 4; j++) nibbles |= (uint64_t)len16[4 * i + j] << (4 * (4 * i + j));
+    }
+    const uint64_t pair0 = ((uint64_t)(uni32(dp->units_off) / 2) + first) * S;
+    uint32_t *my = units + uni32(dp->units_off);
+    for (uint32_t i = threadIdx.x; i < slots_per_group * S; i += 256) {        // (whole wavefronts: slots come in multiples of 64 / S)
+        const uint32_t chunk = first + i / S;
+        const bool alive = chunk < n_full;
+        uint32_t q = 0;
+        if (alive) {
+            const u32x4 c = counts[pair0 + i];
+            const uint32_t last = lasts[pair0 + i];
+            uint32_t sum = 0, bits = 0;
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                sum = __builtin_amdgcn_udot4(c[j], 0x01010101u, sum, false);
+                bits = __builtin_amdgcn_udot4(c[j], lens[j], bits, false);
+            }
+            if (sum != symbols) bits += bits / 255;              // one value in all 256 places
+            uint32_t tail = 0;
+#pragma unroll
+            for (int j = 0; j < 4; j++) tail += (uint32_t)(nibbles >> (4 * ((last >> (4 * j)) & 15u))) & 15u;
+            q = ((bits - tail) >> 5) + 2;
+            q = q < steps ? q : steps;
+        }
+        for (uint32_t o = S / 2; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+        if (alive && (i & (S - 1)) == 0) {
+            my[chunk] = (q + 3) / 4;
+            my[nc + chunk] = cb / 32;                            // 4 bits per element, 16-byte units (flat code and raw alike)
+        }
+    }
+}
+
 int launch_hist_fp8_lanes(bool e5m2, bool delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint64_t *d_hist, uint16_t *d_lane_counts, void *stream)
 {
     if (n_work == 0) return 0;
@@ -329,6 +489,28 @@ static uint32_t parts_of(uint32_t n_work, uint32_t most)
     uint32_t split = 1;
     while (split < most && (uint64_t)n_work * split < 1536) split *= 2;
     return split;
+}
+
+int launch_hist_pages(bool delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint32_t pass_bytes, uint64_t *d_hist, uint8_t *d_counts, uint8_t *d_lasts,
+                      void *stream)
+{
+    if (n_work == 0) return 0;
+    hipStream_t st = (hipStream_t)stream;
+    const uint32_t split = parts_of(n_work, kHistBlockBytes / pass_bytes);
+    const bool once = n_work > 1024;                             // as in launch_hist_planes
+#define ZC_PAGES(D, N) hipLaunchKernelGGL((k_hist_pages<D, N>), dim3(n_work * split), dim3(256), 0, st, d_descs, d_work, split, d_hist, (u32x4 *)d_counts, (uint16_t *)d_lasts)
+    if (delta) { if (once) ZC_PAGES(true, kNt); else ZC_PAGES(true, 0); }
+    else { if (once) ZC_PAGES(false, kNt); else ZC_PAGES(false, 0); }
+#undef ZC_PAGES
+    return (int)hipGetLastError();
+}
+
+int launch_sizes_pages(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint8_t *d_counts, const uint8_t *d_lasts,
+                       uint32_t *d_units, uint32_t slots_per_group, void *stream)
+{
+    if (n_work == 0) return 0;
+    hipLaunchKernelGGL(k_sizes_pages, dim3(n_work), dim3(256), 0, (hipStream_t)stream, d_descs, d_work, d_enc, (const u32x4 *)d_counts, (const uint16_t *)d_lasts, d_units, slots_per_group);
+    return (int)hipGetLastError();
 }
 
 int launch_hist_planes(uint32_t fmt, bool delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const WorkItem *d_scale_work, uint32_t n_scale,

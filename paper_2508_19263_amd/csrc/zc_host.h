@@ -91,6 +91,7 @@ struct LandingLease {
 // where everything lives in the workspace of a compress-side call
 struct Workspace {
     uint64_t descs, hist_work, scale_work, chunk_work, fast_work, whole_work, other_work, hist, enc, units, scan, blobs, lane_counts, total, host_end;
+    uint64_t page_counts, page_lasts, wanted;      // counts per (page, lane) pair, behind what a call needs: used where the workspace has room for them (`wanted`)
     uint32_t n_hist_work, n_scale_work, n_chunk_work;
     uint64_t n_units;
 };
@@ -101,6 +102,7 @@ struct CompressShape {
     bool lanes;                 // the code is built on the device and the histogram pass also counts exponents per chunk lane
     bool lanes8;                // the same for the formats of 8-bit symbols (BF16, FP8 in byte symbols): both fields' symbols per chunk lane
     bool lanes_e5m2;            // the same for FP8 E5M2: 32 exponent and 8 sign+mantissa counts per chunk lane
+    bool pages;                 // FP8 pages whose exponents the histogram pass also counts per (page, lane) pair
     bool bf16;
     bool delta;                 // some tensor has a base
     bool rows8;                 // 64 lanes, whole rows, 8 or 16 symbols of 8 bits per run and field (BF16, FP8 in byte symbols, FP8 E5M2): the 64-lane encoder written for BF16

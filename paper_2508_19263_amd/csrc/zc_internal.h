@@ -147,6 +147,11 @@ int launch_hist(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, 
 // FP8 and FP4 in single symbols (hist_in_planes), blocks of elements and, FP4, of scale bytes in one launch; delta: some tensor has a base (zc_hist_planes.hip)
 int launch_hist_planes(uint32_t fmt, bool delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const WorkItem *d_scale_work, uint32_t n_scale,
                        uint64_t *d_hist, void *stream);
+// FP8 E4M3 pages (page_counts_shape): the same with counts per (page, lane) pair, 16 bytes and 2 bytes per pair, and the sizes from those; pass_bytes: 4 KiB per row of a page
+int launch_hist_pages(bool delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint32_t pass_bytes, uint64_t *d_hist, uint8_t *d_counts, uint8_t *d_lasts,
+                      void *stream);
+int launch_sizes_pages(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint8_t *d_counts, const uint8_t *d_lasts,
+                       uint32_t *d_units, uint32_t slots_per_group, void *stream);
 int launch_zero(uint64_t *d_words, uint64_t n_words, void *stream);
 // between a page-locked host buffer and device memory, either way (both aligned to 16 bytes); flags: hand_over_groups(bytes) words of
 // page-locked memory, set when the bytes have been read, or (to_host) have arrived; clears n_zero words at d_zero too

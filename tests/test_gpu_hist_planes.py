@@ -56,3 +56,29 @@ def test_counts_of_large_tensors(fmt, chunk, lanes, delta):
         assert bytes(info.code_len[f]) == bytes(one.code_len[f]), f
     out, s = zc.decompress(comp, info, xor_base=many[1])
     assert torch.equal(out, many[0]) and (not fp4 or torch.equal(s, many[2]))
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16, 32])
+@pytest.mark.parametrize("rows", [1, 2, 4, 8, 16])
+def test_counts_of_pages(lanes, rows):
+    """Counts per (page, lane) pair: tensors that end within a page, in a histogram block of their own and in the middle of one, pages of one value
+    (a count of 256 at sixteen rows), deltas; and a workspace without room for the counts."""
+    chunk = 16 * rows * lanes
+    for i, nbytes in enumerate((chunk, 3 * chunk + 5, 256 * KIB, 256 * KIB + chunk // 2 + 1, 300 * KIB + 7)):
+        print("case", lanes, rows, nbytes, flush=True)
+        x = values(nbytes, i, False)
+        x[nbytes // 2:] = (x[nbytes // 2:] & 0x87) | 0x38         # (one exponent)
+        base = values(nbytes, 50 + i, False) if i % 2 else None
+        if base is not None:
+            base[nbytes // 2:] &= 0x87
+        p = zc.params(zc.FMT_FP8_E4M3, chunk, streams=lanes)
+        want = o.compress(x, nbytes, o.params(zc.FMT_FP8_E4M3, chunk, (0, 0, 0), lanes), **({} if base is None else {"xor_base": base}))
+        on, under = torch.from_numpy(x).to(DEV), None if base is None else torch.from_numpy(base).to(DEV)
+        pairs = -(-nbytes // chunk) * lanes
+        room = zc.workspace_bytes([nbytes], p)
+        for ws_bytes in (room, room - (pairs * 16 + 255) // 256 * 256 - (pairs * 2 + 255) // 256 * 256):
+            ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+            got, _ = zc.compress(on, nbytes, p, xor_base=under, ws=ws)
+            assert np.array_equal(got.cpu().numpy(), want), (nbytes, ws_bytes == room)
+        with pytest.raises(zc.ZcError):
+            zc.compress(on, nbytes, p, xor_base=under, ws=ws[:-256])
