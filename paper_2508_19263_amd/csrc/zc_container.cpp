@@ -132,10 +132,10 @@ TensorDev make_desc(const zc_info &info)
 
 // slots one workgroup of the sub-wavefront kernel takes: enough passes to amortise its table
 // build, few enough to leave >= ~2048 workgroups
-uint32_t sub_slots_per_group(uint32_t streams, uint64_t slots)
+uint32_t sub_slots_per_group(uint32_t streams, uint64_t slots, uint32_t waves)
 {
-    const uint32_t per_pass = kWavesPerGroup * (64 / streams);
-    uint64_t passes = slots / (2048ull * per_pass);
+    const uint32_t per_pass = waves * (64 / streams);
+    uint64_t passes = slots / (2048ull * kWavesPerGroup / waves * per_pass);
     if (passes < 1) passes = 1;
     if (passes > 8) passes = 8;
     return (uint32_t)passes * per_pass;

@@ -204,14 +204,18 @@ int launch_decode_fp8_sub(uint32_t streams, bool xor_delta, bool scattered, cons
 // one buffer resource over the payload) with the exponent field decoded through the general 11-bit table
 // (codes up to 16 bits, refill period 2, 4 or 8) and a sign+mantissa field that is raw or flat coded.  A row is
 // 8 values per lane: 8 exponent symbols and 8 sign+mantissa bytes (two words, as in the FP8 kernel).
-template <int S, bool XOR>
-__global__ __launch_bounds__(256) void k_decode_bf16_sub(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single,
+// W wavefronts per workgroup share the table: four, or eight in calls of more pages than the card holds at once with four, whose rings and
+// table let seven workgroups onto a compute unit, where four of eight wavefronts fit: an eighth wavefront per SIMD.  A quarter of the pages of 32 caches,
+// 65,536 (8,192 wavefronts' worth: eight per SIMD, or seven and then one): 143 -> 117 us, with the table built without walks and sign+mantissa words asked
+// for a row ahead.
+template <int S, bool XOR, uint32_t W>
+__global__ __launch_bounds__(64 * W) void k_decode_bf16_sub(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single,
                                                          uint32_t slots_per_group)
 {
     constexpr uint32_t kGroups = 64 / S;
     constexpr uint32_t kSeg = 4 * S, kRing = 16 * S;             // words per group
     __shared__ FieldTab tab;
-    __shared__ __attribute__((aligned(16))) uint32_t ring[kWavesPerGroup][kRingWords];
+    __shared__ __attribute__((aligned(16))) uint32_t ring[W][kRingWords];
     __shared__ TensorDev dsh;
     WorkItem it;
     if (use_single) { it.tensor = 0; it.first = blockIdx.x * slots_per_group; }
@@ -255,11 +259,11 @@ __global__ __launch_bounds__(256) void k_decode_bf16_sub(const TensorDev *descs,
 #pragma unroll
     for (int i = 0; i < 4; i++) Hl.lim[i] = uniform32(tab.limit[kLutBits + 1 + i]);
 
-    // the workgroup owns slots [first, first + slots_per_group): each pass takes 4 waves x kGroups of them
-    for (uint32_t pass = 0; pass * kWavesPerGroup * kGroups < slots_per_group; pass++) {
-        const uint32_t slot = it.first + (pass * kWavesPerGroup + wave) * kGroups + grp;
+    // the workgroup owns slots [first, first + slots_per_group): each pass takes W wavefronts x kGroups of them
+    for (uint32_t pass = 0; pass * W * kGroups < slots_per_group; pass++) {
+        const uint32_t slot = it.first + (pass * W + wave) * kGroups + grp;
         uint32_t chunk = slot;
-        bool alive = slot < n_slots && (pass * kWavesPerGroup + wave) * kGroups + grp < slots_per_group;
+        bool alive = slot < n_slots && (pass * W + wave) * kGroups + grp < slots_per_group;
         if (ids && alive) chunk = ids[slot];
         alive = alive && chunk < n_full;                         // short last chunk: the host sends it to the generic kernel
         uint32_t e_off = pay_bytes, m_off = pay_bytes;           // out of range: loads return 0
@@ -281,14 +285,14 @@ __global__ __launch_bounds__(256) void k_decode_bf16_sub(const TensorDev *descs,
             const u32x4 v = ring_piece(q * kSeg + s * 4);
             *reinterpret_cast<u32x4 *>(ring_bytes + (q * kSeg + s * 4) * 4) = v;
         }
-        uint64_t W = (uint64_t)(*reinterpret_cast<const uint32_t *>(ring_bytes + s * 4)) << 32;    // step 0: lane s takes word s
+        uint64_t window = (uint64_t)(*reinterpret_cast<const uint32_t *>(ring_bytes + s * 4)) << 32;    // step 0: lane s takes word s
         uint32_t c = 32, wpos = S, wbase = 0, pslot = 0;
         bool pending = false;
         u32x4 pv = {0, 0, 0, 0};
         // one refill period of R exponent symbols into bytes first .. first+R-1 of ex[]
         auto decode_period = [&](auto r_tag, int first, uint32_t ex[2]) {
             constexpr int R = decltype(r_tag)::value;
-            const uint32_t x0 = (uint32_t)(W >> c);
+            const uint32_t x0 = (uint32_t)(window >> c);
             uint32_t x = x0, e[R];
 #pragma unroll
             for (int j = 0; j < R; j++) {
@@ -319,10 +323,18 @@ __global__ __launch_bounds__(256) void k_decode_bf16_sub(const TensorDev *descs,
             const bool need = c >= 32;
             const uint64_t bm = __ballot(need) & gmask;
             const uint32_t w = *reinterpret_cast<const uint32_t *>(ring_bytes + ((prefix_count64(bm) + wpos) & (kRing - 1)) * 4);
-            W = need ? ((W >> 32) | ((uint64_t)w << 32)) : W;
+            window = need ? ((window >> 32) | ((uint64_t)w << 32)) : window;
             c = need ? c - 32 : c;
             wpos += (uint32_t)__popcll(bm);
         };
+        // sign+mantissa words, 8 bytes per lane and row, asked for a row ahead
+        uint32_t next[2];
+        auto fetch_sm = [&](uint32_t row) {
+#pragma unroll
+            for (int h = 0; h < 2; h++)
+                next[h] = __builtin_amdgcn_raw_buffer_load_b32(ps, (int)(m_off + (sm_raw ? (row * S + s) * 2 + h : (row * 2 + h) * S + s) * 4), 0, 0);
+        };
+        fetch_sm(0);
         for (uint32_t row = 0; row < rows; row++) {
             if (pending) { *reinterpret_cast<u32x4 *>(ring_bytes + (pslot + s * 4) * 4) = pv; pending = false; }
             if (wpos - wbase >= kSeg) {
@@ -331,13 +343,10 @@ __global__ __launch_bounds__(256) void k_decode_bf16_sub(const TensorDev *descs,
                 wbase += kSeg;
                 pending = true;
             }
-            // ---- sign+mantissa: 8 bytes per lane and row
             uint32_t m[2];
 #pragma unroll
-            for (int h = 0; h < 2; h++) {
-                if (sm_raw) m[h] = __builtin_amdgcn_raw_buffer_load_b32(ps, (int)(m_off + ((row * S + s) * 2 + h) * 4), 0, 0);
-                else m[h] = reverse_in_groups<8>(__builtin_amdgcn_raw_buffer_load_b32(ps, (int)(m_off + ((row * 2 + h) * S + s) * 4), 0, 0));
-            }
+            for (int h = 0; h < 2; h++) m[h] = sm_raw ? next[h] : reverse_in_groups<8>(next[h]);
+            fetch_sm(row + 1 < rows ? row + 1 : row);
             // ---- exponents
             uint32_t ex[2] = {0, 0};
             if (period == 2) {
@@ -355,12 +364,12 @@ __global__ __launch_bounds__(256) void k_decode_bf16_sub(const TensorDev *descs,
     }
 }
 
-template <int S>
+template <int S, uint32_t W>
 static int launch_bf16_sub_s(bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev &s, int use_single,
                              uint32_t slots_per_group, hipStream_t st)
 {
-    if (xor_delta) hipLaunchKernelGGL((k_decode_bf16_sub<S, true>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, s, use_single, slots_per_group);
-    else hipLaunchKernelGGL((k_decode_bf16_sub<S, false>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, s, use_single, slots_per_group);
+    if (xor_delta) hipLaunchKernelGGL((k_decode_bf16_sub<S, true, W>), dim3(n_work), dim3(64 * W), 0, st, d_descs, d_work, s, use_single, slots_per_group);
+    else hipLaunchKernelGGL((k_decode_bf16_sub<S, false, W>), dim3(n_work), dim3(64 * W), 0, st, d_descs, d_work, s, use_single, slots_per_group);
     return (int)hipGetLastError();
 }
 
@@ -372,11 +381,12 @@ int launch_decode_bf16_sub(uint32_t streams, bool xor_delta, const TensorDev *d_
     hipStream_t st = (hipStream_t)stream;
     const TensorDev s = single ? *single : TensorDev{};
     const int use_single = single ? 1 : 0;
+    const bool eight = slots_per_group % (8 * (64 / streams)) == 0;      // (sub_slots_per_group)
     switch (streams) {
-    case 4: return launch_bf16_sub_s<4>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
-    case 8: return launch_bf16_sub_s<8>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
-    case 16: return launch_bf16_sub_s<16>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
-    case 32: return launch_bf16_sub_s<32>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
+    case 4: return eight ? launch_bf16_sub_s<4, 8>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st) : launch_bf16_sub_s<4, 4>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
+    case 8: return eight ? launch_bf16_sub_s<8, 8>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st) : launch_bf16_sub_s<8, 4>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
+    case 16: return eight ? launch_bf16_sub_s<16, 8>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st) : launch_bf16_sub_s<16, 4>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
+    case 32: return eight ? launch_bf16_sub_s<32, 8>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st) : launch_bf16_sub_s<32, 4>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
     }
     return (int)hipErrorInvalidValue;
 }

@@ -240,6 +240,13 @@ zc_status check_decode_info(const zc_info &info, uint64_t comp_bytes)
     return ZC_OK;
 }
 
+// pages (or slots of a list) that a workgroup of the page decoders takes.  BF16: eight wavefronts per workgroup where there are more pages than four-wavefront
+// workgroups hold at once (seven wavefronts per SIMD), see k_decode_bf16_sub
+uint32_t page_slots_per_group(uint32_t fmt, uint32_t S, uint64_t slots)
+{
+    return sub_slots_per_group(S, slots, fmt == ZC_FMT_BF16 && slots * S > 64ull * 7 * 4 * kComputeUnits ? 8 : kWavesPerGroup);
+}
+
 zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *info_in, const uint32_t *d_ids, uint32_t n_ids, bool by_ids,
                         void *d_dst, uint64_t dst_capacity, void *d_scales_out, const void *d_xor_base, void *stream)
 {
@@ -278,7 +285,7 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         // small chunks (pages): several per wavefront.  An id list may name a short last chunk, which
         // this kernel does not take, so lists go here only when every chunk is whole.
         const uint32_t n_fast = by_ids ? n_ids : (uint32_t)(info.n_elems / elems_per_chunk);
-        const uint32_t spg = sub_slots_per_group(info.streams, n_fast);
+        const uint32_t spg = page_slots_per_group(info.format, info.streams, n_fast);
         if (info.format == ZC_FMT_BF16) LAUNCH_TRY(launch_decode_bf16_sub(info.streams, info.xor_delta != 0, nullptr, nullptr, (n_fast + spg - 1) / spg, &d, spg, stream));
         else LAUNCH_TRY(launch_decode_fp8_sub(info.streams, info.xor_delta != 0, by_ids, nullptr, nullptr, (n_fast + spg - 1) / spg, &d, spg, stream));
         first_slot = n_fast;
@@ -426,7 +433,7 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
         else if (k > pair_fields) pair_fields = k;
     }
     const PairsShape pairs_as = pair_fields ? pairs_shape(fmt, pair_fields, call) : PairsShape{0, false};
-    const uint32_t spg = pairs_as.chunks ? pairs_as.chunks : sub ? sub_slots_per_group(S, call.slots) : split ? 1u : kWavesPerGroup;
+    const uint32_t spg = pairs_as.chunks ? pairs_as.chunks : sub ? page_slots_per_group(fmt, S, call.slots) : split ? 1u : kWavesPerGroup;
     std::vector<TensorDev> descs(n_tensors);
     std::vector<WorkItem> fast_work, work;
     for (uint32_t t = 0; t < n_tensors; t++) {

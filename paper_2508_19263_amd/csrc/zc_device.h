@@ -204,50 +204,63 @@ struct FieldTab {
     uint32_t lmax;
 };
 
-// all threads of the workgroup; lengths come from the container's table
+// All threads of the workgroup, at least 256; lengths come from the container's table.  Bound by latency, so there is no walk: the symbols of a length
+// are ranked by ballots, the first code of length l is a scan (the sum over the shorter lengths j of cnt(j) * 2^(16 - j), left aligned), and the
+// length of the code an index starts with is one plus the number of limits it reaches.
 __attribute__((unused)) static __device__ void build_field_tab(FieldTab &T, const uint8_t *len_table, int alphabet, uint32_t lmax)
 {
-    const uint32_t tid = threadIdx.x, nt = blockDim.x;
-    if (tid < 17) T.cnt[tid] = 0;
-    for (uint32_t v = tid; v < 256; v += nt) T.len[v] = v < (uint32_t)alphabet ? len_table[v] : 0;
+    __shared__ uint32_t in_wave[4][17];
+    const uint32_t tid = threadIdx.x, nt = blockDim.x, wave = tid >> 6, lane = tid & 63;
     if (lmax > 16) lmax = 16;
-    __syncthreads();
-    for (uint32_t v = tid; v < (uint32_t)alphabet; v += nt)
-        if (T.len[v] && T.len[v] <= 16) atomicAdd(&T.cnt[T.len[v]], 1u);
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t code = 0, idx = 0;
-        for (int l = 1; l <= 16; l++) {
-            code <<= 1;
-            T.first[l] = code; T.start[l] = idx;
-            T.rebase[l] = idx - code;
-            code += T.cnt[l]; idx += T.cnt[l];
-            T.limit[l] = code << (16 - l);
-        }
-        T.limit[0] = 0; T.rebase[0] = 0;
-        const uint32_t bits = lmax < (uint32_t)kLutBits ? lmax : (uint32_t)kLutBits;
-        T.mask = (1u << bits) - 1;
-        T.lmax = lmax;
-    }
-    __syncthreads();
-    for (uint32_t v = tid; v < (uint32_t)alphabet; v += nt) {
-        const uint32_t l = T.len[v];
-        if (l && l <= 16) {
-            uint32_t rank = 0;
-            for (uint32_t u = 0; u < v; u++) rank += T.len[u] == l;
-            T.sorted[T.start[l] + rank] = (uint8_t)v;
+    uint32_t my_len = 0, rank = 0;
+    if (tid < 256) {
+        my_len = tid < (uint32_t)alphabet ? len_table[tid] : 0;
+        if (my_len > 16) my_len = 0;
+        T.len[tid] = (uint8_t)my_len;
+#pragma unroll
+        for (uint32_t l = 1; l <= 16; l++) {
+            const uint64_t m = __ballot(my_len == l);
+            if (my_len == l) rank = prefix_count(m);
+            if (lane == 0) in_wave[wave][l] = (uint32_t)__popcll(m);
         }
     }
     __syncthreads();
+    if (tid < 64) {
+        const bool real = tid >= 1 && tid <= 16;
+        const uint32_t cnt = real ? in_wave[0][tid] + in_wave[1][tid] + in_wave[2][tid] + in_wave[3][tid] : 0u;
+        const uint32_t own = real ? cnt << (16 - tid) : 0u;
+        uint32_t codes = own, symbols = cnt;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const uint32_t a = __shfl_up(codes, o, 64), b = __shfl_up(symbols, o, 64);
+            if (tid >= (uint32_t)o) { codes += a; symbols += b; }
+        }
+        if (tid <= 16) {
+            const uint32_t first = real ? (codes - own) >> (16 - tid) : 0u, start = symbols - cnt;
+            T.cnt[tid] = cnt; T.first[tid] = first; T.start[tid] = start; T.rebase[tid] = start - first; T.limit[tid] = codes;
+        }
+        if (tid == 0) {
+            const uint32_t bits = lmax < (uint32_t)kLutBits ? lmax : (uint32_t)kLutBits;
+            T.mask = (1u << bits) - 1;
+            T.lmax = lmax;
+        }
+    }
+    __syncthreads();
+    if (my_len) {
+        for (uint32_t w = 0; w < wave; w++) rank += in_wave[w][my_len];
+        T.sorted[(T.start[my_len] + rank) & 255u] = (uint8_t)tid;
+    }
     const uint32_t bits = lmax < (uint32_t)kLutBits ? lmax : (uint32_t)kLutBits;
+    uint32_t limit[kLutBits];
+#pragma unroll
+    for (int l = 1; l <= kLutBits; l++) limit[l - 1] = T.limit[l];
+    __syncthreads();
     for (uint32_t idx = tid; idx < (1u << bits); idx += nt) {
-        const uint32_t msb = __brev(idx);                  // stream bits in code order, left aligned
-        uint32_t entry = 0;
-        for (uint32_t l = 1; l <= bits; l++) {
-            const uint32_t code = msb >> (32 - l);
-            if (code - T.first[l] < T.cnt[l] && code >= T.first[l]) { entry = l | ((uint32_t)T.sorted[T.start[l] + code - T.first[l]] << 8); break; }
-        }
-        T.lut[idx] = (uint16_t)entry;
+        const uint32_t w = __brev(idx) >> 16;              // stream bits in code order, left aligned
+        uint32_t l = 1;
+#pragma unroll
+        for (int i = 0; i < kLutBits; i++) l += w >= limit[i] ? 1u : 0u;
+        T.lut[idx] = (uint16_t)(l <= bits ? l | ((uint32_t)T.sorted[(T.rebase[l & 15] + (w >> (16 - l))) & 255u] << 8) : 0u);
     }
     __syncthreads();
 }

@@ -61,7 +61,7 @@ zc_status check_index_field(const uint32_t *idx, uint32_t n_chunks, uint32_t *pr
 // Workgroups are handed to the 8 XCDs in turn; reorder a work list so that every XCD walks one contiguous eighth
 void order_for_xcds(std::vector<WorkItem> &items);
 // slots one workgroup of the sub-wavefront (page) kernels takes
-uint32_t sub_slots_per_group(uint32_t streams, uint64_t slots);
+uint32_t sub_slots_per_group(uint32_t streams, uint64_t slots, uint32_t waves = kWavesPerGroup);
 
 #define HIP_TRY(expr) do { if ((expr) != hipSuccess) return ZC_ERR_DEVICE; } while (0)
 #define LAUNCH_TRY(expr) do { if ((expr) != 0) return ZC_ERR_DEVICE; } while (0)
