@@ -185,7 +185,8 @@ uint64_t zc_compress_bound(uint64_t n_elems, const zc_params *params);
  * for the size pass (so that the source is read twice, not three times): 2 KiB per chunk for FP8 E4M3, 5 KiB for
  * FP8 E5M2, and 64 KiB per chunk, a quarter of the tensor, for BF16 and FP8 in byte symbols; and except for FP8 E4M3 with
  * 4 to 32 lanes and chunks of 1, 2, 4, 8 or 16 runs of 16 bytes per lane (K/V pages), 18 bytes per chunk and lane for the same
- * purpose, without which such a call makes do when it gets less. */
+ * purpose, and for two fields with 64 lanes 8 KiB for each of up to 1,024 chunks, for the bit totals of their parts.  Without these
+ * last two a call makes do when it gets less. */
 uint64_t zc_workspace_bytes(const uint64_t *n_elems, uint32_t n_tensors, const zc_params *params);
 
 /* Compress one tensor: field split (+ XOR delta) and per-field histogram over the tensor,
@@ -221,7 +222,7 @@ zc_status zc_compress_batch_async(zc_tensor *tensors, uint32_t n_tensors, const 
  * file-scope device array of ZC_NOALLOC_SCRATCH_BYTES inside the library (every GPU the library runs on holds
  * its own copy until the process ends), and descriptor, header and work lists are written into it by a kernel
  * from its arguments.  Codes are built on the device; the container is byte for byte what zc_compress writes.
- * Limits: zc_workspace_bytes(&n_elems, 1, params), less those 18 bytes per chunk and lane, must not exceed ZC_NOALLOC_SCRATCH_BYTES (which admits e.g.
+ * Limits: zc_workspace_bytes(&n_elems, 1, params), less what a call makes do without, must not exceed ZC_NOALLOC_SCRATCH_BYTES (which admits e.g.
  * 504 MiB of FP8 in 256 KiB chunks or 901 MiB of FP8 K/V pages of 2 KiB in one call) and dst_capacity
  * must be at least zc_compress_bound(n_elems, params), else ZC_ERR_BUFFER_TOO_SMALL and nothing is queued;
  * ZC_FLAG_HOST_CODES is refused (ZC_ERR_INVALID_ARG).  out size and code are not returned: once the stream has

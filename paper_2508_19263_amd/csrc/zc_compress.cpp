@@ -29,6 +29,7 @@ bool lane_counts8_shape(const Geometry &g) { return (g.fmt == ZC_FMT_BF16 || g.f
 // and for FP8 E5M2 (k_hist_fp8_lanes<true>, k_sizes_e5m2_counts): 40 counts per chunk lane
 bool lane_counts_e5m2_shape(const Geometry &g) { return g.fmt == ZC_FMT_FP8_E5M2 && g.S == 64 && g.chunk_bytes == kHistBlockBytes; }
 // and for FP8 E4M3 pages (k_hist_pages, k_sizes_pages): as many rows as a pair's counts of 8 bits hold, and whole passes of 256 pairs to a histogram block
+constexpr uint32_t kSegChunkBytes = 64u << 20;      // a segment's bits fit 26 bits
 bool page_counts_shape(const Geometry &g)
 {
     if (g.fmt != ZC_FMT_FP8_E4M3 || g.S < 4 || g.S >= 64 || g.chunk_bytes % (16 * g.S)) return false;
@@ -78,6 +79,10 @@ zc_status plan_workspace(const Geometry &g, const uint64_t *n_elems, uint32_t T,
     const uint64_t pairs = page_counts_shape(g) ? units / 2 * g.S : 0;
     w->page_counts = off; off = align256(off + pairs * 16);
     w->page_lasts = off; off = align256(off + pairs * 2);
+    // (a call of few chunks gives all of them to the split kernels, any other a tensor's short last one)
+    const uint64_t seg_items = g.S == 64 && g.nf == 2 && g.chunk_bytes <= kSegChunkBytes ? std::min<uint64_t>(units / 2, kSegItems) : 0;
+    w->seg_bits = off; off = align256(off + seg_items * kSegBytes);
+    w->seg_items = seg_items;
     w->wanted = off;
     w->n_hist_work = (uint32_t)hw; w->n_scale_work = (uint32_t)sw; w->n_chunk_work = (uint32_t)cw; w->n_units = units;
     return ZC_OK;
@@ -204,7 +209,7 @@ zc_status CompressQueue::queue_sizes_and_scan() const
     // what the whole-chunk kernels leave over: with 64 lanes and chunks of whole rows only a tensor's short last chunk, and
     // every chunk of a call of few, sixteen or eight wavefronts each; otherwise every chunk, walked by the generic size pass
     if (sh.fp4_tails) LAUNCH_TRY(launch_fp4_tails(g.fmt, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
-    else if (sh.split_rest) LAUNCH_TRY(launch_sizes_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
+    else if (sh.split_rest) LAUNCH_TRY(launch_sizes_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), d_seg(), stream));
     else LAUNCH_TRY(launch_sizes(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_units(), stream));
     // the chained kernel has placed and written the tensors of its route (FP8: 1, BF16: 2) itself
     LAUNCH_TRY(launch_scan(d_descs(), T, (int)g.nf, g.reversed, chained ? (sh.bf16 ? 0x4 : 0x2) : 0, d_units(), (ScanOut *)(ws + w.scan), stats_only ? nullptr : ws + w.blobs,
@@ -222,7 +227,7 @@ zc_status CompressQueue::queue_encoders() const
     if (sh.rows8) LAUNCH_TRY(launch_encode_bf16(g.fmt, d_descs(), d_list(w.whole_work), n_whole, d_enc(), stream));
     LAUNCH_TRY(launch_encode(g.fmt, 0, 0x6, d_descs(), d_list(w.other_work), n_other, d_enc(), stream));
     if (sh.fp4_tails) LAUNCH_TRY(launch_fp4_tails(g.fmt, 1, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), nullptr, stream));
-    else if (sh.split_rest) LAUNCH_TRY(launch_encode_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
+    else if (sh.split_rest) LAUNCH_TRY(launch_encode_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_seg(), stream));
     else LAUNCH_TRY(launch_encode(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
     return ZC_OK;
 }
@@ -479,6 +484,7 @@ private:
         for (uint32_t t = 0; t < T; t++) delta = delta || tensors[t].d_xor_base;
         sh = compress_shape(g, uses_device_codes(), all_chunks, delta);
         sh.pages = sh.pages && ws_bytes >= w.wanted;
+        sh.seg_bits = ws_bytes >= w.wanted;
         for (uint32_t t = 0; t < T; t++) {
             zc_tensor &x = tensors[t];
             const uint64_t nc = ncs[t];

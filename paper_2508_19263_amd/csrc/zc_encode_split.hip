@@ -257,15 +257,54 @@ __device__ __forceinline__ void load_tables(const TensorDev *dp, const uint32_t 
 
 }  // namespace
 
-// Stream sizes of the chunks of a work list, one chunk per item.  W wavefronts add up the code lengths of a W-th of the rows
-// each; the closed form above, taken at a lane's last step, gives the lane's words.
+// A segment's rows: the chunk's, dealt out to W wavefronts in pieces
+template <uint32_t W>
+struct Segment {
+    uint32_t per_wave, begin, end;
+    __device__ __forceinline__ Segment(uint32_t rows, uint32_t wave)
+    {
+        per_wave = (rows + W - 1) / W;
+        begin = wave * per_wave < rows ? wave * per_wave : rows;
+        end = begin + per_wave < rows ? begin + per_wave : rows;
+    }
+};
+
+// Bits of rows [begin, end) of a chunk, whole runs in every lane, per field that `walk` names, and of their last refill period
+template <int FMT>
+__device__ __forceinline__ void bits_of_rows(const ChunkView<FMT> &C, uint32_t begin, uint32_t end, uint32_t lane, const bool walk[2], const uint32_t period[2], const char *const lut[2],
+                                             uint32_t bits[2], uint32_t last[2])
+{
+    using F_ = Fmt<FMT>;
+    for (uint32_t r0 = begin; r0 < end; r0 += 4) {
+        u32x4 v[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; i++) {
+            const uint64_t at = (uint64_t)((r0 + i < end ? r0 + i : end - 1) * 64 + lane) * 16;
+            v[i] = *reinterpret_cast<const u32x4 *>(C.src + at);
+            if (C.base) v[i] ^= *reinterpret_cast<const u32x4 *>(C.base + at);
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < 4; i++) {
+            if (r0 + i >= end) break;
+            uint32_t w[2][4];
+            split_words<FMT>(v[i], w);
+#pragma unroll
+            for (int f = 0; f < 2; f++)
+                if (walk[f]) run_bits<F_::SB, F_::G>(period[f], w[f], lut[f], bits[f], last[f]);
+        }
+    }
+}
+
+// Stream sizes of the chunks of a work list, one chunk per item.  W wavefronts add up the code lengths of a segment of the rows
+// each; the closed form above, taken at a lane's last step, gives the lane's words.  seg: where the segments' bits and those of their last periods
+// (bits << 6 | last; W * 2 * 64 words per item) are left for the encoder, or null.
 template <int FMT, uint32_t W>
-__global__ __launch_bounds__(64 * W) void k_sizes_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, uint32_t *units)
+__global__ __launch_bounds__(64 * W) void k_sizes_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, uint32_t *units, uint32_t *seg)
 {
     using F_ = Fmt<FMT>;
     static_assert(F_::NF == 2 && (F_::SB == 4 || F_::SB == 8) && F_::G * F_::SB <= 128, "two fields of 4- or 8-bit symbols, at most two 64-bit words per run");
     __shared__ uint32_t enc[2][256], tab[2][256];
-    __shared__ uint32_t part[W][2][64];
+    __shared__ uint32_t part[W][2][64], part_last[2][64];
     const WorkItem it = work[blockIdx.x];
     const TensorDev *dp = descs + it.tensor;
     const uint32_t lane = threadIdx.x & 63, wave = uni32(threadIdx.x >> 6);
@@ -275,37 +314,19 @@ __global__ __launch_bounds__(64 * W) void k_sizes_split(const TensorDev *descs, 
     const uint32_t mode[2] = {uni32(dp->mode[0]), uni32(dp->mode[1])}, kind[2] = {uni32(dp->kind[0]), uni32(dp->kind[1])};
     const uint32_t period[2] = {uni32(dp->period[0]), uni32(dp->period[1])};
     load_tables<FMT>(dp, enc_tables + (uint64_t)it.tensor * 768, enc, tab);
-    // a lane's last run is taken apart from the others: rows before it are whole in every lane that has one
-    const bool coded[2] = {mode[0] == ZC_MODE_HUFF, mode[1] == ZC_MODE_HUFF};
-    const bool walk = (coded[0] && kind[0] != 1) || (coded[1] && kind[1] != 1);          // (a flat code's bits need no data)
-    uint32_t bits[2] = {0, 0};
-    if (walk) {
-        constexpr uint32_t kDepth = 4;
-        for (uint32_t r0 = wave; r0 < C.rows; r0 += W * kDepth) {
-            u32x4 v[kDepth];
+    // the last row is taken apart from the others, whose runs are whole in every lane (a flat code's bits need no data)
+    const bool walk[2] = {mode[0] == ZC_MODE_HUFF && kind[0] != 1, mode[1] == ZC_MODE_HUFF && kind[1] != 1};
+    const char *const lut[2] = {reinterpret_cast<const char *>(tab[0]), reinterpret_cast<const char *>(tab[1])};
+    const Segment<W> R_(C.rows, wave);
+    uint32_t bits[2] = {0, 0}, last[2] = {0, 0};
+    const uint32_t end = R_.end < C.rows ? R_.end : C.rows - 1;  // (rows >= 1)
+    if ((walk[0] || walk[1]) && R_.begin < end) bits_of_rows<FMT>(C, R_.begin, end, lane, walk, period, lut, bits, last);
 #pragma unroll
-            for (uint32_t i = 0; i < kDepth; i++) {
-                const uint32_t run = (r0 + i * W) * 64 + lane;
-                v[i] = u32x4{0, 0, 0, 0};
-                if (run + 64 < C.runs) {
-                    v[i] = *reinterpret_cast<const u32x4 *>(C.src + (uint64_t)run * 16);
-                    if (C.base) v[i] ^= *reinterpret_cast<const u32x4 *>(C.base + (uint64_t)run * 16);
-                }
-            }
-#pragma unroll
-            for (uint32_t i = 0; i < kDepth; i++) {
-                const uint32_t run = (r0 + i * W) * 64 + lane;
-                if (run + 64 >= C.runs) continue;
-                uint32_t w[2][4], last;
-                split_words<FMT>(v[i], w);
-#pragma unroll
-                for (int f = 0; f < 2; f++)
-                    if (coded[f] && kind[f] != 1) run_bits<F_::SB, F_::G>(period[f], w[f], reinterpret_cast<const char *>(tab[f]), bits[f], last);
-            }
-        }
+    for (int f = 0; f < 2; f++) {
+        part[wave][f][lane] = bits[f];
+        if (R_.begin < end && end == C.rows - 1) part_last[f][lane] = last[f];      // of the row before the last one
+        if (seg && walk[f]) seg[(uint64_t)blockIdx.x * (W * 128) + (wave * 2 + f) * 64 + lane] = bits[f] << 6 | last[f];
     }
-    part[wave][0][lane] = bits[0];
-    part[wave][1][lane] = bits[1];
     __syncthreads();
     if (wave >= 2) return;
     const uint32_t f = wave;                                     // wavefront f finishes field f
@@ -323,13 +344,16 @@ __global__ __launch_bounds__(64 * W) void k_sizes_split(const TensorDev *descs, 
             else {
 #pragma unroll
                 for (uint32_t wv = 0; wv < W; wv++) before += part[wv][f][lane];
-                uint32_t w[2][4], x[4];
-                split_words<FMT>(C.run_of(row, lane), w);
+                if (row + 1 < C.rows) before -= part_last[f][lane];          // a whole run, in the row before the last one
+                else {
+                    uint32_t w[2][4], x[4];
+                    split_words<FMT>(C.run_of(row, lane), w);
 #pragma unroll
-                for (int i = 0; i < 4; i++) x[i] = f ? w[1][i] : w[0][i];
-                const uint32_t in_last = nsym - (steps - 1 - row * F_::G / R) * R;        // symbols of the last step (R divides G)
+                    for (int i = 0; i < 4; i++) x[i] = f ? w[1][i] : w[0][i];
+                    const uint32_t in_last = nsym - (steps - 1 - row * F_::G / R) * R;        // symbols of the last step (R divides G)
 #pragma unroll 1
-                for (uint32_t j = 0; j < nsym - in_last; j++) before += enc[f][symbol_at<F_::SB>(x, j)] >> 16;
+                    for (uint32_t j = 0; j < nsym - in_last; j++) before += enc[f][symbol_at<F_::SB>(x, j)] >> 16;
+                }
             }
             q = before / 32 + 2;
             q = q < steps ? q : steps;
@@ -346,8 +370,10 @@ __global__ __launch_bounds__(64 * W) void k_sizes_split(const TensorDev *descs, 
 // FP8 chunks where one wavefront each takes 157 us, 54 us for BF16 deltas (both fields table coded), and 36 us for a set's
 // short last chunks instead of 435 - 500 us in the generic encoder.  Its size pass: 11 - 17 us (15 - 52 us before it asked for
 // four rows at a time).
+// seg: the segments' bits as k_sizes_split left them, or null: they are added up here, which reads the source once more.  (Seven FP8 tensors, 517 chunks and
+// their short last ones: 91 -> 71 us; 32 chunks of BF16 19 -> 16.)
 template <int FMT, uint32_t W>
-__global__ __launch_bounds__(64 * W) void k_encode_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables)
+__global__ __launch_bounds__(64 * W) void k_encode_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, const uint32_t *seg)
 {
     using F_ = Fmt<FMT>;
     constexpr int SB = F_::SB, G = F_::G, WPR = G * SB / 32;     // WPR: words of a plainly stored field per run
@@ -380,32 +406,33 @@ __global__ __launch_bounds__(64 * W) void k_encode_split(const TensorDev *descs,
     // table-coded fields have a state that runs through the rows; flat, raw and constant ones do not
     const bool table[2] = {mode[0] == ZC_MODE_HUFF && (WPR == 4 || kind[0] != 1), mode[1] == ZC_MODE_HUFF && (WPR == 4 || kind[1] != 1)};
     const bool flat[2] = {mode[0] == ZC_MODE_HUFF && !table[0], mode[1] == ZC_MODE_HUFF && !table[1]};
-    const char *lut[2] = {reinterpret_cast<const char *>(tab[0]), reinterpret_cast<const char *>(tab[1])};
+    const char *const lut[2] = {reinterpret_cast<const char *>(tab[0]), reinterpret_cast<const char *>(tab[1])};
 
-    const uint32_t per_wave = (C.rows + W - 1) / W, segments = (C.rows + per_wave - 1) / per_wave;
-    const uint32_t row_begin = wave * per_wave < C.rows ? wave * per_wave : C.rows;
-    const uint32_t row_end = row_begin + per_wave < C.rows ? row_begin + per_wave : C.rows;
+    const Segment<W> R_(C.rows, wave);
+    const uint32_t segments = (C.rows + R_.per_wave - 1) / R_.per_wave, row_begin = R_.begin, row_end = R_.end;
+    const uint32_t whole = C.nbytes / 1024 < row_end ? C.nbytes / 1024 : row_end;         // rows of this segment in which every lane holds a whole run end here
+    // two rows are asked for ahead of the one that is coded
+    auto fetch = [&](uint32_t row) {
+        u32x4 v = {0, 0, 0, 0};
+        if (row < whole) {
+            const uint64_t at = (uint64_t)(row * 64 + lane) * 16;
+            v = *reinterpret_cast<const u32x4 *>(C.src + at);
+            if (C.base) v ^= *reinterpret_cast<const u32x4 *>(C.base + at);
+        } else if (row < row_end) v = C.run_of(row, lane);
+        return v;
+    };
+    u32x4 next = fetch(row_begin), after = fetch(row_begin + 1);
     // ---- bits of every segment but the last (whose rows may be incomplete, and whose bits nobody asks for)
     if ((table[0] || table[1]) && wave + 1 < segments) {
         uint32_t bits[2] = {0, 0}, last[2] = {0, 0};
-        for (uint32_t r0 = row_begin; r0 < row_end; r0 += 4) {
-            u32x4 v[4];
+        if (seg) {
 #pragma unroll
-            for (uint32_t i = 0; i < 4; i++) {
-                const uint64_t at = (uint64_t)((r0 + i < row_end ? r0 + i : row_end - 1) * 64 + lane) * 16;
-                v[i] = *reinterpret_cast<const u32x4 *>(C.src + at);
-                if (C.base) v[i] ^= *reinterpret_cast<const u32x4 *>(C.base + at);
-            }
-#pragma unroll
-            for (uint32_t i = 0; i < 4; i++) {
-                if (r0 + i >= row_end) break;
-                uint32_t w[2][4];
-                split_words<FMT>(v[i], w);
-#pragma unroll
-                for (int f = 0; f < 2; f++)
-                    if (table[f]) run_bits<SB, G>(period[f], w[f], lut[f], bits[f], last[f]);
-            }
-        }
+            for (int f = 0; f < 2; f++)
+                if (table[f]) {
+                    const uint32_t x = seg[(uint64_t)blockIdx.x * (W * 128) + (wave * 2 + f) * 64 + lane];
+                    bits[f] = x >> 6; last[f] = x & 63u;
+                }
+        } else bits_of_rows<FMT>(C, row_begin, row_end, lane, table, period, lut, bits, last);
 #pragma unroll
         for (int f = 0; f < 2; f++) { seg_bits[wave][f][lane] = bits[f]; seg_last[wave][f][lane] = last[f]; }
     }
@@ -439,12 +466,10 @@ __global__ __launch_bounds__(64 * W) void k_encode_split(const TensorDev *descs,
             else __builtin_amdgcn_raw_buffer_store_b128(u32x4{w[0], w[1], w[2], w[3]}, out[f], (int)((row * 64 + lane) * 16), 0, 0);
         }
     };
-    const uint32_t whole = C.nbytes / 1024 < row_end ? C.nbytes / 1024 : row_end;         // rows of this segment in which every lane holds a whole run end here
-    u32x4 next = {0, 0, 0, 0};
-    if (row_begin < row_end) next = C.run_of(row_begin, lane);
     for (uint32_t row = row_begin; row < whole; row++) {
         const u32x4 v = next;
-        if (row + 1 < row_end) next = C.run_of(row + 1, lane);
+        next = after;
+        after = fetch(row + 2);
         uint32_t w[2][4];
         split_words<FMT>(v, w);
 #pragma unroll
@@ -511,7 +536,7 @@ __global__ __launch_bounds__(64 * W) void k_encode_split(const TensorDev *descs,
     if (lane < ((4 - (words & 3)) & 3)) __builtin_amdgcn_raw_buffer_store_b32(0u, o, (int)((words + lane) * 4), 0, 0);
 }
 
-int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream)
+int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, uint32_t *d_seg, void *stream)
 {
     if (n_work == 0) return 0;
     hipStream_t st = (hipStream_t)stream;
@@ -519,21 +544,21 @@ int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d
     const dim3 grid(n_work), block(64 * waves);
     switch (fmt) {
     case ZC_FMT_BF16:
-        if (waves == 8) hipLaunchKernelGGL((k_sizes_split<ZC_FMT_BF16, 8>), grid, block, 0, st, d_descs, d_work, d_enc, d_units);
-        else hipLaunchKernelGGL((k_sizes_split<ZC_FMT_BF16, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units);
+        if (waves == 8) hipLaunchKernelGGL((k_sizes_split<ZC_FMT_BF16, 8>), grid, block, 0, st, d_descs, d_work, d_enc, d_units, d_seg);
+        else hipLaunchKernelGGL((k_sizes_split<ZC_FMT_BF16, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units, d_seg);
         break;
     case ZC_FMT_FP8_E4M3:
-        if (waves == 8) hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3, 8>), grid, block, 0, st, d_descs, d_work, d_enc, d_units);
-        else hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units);
+        if (waves == 8) hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3, 8>), grid, block, 0, st, d_descs, d_work, d_enc, d_units, d_seg);
+        else hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units, d_seg);
         break;
-    case ZC_FMT_FP8_E4M3_BYTES: hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3_BYTES, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units); break;
-    case ZC_FMT_FP8_E5M2: hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E5M2, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units); break;
+    case ZC_FMT_FP8_E4M3_BYTES: hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E4M3_BYTES, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units, d_seg); break;
+    case ZC_FMT_FP8_E5M2: hipLaunchKernelGGL((k_sizes_split<ZC_FMT_FP8_E5M2, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_units, d_seg); break;
     default: return 1;
     }
     return (int)hipGetLastError();
 }
 
-int launch_encode_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream)
+int launch_encode_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint32_t *d_seg, void *stream)
 {
     if (n_work == 0) return 0;
     hipStream_t st = (hipStream_t)stream;
@@ -541,15 +566,15 @@ int launch_encode_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *
     const dim3 grid(n_work), block(64 * waves);
     switch (fmt) {
     case ZC_FMT_BF16:
-        if (waves == 8) hipLaunchKernelGGL((k_encode_split<ZC_FMT_BF16, 8>), grid, block, 0, st, d_descs, d_work, d_enc);
-        else hipLaunchKernelGGL((k_encode_split<ZC_FMT_BF16, 16>), grid, block, 0, st, d_descs, d_work, d_enc);
+        if (waves == 8) hipLaunchKernelGGL((k_encode_split<ZC_FMT_BF16, 8>), grid, block, 0, st, d_descs, d_work, d_enc, d_seg);
+        else hipLaunchKernelGGL((k_encode_split<ZC_FMT_BF16, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_seg);
         break;
     case ZC_FMT_FP8_E4M3:
-        if (waves == 8) hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3, 8>), grid, block, 0, st, d_descs, d_work, d_enc);
-        else hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3, 16>), grid, block, 0, st, d_descs, d_work, d_enc);
+        if (waves == 8) hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3, 8>), grid, block, 0, st, d_descs, d_work, d_enc, d_seg);
+        else hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_seg);
         break;
-    case ZC_FMT_FP8_E4M3_BYTES: hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3_BYTES, 16>), grid, block, 0, st, d_descs, d_work, d_enc); break;
-    case ZC_FMT_FP8_E5M2: hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E5M2, 16>), grid, block, 0, st, d_descs, d_work, d_enc); break;
+    case ZC_FMT_FP8_E4M3_BYTES: hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E4M3_BYTES, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_seg); break;
+    case ZC_FMT_FP8_E5M2: hipLaunchKernelGGL((k_encode_split<ZC_FMT_FP8_E5M2, 16>), grid, block, 0, st, d_descs, d_work, d_enc, d_seg); break;
     default: return 1;
     }
     return (int)hipGetLastError();

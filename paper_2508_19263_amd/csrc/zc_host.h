@@ -91,7 +91,8 @@ struct LandingLease {
 // where everything lives in the workspace of a compress-side call
 struct Workspace {
     uint64_t descs, hist_work, scale_work, chunk_work, fast_work, whole_work, other_work, hist, enc, units, scan, blobs, lane_counts, total, host_end;
-    uint64_t page_counts, page_lasts, wanted;      // counts per (page, lane) pair, behind what a call needs: used where the workspace has room for them (`wanted`)
+    uint64_t page_counts, page_lasts, seg_bits, wanted;      // counts per (page, lane) pair and bits of chunks' segments, behind what a call needs: used where the workspace has room for them (`wanted`)
+    uint64_t seg_items;
     uint32_t n_hist_work, n_scale_work, n_chunk_work;
     uint64_t n_units;
 };
@@ -108,6 +109,7 @@ struct CompressShape {
     bool rows8;                 // 64 lanes, whole rows, 8 or 16 symbols of 8 bits per run and field (BF16, FP8 in byte symbols, FP8 E5M2): the 64-lane encoder written for BF16
     bool whole_shape;           // 64 lanes, chunks of whole 1 KiB rows: the generic encoder's whole-chunk build
     bool split_rest;            // 64 lanes, two fields: what the whole-chunk kernels leave over goes through the kernels that give a chunk sixteen or eight wavefronts
+    bool seg_bits;              // the size pass of those kernels leaves its bit totals for their encoder
     bool split_all;             // so few chunks that all of them do (then no other chunk list and no counts per lane)
     bool fp4_tails;             // FP4, 64 lanes, chunks of whole rows: what is left over is a tensor's short last chunk, for k_encode_fp4_tail
     int whole_mode;             // 2: one whole chunk per work item, shared by its four wavefronts
@@ -152,6 +154,7 @@ struct CompressQueue {
     uint32_t *d_enc() const { return (uint32_t *)(ws + w.enc); }
     uint32_t *d_units() const { return (uint32_t *)(ws + w.units); }
     uint16_t *d_lane_counts() const { return (uint16_t *)(ws + w.lane_counts); }
+    uint32_t *d_seg() const { return sh.seg_bits && n_slow <= w.seg_items ? (uint32_t *)(ws + w.seg_bits) : nullptr; }
     const WorkItem *d_list(uint64_t off) const { return (const WorkItem *)(ws + off); }
 
     zc_status queue_histogram(bool cleared = false) const;          // cleared: the bins are

@@ -106,6 +106,8 @@ constexpr uint32_t kWavesPerGroup = 4;
 // 896: 305 | 300; E5M2, whose runs have twice the symbols, 1024: 464 | 395, 1536: 582 | 558; BF16 deltas, both fields table
 // coded, 512: 362 | 296, 640: 386 | 397.  Chunks of 64 KiB cross at the same counts (both sides are proportional to the rows).
 constexpr uint32_t kSplitChunkBytes = 32 * 1024;
+constexpr uint64_t kSegBytes = 16 * 2 * 64 * 4;           // bit totals of a chunk's segments, per lane and field
+constexpr uint32_t kSegItems = 1024;                      // for as many chunks at most
 inline uint64_t split_chunk_limit(uint32_t fmt, bool delta) { return delta ? 512 : fmt == ZC_FMT_FP8_E5M2 ? 1024 : 768; }
 
 // The tensor's bins of the formats that are counted in bit planes: their fields have at most 40 values together, and the first two
@@ -219,8 +221,9 @@ int launch_hist_rows8_lanes(uint32_t fmt, const TensorDev *d_descs, const WorkIt
 int launch_sizes_rows8_counts(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc,
                               const uint32_t *d_lane_counts, uint32_t *d_units, void *stream);
 // Two-field formats, 64 lanes, any chunks, one per work item: sixteen or eight wavefronts to a chunk (zc_encode_split.hip)
-int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream);
-int launch_encode_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream);
+// (the same list for both; d_seg: kSegBytes per item that the first leaves for the second, or null)
+int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, uint32_t *d_seg, void *stream);
+int launch_encode_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint32_t *d_seg, void *stream);
 int launch_sizes_fp8_counts(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, const uint16_t *d_lane_counts,
                             uint32_t *d_units, void *stream);
 int launch_encode_fp8(const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream);

@@ -106,6 +106,7 @@ zc_status compress_single_device_setup(const zc_tensor &x, const zc_params *para
     if (x.comp_capacity < bound) return ZC_ERR_BUFFER_TOO_SMALL;          // the sizes are not read back before the encoder runs
     q.sh = compress_shape(g, true, nc, x.d_xor_base != nullptr);
     q.sh.pages = q.sh.pages && ws_bytes >= q.w.wanted;
+    q.sh.seg_bits = ws_bytes >= q.w.wanted;
     q.ws = d_ws; q.stream = stream; q.T = 1; q.stats_only = false;
     const bool fs = compress_fast_shape(g, x.n_elems, bound);
     const TensorLists L = device_code_lists(g, q.sh, x.n_elems, nc, fs);
