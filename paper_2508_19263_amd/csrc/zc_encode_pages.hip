@@ -61,6 +61,9 @@ __device__ __forceinline__ uint32_t encode_pages(const TensorDev *dp, uint32_t f
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t s = lane & (S - 1), grp = lane / S;
     const uint64_t gmask = ((1ull << S) - 1) << (lane - s);
+    // which bytes of a ballot are the group's (S == 4: the byte it is half of), and the lanes of the group below this one
+    const uint32_t first_byte = lane / 8 * 8 / S * S / 8, below_lane = (1u << s) - 1;
+    const uint32_t group_bytes = S <= 8 ? 0x0C0C0C00u | lane / 8 : S == 16 ? 0x0C0C0100u + first_byte * 0x0101u : 0x03020100u + first_byte * 0x01010101u;
     const uint32_t cb = uni32(dp->chunk_bytes);                  // FP8: one element per byte; BF16: two bytes per element
     const uint64_t n_elems = uni64(dp->n_elems) * (BF ? 2 : 1);  // in bytes
     const uint32_t n_full = (uint32_t)(n_elems / cb);
@@ -188,11 +191,14 @@ __device__ __forceinline__ uint32_t encode_pages(const TensorDev *dp, uint32_t f
             for (int g = 0; g < kPeriods; g++) {
                 const bool req = k <= 32;
                 if (WRITE) {
-                    const uint64_t bm = __ballot(req) & gmask;
-                    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(bm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bm, wpos));
+                    // (the group's bits of the ballot, picked out as bytes: two instructions less than masking it and counting across all lanes)
+                    const uint64_t all = __ballot(req);
+                    uint32_t asked = __builtin_amdgcn_perm((uint32_t)(all >> 32), (uint32_t)all, group_bytes);
+                    if (S == 4) asked = (asked >> (lane & 4)) & 15u;
+                    const uint32_t pos = wpos + (uint32_t)__popc(asked & below_lane);
                     p0 = k == 0 ? pos : p0;              // nothing owed: the word asked for is the one due
                     p1 = req ? pos : p1;
-                    wpos += (uint32_t)__popcll(bm);
+                    wpos += (uint32_t)__popc(asked);
                 } else q += req ? 1u : 0u;
                 k += req ? 32 : 0;
                 uint32_t code = 0, len = 0;

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void k_hist(const TensorDev *descs, const Work
     constexpr bool TWO = FMT != 0;
     static_assert(kHistBlockBytes / 16 * 8 / 32 < 65536, "a copy counts at most 8 symbols per 16-byte run of the block, over 32 copies");
     __shared__ uint32_t h[256 * 32];
-    // split: workgroups per block of the work list (1, 2 or 4), each counting its part of the block: a list of few blocks is
+    // split: workgroups per block of the work list (1, 2, 4 or 16), each counting its part of the block: a list of few blocks is
     // spread over more workgroups than the compute units hold at once, so that no second round of a few stragglers forms
     const WorkItem it = work[blockIdx.x / split];
     const uint32_t part_bytes = kHistBlockBytes / split;
@@ -110,11 +110,11 @@ int launch_hist(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, 
 {
     if (n_work == 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-    static_assert(kHistBlockBytes % (4 * 4 * 256 * 16) == 0, "a quarter of a block is whole rounds of the kernel's loads");
+    static_assert(kHistBlockBytes % (16 * 4 * 256 * 16) == 0, "a sixteenth of a block is whole rounds of the kernel's loads");
     // A list of so few blocks that the compute units are not full: two or four workgroups per block.  (Longer lists lose by
     // it: every workgroup clears and folds its 32 KiB of counters and adds up to 256 totals to the tensor's bins, and C3's
-    // 1,344 blocks took 115 instead of 92 us in quarters.)
-    const uint32_t split = n_work <= 320 ? 4u : n_work <= 640 ? 2u : 1u;
+    // 1,344 blocks took 115 instead of 92 us in quarters.)  A handful of blocks in sixteenths, a round of loads each.
+    const uint32_t split = n_work <= 16 ? 16u : n_work <= 320 ? 4u : n_work <= 640 ? 2u : 1u;
     const dim3 grid(n_work * split);
     if (fmt == ZC_FMT_BF16 && !scales_view)
         hipLaunchKernelGGL(k_hist<ZC_FMT_BF16>, grid, dim3(256), 0, st, d_descs, d_work, 16, 0, d_hist, split);
