@@ -171,7 +171,7 @@ zc_status CompressQueue::queue_histogram(bool cleared) const
         return ZC_OK;
     }
     LAUNCH_TRY(launch_hist(g.fmt, d_descs(), d_list(w.hist_work), n_hist, 0, d_hist(), stream));
-    LAUNCH_TRY(launch_hist_rows8_lanes(g.fmt, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), (uint32_t *)d_lane_counts(), stream));
+    LAUNCH_TRY(launch_hist_rows8_lanes(g.fmt, d_descs(), d_list(w.hist_work) + n_hist, n_lane_hist, d_hist(), (uint32_t *)d_lane_counts(), d_present(), stream));
     if (g.nf == 3) LAUNCH_TRY(launch_hist(g.fmt, d_descs(), d_list(w.scale_work), n_scale, (int)scale_block(g.fmt), d_hist(), stream));
     return ZC_OK;
 }
@@ -200,7 +200,7 @@ zc_status CompressQueue::queue_sizes_and_scan() const
     // generic kernels: the whole-chunk list leaves route 1 to the FP8 kernels (route 2 there is the BF16 encoder,
     // whose sizes come from this pass); the list of page-shaped tensors leaves both routes to the page kernels
     // (with the symbols counted per lane, route 2 has its sizes from the counts)
-    if (sh.lanes8) LAUNCH_TRY(launch_sizes_rows8_counts(g.fmt, d_descs(), d_list(w.whole_work), n_whole, d_enc(), (const uint32_t *)d_lane_counts(), d_units(), stream));
+    if (sh.lanes8) LAUNCH_TRY(launch_sizes_rows8_counts(g.fmt, d_descs(), d_list(w.whole_work), n_whole, d_enc(), (const uint32_t *)d_lane_counts(), d_present(), d_units(), stream));
     // (E5M2 has no encoder of its own, route 0, and all its whole chunks are sized from the counts)
     if (sh.lanes_e5m2) LAUNCH_TRY(launch_sizes_e5m2_counts(d_descs(), d_list(w.whole_work), n_whole, d_enc(), d_lane_counts(), d_units(), stream));
     else

@@ -155,6 +155,12 @@ struct CompressQueue {
     uint32_t *d_units() const { return (uint32_t *)(ws + w.units); }
     uint16_t *d_lane_counts() const { return (uint16_t *)(ws + w.lane_counts); }
     uint32_t *d_seg() const { return sh.seg_bits && n_slow <= w.seg_items ? (uint32_t *)(ws + w.seg_bits) : nullptr; }
+    // 64 bytes per chunk behind those, where they fit: a call whose histogram pass counts 8-bit symbols per chunk lane has few chunks there
+    uint64_t *d_present() const
+    {
+        const uint64_t taken = (uint64_t)n_slow * kSegBytes;
+        return sh.seg_bits && taken + w.n_units / 2 * 64 <= w.seg_items * kSegBytes ? (uint64_t *)(ws + w.seg_bits + taken) : nullptr;
+    }
     const WorkItem *d_list(uint64_t off) const { return (const WorkItem *)(ws + off); }
 
     zc_status queue_histogram(bool cleared = false) const;          // cleared: the bins are

@@ -217,9 +217,10 @@ int launch_sizes_e5m2_counts(const TensorDev *d_descs, const WorkItem *d_work, u
 // BF16 / FP8 in byte symbols, 64 lanes, chunks of kHistBlockBytes: the same for fields of 8-bit symbols (256 counts
 // of 16 bits per lane and field, 64 KiB per chunk, at lane_counts + (units_off / 2 + chunk) * 16384 words), and the size pass of
 // the tensors of route 2 from those counts (zc_hist_lanes.hip)
-int launch_hist_rows8_lanes(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint64_t *d_hist, uint32_t *d_lane_counts, void *stream);
+// (d_present: 512 bits per chunk, the symbols of either field that it has, whose counts alone are written then, or null)
+int launch_hist_rows8_lanes(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint64_t *d_hist, uint32_t *d_lane_counts, uint64_t *d_present, void *stream);
 int launch_sizes_rows8_counts(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc,
-                              const uint32_t *d_lane_counts, uint32_t *d_units, void *stream);
+                              const uint32_t *d_lane_counts, const uint64_t *d_present, uint32_t *d_units, void *stream);
 // Two-field formats, 64 lanes, any chunks, one per work item: sixteen or eight wavefronts to a chunk (zc_encode_split.hip)
 // (the same list for both; d_seg: kSegBytes per item that the first leaves for the second, or null)
 int launch_sizes_split(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, uint32_t *d_seg, void *stream);
