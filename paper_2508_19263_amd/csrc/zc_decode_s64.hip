@@ -17,6 +17,13 @@ namespace zc {
 // Their whole rows are decoded as above; the row after them, in which a lane owns a whole run, part of one or
 // nothing, takes its stream words by the same rule with the lanes that own nothing left out, and is stored byte by
 // byte where a run is cut.  Formats with two fields only.  skip_whole: leave whole chunks to the kernel that has them.
+// Shared FP4 chunks (SPLIT, three fields): `skip_whole` is the number of workgroups that share a chunk's rows, in front of all of which come the
+// workgroups whose first wavefront decodes a chunk's scales, one serial chain; or 0, where the four wavefronts of one workgroup share the rows, and the first one takes fewer and
+// then the scales.  A chain beside wavefronts that keep the memory busy waits longer for its words: sixteen rows of scales (MXFP4) hide behind the
+// elements all the same, NVFP4's thirty-two do where there are more chunks than SIMDs.  Decode calls, one | four workgroups and the scales', us: MXFP4, 4 chunks 29.8 | 21.1,
+// 448: 46.7 | 44.2, 5,376: 591 | 561; NVFP4, 448: 76.7 | 82.7, 1,344: 174 | 151, 1,885 of 64 KiB 67 | 56 (eight: 21.1, 43.4, 566; 80.9, 145, 66).
+constexpr uint32_t kPlainParts = 4;
+inline uint32_t plain_parts(uint32_t fmt, uint32_t n_work) { return n_work <= (1u << 24) && (fmt != ZC_FMT_FP4_E2M1_NV || n_work > 1024) ? kPlainParts : 0; }
 template <int FMT, bool XOR, bool SPLIT, bool TAIL>
 __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single, uint32_t first_slot,
                                                     uint32_t skip_whole)
@@ -25,18 +32,21 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
     using F_ = Fmt<FMT>;
     static_assert(!TAIL || (F_::NF == 2 && !SPLIT), "the tail build has no scale field and no shared chunks");
     extern __shared__ __attribute__((aligned(16))) uint32_t rings[];     // [ring][wave][kRing2Words], sized by the host
-    __shared__ FieldTab tab[F_::NF];
+    __shared__ FieldTab tab[SPLIT ? 1 : F_::NF];                 // (shared chunks: the scales' alone)
     __shared__ TensorDev dsh;
     WorkItem it;
-    if (use_single) { it.tensor = 0; it.first = first_slot + blockIdx.x * (split ? 1u : kWavesPerGroup); }
-    else it = work[blockIdx.x];
+    const uint32_t parts = SPLIT && F_::NF == 3 ? skip_whole : 0u, items = parts ? gridDim.x / (parts + 1) : gridDim.x, at_item = blockIdx.x - items;
+    const bool elements = blockIdx.x >= items;                   // (of a chunk whose scales are another workgroup's)
+    const uint32_t item = elements ? at_item / (parts ? parts : 1u) : blockIdx.x;
+    if (use_single) { it.tensor = 0; it.first = first_slot + item * (split ? 1u : kWavesPerGroup); }
+    else it = work[item];
     if (threadIdx.x == 0) dsh = use_single ? single : descs[it.tensor];
     __syncthreads();
     const TensorDev &d = dsh;
     uint32_t kind[F_::NF];
     for (int f = 0; f < F_::NF; f++) {
         kind[f] = uniform32(d.kind[f]);
-        if (kind[f] == KIND_HUFF && !(SPLIT && f < 2)) build_field_tab(tab[f], d.comp + d.table_off[f], 1 << (f == 2 ? 8 : F_::SB), d.lmax[f]);
+        if (kind[f] == KIND_HUFF && !(SPLIT && f < 2) && !elements) build_field_tab(tab[SPLIT ? 0 : f], d.comp + d.table_off[f], 1 << (f == 2 ? 8 : F_::SB), d.lmax[f]);
     }
     const uint32_t lane = threadIdx.x & 63, wave = uniform32(threadIdx.x >> 6);       // (uniform: so are the rows, their loop and the stores' places)
     const uint32_t slot = uniform32(it.first + (split ? 0u : wave));
@@ -91,12 +101,17 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
     HuffStream H0, H1;
     const bool first = !TAIL || whole_rows > 0 || tail_sym > 0;                  // does this lane own a symbol at step 0?
     if (!SPLIT && kind[0] == KIND_HUFF) huff_open(H0, tab[0], r0, ring0, lane, rw, first);
-    if (!SPLIT && kind[1] == KIND_HUFF) huff_open(H1, tab[1], r1, ring1, lane, rw, first);
+    if (!SPLIT && kind[1] == KIND_HUFF) huff_open(H1, tab[SPLIT ? 0 : 1], r1, ring1, lane, rw, first);
 
     const uint32_t rows = TAIL ? whole_rows : cb / 1024;      // 64 lanes x 16 bytes per row
     if (split && (kind[0] == KIND_HUFF || kind[1] == KIND_HUFF)) return;          // the host never asks for this
     uint32_t row_begin = 0, row_end = rows;
-    if (split) shared_chunk_rows(rows, F_::NF == 3 ? (uint32_t)(E / F_::SCALE / 1024) : 0u, wave, row_begin, row_end);
+    if (parts) {
+        const uint32_t unit = at_item % (parts ? parts : 1u) * kWavesPerGroup + wave, units = parts * kWavesPerGroup;
+        if (!elements && wave != 0) return;
+        row_begin = elements ? (uint32_t)((uint64_t)unit * rows / units) : 0u;
+        row_end = elements ? (uint32_t)((uint64_t)(unit + 1) * rows / units) : 0u;
+    } else if (split) shared_chunk_rows(rows, F_::NF == 3 ? (uint32_t)(E / F_::SCALE / 1024) : 0u, wave, row_begin, row_end);
     // what a row takes from global memory besides its stream words (plainly stored fields, the base of a delta) is asked
     // for one row ahead
     constexpr int WPR = F_::G * F_::SB / 32;
@@ -138,7 +153,7 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
         const uint32_t next_sym = (TAIL && row + 1 == rows) ? tail_sym : (uint32_t)F_::G;
         if (!SPLIT && kind[0] == KIND_HUFF) huff_run<F_::SB, F_::G>(H0, tab[0], p0, P0, Q0, lane, F_::G, next_sym);
         else plain_finish<F_::SB, F_::G>(kind[0], w0, K0, P0, Q0);
-        if (!SPLIT && kind[1] == KIND_HUFF) huff_run<F_::SB, F_::G>(H1, tab[1], p1, P1, Q1, lane, F_::G, next_sym);
+        if (!SPLIT && kind[1] == KIND_HUFF) huff_run<F_::SB, F_::G>(H1, tab[SPLIT ? 0 : 1], p1, P1, Q1, lane, F_::G, next_sym);
         else plain_finish<F_::SB, F_::G>(kind[1], w1, K1, P1, Q1);
         const uint4 j = join_run4<FMT>(P0, Q0, P1, Q1);
         u32x4 v = {j.x, j.y, j.z, j.w};
@@ -150,7 +165,7 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
         uint64_t P0 = 0, P1 = 0, Q0 = 0, Q1 = 0;
         if (kind[0] == KIND_HUFF) huff_run<F_::SB, F_::G>(H0, tab[0], p0, P0, Q0, lane, tail_sym, 0u);
         else plain_tail<F_::SB, F_::G>(kind[0], r0, whole_rows, lane, tail_sym, K0, P0, Q0);
-        if (kind[1] == KIND_HUFF) huff_run<F_::SB, F_::G>(H1, tab[1], p1, P1, Q1, lane, tail_sym, 0u);
+        if (kind[1] == KIND_HUFF) huff_run<F_::SB, F_::G>(H1, tab[SPLIT ? 0 : 1], p1, P1, Q1, lane, tail_sym, 0u);
         else plain_tail<F_::SB, F_::G>(kind[1], r1, whole_rows, lane, tail_sym, K1, P1, Q1);
         if (tail_bytes) {
             const uint32_t at = whole_rows * 1024 + lane * 16;
@@ -160,7 +175,8 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
         }
     }
 
-    if (F_::NF == 3 && !(split && wave != 0)) {
+    if (F_::NF == 3 && !elements && !(split && wave != 0)) {
+        if (parts) __builtin_amdgcn_s_setprio(3);                // (a serial chain, beside wavefronts that wait for memory)
         // block scales: one byte per 32 elements, 16 per run, the chunk's E/32 scales in rows of 1024
         constexpr int F2 = F_::NF - 1;
         const uint32_t n_sc = (uint32_t)(E / F_::SCALE);
@@ -169,10 +185,10 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
         const uint32_t p2 = uniform32(d.period[F2]);
         const uint64_t K2 = splat(uniform32(d.konst[F2]), 8);
         HuffStream H2;
-        if (kind[F2] == KIND_HUFF) huff_open(H2, tab[F2], r2, ring0, lane, rw);      // this wavefront's first element ring is free again
+        if (kind[F2] == KIND_HUFF) huff_open(H2, tab[SPLIT ? 0 : F2], r2, ring0, lane, rw);      // this wavefront's first element ring is free again
         for (uint32_t row = 0; row < n_sc / 1024; row++) {
             uint64_t P0 = 0, P1 = 0;
-            if (kind[F2] == KIND_HUFF) huff_run<8, 16>(H2, tab[F2], p2, P0, P1, lane);
+            if (kind[F2] == KIND_HUFF) huff_run<8, 16>(H2, tab[SPLIT ? 0 : F2], p2, P0, P1, lane);
             else plain_run<8, 16>(kind[F2], r2, row, lane, K2, P0, P1);
             const u32x4 v = {(uint32_t)P0, (uint32_t)(P0 >> 32), (uint32_t)P1, (uint32_t)(P1 >> 32)};
             store_row<0>(v, ss, lane, row);
@@ -184,8 +200,10 @@ template <int FMT>
 static int launch_s64_x(bool xor_delta, int split, uint32_t lds_bytes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev &s, int use_single, hipStream_t st)
 {
     if (split) {
-        if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, true, false>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u);
-        else hipLaunchKernelGGL((k_decode_s64<FMT, false, true, false>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u);
+        const uint32_t parts = Fmt<FMT>::NF == 3 ? plain_parts(FMT, n_work) : 0u, n_groups = n_work * (parts + 1);
+        lds_bytes = kRing2Words * 4;                             // (one ring: the scales')
+        if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, true, false>), dim3(n_groups), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, parts);
+        else hipLaunchKernelGGL((k_decode_s64<FMT, false, true, false>), dim3(n_groups), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, parts);
     } else {
         if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, false, false>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u);
         else hipLaunchKernelGGL((k_decode_s64<FMT, false, false, false>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u);

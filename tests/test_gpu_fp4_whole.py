@@ -32,3 +32,26 @@ def test_whole_chunks(fmt, chunk, policy):
         assert np.array_equal(got.cpu().numpy(), want), (values, spread)
         out, s = zc.decompress(got, info, xor_base=on[1])
         assert torch.equal(out, on[0]) and torch.equal(s, on[2])
+
+
+@pytest.mark.parametrize("fmt", [zc.FMT_FP4_E2M1_MX, zc.FMT_FP4_E2M1_NV])
+@pytest.mark.parametrize("chunk", [2, 4, 16])
+def test_many_chunks_decode(fmt, chunk):
+    """On both sides of 1,024 chunks, from which NVFP4's scales have workgroups of their own; one tensor and a set."""
+    rng = np.random.default_rng(chunk)
+    p = zc.params(fmt, chunk * KIB, streams=64)
+    for chunks in (1024, 1025, 1700):
+        print("case", fmt, chunk, chunks, flush=True)
+        nbytes = chunks * chunk * KIB
+        x = torch.from_numpy(rng.integers(0, 256, nbytes).astype(np.uint8)).to(DEV)
+        scales = torch.from_numpy((100 + np.minimum(rng.geometric(0.3, 2 * nbytes // zc.scale_block(fmt)), 155)).astype(np.uint8)).to(DEV)
+        comp, info = zc.compress(x, 2 * nbytes, p, scales=scales)
+        out, s = zc.decompress(comp, info)
+        assert torch.equal(out, x) and torch.equal(s, scales)
+        half = nbytes // 2 // (chunk * KIB) * (chunk * KIB)
+        per = zc.scale_block(fmt) // 2
+        b = zc.Batch([x[:half], x[half:]], [2 * half, 2 * (nbytes - half)], p, scales=[scales[:half // per], scales[half // per:].clone()])
+        b.compress()
+        a, c = b.decompress()
+        assert torch.equal(a, x[:half]) and torch.equal(c, x[half:])
+        assert torch.equal(torch.cat(b.scales_out), scales)
