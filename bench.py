@@ -220,15 +220,15 @@ def other_workloads(torch, wl, zc, dev, extras, copy_gbps):
         run("c2_fp8_plain_symbols_auto", zc.FMT_FP8_E4M3, set2, n2, 262144, 64, policy=zc.POLICY_AUTO, decode_kernel="k_decode_fp8", compress_kernels="k_hist_fp8_lanes + k_codes + k_sizes_fp8_counts + k_scan + k_encode_fp8")
         # the generic paths beside their specialised neighbours: a chunk size that is not whole rows of 1 KiB takes the
         # chunks that are not whole rows: the generic encoder, the 64-lane decoder's build for such chunks
-        run("c2_fp8_chunks_of_48KiB_plus_16", zc.FMT_FP8_E4M3, set2, n2, 48 * 1024 + 16, 64, decode_kernel="k_decode_s64<TAIL>", compress_kernels="k_hist + k_codes + k_encode<false> + k_scan + k_encode<true>")
-        run("c2_fp8_chunks_of_48KiB_specialised_kernels", zc.FMT_FP8_E4M3, set2, n2, 48 * 1024, 64, decode_kernel="k_decode_fp8", compress_kernels="k_hist + k_codes + k_sizes_fp8 + k_scan + k_encode_fp8")
+        run("c2_fp8_chunks_of_48KiB_plus_16", zc.FMT_FP8_E4M3, set2, n2, 48 * 1024 + 16, 64, decode_kernel="k_decode_s64<TAIL>", compress_kernels="k_hist_planes + k_codes + k_encode<false> + k_scan + k_encode<true>")
+        run("c2_fp8_chunks_of_48KiB_specialised_kernels", zc.FMT_FP8_E4M3, set2, n2, 48 * 1024, 64, decode_kernel="k_decode_fp8", compress_kernels="k_hist_planes + k_codes + k_sizes_fp8 + k_scan + k_encode_fp8")
         # random access to the chunks of weights (Sec. 3.1): a seeded quarter of every tensor's 256 KiB chunks, in random order
         chunk_ids = [wl.page_sample(t.numel() // 262144, 0.25, device=dev, seed=900 + i) for i, t in enumerate(set2)]
         run("c2_fp8_chunk_list", zc.FMT_FP8_E4M3, set2, n2, 262144, 64, ids=chunk_ids, decode_kernel="k_decode_fp8; the list: its build for lists",
             compress_kernels="k_hist_fp8_lanes + k_codes + k_sizes_fp8_counts + k_scan + k_encode_fp8")
         del chunk_ids
         ragged = [t[:t.numel() - 4096 - 7 * 16] for t in set2]
-        run("c2_fp8_ragged_tails", zc.FMT_FP8_E4M3, ragged, [t.numel() for t in ragged], 262144, 64, decode_kernel="k_decode_fp8 + k_decode_pairs (last chunks)", compress_kernels="k_hist_fp8_lanes + k_hist + k_codes + k_sizes_fp8_counts + k_sizes_split (last chunks) + k_scan + k_encode_fp8 + k_encode_split (last chunks)")
+        run("c2_fp8_ragged_tails", zc.FMT_FP8_E4M3, ragged, [t.numel() for t in ragged], 262144, 64, decode_kernel="k_decode_fp8 + k_decode_pairs (last chunks)", compress_kernels="k_hist_fp8_lanes + k_hist_planes + k_codes + k_sizes_fp8_counts + k_sizes_split (last chunks) + k_scan + k_encode_fp8 + k_encode_split (last chunks)")
         del set2, ragged
         set2 = [t for _, t in wl.fp8_weight_set(32, device=dev, e5m2=True)]
         run("c2_shapes_in_fp8_e5m2", zc.FMT_FP8_E5M2, set2, [t.numel() for t in set2], 262144, 64, decode_kernel="k_decode_pairs", compress_kernels="k_hist_fp8_lanes<E5M2> + k_codes + k_sizes_e5m2_counts + k_scan + k_encode_bf16<E5M2>")
@@ -238,16 +238,16 @@ def other_workloads(torch, wl, zc, dev, extras, copy_gbps):
     run("c1_bf16_1M", zc.FMT_BF16, [x], [1 << 20], 65536, 64, limit=(16, 16, 0), decode_kernel="k_decode_pairs", compress_kernels="k_hist + k_codes + k_sizes_split + k_scan + k_encode_split")
     mats = [wl.mxfp4_weight(8192, 28672, device=dev, seed=300 + i) for i in range(3)]
     run("c3_mxfp4_70b_mlp", zc.FMT_FP4_E2M1_MX, [m[0] for m in mats], [8192 * 28672] * 3, 262144, 64, scales=[m[1] for m in mats],
-        decode_kernel="k_decode_s64 (chunk shared by four wavefronts)", compress_kernels="k_hist x2 + k_codes + k_encode (sizes) + k_scan + k_encode")
+        decode_kernel="k_decode_s64 (chunk shared by four workgroups)", compress_kernels="k_hist_planes + k_codes + k_encode (sizes) + k_scan + k_encode")
     if extras:
         # the same matrices 12 times over (36 matrices, 4.5 GB): enough chunks to fill the GPU, which 3 matrices do not
         big = [m for _ in range(12) for m in mats]
-        run("c3_mxfp4_36_matrices", zc.FMT_FP4_E2M1_MX, [m[0] for m in big], [8192 * 28672] * 36, 262144, 64, scales=[m[1] for m in big], decode_kernel=S64, compress_kernels="k_hist x2 + k_codes + k_encode (sizes) + k_scan + k_encode")
+        run("c3_mxfp4_36_matrices", zc.FMT_FP4_E2M1_MX, [m[0] for m in big], [8192 * 28672] * 36, 262144, 64, scales=[m[1] for m in big], decode_kernel=S64, compress_kernels="k_hist_planes + k_codes + k_encode (sizes) + k_scan + k_encode")
         del big
         run("c3_mxfp4_70b_mlp_byte_symbols", zc.FMT_FP4_E2M1_MX_BYTES, [m[0] for m in mats], [8192 * 28672] * 3, 262144, 64,
             scales=[m[1] for m in mats], policy=zc.POLICY_AUTO, decode_kernel=S64, compress_kernels="k_hist x2 + k_codes + k_encode (sizes) + k_scan + k_encode")
         mats = [wl.nvfp4_weight(8192, 28672, device=dev, seed=310 + i) for i in range(3)]
-        run("nvfp4_70b_mlp", zc.FMT_FP4_E2M1_NV, [m[0] for m in mats], [8192 * 28672] * 3, 262144, 64, scales=[m[1] for m in mats], decode_kernel=S64, compress_kernels="k_hist x2 + k_codes + k_encode (sizes) + k_scan + k_encode")
+        run("nvfp4_70b_mlp", zc.FMT_FP4_E2M1_NV, [m[0] for m in mats], [8192 * 28672] * 3, 262144, 64, scales=[m[1] for m in mats], decode_kernel=S64, compress_kernels="k_hist_planes + k_codes + k_encode (sizes) + k_scan + k_encode")
     del mats
     pairs = [wl.bf16_checkpoint_pair(4096 * 16384, device=dev, seed=400 + i) for i in range(16)]
     w0, w1 = [q[0] for q in pairs], [q[1] for q in pairs]
@@ -265,17 +265,17 @@ def other_workloads(torch, wl, zc, dev, extras, copy_gbps):
         kv += [k.reshape(-1), v.reshape(-1)]
     n_pages = kv[0].numel() // 2048
     ids = [wl.page_sample(n_pages, 0.25, device=dev, seed=600 + i) for i in range(len(kv))]
-    page_c = "k_hist + k_codes + k_encode_fp8_sub (sizes) + k_scan + k_encode_fp8_sub"
+    page_c = "k_hist_pages + k_codes + k_sizes_pages + k_scan + k_encode_fp8_sub"
     run("c5_fp8_kv_pages", zc.FMT_FP8_E4M3, kv, [t.numel() for t in kv], 2048, 8, ids=ids, dictionary=True, decode_kernel="k_decode_fp8_sub<8>", compress_kernels=page_c)
     # the same with the fields in reverse order in the payload (ZC_FLAG_REVERSE_FIELDS): the dictionary call is one pass
     run("c5_fp8_kv_pages_reverse_fields", zc.FMT_FP8_E4M3, kv, [t.numel() for t in kv], 2048, 8, ids=ids, dictionary=True, decode_kernel="k_decode_fp8_sub<8>",
-        compress_kernels="k_hist + k_codes + k_compress_pages_chained (sizes, scan and encoder in one pass over the source)", flags=zc.FLAG_REVERSE_FIELDS)
+        compress_kernels="k_hist_planes + k_codes + k_compress_pages_chained (sizes, scan and encoder in one pass over the source)", flags=zc.FLAG_REVERSE_FIELDS)
     if extras:
         # lanes per page: the tuning of configuration 5 (S = 8 is what the other rows use), and 64 lanes per page, which
         # takes the generic kernels
         for S in (4, 16, 32, 64):
             run("c5_fp8_kv_pages_S%d" % S, zc.FMT_FP8_E4M3, kv, [t.numel() for t in kv], 2048, S, ids=ids,
-                decode_kernel="k_decode_fp8_sub<%d>" % S if S < 64 else "k_decode (generic)", compress_kernels=page_c if S < 64 else "k_hist + k_codes + k_encode<false> + k_scan + k_encode<true>")
+                decode_kernel="k_decode_fp8_sub<%d>" % S if S < 64 else "k_decode (generic)", compress_kernels="k_hist_planes + k_codes + k_encode<false> + k_scan + k_encode<true>" if S == 64 else page_c if S > 4 else page_c.replace("k_hist_pages", "k_hist_planes").replace("k_sizes_pages", "k_encode_fp8_sub (sizes)"))
     # one decoding step's worth of new pages: 64 tensors x 32 pages of 2 KiB, dictionary known: latency, not throughput
     step_pages = [t[:32 * 2048].contiguous() for t in kv]
     p5 = zc.params(zc.FMT_FP8_E4M3, 2048, (0, 0, 0), 8)

@@ -26,7 +26,7 @@ namespace zc {
 bool lane_counts_shape(const Geometry &g) { return g.fmt == ZC_FMT_FP8_E4M3 && g.S == 64 && g.chunk_bytes == kHistBlockBytes; }
 // The same for BF16 and FP8 in byte symbols (k_hist_rows8_lanes, k_sizes_rows8_counts): 64 KiB of counts per chunk
 bool lane_counts8_shape(const Geometry &g) { return (g.fmt == ZC_FMT_BF16 || g.fmt == ZC_FMT_FP8_E4M3_BYTES) && g.S == 64 && g.chunk_bytes == kHistBlockBytes; }
-// and for FP8 E5M2 (k_hist_fp8_lanes<true>, k_sizes_e5m2_counts): 40 counts per chunk lane
+// and for FP8 E5M2 (k_hist_fp8_lanes<E5M2>, k_sizes_e5m2_counts): 40 counts per chunk lane
 bool lane_counts_e5m2_shape(const Geometry &g) { return g.fmt == ZC_FMT_FP8_E5M2 && g.S == 64 && g.chunk_bytes == kHistBlockBytes; }
 // and for FP8 E4M3 pages (k_hist_pages, k_sizes_pages): as many rows as a pair's counts of 8 bits hold, and whole passes of 256 pairs to a histogram block
 constexpr uint32_t kSegChunkBytes = 64u << 20;      // a segment's bits fit 26 bits

@@ -250,7 +250,7 @@ int launch_sizes_fp8_counts(const TensorDev *d_descs, const WorkItem *d_work, ui
     return (int)hipGetLastError();
 }
 
-// The same for FP8 E5M2 from the 40 counts per lane that k_hist_fp8_lanes<true> leaves (32 exponents, 8 sign+mantissa
+// The same for FP8 E5M2 from the 40 counts per lane that k_hist_fp8_lanes<E5M2> leaves (32 exponents, 8 sign+mantissa
 // symbols): either field, when table coded, takes min(steps, floor((bits - bits of its last R codes) / 32) + 2) words
 // per lane with R symbols per refill step (2, 4, 8 or 16 of the 16 symbols of a run).  One wavefront per chunk, work
 // items of kWavesPerGroup whole chunks (the list of the generic whole-chunk size pass, which leaves these tensors alone).
