@@ -269,6 +269,10 @@ struct Segment {
     }
 };
 
+// Does a field's number of bits follow from its data?  (A flat code's is the symbols' plain length, a field that is not coded has none.)  What k_sizes_split
+// leaves for the encoder it leaves for these fields.
+__device__ __forceinline__ bool bits_vary(uint32_t mode, uint32_t kind) { return mode == ZC_MODE_HUFF && kind != 1; }
+
 // Bits of rows [begin, end) of a chunk, whole runs in every lane, per field that `walk` names, and of their last refill period
 template <int FMT>
 __device__ __forceinline__ void bits_of_rows(const ChunkView<FMT> &C, uint32_t begin, uint32_t end, uint32_t lane, const bool walk[2], const uint32_t period[2], const char *const lut[2],
@@ -297,7 +301,7 @@ __device__ __forceinline__ void bits_of_rows(const ChunkView<FMT> &C, uint32_t b
 
 // Stream sizes of the chunks of a work list, one chunk per item.  W wavefronts add up the code lengths of a segment of the rows
 // each; the closed form above, taken at a lane's last step, gives the lane's words.  seg: where the segments' bits and those of their last periods
-// (bits << 6 | last; W * 2 * 64 words per item) are left for the encoder, or null.
+// (bits << 6 | last; W * 2 * 64 words per item) are left for the encoder where a field's bits_vary, or null.
 template <int FMT, uint32_t W>
 __global__ __launch_bounds__(64 * W) void k_sizes_split(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, uint32_t *units, uint32_t *seg)
 {
@@ -314,8 +318,8 @@ __global__ __launch_bounds__(64 * W) void k_sizes_split(const TensorDev *descs, 
     const uint32_t mode[2] = {uni32(dp->mode[0]), uni32(dp->mode[1])}, kind[2] = {uni32(dp->kind[0]), uni32(dp->kind[1])};
     const uint32_t period[2] = {uni32(dp->period[0]), uni32(dp->period[1])};
     load_tables<FMT>(dp, enc_tables + (uint64_t)it.tensor * 768, enc, tab);
-    // the last row is taken apart from the others, whose runs are whole in every lane (a flat code's bits need no data)
-    const bool walk[2] = {mode[0] == ZC_MODE_HUFF && kind[0] != 1, mode[1] == ZC_MODE_HUFF && kind[1] != 1};
+    // the last row is taken apart from the others, whose runs are whole in every lane
+    const bool walk[2] = {bits_vary(mode[0], kind[0]), bits_vary(mode[1], kind[1])};
     const char *const lut[2] = {reinterpret_cast<const char *>(tab[0]), reinterpret_cast<const char *>(tab[1])};
     const Segment<W> R_(C.rows, wave);
     uint32_t bits[2] = {0, 0}, last[2] = {0, 0};
@@ -403,7 +407,8 @@ __global__ __launch_bounds__(64 * W) void k_encode_split(const TensorDev *descs,
         out[f] = rsrc_of(comp + payload + 16 * a, (uint32_t)((b - a) * 16));
     }
     load_tables<FMT>(dp, enc_tables + (uint64_t)it.tensor * 768, enc, tab);
-    // table-coded fields have a state that runs through the rows; flat, raw and constant ones do not
+    // table-coded fields have a state that runs through the rows; flat, raw and constant ones do not (16 symbols of 8 bits to a run: a flat code's words are
+    // written like those of any other)
     const bool table[2] = {mode[0] == ZC_MODE_HUFF && (WPR == 4 || kind[0] != 1), mode[1] == ZC_MODE_HUFF && (WPR == 4 || kind[1] != 1)};
     const bool flat[2] = {mode[0] == ZC_MODE_HUFF && !table[0], mode[1] == ZC_MODE_HUFF && !table[1]};
     const char *const lut[2] = {reinterpret_cast<const char *>(tab[0]), reinterpret_cast<const char *>(tab[1])};
@@ -424,15 +429,17 @@ __global__ __launch_bounds__(64 * W) void k_encode_split(const TensorDev *descs,
     u32x4 next = fetch(row_begin), after = fetch(row_begin + 1);
     // ---- bits of every segment but the last (whose rows may be incomplete, and whose bits nobody asks for)
     if ((table[0] || table[1]) && wave + 1 < segments) {
+        const bool vary[2] = {bits_vary(mode[0], kind[0]), bits_vary(mode[1], kind[1])};
         uint32_t bits[2] = {0, 0}, last[2] = {0, 0};
-        if (seg) {
+        if (!seg && (vary[0] || vary[1])) bits_of_rows<FMT>(C, row_begin, row_end, lane, vary, period, lut, bits, last);
 #pragma unroll
-            for (int f = 0; f < 2; f++)
-                if (table[f]) {
-                    const uint32_t x = seg[(uint64_t)blockIdx.x * (W * 128) + (wave * 2 + f) * 64 + lane];
-                    bits[f] = x >> 6; last[f] = x & 63u;
-                }
-        } else bits_of_rows<FMT>(C, row_begin, row_end, lane, table, period, lut, bits, last);
+        for (int f = 0; f < 2; f++) {
+            if (!vary[f]) { bits[f] = (row_end - row_begin) * (G * SB); last[f] = period[f] * SB; }
+            else if (seg) {
+                const uint32_t x = seg[(uint64_t)blockIdx.x * (W * 128) + (wave * 2 + f) * 64 + lane];
+                bits[f] = x >> 6; last[f] = x & 63u;
+            }
+        }
 #pragma unroll
         for (int f = 0; f < 2; f++) { seg_bits[wave][f][lane] = bits[f]; seg_last[wave][f][lane] = last[f]; }
     }
