@@ -17,16 +17,15 @@ namespace zc {
 // Their whole rows are decoded as above; the row after them, in which a lane owns a whole run, part of one or
 // nothing, takes its stream words by the same rule with the lanes that own nothing left out, and is stored byte by
 // byte where a run is cut.  Formats with two fields only.  skip_whole: leave whole chunks to the kernel that has them.
-// Shared FP4 chunks (SPLIT, three fields): `skip_whole` is the number of workgroups that share a chunk's rows, in front of all of which come the
-// workgroups whose first wavefront decodes a chunk's scales, one serial chain; or 0, where the four wavefronts of one workgroup share the rows, and the first one takes fewer and
-// then the scales.  A chain beside wavefronts that keep the memory busy waits longer for its words: sixteen rows of scales (MXFP4) hide behind the
-// elements all the same, NVFP4's thirty-two do where there are more chunks than SIMDs.  Decode calls, one | four workgroups and the scales', us: MXFP4, 4 chunks 29.8 | 21.1,
+//
+// SPLIT, FP4: `shared_by` > 1 workgroups share a chunk's rows (plain_decode_parts), and in front of all of those come the workgroups whose first wavefront decodes a
+// chunk's scales, one serial chain.  shared_by <= 1: the four wavefronts of one workgroup share the rows, and the first one takes fewer and then the scales.
+// A chain beside wavefronts that keep the memory busy waits longer for its words: sixteen rows of scales (MXFP4) hide behind the elements all the same,
+// NVFP4's thirty-two do where there are more chunks than SIMDs.  Decode calls, one | four workgroups and the scales', us: MXFP4, 4 chunks 29.8 | 21.1,
 // 448: 46.7 | 44.2, 5,376: 591 | 561; NVFP4, 448: 76.7 | 82.7, 1,344: 174 | 151, 1,885 of 64 KiB 67 | 56 (eight: 21.1, 43.4, 566; 80.9, 145, 66).
-constexpr uint32_t kPlainParts = 4;
-inline uint32_t plain_parts(uint32_t fmt, uint32_t n_work) { return n_work <= (1u << 24) && (fmt != ZC_FMT_FP4_E2M1_NV || n_work > 1024) ? kPlainParts : 0; }
 template <int FMT, bool XOR, bool SPLIT, bool TAIL>
 __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single, uint32_t first_slot,
-                                                    uint32_t skip_whole)
+                                                    uint32_t skip_whole, uint32_t shared_by)
 {
     constexpr bool split = SPLIT;
     using F_ = Fmt<FMT>;
@@ -35,7 +34,7 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
     __shared__ FieldTab tab[SPLIT ? 1 : F_::NF];                 // (shared chunks: the scales' alone)
     __shared__ TensorDev dsh;
     WorkItem it;
-    const uint32_t parts = SPLIT && F_::NF == 3 ? skip_whole : 0u, items = parts ? gridDim.x / (parts + 1) : gridDim.x, at_item = blockIdx.x - items;
+    const uint32_t parts = SPLIT && F_::NF == 3 && shared_by > 1 ? shared_by : 0u, items = parts ? gridDim.x / (parts + 1) : gridDim.x, at_item = blockIdx.x - items;
     const bool elements = blockIdx.x >= items;                   // (of a chunk whose scales are another workgroup's)
     const uint32_t item = elements ? at_item / (parts ? parts : 1u) : blockIdx.x;
     if (use_single) { it.tensor = 0; it.first = first_slot + item * (split ? 1u : kWavesPerGroup); }
@@ -200,13 +199,13 @@ template <int FMT>
 static int launch_s64_x(bool xor_delta, int split, uint32_t lds_bytes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev &s, int use_single, hipStream_t st)
 {
     if (split) {
-        const uint32_t parts = Fmt<FMT>::NF == 3 ? plain_parts(FMT, n_work) : 0u, n_groups = n_work * (parts + 1);
+        const uint32_t parts = Fmt<FMT>::NF == 3 ? plain_decode_parts(FMT, n_work) : 1u, n_groups = parts > 1 ? n_work * (parts + 1) : n_work;
         lds_bytes = kRing2Words * 4;                             // (one ring: the scales')
-        if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, true, false>), dim3(n_groups), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, parts);
-        else hipLaunchKernelGGL((k_decode_s64<FMT, false, true, false>), dim3(n_groups), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, parts);
+        if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, true, false>), dim3(n_groups), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u, parts);
+        else hipLaunchKernelGGL((k_decode_s64<FMT, false, true, false>), dim3(n_groups), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u, parts);
     } else {
-        if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, false, false>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u);
-        else hipLaunchKernelGGL((k_decode_s64<FMT, false, false, false>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u);
+        if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, false, false>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u, 1u);
+        else hipLaunchKernelGGL((k_decode_s64<FMT, false, false, false>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u, 1u);
     }
     return (int)hipGetLastError();
 }
@@ -215,8 +214,8 @@ template <int FMT>
 static int launch_s64_tail_x(bool xor_delta, uint32_t lds_bytes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev &s, int use_single,
                              uint32_t first_slot, uint32_t skip_whole, hipStream_t st)
 {
-    if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, false, true>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, first_slot, skip_whole);
-    else hipLaunchKernelGGL((k_decode_s64<FMT, false, false, true>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, first_slot, skip_whole);
+    if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, false, true>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, first_slot, skip_whole, 1u);
+    else hipLaunchKernelGGL((k_decode_s64<FMT, false, false, true>), dim3(n_work), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, first_slot, skip_whole, 1u);
     return (int)hipGetLastError();
 }
 

@@ -82,6 +82,14 @@ struct alignas(16) TensorDev {
 
 struct WorkItem { uint32_t tensor, first; };   // `first`: first chunk / block of the item
 
+// HIP launches fewer than 2^32 threads: so many workgroups of 256
+constexpr uint32_t kMostGroups = 0xFFFFFFFFu / 256;
+// Whole FP4 chunks whose element fields are stored plainly: the workgroups that share the rows of each of n_work chunks, one more of which, in front of all
+// those, has the chunk's scales; or 1: one workgroup has both, as it does in calls of more chunks than such launches hold.
+constexpr uint32_t parts_that_fit(uint32_t n_work, uint32_t parts) { return parts > 1 && (uint64_t)n_work * (parts + 1) <= kMostGroups ? parts : 1; }
+constexpr uint32_t plain_encode_parts(uint32_t n_work) { return parts_that_fit(n_work, 8); }
+constexpr uint32_t plain_decode_parts(uint32_t fmt, uint32_t n_work) { return fmt == ZC_FMT_FP4_E2M1_NV && n_work <= 1024 ? 1 : parts_that_fit(n_work, 4); }
+
 // Workgroups are handed to the 8 XCDs (each with an L2 of its own) in turn, so workgroup p runs on XCD p % 8.
 // Work lists are ordered so that every XCD walks one contiguous eighth of the list: position p of the ordered list
 // holds the item at this position of the natural list of n items.

@@ -255,96 +255,65 @@ __device__ __forceinline__ uint32_t enc_finish(EncField &F, uint8_t *stream, con
     return (words + 3) / 4;
 }
 
-// A whole FP4 chunk whose element fields are stored plainly (flat code, raw, constant).  Its rows do not depend on each other, so the
-// encoder deals them out to `units` wavefronts, of which this is number `unit` (elements), four rows of loads in flight each: bound by memory.  One
-// wavefront codes the block scales (!elements), whose one stream is a serial chain, and asks for a row while the two before it are coded; its workgroups come first in
-// the launch, so that no chain begins when the rows are through, and go first on their SIMDs.  Whole calls, one workgroup per chunk whose first
-// wavefront had the scales and fewer rows | two, four, eight workgroups for the rows, us: a matrix of 448 chunks of MXFP4 156 | 102, 97, 98, of NVFP4 187 | 131, 130, 123;
-// three of them 348 | 256, 254, 248 and 392 | 296, 292, 291; twelve of MXFP4 1,012 | 903, 874, 867.  (With the scales in the first of eight workgroups of a chunk:
-// 102, 174, 280, 433, 1,000.)  The size pass needs no
-// element data at all: four wavefronts add up the scales' code lengths, and the words of a lane follow from its bits (min(steps, floor((bits - bits of
-// its last step) / 32) + 2), as in the size passes from counts); 12.6 -> 6.4 us for 448 chunks.
-template <int FMT, bool WRITE>
-__device__ __forceinline__ void plain_chunk(const TensorDev &d, uint32_t chunk, uint32_t rows, bool elements, uint32_t unit, uint32_t units, const uint8_t *src,
-                                            const uint8_t *base, uint8_t *const stream[3], const uint32_t *enc, uint32_t *my_units, const Lanes &L)
+// A whole FP4 chunk whose element fields are stored plainly (flat code, raw, constant), in three parts.
+//
+// Sizes: no element data is needed, a flat code takes two words per run whatever the data.  The workgroup's four wavefronts add up the scales' code lengths,
+// and the words of a lane follow from its bits (min(steps, floor((bits - bits of its last step) / 32) + 2), as in the size passes from counts).  Bound by
+// latency; 12.6 -> 6.4 us for 448 chunks.
+template <int FMT>
+__device__ __forceinline__ void plain_sizes(const TensorDev &d, uint32_t chunk, uint32_t rows, const uint32_t *enc, uint32_t *my_units, const Lanes &L)
 {
     using F_ = Fmt<FMT>;
-    const uint32_t lane = L.lane, wave = threadIdx.x >> 6;
-    const uint32_t m[2] = {d.mode[0], d.mode[1]}, m2 = d.mode[2];
+    __shared__ uint32_t part[kWavesPerGroup][64], tail[64];
+    const uint32_t lane = L.lane, wave = threadIdx.x >> 6, m2 = d.mode[2];
     const uint64_t E = (uint64_t)d.chunk_bytes * 8 / F_::EB;
     const uint32_t ns = (uint32_t)(E / F_::SCALE), runs = ns / 16, srows = (runs + 63) / 64;       // (whole rows of elements: whole runs of scales)
     const uint8_t *sc = d.scales + (uint64_t)chunk * ns;
-    if (!WRITE) {
-        __shared__ uint32_t part[kWavesPerGroup][64], tail[64];
-        const uint32_t R = d.period[2], last_row = lane < runs ? (runs - 1 - lane) / 64 : 0u;
-        uint32_t bits = 0;
-        if (m2 == ZC_MODE_HUFF)
-            for (uint32_t i = wave; i < srows; i += kWavesPerGroup) {
-                const uint32_t run = i * 64 + lane;
-                if (run >= runs) continue;
-                const uint4 v = *reinterpret_cast<const uint4 *>(sc + (uint64_t)run * 16);
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-                uint32_t last = 0;
+    const uint32_t R = d.period[2], last_row = lane < runs ? (runs - 1 - lane) / 64 : 0u;
+    uint32_t bits = 0;
+    if (m2 == ZC_MODE_HUFF)
+        for (uint32_t i = wave; i < srows; i += kWavesPerGroup) {
+            const uint32_t run = i * 64 + lane;
+            if (run >= runs) continue;
+            const uint4 v = *reinterpret_cast<const uint4 *>(sc + (uint64_t)run * 16);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            uint32_t last = 0;
 #pragma unroll
-                for (int j = 0; j < 16; j++) {
-                    const uint32_t l = enc[(w[j >> 2] >> (8 * (j & 3))) & 0xFFu] >> 16;
-                    bits += l;
-                    last += (uint32_t)j >= 16 - R ? l : 0u;
-                }
-                if (i == last_row) tail[lane] = last;
+            for (int j = 0; j < 16; j++) {
+                const uint32_t l = enc[(w[j >> 2] >> (8 * (j & 3))) & 0xFFu] >> 16;
+                bits += l;
+                last += (uint32_t)j >= 16 - R ? l : 0u;
             }
-        part[wave][lane] = bits;
-        __syncthreads();
-        if (wave != 0) return;
-        uint32_t u2 = 0;
-        if (m2 == ZC_MODE_HUFF) {
-            uint32_t q = 0;
-            if (lane < runs) {
-                const uint32_t steps = (last_row + 1) * (16 / R), before = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane] - tail[lane];
-                q = before / 32 + 2;
-                q = q < steps ? q : steps;
-            }
+            if (i == last_row) tail[lane] = last;
+        }
+    part[wave][lane] = bits;
+    __syncthreads();
+    if (wave != 0) return;
+    uint32_t u2 = 0;
+    if (m2 == ZC_MODE_HUFF) {
+        uint32_t q = 0;
+        if (lane < runs) {
+            const uint32_t steps = (last_row + 1) * (16 / R), before = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane] - tail[lane];
+            q = before / 32 + 2;
+            q = q < steps ? q : steps;
+        }
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
-            u2 = (q + 3) / 4;
-        } else if (m2 == ZC_MODE_RAW) u2 = (ns + 15) / 16;
-        if (lane == 0) {
-            // a flat code takes two words per run whatever the data
-            const uint32_t nsyms = (uint32_t)((E + F_::GRP - 1) / F_::GRP), raw = (uint32_t)((((uint64_t)nsyms * F_::SB + 7) / 8 + 15) / 16);
-            for (int f = 0; f < 2; f++) my_units[f * d.n_chunks + chunk] = m[f] == ZC_MODE_HUFF ? 32 * rows : m[f] == ZC_MODE_RAW ? raw : 0u;
-            my_units[2 * d.n_chunks + chunk] = u2;
-        }
-        return;
+        for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+        u2 = (q + 3) / 4;
+    } else if (m2 == ZC_MODE_RAW) u2 = (ns + 15) / 16;
+    if (lane == 0) {
+        const uint32_t nsyms = (uint32_t)((E + F_::GRP - 1) / F_::GRP), raw = (uint32_t)((((uint64_t)nsyms * F_::SB + 7) / 8 + 15) / 16);
+        for (int f = 0; f < 2; f++) my_units[f * d.n_chunks + chunk] = d.mode[f] == ZC_MODE_HUFF ? 32 * rows : d.mode[f] == ZC_MODE_RAW ? raw : 0u;
+        my_units[2 * d.n_chunks + chunk] = u2;
     }
-    if (!elements) {
-        __builtin_amdgcn_s_setprio(3);
-        EncField S = {0, 0, 0, 0, 0, 0, 0};
-        auto fetch = [&](uint32_t row) {
-            const uint32_t run = row * 64 + lane;
-            return run < runs ? *reinterpret_cast<const uint4 *>(sc + (uint64_t)run * 16) : make_uint4(0, 0, 0, 0);
-        };
-        auto put = [&](uint32_t row, const uint4 &v) {
-            const uint32_t run = row * 64 + lane, nsym = run < runs ? 16u : 0u;
-            const uint64_t P = (uint64_t)v.x | ((uint64_t)v.y << 32), Q = (uint64_t)v.z | ((uint64_t)v.w << 32);
-            if (m2 == ZC_MODE_HUFF) {
-                if (__all(nsym == 16u)) enc_run<true, 8, 16, true>(S, d.period[2], P, Q, nsym, enc, stream[2], L);
-                else enc_run<true, 8, 16, false>(S, d.period[2], P, Q, nsym, enc, stream[2], L);
-            } else if (m2 == ZC_MODE_RAW && nsym) {
-                reinterpret_cast<uint64_t *>(stream[2])[2 * run] = P;
-                reinterpret_cast<uint64_t *>(stream[2])[2 * run + 1] = Q;
-            }
-        };
-        uint4 a = fetch(0), b = fetch(1);
-        for (uint32_t i = 0; i < srows; i += 2) {
-            put(i, a);
-            a = fetch(i + 2);
-            if (i + 1 < srows) put(i + 1, b);
-            b = fetch(i + 3);
-        }
-        if (m2 == ZC_MODE_HUFF) enc_finish<true>(S, stream[2], L);
-        return;
-    }
-    const uint32_t first = (uint32_t)((uint64_t)unit * rows / units), end = (uint32_t)((uint64_t)(unit + 1) * rows / units);
+}
+
+// Rows first .. end - 1 of the elements, by one wavefront: they do not depend on each other.  Bound by memory: four rows of loads in flight.
+template <int FMT>
+__device__ __forceinline__ void plain_rows(const TensorDev &d, uint32_t first, uint32_t end, const uint8_t *src, const uint8_t *base, uint8_t *const stream[3], uint32_t lane)
+{
+    using F_ = Fmt<FMT>;
+    const uint32_t m[2] = {d.mode[0], d.mode[1]};
     constexpr int K = 4;
     for (uint32_t r0 = first; r0 < end; r0 += K) {
         uint4 v[K];
@@ -372,20 +341,56 @@ __device__ __forceinline__ void plain_chunk(const TensorDev &d, uint32_t chunk, 
     }
 }
 
+// The block scales, by one wavefront: their one stream is a serial chain.  A row is asked for while the two before it are coded.
+template <int FMT>
+__device__ __forceinline__ void plain_scales(const TensorDev &d, uint32_t chunk, uint8_t *stream, const uint32_t *enc, const Lanes &L)
+{
+    using F_ = Fmt<FMT>;
+    const uint32_t lane = L.lane, m2 = d.mode[2];
+    const uint64_t E = (uint64_t)d.chunk_bytes * 8 / F_::EB;
+    const uint32_t ns = (uint32_t)(E / F_::SCALE), runs = ns / 16, srows = (runs + 63) / 64;
+    const uint8_t *sc = d.scales + (uint64_t)chunk * ns;
+    __builtin_amdgcn_s_setprio(3);
+    EncField S = {0, 0, 0, 0, 0, 0, 0};
+    auto fetch = [&](uint32_t row) {
+        const uint32_t run = row * 64 + lane;
+        return run < runs ? *reinterpret_cast<const uint4 *>(sc + (uint64_t)run * 16) : make_uint4(0, 0, 0, 0);
+    };
+    auto put = [&](uint32_t row, const uint4 &v) {
+        const uint32_t run = row * 64 + lane, nsym = run < runs ? 16u : 0u;
+        const uint64_t P = (uint64_t)v.x | ((uint64_t)v.y << 32), Q = (uint64_t)v.z | ((uint64_t)v.w << 32);
+        if (m2 == ZC_MODE_HUFF) {
+            if (__all(nsym == 16u)) enc_run<true, 8, 16, true>(S, d.period[2], P, Q, nsym, enc, stream, L);
+            else enc_run<true, 8, 16, false>(S, d.period[2], P, Q, nsym, enc, stream, L);
+        } else if (m2 == ZC_MODE_RAW && nsym) {
+            reinterpret_cast<uint64_t *>(stream)[2 * run] = P;
+            reinterpret_cast<uint64_t *>(stream)[2 * run + 1] = Q;
+        }
+    };
+    uint4 a = fetch(0), b = fetch(1);
+    for (uint32_t i = 0; i < srows; i += 2) {
+        put(i, a);
+        a = fetch(i + 2);
+        if (i + 1 < srows) put(i + 1, b);
+        b = fetch(i + 3);
+    }
+    if (m2 == ZC_MODE_HUFF) enc_finish<true>(S, stream, L);
+}
+
 // Encoder body for the symbols of one field kind.  ELEM = true: fields 0 and 1 of the
 // element array; false: the FP4 scale field.
 // WHOLE: the launch covers only whole chunks of tensors with 64 lanes per chunk (one wavefront per chunk, every
 // run complete), which lets the compiler drop the lane-group masks and every partial-run path.
-// shared_chunk (WHOLE only; 0: not): a work item is ONE chunk for so many workgroups.  When both element fields are stored plainly (flat code, raw,
-// constant) they share it (plain_chunk).  Otherwise the first wavefront takes the chunk alone.  The host asks for this where plain element
-// fields are the rule (FP4).
+// shared_chunk (WHOLE only): 0, a work item is up to four chunks, one per wavefront; else it is ONE chunk.  When both its element fields are stored plainly (flat
+// code, raw, constant) it is shared, otherwise the first wavefront of one workgroup takes it alone.  1: by the four wavefronts of one workgroup, the first of which
+// codes the scales too; n > 1 (encoder only): n workgroups have the rows, and one more, in front of those of all chunks, has the scales, so that no chain begins when
+// the rows are through.  The host asks for this where plain element fields are the rule (FP4).
 template <int FMT, bool WRITE, bool WHOLE>
 __global__ __launch_bounds__(256) void k_encode(const TensorDev *descs, const WorkItem *work, const uint32_t *enc_tables, uint32_t *units, int skip_routes,
                                                 int shared_chunk)
 {
-    // a chunk shared by `parts` workgroups and, in front of all of those, one for its scales; see plain_chunk
-    const uint32_t parts = WHOLE && WRITE && shared_chunk > 0 ? (uint32_t)shared_chunk : 1u, items = WHOLE && WRITE && shared_chunk > 0 ? gridDim.x / (parts + 1) : gridDim.x;
-    const bool elements = blockIdx.x >= items;
+    const uint32_t parts = WHOLE && WRITE && shared_chunk > 1 ? (uint32_t)shared_chunk : 1u, items = parts > 1 ? gridDim.x / (parts + 1) : gridDim.x;
+    const bool elements = blockIdx.x >= items;                   // (of a chunk whose scales are another workgroup's)
     const uint32_t part = elements ? (blockIdx.x - items) % parts : 0u;
     using F_ = Fmt<FMT>;
     __shared__ uint32_t enc[3][256];
@@ -432,8 +437,15 @@ __global__ __launch_bounds__(256) void k_encode(const TensorDev *descs, const Wo
     const bool plain = plain0 && plain1;
     if constexpr (WHOLE && F_::NF == 3)
         if (shared && plain) {
-            if (WRITE && !elements && wave != 0) return;
-            plain_chunk<FMT, WRITE>(d, chunk, rows, elements, part * kWavesPerGroup + wave, parts * kWavesPerGroup, src, base, stream, enc[2], my_units, L);
+            if constexpr (!WRITE) plain_sizes<FMT>(d, chunk, rows, enc[2], my_units, L);
+            else {
+                uint32_t begin = 0, end = 0;
+                const uint32_t unit = part * kWavesPerGroup + wave, units_of_rows = parts * kWavesPerGroup;
+                if (elements) { begin = (uint32_t)((uint64_t)unit * rows / units_of_rows); end = (uint32_t)((uint64_t)(unit + 1) * rows / units_of_rows); }
+                else if (parts == 1) shared_chunk_rows(rows, (uint32_t)((E / F_::SCALE + 1023) / 1024), wave, begin, end);
+                plain_rows<FMT>(d, begin, end, src, base, stream, L.lane);
+                if (!elements && wave == 0) plain_scales<FMT>(d, chunk, stream[2], enc[2], L);
+            }
             return;
         }
     if (shared && (wave != 0 || elements)) return;
@@ -624,12 +636,11 @@ __global__ __launch_bounds__(WRITE ? 64 * kFp4TailWaves : 64) void k_encode_fp4_
     if (wave == kFp4TailWaves - 1 && nbytes % 1024) put(rows, tail_bytes, tail_sym, false);
 }
 
-constexpr uint32_t kPartsOfPlainChunk = 8;
 template <int FMT, bool WRITE>
 static void launch_encode_f(int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, hipStream_t st)
 {
-    const uint32_t parts = whole == 2 && WRITE && n_work < (1u << 24) ? kPartsOfPlainChunk : 1;
-    if (whole == 1 || whole == 2) hipLaunchKernelGGL((k_encode<FMT, WRITE, true>), dim3(whole == 2 && WRITE ? n_work * (parts + 1) : n_work), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, whole == 2 ? (int)parts : 0);
+    const uint32_t shared = whole != 2 ? 0u : WRITE ? plain_encode_parts(n_work) : 1u, groups = shared > 1 ? n_work * (shared + 1) : n_work;
+    if (whole == 1 || whole == 2) hipLaunchKernelGGL((k_encode<FMT, WRITE, true>), dim3(groups), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, (int)shared);
     else hipLaunchKernelGGL((k_encode<FMT, WRITE, false>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, whole == kFp4Tails ? 1 : 0);
 }
 

@@ -55,3 +55,30 @@ def test_many_chunks_decode(fmt, chunk):
         a, c = b.decompress()
         assert torch.equal(a, x[:half]) and torch.equal(c, x[half:])
         assert torch.equal(torch.cat(b.scales_out), scales)
+
+
+def test_more_chunks_than_a_launch_of_nine_workgroups_each_holds():
+    """1,900,000 chunks of 1 KiB, a thousand of them over and over, so that the code is that of the thousand and so is every stream: the thousand against the oracle, the rest
+    against the thousand.  (HIP launches fewer than 2^32 threads: 1,864,135 chunks at nine workgroups of 256.)"""
+    rng = np.random.default_rng(5)
+    fmt, few, times = zc.FMT_FP4_E2M1_MX, 1000, 1900
+    x = rng.integers(0, 256, few * KIB).astype(np.uint8)
+    scales = (100 + np.minimum(rng.geometric(0.3, 2 * x.size // 32), 155)).astype(np.uint8)
+    small = o.compress(x, 2 * x.size, o.params(fmt, KIB, (0, 0, 0), 64), scales=scales)
+    p = zc.params(fmt, KIB, streams=64)
+    on = [torch.from_numpy(a).to(DEV).repeat(times) for a in (x, scales)]
+    got, info = zc.compress(on[0], 2 * on[0].numel(), p, scales=on[1])
+    one = zc.validate_container(small)
+    assert info.n_chunks == few * times and [bytes(c) for c in info.code_len] == [bytes(c) for c in one.code_len] and list(info.mode) == list(one.mode)
+    small = torch.from_numpy(small).to(DEV)
+    word = lambda t, at, n: t[at:at + 4 * n].view(torch.int32).long()
+    at_small, at_big = one.payload_offset, info.payload_offset
+    for f in range(3):
+        index, index_of_few = word(got, info.index_offset[f], few * times + 1), word(small, one.index_offset[f], few + 1)
+        assert torch.equal(index.diff(), index_of_few.diff().repeat(times)), f
+        n = 16 * int(index_of_few[-1] - index_of_few[0])
+        assert torch.equal(got[at_big:at_big + n * times].view(times, n), small[at_small:at_small + n].expand(times, n)), f
+        at_small, at_big = at_small + n, at_big + n * times
+    assert at_big == got.numel() == info.total_bytes and at_small == small.numel()
+    out, s = zc.decompress(got, info)
+    assert torch.equal(out, on[0]) and torch.equal(s, on[1])
