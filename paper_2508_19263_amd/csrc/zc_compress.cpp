@@ -223,12 +223,12 @@ zc_status CompressQueue::queue_encoders() const
     if (chained) {}                                             // encoded where they were sized
     else if (g.S == 64) LAUNCH_TRY(launch_encode_fp8(d_descs(), d_list(w.fast_work), n_fast, d_enc(), stream));
     else LAUNCH_TRY(launch_encode_fp8_sub(g.S, 1, sh.bf16, d_descs(), d_list(w.fast_work), n_fast, d_enc(), d_units(), sh.fast_step, stream));
-    LAUNCH_TRY(launch_encode(g.fmt, sh.whole_mode, 0x6, d_descs(), d_list(w.whole_work), n_whole, d_enc(), stream));
+    LAUNCH_TRY(launch_encode(g.fmt, sh.whole_mode, g.chunk_bytes / 1024, 0x6, d_descs(), d_list(w.whole_work), n_whole, d_enc(), stream));
     if (sh.rows8) LAUNCH_TRY(launch_encode_bf16(g.fmt, d_descs(), d_list(w.whole_work), n_whole, d_enc(), stream));
-    LAUNCH_TRY(launch_encode(g.fmt, 0, 0x6, d_descs(), d_list(w.other_work), n_other, d_enc(), stream));
+    LAUNCH_TRY(launch_encode(g.fmt, 0, 0, 0x6, d_descs(), d_list(w.other_work), n_other, d_enc(), stream));
     if (sh.fp4_tails) LAUNCH_TRY(launch_fp4_tails(g.fmt, 1, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), nullptr, stream));
     else if (sh.split_rest) LAUNCH_TRY(launch_encode_split(g.fmt, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), d_seg(), stream));
-    else LAUNCH_TRY(launch_encode(g.fmt, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
+    else LAUNCH_TRY(launch_encode(g.fmt, 0, 0, 0, d_descs(), d_list(w.chunk_work), n_slow, d_enc(), stream));
     return ZC_OK;
 }
 

@@ -87,7 +87,13 @@ constexpr uint32_t kMostGroups = 0xFFFFFFFFu / 256;
 // Whole FP4 chunks whose element fields are stored plainly: the workgroups that share the rows of each of n_work chunks, one more of which, in front of all
 // those, has the chunk's scales; or 1: one workgroup has both, as it does in calls of more chunks than such launches hold.
 constexpr uint32_t parts_that_fit(uint32_t n_work, uint32_t parts) { return parts > 1 && (uint64_t)n_work * (parts + 1) <= kMostGroups ? parts : 1; }
-constexpr uint32_t plain_encode_parts(uint32_t n_work) { return parts_that_fit(n_work, 8); }
+//
+// Encoder: 32 rows (1 KiB of elements each) to a workgroup at least, eight to a wavefront.  With fewer the workgroups' starts are what a call waits for.  Whole calls of
+// MXFP4, one workgroup | two | four | eight, us: 65,536 chunks of 1 KiB 662 before chunks were shared out, 1,795 with eight; 32,768 of 1 KiB 261 | 402 | 574 | 919,
+// of 16 KiB 532 | 670 | 903 | 1,225; 8,192 of 32 KiB 227 | 240 | 294 | 395, of 64 KiB 380 | 383 | 394 | 507; few chunks, 64 of 64 KiB 43.8 | 42.6 | 42.5 | 42.5, of 128 KiB
+// 49.4 | 44.4 | 43.5 | 43.2, of 256 KiB 67 | 53 | 51 | 51; many, 4,096 of 128 KiB 379 | 366 | 360 | 371, 2,048 of 256 KiB 389 | 370 | 360 | 366.  NVFP4, whose scales take
+// twice as long, moves by 2 % at most with the parts where few chunks are left (64 of 256 KiB 86 | 85 | 85 | 85) and by as much as MXFP4 where there are many.
+constexpr uint32_t plain_encode_parts(uint32_t n_work, uint32_t rows) { return parts_that_fit(n_work, rows >= 256 ? 8 : rows >= 128 ? 4 : rows >= 64 ? 2 : 1); }
 constexpr uint32_t plain_decode_parts(uint32_t fmt, uint32_t n_work) { return fmt == ZC_FMT_FP4_E2M1_NV && n_work <= 1024 ? 1 : parts_that_fit(n_work, 4); }
 
 // Workgroups are handed to the 8 XCDs (each with an L2 of its own) in turn, so workgroup p runs on XCD p % 8.
@@ -178,7 +184,7 @@ int launch_fp4_tails(uint32_t fmt, int write, const TensorDev *d_descs, const Wo
 // to: what the host waits for (no flags: nothing)
 int launch_scan(const TensorDev *d_descs, uint32_t n_tensors, int n_fields, bool reversed, int skip_routes, const uint32_t *d_units, ScanOut *d_out, const uint8_t *d_blobs,
                 uint32_t blob_bytes, const HostRecords &to, void *stream);
-int launch_encode(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
+int launch_encode(uint32_t fmt, int whole, uint32_t rows, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                   const uint32_t *d_enc_tables, void *stream);
 int launch_decode(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, uint32_t chunks_per_item,
                   const TensorDev *single, uint32_t first_slot, void *stream);

@@ -637,25 +637,25 @@ __global__ __launch_bounds__(WRITE ? 64 * kFp4TailWaves : 64) void k_encode_fp4_
 }
 
 template <int FMT, bool WRITE>
-static void launch_encode_f(int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, hipStream_t st)
+static void launch_encode_f(int whole, uint32_t rows, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, hipStream_t st)
 {
-    const uint32_t shared = whole != 2 ? 0u : WRITE ? plain_encode_parts(n_work) : 1u, groups = shared > 1 ? n_work * (shared + 1) : n_work;
+    const uint32_t shared = whole != 2 ? 0u : WRITE ? plain_encode_parts(n_work, rows) : 1u, groups = shared > 1 ? n_work * (shared + 1) : n_work;
     if (whole == 1 || whole == 2) hipLaunchKernelGGL((k_encode<FMT, WRITE, true>), dim3(groups), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, (int)shared);
     else hipLaunchKernelGGL((k_encode<FMT, WRITE, false>), dim3(n_work), dim3(256), 0, st, d_descs, d_work, d_enc, d_units, skip_routes, whole == kFp4Tails ? 1 : 0);
 }
 
 template <bool WRITE>
-static int launch_encode_t(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, hipStream_t st)
+static int launch_encode_t(uint32_t fmt, int whole, uint32_t rows, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, hipStream_t st)
 {
     if (n_work == 0) return 0;
     switch (fmt) {
-    case ZC_FMT_BF16: launch_encode_f<ZC_FMT_BF16, WRITE>(whole, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
-    case ZC_FMT_FP8_E4M3: launch_encode_f<ZC_FMT_FP8_E4M3, WRITE>(whole, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
-    case ZC_FMT_FP4_E2M1_MX: launch_encode_f<ZC_FMT_FP4_E2M1_MX, WRITE>(whole, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
-    case ZC_FMT_FP8_E4M3_BYTES: launch_encode_f<ZC_FMT_FP8_E4M3_BYTES, WRITE>(whole, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
-    case ZC_FMT_FP4_E2M1_MX_BYTES: launch_encode_f<ZC_FMT_FP4_E2M1_MX_BYTES, WRITE>(whole, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
-    case ZC_FMT_FP4_E2M1_NV: launch_encode_f<ZC_FMT_FP4_E2M1_NV, WRITE>(whole, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
-    case ZC_FMT_FP8_E5M2: launch_encode_f<ZC_FMT_FP8_E5M2, WRITE>(whole, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
+    case ZC_FMT_BF16: launch_encode_f<ZC_FMT_BF16, WRITE>(whole, rows, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
+    case ZC_FMT_FP8_E4M3: launch_encode_f<ZC_FMT_FP8_E4M3, WRITE>(whole, rows, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
+    case ZC_FMT_FP4_E2M1_MX: launch_encode_f<ZC_FMT_FP4_E2M1_MX, WRITE>(whole, rows, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
+    case ZC_FMT_FP8_E4M3_BYTES: launch_encode_f<ZC_FMT_FP8_E4M3_BYTES, WRITE>(whole, rows, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
+    case ZC_FMT_FP4_E2M1_MX_BYTES: launch_encode_f<ZC_FMT_FP4_E2M1_MX_BYTES, WRITE>(whole, rows, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
+    case ZC_FMT_FP4_E2M1_NV: launch_encode_f<ZC_FMT_FP4_E2M1_NV, WRITE>(whole, rows, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
+    case ZC_FMT_FP8_E5M2: launch_encode_f<ZC_FMT_FP8_E5M2, WRITE>(whole, rows, skip_routes, d_descs, d_work, n_work, d_enc, d_units, st); break;
     default: return 1;
     }
     return (int)hipGetLastError();
@@ -680,19 +680,19 @@ int launch_fp4_tails(uint32_t fmt, int write, const TensorDev *d_descs, const Wo
 #undef ZC_TAIL
     const int e = (int)hipGetLastError();
     if (e) return e;
-    return write ? launch_encode_t<true>(fmt, kFp4Tails, 0, d_descs, d_work, n_work, d_enc, nullptr, st) : launch_encode_t<false>(fmt, kFp4Tails, 0, d_descs, d_work, n_work, d_enc, d_units, st);
+    return write ? launch_encode_t<true>(fmt, kFp4Tails, 0, 0, d_descs, d_work, n_work, d_enc, nullptr, st) : launch_encode_t<false>(fmt, kFp4Tails, 0, 0, d_descs, d_work, n_work, d_enc, d_units, st);
 }
 
 // whole: 1 = every work item is up to four whole chunks of a tensor with 64 lanes per chunk and chunks of whole
-// 1 KiB rows; 2 = every work item is one such chunk, shared by the workgroup's four wavefronts; 0 = any chunks
+// 1 KiB rows; 2 = every work item is one such chunk, of `rows` rows; 0 = any chunks
 int launch_sizes(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, uint32_t *d_units, void *stream)
 {
-    return launch_encode_t<false>(fmt, whole, skip_routes, d_descs, d_work, n_work, d_enc, d_units, (hipStream_t)stream);
+    return launch_encode_t<false>(fmt, whole, 0, skip_routes, d_descs, d_work, n_work, d_enc, d_units, (hipStream_t)stream);
 }
 
-int launch_encode(uint32_t fmt, int whole, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream)
+int launch_encode(uint32_t fmt, int whole, uint32_t rows, int skip_routes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream)
 {
-    return launch_encode_t<true>(fmt, whole, skip_routes, d_descs, d_work, n_work, d_enc, nullptr, (hipStream_t)stream);
+    return launch_encode_t<true>(fmt, whole, rows, skip_routes, d_descs, d_work, n_work, d_enc, nullptr, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------------------- scan
