@@ -346,7 +346,7 @@ typedef struct {
                                                    8 BF16, FP8 and FP8 in byte symbols with 64 lanes: 7 and 8 look up two symbols at
                                                    a time and take every chunk, short last ones and id lists included,
                                                    9 E5M2 as 7, a symbol per lookup, whole chunks: sets of many tensors of few chunks */
-    uint32_t fast_exp_kind, fast_sm_kind, n_rings /* kernels 3, 5: slots per workgroup; 7, 8: table-decoded fields * 64 + chunks per
+    uint32_t fast_exp_kind, fast_sm_kind, n_rings /* kernels 3, 5: slots per workgroup; 4: + 256 * workgroups per chunk (0: one); 7, 8: table-decoded fields * 64 + chunks per
                                                    workgroup, + 32 with long rings */, xor_delta;
     uint32_t scattered;                         /* some tensor decodes an id list */
     uint32_t tail_kernel;                       /* the second work list (chunks that are not whole rows, id lists with 64 lanes):

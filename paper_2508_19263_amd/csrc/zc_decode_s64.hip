@@ -20,9 +20,6 @@ namespace zc {
 //
 // SPLIT, FP4: `shared_by` > 1 workgroups share a chunk's rows (plain_decode_parts), and in front of all of those come the workgroups whose first wavefront decodes a
 // chunk's scales, one serial chain.  shared_by <= 1: the four wavefronts of one workgroup share the rows, and the first one takes fewer and then the scales.
-// A chain beside wavefronts that keep the memory busy waits longer for its words: sixteen rows of scales (MXFP4) hide behind the elements all the same,
-// NVFP4's thirty-two do where there are more chunks than SIMDs.  Decode calls, one | four workgroups and the scales', us: MXFP4, 4 chunks 29.8 | 21.1,
-// 448: 46.7 | 44.2, 5,376: 591 | 561; NVFP4, 448: 76.7 | 82.7, 1,344: 174 | 151, 1,885 of 64 KiB 67 | 56 (eight: 21.1, 43.4, 566; 80.9, 145, 66).
 template <int FMT, bool XOR, bool SPLIT, bool TAIL>
 __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, const WorkItem *work, TensorDev single, int use_single, uint32_t first_slot,
                                                     uint32_t skip_whole, uint32_t shared_by)
@@ -196,10 +193,11 @@ __global__ __launch_bounds__(256) void k_decode_s64(const TensorDev *descs, cons
 }
 
 template <int FMT>
-static int launch_s64_x(bool xor_delta, int split, uint32_t lds_bytes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev &s, int use_single, hipStream_t st)
+static int launch_s64_x(bool xor_delta, bool split, uint32_t parts, uint32_t lds_bytes, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev &s, int use_single, hipStream_t st)
 {
     if (split) {
-        const uint32_t parts = Fmt<FMT>::NF == 3 ? plain_decode_parts(FMT, n_work) : 1u, n_groups = parts > 1 ? n_work * (parts + 1) : n_work;
+        parts = Fmt<FMT>::NF == 3 ? parts_that_fit(n_work, parts) : 1u;
+        const uint32_t n_groups = parts > 1 ? n_work * (parts + 1) : n_work;
         lds_bytes = kRing2Words * 4;                             // (one ring: the scales')
         if (xor_delta) hipLaunchKernelGGL((k_decode_s64<FMT, true, true, false>), dim3(n_groups), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u, parts);
         else hipLaunchKernelGGL((k_decode_s64<FMT, false, true, false>), dim3(n_groups), dim3(256), lds_bytes, st, d_descs, d_work, s, use_single, 0u, 0u, parts);
@@ -219,9 +217,7 @@ static int launch_s64_tail_x(bool xor_delta, uint32_t lds_bytes, const TensorDev
     return (int)hipGetLastError();
 }
 
-// n_rings: 1 or 2 rings per wavefront (2 only when both element fields are table decoded); split: one chunk per
-// work item, its rows shared by the four wavefronts (both element fields stored plainly)
-int launch_decode_s64(uint32_t fmt, uint32_t n_rings, bool xor_delta, bool split, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
+int launch_decode_s64(uint32_t fmt, bool xor_delta, bool split, uint32_t parts, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                       const TensorDev *single, void *stream)
 {
     if (n_work == 0) return 0;
@@ -229,16 +225,15 @@ int launch_decode_s64(uint32_t fmt, uint32_t n_rings, bool xor_delta, bool split
     const TensorDev s = single ? *single : TensorDev{};
     const int use_single = single ? 1 : 0;
     // the rings of a workgroup take 8 KiB whether one or two fields are table decoded (see huff_open)
-    (void)n_rings;
     const uint32_t lds = kWavesPerGroup * kRing2Words * 4;
     switch (fmt) {
-    case ZC_FMT_BF16: return launch_s64_x<ZC_FMT_BF16>(xor_delta, split ? 1 : 0, lds, d_descs, d_work, n_work, s, use_single, st);
-    case ZC_FMT_FP8_E4M3: return launch_s64_x<ZC_FMT_FP8_E4M3>(xor_delta, split ? 1 : 0, lds, d_descs, d_work, n_work, s, use_single, st);
-    case ZC_FMT_FP4_E2M1_MX: return launch_s64_x<ZC_FMT_FP4_E2M1_MX>(xor_delta, split ? 1 : 0, lds, d_descs, d_work, n_work, s, use_single, st);
-    case ZC_FMT_FP8_E4M3_BYTES: return launch_s64_x<ZC_FMT_FP8_E4M3_BYTES>(xor_delta, split ? 1 : 0, lds, d_descs, d_work, n_work, s, use_single, st);
-    case ZC_FMT_FP4_E2M1_MX_BYTES: return launch_s64_x<ZC_FMT_FP4_E2M1_MX_BYTES>(xor_delta, split ? 1 : 0, lds, d_descs, d_work, n_work, s, use_single, st);
-    case ZC_FMT_FP4_E2M1_NV: return launch_s64_x<ZC_FMT_FP4_E2M1_NV>(xor_delta, split ? 1 : 0, lds, d_descs, d_work, n_work, s, use_single, st);
-    case ZC_FMT_FP8_E5M2: return launch_s64_x<ZC_FMT_FP8_E5M2>(xor_delta, split ? 1 : 0, lds, d_descs, d_work, n_work, s, use_single, st);
+    case ZC_FMT_BF16: return launch_s64_x<ZC_FMT_BF16>(xor_delta, split, parts, lds, d_descs, d_work, n_work, s, use_single, st);
+    case ZC_FMT_FP8_E4M3: return launch_s64_x<ZC_FMT_FP8_E4M3>(xor_delta, split, parts, lds, d_descs, d_work, n_work, s, use_single, st);
+    case ZC_FMT_FP4_E2M1_MX: return launch_s64_x<ZC_FMT_FP4_E2M1_MX>(xor_delta, split, parts, lds, d_descs, d_work, n_work, s, use_single, st);
+    case ZC_FMT_FP8_E4M3_BYTES: return launch_s64_x<ZC_FMT_FP8_E4M3_BYTES>(xor_delta, split, parts, lds, d_descs, d_work, n_work, s, use_single, st);
+    case ZC_FMT_FP4_E2M1_MX_BYTES: return launch_s64_x<ZC_FMT_FP4_E2M1_MX_BYTES>(xor_delta, split, parts, lds, d_descs, d_work, n_work, s, use_single, st);
+    case ZC_FMT_FP4_E2M1_NV: return launch_s64_x<ZC_FMT_FP4_E2M1_NV>(xor_delta, split, parts, lds, d_descs, d_work, n_work, s, use_single, st);
+    case ZC_FMT_FP8_E5M2: return launch_s64_x<ZC_FMT_FP8_E5M2>(xor_delta, split, parts, lds, d_descs, d_work, n_work, s, use_single, st);
     default: return 1;
     }
 }
@@ -646,7 +641,6 @@ int launch_decode_bf16_s64(uint32_t n_rings, bool xor_delta, const TensorDev *d_
     const TensorDev s = single ? *single : TensorDev{};
     const int use_single = single ? 1 : 0;
     const uint32_t lds = kWavesPerGroup * 2048;
-    (void)n_rings;
     if (xor_delta) hipLaunchKernelGGL((k_decode_bf16_s64<true>), dim3(n_work), dim3(256), lds, st, d_descs, d_work, s, use_single);
     else hipLaunchKernelGGL((k_decode_bf16_s64<false>), dim3(n_work), dim3(256), lds, st, d_descs, d_work, s, use_single);
     return (int)hipGetLastError();

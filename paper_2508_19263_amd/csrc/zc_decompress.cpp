@@ -301,7 +301,8 @@ zc_status decode_common(const void *d_comp, uint64_t comp_bytes, const zc_info *
         else if (bf16_s64_rings(info)) LAUNCH_TRY(launch_decode_bf16_s64(bf16_s64_rings(info), info.xor_delta != 0, nullptr, nullptr, n_fast, &d, stream));
         else {
             const bool split = s64_split_ok(info);
-            LAUNCH_TRY(launch_decode_s64(info.format, rings, info.xor_delta != 0, split, nullptr, nullptr, split ? n_full : n_fast, &d, stream));
+            LAUNCH_TRY(launch_decode_s64(info.format, info.xor_delta != 0, split, plain_decode_parts(info.format, n_full, info.chunk_bytes / 1024), nullptr, nullptr,
+                                         split ? n_full : n_fast, &d, stream));
         }
         first_slot = n_full;
     } else if (fk.ok && by_ids) {
@@ -412,7 +413,11 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
         if (rings) rings = most;
     }
     bool split = rings != 0;
-    for (uint32_t t = 0; t < n_tensors && split; t++) split = s64_split_ok(tensors[t].info);
+    uint32_t least_rows = 0xFFFFFFFFu;                          // of the tensors' chunks
+    for (uint32_t t = 0; t < n_tensors && split; t++) {
+        split = s64_split_ok(tensors[t].info);
+        least_rows = std::min(least_rows, tensors[t].info.chunk_bytes / 1024);
+    }
     bool e5m2 = rings != 0;
     for (uint32_t t = 0; t < n_tensors && e5m2; t++) e5m2 = e5m2_s64_ok(tensors[t].info);
     // BF16 sets whose every tensor has the shape of the BF16 kernel go there instead
@@ -484,6 +489,7 @@ zc_status zc_decompress_batch_plan(const zc_tensor *tensors, uint32_t n_tensors,
     plan->fast_exp_kind = (uint32_t)fk.exp_kind; plan->fast_sm_kind = (uint32_t)fk.sm_kind; plan->xor_delta = tensors[0].info.xor_delta;
     plan->fast_kernel = pairs_as.chunks ? (fmt == ZC_FMT_FP8_E5M2 ? 7u : 8u) : fk.ok ? 1u : (rings ? (e5m2 ? 9u : bf16_rings ? 6u : split ? 4u : 2u) : (sub ? (fmt == ZC_FMT_BF16 ? 5u : 3u) : 0u));
     plan->n_rings = pairs_as.chunks ? pair_fields * 64 + (pairs_as.long_rings ? 32 : 0) + pairs_as.chunks : sub ? spg : (bf16_rings ? bf16_rings : rings);
+    if (plan->fast_kernel == 4) plan->n_rings |= plain_decode_parts(fmt, plan->n_fast_work, least_rows) << 8;
     plan->scattered = 0;
     for (uint32_t t = 0; t < n_tensors; t++) if (tensors[t].d_chunk_ids) plan->scattered = 1;
     // the second list (chunks that are not whole rows, id lists with 64 lanes) goes through the 64-lane kernel's build for
@@ -514,7 +520,7 @@ zc_status zc_decompress_batch_run(const zc_batch_plan *plan, const void *d_ws, v
         LAUNCH_TRY(launch_decode_fp8_fast((int)plan->fast_exp_kind, (int)plan->fast_sm_kind, plan->xor_delta != 0, plan->scattered != 0, (const TensorDev *)ws,
                                           (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
     else if (plan->n_fast_work && (plan->fast_kernel == 2 || plan->fast_kernel == 4))
-        LAUNCH_TRY(launch_decode_s64(plan->format, plan->n_rings, plan->xor_delta != 0, plan->fast_kernel == 4, (const TensorDev *)ws,
+        LAUNCH_TRY(launch_decode_s64(plan->format, plan->xor_delta != 0, plan->fast_kernel == 4, plan->n_rings >> 8, (const TensorDev *)ws,
                                      (const WorkItem *)(ws + plan->fast_work_offset), plan->n_fast_work, nullptr, stream));
     else if (plan->n_fast_work && plan->fast_kernel == 6)
         LAUNCH_TRY(launch_decode_bf16_s64(plan->n_rings, plan->xor_delta != 0, (const TensorDev *)ws,

@@ -94,7 +94,16 @@ constexpr uint32_t parts_that_fit(uint32_t n_work, uint32_t parts) { return part
 // 49.4 | 44.4 | 43.5 | 43.2, of 256 KiB 67 | 53 | 51 | 51; many, 4,096 of 128 KiB 379 | 366 | 360 | 371, 2,048 of 256 KiB 389 | 370 | 360 | 366.  NVFP4, whose scales take
 // twice as long, moves by 2 % at most with the parts where few chunks are left (64 of 256 KiB 86 | 85 | 85 | 85) and by as much as MXFP4 where there are many.
 constexpr uint32_t plain_encode_parts(uint32_t n_work, uint32_t rows) { return parts_that_fit(n_work, rows >= 256 ? 8 : rows >= 128 ? 4 : rows >= 64 ? 2 : 1); }
-constexpr uint32_t plain_decode_parts(uint32_t fmt, uint32_t n_work) { return fmt == ZC_FMT_FP4_E2M1_NV && n_work <= 1024 ? 1 : parts_that_fit(n_work, 4); }
+//
+// Decoder: eight rows to a workgroup at least.  A chain of scales beside wavefronts that keep the memory busy waits longer for its words: sixteen rows of scales (MXFP4)
+// hide behind the elements all the same, NVFP4's thirty-two do where there are more chunks than SIMDs.  Decode calls, one workgroup | two | four, us: MXFP4, 64 chunks of
+// 256 KiB 31.0 | 21.9 | 22.1, of 64 KiB 12.6 | 9.9 | 10.1, of 32 KiB 9.4 | 8.0 | 8.2; 8,192 of 64 KiB 225 | 227 | 218, of 32 KiB 127 | 127 | 165, of 16 KiB 52 | 76 | 112; 32,768 of
+// 16 KiB 232 | 356 | 507 (326 before chunks were shared out).  NVFP4, 256 of 256 KiB 67.6 | 68.5 | 73.1, 2,048 of 64 KiB 56.3 | 54.5 | 54.0, of 32 KiB 33.8 | 32.9 | 39.5,
+// of 16 KiB 21.9 | 25.7 | 34.6; 32,768 of 16 KiB 285 | 416 | 572.
+constexpr uint32_t plain_decode_parts(uint32_t fmt, uint32_t n_work, uint32_t rows)
+{
+    return fmt == ZC_FMT_FP4_E2M1_NV && n_work <= 1024 ? 1 : parts_that_fit(n_work, rows >= 64 ? 4 : rows >= 32 ? 2 : 1);
+}
 
 // Workgroups are handed to the 8 XCDs (each with an L2 of its own) in turn, so workgroup p runs on XCD p % 8.
 // Work lists are ordered so that every XCD walks one contiguous eighth of the list: position p of the ordered list
@@ -197,8 +206,9 @@ int launch_decode_fp8_sub(uint32_t streams, bool xor_delta, bool scattered, cons
 // BF16, fewer than 64 lanes per chunk (pages), exponent field table decoded, sign+mantissa flat or raw, optional id list
 int launch_decode_bf16_sub(uint32_t streams, bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                            const TensorDev *single, uint32_t slots_per_group, void *stream);
-// any format, 64 lanes per chunk, full chunks (zc_decode_fast.hip); n_rings = element fields that are table decoded (1..2)
-int launch_decode_s64(uint32_t fmt, uint32_t n_rings, bool xor_delta, bool split, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
+// any format, 64 lanes per chunk, full chunks (zc_decode_s64.hip); split: one chunk per work item, both element fields stored plainly, FP4: shared by `parts` workgroups
+// (plain_decode_parts; fewer where that many do not fit a launch)
+int launch_decode_s64(uint32_t fmt, bool xor_delta, bool split, uint32_t parts, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                       const TensorDev *single, void *stream);
 int launch_decode_s64_tail(uint32_t fmt, bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const TensorDev *single,
                            uint32_t first_slot, bool skip_whole, void *stream);

@@ -35,7 +35,7 @@ def test_whole_chunks(fmt, chunk, policy):
 
 
 @pytest.mark.parametrize("fmt", [zc.FMT_FP4_E2M1_MX, zc.FMT_FP4_E2M1_NV])
-@pytest.mark.parametrize("chunk", [2, 4, 16])
+@pytest.mark.parametrize("chunk", [2, 4, 16, 33])
 def test_many_chunks_decode(fmt, chunk):
     """On both sides of 1,024 chunks, from which NVFP4's scales have workgroups of their own; one tensor and a set."""
     rng = np.random.default_rng(chunk)

@@ -1,5 +1,5 @@
 """Into how many workgroups whole FP4 chunks are split: no launch of 2^32 threads or more, whatever the number of chunks, and one workgroup per chunk where nothing
-else fits or where a workgroup of the encoder would have fewer than 32 rows."""
+else fits or where a workgroup would have fewer rows than 32 (encoder) or about as many as it has wavefronts (decoder)."""
 import os
 import shutil
 import subprocess
@@ -17,7 +17,9 @@ int main(int argc, char **argv)
     for (int i = 1; i < argc; i++) {
         const uint32_t n = (uint32_t)strtoul(argv[i], nullptr, 10);
         for (uint32_t rows : {1u, 63u, 64u, 127u, 128u, 255u, 256u, 1024u}) printf("%u ", zc::plain_encode_parts(n, rows));
-        printf("%u %u\\n", zc::plain_decode_parts(ZC_FMT_FP4_E2M1_MX, n), zc::plain_decode_parts(ZC_FMT_FP4_E2M1_NV, n));
+        for (uint32_t fmt : {ZC_FMT_FP4_E2M1_MX, ZC_FMT_FP4_E2M1_NV})
+            for (uint32_t rows : {16u, 31u, 32u, 63u, 64u, 1024u}) printf("%u ", zc::plain_decode_parts(fmt, n, rows));
+        printf("\\n");
     }
 }
 """
@@ -34,7 +36,7 @@ def test_launches_stay_below_the_limit(tmp_path):
     counts = sorted({1, 2, 448, 1024, 1025, 5376, 1 << 20, most, most - 1} | {most // k + d for k in (2, 3, 5, 9) for d in (-1, 0, 1)})
     lines = subprocess.run([program] + [str(n) for n in counts], capture_output=True, text=True, check=True).stdout.split("\n")
     for n, line in zip(counts, lines):
-        for parts, usual in zip(map(int, line.split()), (1, 1, 2, 2, 4, 4, 8, 8, 4, 4 if n > 1024 else 1)):
+        for parts, usual in zip(map(int, line.split()), (1, 1, 2, 2, 4, 4, 8, 8) + (1, 1, 2, 2, 4, 4) + ((1, 1, 2, 2, 4, 4) if n > 1024 else (1,) * 6)):
             assert parts in (1, usual), (n, line)
             assert n * (parts + 1 if parts > 1 else 1) * 256 < 2 ** 32, (n, line)
             assert parts == usual or n * (usual + 1) * 256 >= 2 ** 32, (n, line)
