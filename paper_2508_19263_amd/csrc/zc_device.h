@@ -9,8 +9,10 @@ namespace zc {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// A word the host waits for, set once all that this wavefront has written is on its way to memory and in front of it (and, after a
-// workgroup barrier, all that its workgroup has).  One thread: the write-back that goes with it is the compute unit's.
+// A word the host waits for, set once all that this wavefront has written has reached memory.  One thread: the write-back that goes with it is the L2's.
+// What the workgroup's other wavefronts have written is in front of it only where each calls wait_for_stores() before a barrier: the barrier by itself
+// lets their stores be under way to the L2 still.
+__device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void tell_host(uint32_t *flag) { __hip_atomic_store(flag, kTold, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM); }
 
 // ------------------------------------------------------------------ lane helpers

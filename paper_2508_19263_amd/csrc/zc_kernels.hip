@@ -867,7 +867,9 @@ __global__ __launch_bounds__(256) void k_hand_over(const uint8_t *src, uint8_t *
     if (i < bytes % 16) dst[n16 * 16 + i] = src[n16 * 16 + i];
     if (i < n_zero) zero[i] = 0;
     if (blockIdx.x >= hand_over_groups(bytes)) return;
-    // what a thread has read is in its registers once its store is issued, and the barrier is behind that of every thread
+    // what a thread has read is in its registers once its store is issued, and the barrier is behind that of every thread; a host destination has to
+    // have been written, too
+    if (TO_HOST) wait_for_stores();
     __syncthreads();
     if (threadIdx.x == 0) {
         if (TO_HOST) tell_host(flags + blockIdx.x);

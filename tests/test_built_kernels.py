@@ -74,6 +74,30 @@ def test_only_what_the_host_reads_is_written_back_to_the_system(tmp_path, to_hos
     assert "global_store" in listing and ("buffer_wbl2" in listing) == to_host
 
 
+def waits_before_barrier(listing):
+    """For every barrier of a listing: is the last instruction in front of it that concerns memory a wait for all of the wavefront's stores?"""
+    lines = [line.split("//")[0].split() for line in listing.split("\n")]
+    barriers, ok = [i for i, w in enumerate(lines) if w and w[0] == "s_barrier"], []
+    for i in barriers:
+        before = [" ".join(w) for w in lines[:i] if w and re.match(r"s_waitcnt|global_|buffer_|flat_", w[0])]
+        ok.append(bool(before) and re.match(r"s_waitcnt.*vmcnt\(0\)", before[-1]) is not None)
+    return ok
+
+
+def test_the_waits_are_found():
+    assert waits_before_barrier("\tglobal_store_dword v0, v1, s[0:1]  // 0\n\ts_waitcnt vmcnt(0)  // 4\n\ts_mov_b32 s0, 0  // 8\n\ts_barrier  // c") == [True]
+    assert waits_before_barrier("\ts_waitcnt vmcnt(0)  // 0\n\tglobal_store_dword v0, v1, s[0:1]  // 4\n\ts_waitcnt lgkmcnt(0)  // 8\n\ts_barrier  // c") == [False]
+    assert waits_before_barrier("\ts_barrier  // 0") == [False]
+
+
+def test_what_the_host_is_told_of_has_been_stored(tmp_path):
+    """One thread tells the host that the workgroup's bytes are there: every wavefront has waited for its stores in front of the barrier before that."""
+    if not os.path.exists(LLVM + "/llvm-objdump"):
+        pytest.skip("llvm-objdump not found")
+    zc.lib()
+    assert waits_before_barrier(listing_of(tmp_path, "_ZN2zc11k_hand_overILb1")) == [True]
+
+
 def test_registers_of_the_decoder_whose_workgroups_share_a_compute_unit(tmp_path):
     """BF16 deltas with short rings: seven wavefronts per SIMD (85 registers and five of them made sets of small deltas 5 - 15 % slower)."""
     if not os.path.exists(LLVM + "/llvm-objdump"):
