@@ -16,8 +16,13 @@
  *   - "device" pointers are GPU memory of the current HIP device, 16-byte
  *     aligned, owned by the caller; "host" pointers are ordinary memory.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
- *     Kernels are enqueued on it.  Calls that must read results back (noted
- *     below) synchronise that stream before returning.
+ *     Kernels are enqueued on it.  Calls that read results back (noted below)
+ *     wait for them.  zc_compress and its batched and dictionary forms return once
+ *     the sizes are known: sources, d_ws and containers are in use until the stream
+ *     has reached that point, but for the dictionary calls that one kernel serves
+ *     (see there), which return when it is through, and for ZC_ERR_BUFFER_TOO_SMALL,
+ *     after which nothing is written any more.  Every other call that waits
+ *     synchronises the stream.
  *   - The library never allocates or frees device memory: scratch space comes in
  *     through `d_ws`.  The only state it keeps between calls is page-locked host
  *     memory: a few buffers through which descriptors, work lists and tables are
@@ -27,9 +32,9 @@
  *     the process).  No environment variable is read.
  *   - HIP graphs: only zc_decompress_batch_run may be recorded by stream capture (it
  *     launches kernels and nothing else).  Every other entry point that takes a stream
- *     copies from or to the library's page-locked buffers, may wait on an event and may
- *     allocate page-locked memory, none of which a capture allows; a captured copy would
- *     also replay whatever a later call left in the buffer.
+ *     copies from or to the library's page-locked buffers, may wait for what kernels leave
+ *     there or on an event and may allocate page-locked memory, none of which a capture
+ *     allows; a captured copy would also replay whatever a later call left in the buffer.
  *   - Errors are returned as zc_status; nothing is thrown.  On error the
  *     destination contents are unspecified but nothing is written outside the
  *     capacities given.
@@ -246,8 +251,8 @@ zc_status zc_compress_noalloc(const void *d_src, uint64_t n_elems, const zc_para
  * no histogram pass and no code construction.  The container is an ordinary one (it carries the dictionary's length tables), so
  * every decompress entry point reads it.  A dictionary whose Huffman fields do not form a
  * complete prefix code over the whole alphabet is rejected with ZC_ERR_INVALID_ARG.
- * K/V pages (FP8 or BF16, 4 to 32 lanes, every tensor whole pages): a call whose tensors have at most 512 pages each runs as
- * one kernel, one workgroup per tensor; with ZC_FLAG_REVERSE_FIELDS a call over tensors of any number of pages runs as
+ * K/V pages (FP8 or BF16, 4 to 32 lanes, every tensor whole pages, no sign+mantissa field table coded): a call whose tensors have at most
+ * 512 pages each runs as one kernel, one workgroup per tensor; with ZC_FLAG_REVERSE_FIELDS a call over tensors of any number of pages runs as
  * one kernel that reads the pages once (on MI355X 1.4 against 1.7 ms for 2.1 GB of FP8 pages; fastest for FP8 pages of
  * at most 2 KiB and BF16 pages of at most 4 KiB, whose coded exponents wait on chip for their place, and with a
  * dictionary that suits the data: a page whose coded exponents are longer than the plain ones is coded twice);

@@ -511,7 +511,9 @@ private:
         const zc_status queued = roomy ? q.queue_encoders() : ZC_OK;
         const zc_status known = wait_for_records(q.to_host, T, stream);       // (whatever was queued: the buffer is the scan's until then)
         if (queued || known) return queued ? queued : known;
-        return read_sizes(true);
+        const zc_status st = read_sizes(true);
+        if (stats_only || st == ZC_ERR_BUFFER_TOO_SMALL) HIP_TRY(hipStreamSynchronize(hs));       // (the scan's last stores: the caller may use the workspace elsewhere at once)
+        return st;
     }
     // the sizes in q.to_host, and, when the encoders are not queued yet, those
     zc_status read_sizes(bool then_encode)
@@ -557,24 +559,27 @@ private:
         if (!no_sync) {
             if (!landing.ptr) return ZC_ERR_DEVICE;
             q.to_host = landing.records(T, false);
+            std::memset(q.to_host.records, 0xFF, T * sizeof(ScanOut));  // (as a workgroup that gave up would leave it)
         }
         uint32_t periods = 0;                                           // BF16: one build per refill period of the exponent field
         if (sh.bf16)
             for (uint32_t t = 0; t < T; t++) periods |= descs[t].period[0];
         LAUNCH_TRY(launch_compress_pages_fused(g.S, periods, g.reversed, q.d_descs(), T, (const uint32_t *)(ws + w.descs + enc_off), ws + w.descs + blob_off, (ScanOut *)(ws + w.scan),
-                                               q.to_host, stream));
-        return placed_by_one_kernel(T);
+                                               q.to_host.records, stream));
+        if (no_sync) return sizes_stay_behind();
+        HIP_TRY(hipStreamSynchronize(hs));
+        return placed_by_one_kernel();
     }
-    // The rest of a call whose containers one kernel has sized, placed and written (words: set when the sizes are there).  A destination below the worst case only
-    // loses what lies beyond it (the encoder's stores are range checked) and the call reports that it was too small.
-    zc_status placed_by_one_kernel(uint32_t words)
+    zc_status sizes_stay_behind()
     {
-        if (no_sync) {
-            for (uint32_t t = 0; t < T; t++) tensors[t].out_bytes = 0;
-            return ZC_OK;
-        }
-        const zc_status known = wait_for_records(q.to_host, words, stream);
-        if (known) return known;
+        for (uint32_t t = 0; t < T; t++) tensors[t].out_bytes = 0;
+        return ZC_OK;
+    }
+    // The end of a call whose containers one kernel has sized, placed and written, once that kernel is through: the containers are there when the call returns, and
+    // the workspace is free.  A destination below the worst case only loses what lies beyond it (the encoder's stores are range checked) and the call reports
+    // that it was too small.
+    zc_status placed_by_one_kernel()
+    {
         const zc_status st = read_sizes(false);
         for (uint32_t t = 0; t < T; t++) tensors[t].info.total_bytes = tensors[t].out_bytes;
         return st;
@@ -622,19 +627,20 @@ private:
         uint64_t *status = reinterpret_cast<uint64_t *>(ws + w.units), *counter = reinterpret_cast<uint64_t *>(ws + w.hist);
         LAUNCH_TRY(launch_compress_pages_chained(g.S, sh.bf16 ? descs[0].period[0] : 0u, chained_hold(), q.d_descs(), q.d_list(w.fast_work), q.n_fast, chained_step(), q.d_enc(),
                                                  ws + w.blobs, (uint32_t)kBlobBytes, status, counter, (ScanOut *)(ws + w.scan), stream));
-        if (no_sync) return placed_by_one_kernel(0);
+        if (no_sync) return sizes_stay_behind();
         LandingLease landing(LandingLease::record_bytes(T, false));
         if (!landing.ptr) return ZC_ERR_DEVICE;
         q.to_host = landing.records(T, false);
         const uint32_t bytes = (uint32_t)(T * sizeof(ScanOut)), groups = hand_over_groups(bytes);      // (a word per workgroup: no more than tensors)
         LAUNCH_TRY(launch_hand_over(ws + w.scan, q.to_host.records, bytes, true, nullptr, 0, q.to_host.flags, stream));
-        return placed_by_one_kernel(groups);
+        const zc_status known = wait_for_records(q.to_host, groups, stream);       // (set behind the kernel that writes the containers)
+        return known ? known : placed_by_one_kernel();
     }
 
     // a call that waits for nothing: the sizes stay in the containers' headers
     zc_status queue_encoders_without_sizes()
     {
-        for (uint32_t t = 0; t < T; t++) tensors[t].out_bytes = 0;
+        (void)sizes_stay_behind();
         return q.queue_encoders();
     }
 

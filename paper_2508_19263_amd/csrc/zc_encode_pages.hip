@@ -320,7 +320,7 @@ constexpr uint32_t kFusedMaxPages = 512;
 // tensor has another one returns at once: the host launches one build per period that occurs in the call).
 template <int S, int BF>
 __global__ __launch_bounds__(256) void k_compress_pages_fused(const TensorDev *descs, const uint32_t *enc_table, const uint8_t *blob, ScanOut *out, int reversed,
-                                                              HostRecords to)
+                                                              uint8_t *records)
 {
     constexpr uint32_t kGroups = 64 / S, kRing = 32 * S, kPerPass = kWavesPerGroup * kGroups;
     __shared__ uint32_t pair[256];
@@ -389,10 +389,7 @@ __global__ __launch_bounds__(256) void k_compress_pages_fused(const TensorDev *d
             ScanOut o = {{idx0[nc] - idx0[0], idx1[nc] - idx1[0], 0}, total};
             out[blockIdx.x] = o;
             *reinterpret_cast<uint64_t *>(comp + 48) = uni64(dp->payload_off) + 16ull * total;
-            if (to.flags) {                                      // (the host need not wait for the encoder)
-                reinterpret_cast<ScanOut *>(to.records)[blockIdx.x] = o;
-                tell_host(to.flags + blockIdx.x);
-            }
+            if (records) reinterpret_cast<ScanOut *>(records)[blockIdx.x] = o;         // (for a host that waits for the whole kernel)
         }
     }
     encode_pages<S, kPagesWrite, BF>(dp, 0, slots, pair, stage, pairs_of_rows, idx0, idx1, nullptr, 0);
@@ -400,28 +397,28 @@ __global__ __launch_bounds__(256) void k_compress_pages_fused(const TensorDev *d
 
 template <int S>
 static void launch_fused_s(uint32_t bf16_periods, const TensorDev *d_descs, uint32_t n_tensors, const uint32_t *d_enc, const uint8_t *d_blob, ScanOut *d_out, int rev,
-                           const HostRecords &to, hipStream_t st)
+                           uint8_t *records, hipStream_t st)
 {
-    if (!bf16_periods) { hipLaunchKernelGGL((k_compress_pages_fused<S, 0>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, to); return; }
-    if (bf16_periods & 2) hipLaunchKernelGGL((k_compress_pages_fused<S, 2>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, to);
-    if (bf16_periods & 4) hipLaunchKernelGGL((k_compress_pages_fused<S, 4>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, to);
-    if (bf16_periods & 8) hipLaunchKernelGGL((k_compress_pages_fused<S, 8>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, to);
+    if (!bf16_periods) { hipLaunchKernelGGL((k_compress_pages_fused<S, 0>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, records); return; }
+    if (bf16_periods & 2) hipLaunchKernelGGL((k_compress_pages_fused<S, 2>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, records);
+    if (bf16_periods & 4) hipLaunchKernelGGL((k_compress_pages_fused<S, 4>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, records);
+    if (bf16_periods & 8) hipLaunchKernelGGL((k_compress_pages_fused<S, 8>), dim3(n_tensors), dim3(256), 0, st, d_descs, d_enc, d_blob, d_out, rev, records);
 }
 
 // streams: 4, 8, 16 or 32; one workgroup per tensor.  bf16_periods: 0 for FP8 tensors (route 1); for BF16 tensors (route 2)
 // the refill periods of the exponent field that occur among them, or-ed together (2, 4, 8): one launch per period.
 int launch_compress_pages_fused(uint32_t streams, uint32_t bf16_periods, bool reversed, const TensorDev *d_descs, uint32_t n_tensors, const uint32_t *d_enc,
-                                const uint8_t *d_blob, ScanOut *d_out, const HostRecords &to, void *stream)
+                                const uint8_t *d_blob, ScanOut *d_out, uint8_t *records, void *stream)
 {
     const int rev = reversed ? 1 : 0;
     if (n_tensors == 0) return 0;
     if (bf16_periods & ~14u) return 1;
     hipStream_t st = (hipStream_t)stream;
     switch (streams) {
-    case 4: launch_fused_s<4>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, to, st); break;
-    case 8: launch_fused_s<8>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, to, st); break;
-    case 16: launch_fused_s<16>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, to, st); break;
-    case 32: launch_fused_s<32>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, to, st); break;
+    case 4: launch_fused_s<4>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, records, st); break;
+    case 8: launch_fused_s<8>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, records, st); break;
+    case 16: launch_fused_s<16>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, records, st); break;
+    case 32: launch_fused_s<32>(bf16_periods, d_descs, n_tensors, d_enc, d_blob, d_out, rev, records, st); break;
     default: return 1;
     }
     return (int)hipGetLastError();

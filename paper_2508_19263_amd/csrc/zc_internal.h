@@ -256,9 +256,9 @@ int launch_encode_fp8(const TensorDev *d_descs, const WorkItem *d_work, uint32_t
 // work items as for the generic whole-chunk build (zc_encode_fast.hip)
 int launch_encode_bf16(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work, const uint32_t *d_enc, void *stream);
 // K/V pages, 4 to 32 lanes per chunk (zc_encode_pages.hip)
-// (d_enc, d_blob: the one code's tables and the header of one of the tensors)
+// (d_enc, d_blob: the one code's tables and the header of one of the tensors; records: page-locked memory for a ScanOut per tensor, or null)
 int launch_compress_pages_fused(uint32_t streams, uint32_t bf16_periods, bool reversed, const TensorDev *d_descs, uint32_t n_tensors, const uint32_t *d_enc,
-                                const uint8_t *d_blob, ScanOut *d_out, const HostRecords &to, void *stream);
+                                const uint8_t *d_blob, ScanOut *d_out, uint8_t *records, void *stream);
 uint32_t compress_pages_fused_limit();      // most pages per tensor the fused kernel takes
 // pages in one pass over the source: containers with their fields in reverse order, dictionary calls; see the kernel
 int launch_compress_pages_chained(uint32_t streams, uint32_t bf16_period, uint32_t hold, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
