@@ -31,7 +31,7 @@ bool told(const uint32_t *flags, uint32_t n)
     return true;
 }
 // Waits until all are set.  Looks without a pause for a while, as the runtime's own waits do, then lets other threads run between looks;
-// once a second idle() says whether the work has ended without them (an error): ZC_OK and not yet set then means it never will be.
+// once a second idle(), which does not wait, says whether the work has ended without them (an error): hipSuccess and not yet set then means they never will be.
 template <typename Idle>
 zc_status wait_until_told(const uint32_t *flags, uint32_t n, const Idle &idle)
 {
@@ -93,9 +93,11 @@ public:
         if (need <= kHandOver && (uintptr_t)(d_ws + lo) % 16 == 0) {
             const uint32_t groups = hand_over_groups((uint32_t)need);
             std::memset(k.flags(), 0, groups * sizeof(uint32_t));
-            if (hipGetDevice(&k.device) != hipSuccess) return ZC_ERR_DEVICE;
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;         // (the null stream is never captured)
+            if (hs && hipStreamIsCapturing(hs, &capture) != hipSuccess) return ZC_ERR_DEVICE;
             LAUNCH_TRY(launch_hand_over(buf, d_ws + lo, need, false, d_zero, n_zero, k.flags(), hs));
             k.groups = groups;
+            k.captured = capture != hipStreamCaptureStatusNone;
         } else {
             if (!k.ev && hipEventCreateWithFlags(&k.ev, hipEventDisableTiming) != hipSuccess) return ZC_ERR_DEVICE;
             HIP_TRY(hipMemcpyAsync(d_ws + lo, buf, need, hipMemcpyHostToDevice, hs));
@@ -112,7 +114,7 @@ public:
         for (Slot &k : slot_) {
             std::lock_guard<std::mutex> lock(k.m);
             if (k.wait()) st = ZC_ERR_DEVICE;
-            k.copying = false; k.groups = 0;
+            k.copying = k.captured = false; k.groups = 0;
             if (k.mem && hipHostFree(k.mem) != hipSuccess) st = ZC_ERR_DEVICE;
             k.mem = nullptr; k.cap = 0;
             if (k.ev) (void)hipEventDestroy(k.ev);
@@ -131,23 +133,17 @@ private:
         hipEvent_t ev = nullptr;
         bool copying = false;               // a copy with the event behind it is in flight
         uint32_t groups = 0;                // words that the kernel in flight has still to set
-        int device = 0;                     // whose kernel that is
+        bool captured = false;              // that kernel went into a graph: nobody knows when it reads the buffer
         uint32_t *flags() const { return reinterpret_cast<uint32_t *>(mem); }
+        // For the words as long as it takes: the stream may be gone by now, so there is nothing to ask but the device, and that would be to wait for every
+        // stream's work, among it what this thread would have to do first, and would spoil another thread's capture.
         zc_status wait()
         {
-            if (copying && hipEventSynchronize(ev) != hipSuccess) return ZC_ERR_DEVICE;
+            if (captured || (copying && hipEventSynchronize(ev) != hipSuccess)) return ZC_ERR_DEVICE;
             copying = false;
-            const uint32_t n = groups;
-            groups = 0;                                          // (words that will never be set are not waited for twice)
-            if (n == 0 || told(flags(), n)) return ZC_OK;
-            return wait_until_told(flags(), n, [this] {
-                // the stream may be gone by now: the device
-                int now = 0;
-                if (hipGetDevice(&now) != hipSuccess || hipSetDevice(device) != hipSuccess) return hipErrorUnknown;
-                const hipError_t e = hipDeviceSynchronize();
-                (void)hipSetDevice(now);
-                return e;
-            });
+            const zc_status st = groups ? wait_until_told(flags(), groups, [] { return hipErrorNotReady; }) : ZC_OK;
+            groups = 0;
+            return st;
         }
     };
     std::mutex m_;              // guards next_ only
