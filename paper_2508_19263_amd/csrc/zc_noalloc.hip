@@ -128,7 +128,7 @@ zc_status compress_single_device_setup(const zc_tensor &x, const zc_params *para
     q.n_fast = L.fast.count(); q.n_whole = L.whole.count(); q.n_other = L.other.count(); q.n_slow = L.slow.count();
     // the same places and the same order as CompressCall::run_with_device_codes gives them
     a.list[0] = {q.w.hist_work, q.n_hist, L.hist.first, L.hist.step, 0};
-    a.list[1] = {q.w.hist_work + (uint64_t)q.n_hist * sizeof(WorkItem), q.n_lane_hist, L.lane_hist.first, L.lane_hist.step, 1};
+    a.list[1] = {q.w.hist_work + (uint64_t)q.n_hist * sizeof(WorkItem), q.n_lane_hist, L.lane_hist.first, L.lane_hist.step, 0};
     a.list[2] = {q.w.scale_work, q.n_scale, L.scale.first, L.scale.step, 0};
     a.list[3] = {q.w.chunk_work, q.n_slow, L.slow.first, L.slow.step, 1};
     a.list[4] = {q.w.fast_work, q.n_fast, L.fast.first, L.fast.step, 1};
