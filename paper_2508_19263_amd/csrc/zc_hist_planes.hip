@@ -497,7 +497,9 @@ int launch_hist_pages(bool delta, const TensorDev *d_descs, const WorkItem *d_wo
     if (n_work == 0) return 0;
     hipStream_t st = (hipStream_t)stream;
     const uint32_t split = parts_of(n_work, kHistBlockBytes / pass_bytes);
-    const bool once = n_work > 1024;                             // as in launch_hist_planes
+    // Non-temporal loads as in launch_hist_planes.  Whole calls over pages of 2 KiB, 8 lanes, without | with the hint, us: 512 blocks 136 | 145, 900 256 | 255,
+    // 1,100 315 | 312, 2,000 586 | 568, 6,000 1,695 | 1,654; of 4 KiB, 16 lanes: 512 126 | 135, 1,024 236 | 241, 1,300 317 | 309, 3,000 723 | 696.
+    const bool once = n_work > 1024;
 #define ZC_PAGES(D, N) hipLaunchKernelGGL((k_hist_pages<D, N>), dim3(n_work * split), dim3(256), 0, st, d_descs, d_work, split, d_hist, (u32x4 *)d_counts, (uint16_t *)d_lasts)
     if (delta) { if (once) ZC_PAGES(true, kNt); else ZC_PAGES(true, 0); }
     else { if (once) ZC_PAGES(false, kNt); else ZC_PAGES(false, 0); }

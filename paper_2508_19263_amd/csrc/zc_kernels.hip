@@ -113,8 +113,10 @@ int launch_hist(uint32_t fmt, const TensorDev *d_descs, const WorkItem *d_work, 
     static_assert(kHistBlockBytes % (16 * 4 * 256 * 16) == 0, "a sixteenth of a block is whole rounds of the kernel's loads");
     // A list of so few blocks that the compute units are not full: two or four workgroups per block.  (Longer lists lose by
     // it: every workgroup clears and folds its 32 KiB of counters and adds up to 256 totals to the tensor's bins, and C3's
-    // 1,344 blocks took 115 instead of 92 us in quarters.)  A handful of blocks in sixteenths, a round of loads each.
-    const uint32_t split = n_work <= 16 ? 16u : n_work <= 320 ? 4u : n_work <= 640 ? 2u : 1u;
+    // 1,344 blocks took 115 instead of 92 us in quarters.)  A handful of blocks in sixteenths, a round of loads each: whole calls in quarters | in sixteenths, us, BF16
+    // of 1 block 88.2 | 85.5, of 4 89.0 | 86.8, of 8 90.1 | 89.1, of 12 90.8 | 91.0, of 16 91.2 | 92.4, of 32 93.0 | 98.4; byte symbols of 8 97.5 | 96.1, of 16
+    // 98.5 | 99.4; deltas of 8 99.5 | 98.2, of 16 100.6 | 101.3.
+    const uint32_t split = n_work <= 8 ? 16u : n_work <= 320 ? 4u : n_work <= 640 ? 2u : 1u;
     const dim3 grid(n_work * split);
     if (fmt == ZC_FMT_BF16 && !scales_view)
         hipLaunchKernelGGL(k_hist<ZC_FMT_BF16>, grid, dim3(256), 0, st, d_descs, d_work, 16, 0, d_hist, split);
