@@ -381,7 +381,7 @@ int launch_decode_bf16_sub(uint32_t streams, bool xor_delta, const TensorDev *d_
     hipStream_t st = (hipStream_t)stream;
     const TensorDev s = single ? *single : TensorDev{};
     const int use_single = single ? 1 : 0;
-    const bool eight = slots_per_group % (8 * (64 / streams)) == 0;      // (sub_slots_per_group)
+    const bool eight = bf16_page_waves(streams, slots_per_group) == 8;
     switch (streams) {
     case 4: return eight ? launch_bf16_sub_s<4, 8>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st) : launch_bf16_sub_s<4, 4>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);
     case 8: return eight ? launch_bf16_sub_s<8, 8>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st) : launch_bf16_sub_s<8, 4>(xor_delta, d_descs, d_work, n_work, s, use_single, slots_per_group, st);

@@ -203,7 +203,10 @@ int launch_decode_fp8_fast(int exp_kind, int sm_kind, bool xor_delta, bool with_
 // FP8, fewer than 64 lanes per chunk (pages), optional id list (zc_decode_fast.hip)
 int launch_decode_fp8_sub(uint32_t streams, bool xor_delta, bool scattered, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                           const TensorDev *single, uint32_t slots_per_group, void *stream);
-// BF16, fewer than 64 lanes per chunk (pages), exponent field table decoded, sign+mantissa flat or raw, optional id list
+// BF16, fewer than 64 lanes per chunk (pages), exponent field table decoded, sign+mantissa flat or raw, optional id list.  A workgroup's wavefronts follow from its slots, which
+// a plan holds: eight where they are whole passes of eight.  (Four-wavefront workgroups are for calls small enough that each takes one pass of four: page_slots_per_group.
+// A plan with any other number is decoded by the build it names, with wavefronts that idle in its last pass.)
+constexpr uint32_t bf16_page_waves(uint32_t streams, uint32_t slots_per_group) { return slots_per_group % (8 * (64 / streams)) == 0 ? 8 : 4; }
 int launch_decode_bf16_sub(uint32_t streams, bool xor_delta, const TensorDev *d_descs, const WorkItem *d_work, uint32_t n_work,
                            const TensorDev *single, uint32_t slots_per_group, void *stream);
 // any format, 64 lanes per chunk, full chunks (zc_decode_s64.hip); split: one chunk per work item, both element fields stored plainly, FP4: shared by `parts` workgroups

@@ -7,6 +7,7 @@ import torch
 
 from oracle import zc_oracle as o
 from paper_2508_19263_amd import zc
+from tiled import assert_few_over_and_over
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -68,17 +69,6 @@ def test_more_chunks_than_a_launch_of_nine_workgroups_each_holds():
     p = zc.params(fmt, KIB, streams=64)
     on = [torch.from_numpy(a).to(DEV).repeat(times) for a in (x, scales)]
     got, info = zc.compress(on[0], 2 * on[0].numel(), p, scales=on[1])
-    one = zc.validate_container(small)
-    assert info.n_chunks == few * times and [bytes(c) for c in info.code_len] == [bytes(c) for c in one.code_len] and list(info.mode) == list(one.mode)
-    small = torch.from_numpy(small).to(DEV)
-    word = lambda t, at, n: t[at:at + 4 * n].view(torch.int32).long()
-    at_small, at_big = one.payload_offset, info.payload_offset
-    for f in range(3):
-        index, index_of_few = word(got, info.index_offset[f], few * times + 1), word(small, one.index_offset[f], few + 1)
-        assert torch.equal(index.diff(), index_of_few.diff().repeat(times)), f
-        n = 16 * int(index_of_few[-1] - index_of_few[0])
-        assert torch.equal(got[at_big:at_big + n * times].view(times, n), small[at_small:at_small + n].expand(times, n)), f
-        at_small, at_big = at_small + n, at_big + n * times
-    assert at_big == got.numel() == info.total_bytes and at_small == small.numel()
+    assert_few_over_and_over(got, info, small, times)
     out, s = zc.decompress(got, info)
     assert torch.equal(out, on[0]) and torch.equal(s, on[1])
