@@ -191,7 +191,7 @@ __device__ __forceinline__ uint32_t encode_pages(const TensorDev *dp, uint32_t f
             for (int g = 0; g < kPeriods; g++) {
                 const bool req = k <= 32;
                 if (WRITE) {
-                    // (the group's bits of the ballot, picked out as bytes: two instructions less than masking it and counting across all lanes)
+                    // (the group's bits of the ballot, picked out as bytes: eight instructions per row less than masking it and counting across all lanes, with no time to show for it)
                     const uint64_t all = __ballot(req);
                     uint32_t asked = __builtin_amdgcn_perm((uint32_t)(all >> 32), (uint32_t)all, group_bytes);
                     if (S == 4) asked = (asked >> (lane & 4)) & 15u;

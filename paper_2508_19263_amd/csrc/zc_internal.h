@@ -88,18 +88,26 @@ constexpr uint32_t kMostGroups = 0xFFFFFFFFu / 256;
 // those, has the chunk's scales; or 1: one workgroup has both, as it does in calls of more chunks than such launches hold.
 constexpr uint32_t parts_that_fit(uint32_t n_work, uint32_t parts) { return parts > 1 && (uint64_t)n_work * (parts + 1) <= kMostGroups ? parts : 1; }
 //
-// Encoder: 32 rows (1 KiB of elements each) to a workgroup at least, eight to a wavefront.  With fewer the workgroups' starts are what a call waits for.  Whole calls of
-// MXFP4, one workgroup | two | four | eight, us: 65,536 chunks of 1 KiB 662 before chunks were shared out, 1,795 with eight; 32,768 of 1 KiB 261 | 402 | 574 | 919,
-// of 16 KiB 532 | 670 | 903 | 1,225; 8,192 of 32 KiB 227 | 240 | 294 | 395, of 64 KiB 380 | 383 | 394 | 507; few chunks, 64 of 64 KiB 43.8 | 42.6 | 42.5 | 42.5, of 128 KiB
-// 49.4 | 44.4 | 43.5 | 43.2, of 256 KiB 67 | 53 | 51 | 51; many, 4,096 of 128 KiB 379 | 366 | 360 | 371, 2,048 of 256 KiB 389 | 370 | 360 | 366.  NVFP4, whose scales take
-// twice as long, moves by 2 % at most with the parts where few chunks are left (64 of 256 KiB 86 | 85 | 85 | 85) and by as much as MXFP4 where there are many.
+// Encoder: 32 rows (1 KiB of elements each) to a workgroup at least, eight to a wavefront.  Below that the workgroups' starts are what a call waits for.
+// Whole calls of MXFP4, us, by workgroups per chunk:      one | two | four | eight
+//   32,768 chunks of 1 KiB                                261 | 402 | 574 | 919
+//   32,768 of 16 KiB                                      532 | 670 | 903 | 1,225
+//   8,192 of 32 KiB                                       227 | 240 | 294 | 395
+//   64 of 64 KiB; 8,192                                   43.8 | 42.6 | 42.5 | 42.5; 380 | 383 | 394 | 507
+//   64 of 128 KiB; 4,096                                  49.4 | 44.4 | 43.5 | 43.2; 379 | 366 | 360 | 371
+//   64 of 256 KiB; 2,048                                  67 | 53 | 51 | 51; 389 | 370 | 360 | 366
+// NVFP4, whose scales take twice as long, the same where there are many chunks; few are a matter of the scales (64 of 256 KiB 86 | 85 | 85 | 85).
 constexpr uint32_t plain_encode_parts(uint32_t n_work, uint32_t rows) { return parts_that_fit(n_work, rows >= 256 ? 8 : rows >= 128 ? 4 : rows >= 64 ? 2 : 1); }
 //
-// Decoder: eight rows to a workgroup at least.  A chain of scales beside wavefronts that keep the memory busy waits longer for its words: sixteen rows of scales (MXFP4)
-// hide behind the elements all the same, NVFP4's thirty-two do where there are more chunks than SIMDs.  Decode calls, one workgroup | two | four, us: MXFP4, 64 chunks of
-// 256 KiB 31.0 | 21.9 | 22.1, of 64 KiB 12.6 | 9.9 | 10.1, of 32 KiB 9.4 | 8.0 | 8.2; 8,192 of 64 KiB 225 | 227 | 218, of 32 KiB 127 | 127 | 165, of 16 KiB 52 | 76 | 112; 32,768 of
-// 16 KiB 232 | 356 | 507 (326 before chunks were shared out).  NVFP4, 256 of 256 KiB 67.6 | 68.5 | 73.1, 2,048 of 64 KiB 56.3 | 54.5 | 54.0, of 32 KiB 33.8 | 32.9 | 39.5,
-// of 16 KiB 21.9 | 25.7 | 34.6; 32,768 of 16 KiB 285 | 416 | 572.
+// Decoder: sixteen rows to a workgroup at least, four to a wavefront.  A chain of scales beside wavefronts that keep the memory busy waits longer for its words: sixteen
+// rows of scales (MXFP4) hide behind the elements all the same, NVFP4's thirty-two do where there are more chunks than SIMDs.
+// Decode calls, us, by workgroups per chunk:              one | two | four
+//   MXFP4, 64 chunks of 256 KiB; 2,048                    31.0 | 21.9 | 22.1; 241 | 253 | 241
+//   64 of 64 KiB; 8,192                                   12.6 | 9.9 | 10.1; 225 | 227 | 218
+//   64 of 32 KiB; 8,192                                   9.4 | 8.0 | 8.2; 127 | 127 | 165
+//   8,192 of 16 KiB; 32,768                               52 | 76 | 112; 232 | 356 | 507
+//   NVFP4, 256 of 256 KiB; 2,048                          67.6 | 68.5 | 73.1; 228 | 237 | 226
+//   2,048 of 64 KiB; of 32 KiB; of 16 KiB                 56.3 | 54.5 | 54.0; 33.8 | 32.9 | 39.5; 21.9 | 25.7 | 34.6
 constexpr uint32_t plain_decode_parts(uint32_t fmt, uint32_t n_work, uint32_t rows)
 {
     return fmt == ZC_FMT_FP4_E2M1_NV && n_work <= 1024 ? 1 : parts_that_fit(n_work, rows >= 64 ? 4 : rows >= 32 ? 2 : 1);
