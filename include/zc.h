@@ -30,8 +30,9 @@
  *     other's copies) and a few through which sizes and headers are read back (allocated
  *     on first use, grown when needed, held until zc_release_host_buffers() or the end of
  *     the process).  No environment variable is read.
- *   - HIP graphs: only zc_decompress_batch_run may be recorded by stream capture (it
- *     launches kernels and nothing else).  Every other entry point that takes a stream
+ *   - HIP graphs: only zc_decompress_batch_run and zc_compress_noalloc may be recorded by
+ *     stream capture (they launch kernels and nothing else; zc_compress_noalloc after a
+ *     first call outside one).  Every other entry point that takes a stream
  *     copies from or to the library's page-locked buffers, may wait for what kernels leave
  *     there or on an event and may allocate page-locked memory, none of which a capture
  *     allows; a captured copy would also replay whatever a later call left in the buffer.
@@ -345,7 +346,7 @@ typedef struct {
     uint32_t format, streams, n_tensors;
     uint32_t n_fast_work, n_work;               /* work items of the specialised / generic kernel */
     uint32_t fast_kernel;                       /* 0 none, 1 FP8 specialised, 2 64-lane full-chunk kernel, 3 FP8 small chunks,
-                                                   4 = 2 with every chunk shared by four wavefronts (no table-decoded element field),
+                                                   4 = 2 with every chunk's rows shared by several wavefronts (no table-decoded element field),
                                                    5 BF16 small chunks, 6 BF16 with 64 lanes (table-decoded exponents),
                                                    7 FP8 E5M2 with 64 lanes (table-decoded exponents, flat 3-bit sign+mantissa code),
                                                    8 BF16, FP8 and FP8 in byte symbols with 64 lanes: 7 and 8 look up two symbols at

@@ -80,3 +80,29 @@ def test_noalloc_limits_are_errors():
     with pytest.raises(zc.ZcError) as e:
         zc.compress_noalloc(x, 50000, zc.params(zc.FMT_FP8_E4M3, 2048, streams=8, flags=zc.FLAG_HOST_CODES), torch.empty(zc.compress_bound(50000, p), dtype=torch.uint8, device=DEV))
     assert e.value.status == zc.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("fmt,chunk,lanes,n", [(zc.FMT_FP8_E4M3, 262144, 64, 3 * 262144 + 77), (zc.FMT_FP8_E4M3, 2048, 8, 200 * 2048), (zc.FMT_BF16, 65536, 64, 5 * 32768 + 3)])
+def test_noalloc_replays_from_a_captured_graph(fmt, chunk, lanes, n):
+    """Recorded once; every replay compresses what the source holds then, with codes of its own, and is held against zc_compress."""
+    print("case", fmt, chunk, lanes, n, flush=True)
+    make = wl.fp8_weight if fmt == zc.FMT_FP8_E4M3 else wl.bf16_weight
+    p = zc.params(fmt, chunk, streams=lanes)
+    src = make(n, seed=90).to(DEV)
+    dst = torch.zeros(zc.compress_bound(n, p), dtype=torch.uint8, device=DEV)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        zc.compress_noalloc(src, n, p, dst)
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            zc.compress_noalloc(src, n, p, dst)
+    for replay in range(4):
+        src.copy_(make(n, seed=91 + replay, std=0.02 * 3 ** replay))
+        dst.fill_(0xA5)
+        want, _ = zc.compress(src, n, p)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert zc.read_info(dst, check_index=True).total_bytes == want.numel()
+        assert torch.equal(dst[:want.numel()], want), replay
